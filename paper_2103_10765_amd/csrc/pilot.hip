@@ -590,23 +590,37 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const uint16_t* __restrict__
   }
 }
 
-// grad (canonical layout of one layer) = sum over workgroups of the partials
-__global__ void wgrad_reduce_kernel(const float* __restrict__ partial, int n_part, int ci_n, int co_n,
-                                    float* __restrict__ grad) {
-  const int n_w = kTaps * ci_n * co_n;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_w + co_n) return;
+// grad (canonical layout of one layer) = sum over workgroups of the partials,
+// in double.  Bound by memory latency: a thread that walked all the partials
+// of an output alone had 512 dependent-in-time strided loads in only 37
+// workgroups (125 us per 32 -> 32 layer).  Here a workgroup takes 64 outputs
+// and each of its 16 waves every 16th partial, eight loads in flight, and the
+// waves' sums are added in wave order: 4.8 us.
+constexpr int kRedWaves = 16;
+__global__ __launch_bounds__(64 * kRedWaves) void wgrad_reduce_kernel(const float* __restrict__ partial, int n_part,
+                                                                      int ci_n, int co_n, float* __restrict__ grad) {
+  __shared__ double sums[kRedWaves][64];
+  const int n_w = kTaps * ci_n * co_n, n_out = n_w + co_n;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i = blockIdx.x * 64 + lane, o = min(i, n_out - 1);
   int src;
-  if (i < n_w) {
-    const int t = i / (ci_n * co_n), rem = i - t * ci_n * co_n;
+  if (o < n_w) {
+    const int t = o / (ci_n * co_n), rem = o - t * ci_n * co_n;
     const int ci = rem / co_n, co = rem - ci * co_n;
     src = (t * kC + ci) * kC + co;
   } else {
-    src = kWmat + (i - n_w);
+    src = kWmat + (o - n_w);
   }
   double s = 0.0;
-  for (int k = 0; k < n_part; ++k) s += partial[static_cast<size_t>(k) * (kWmat + kC) + src];
-  grad[i] = static_cast<float>(s);
+#pragma unroll 8
+  for (int k = wave; k < n_part; k += kRedWaves) s += partial[static_cast<size_t>(k) * (kWmat + kC) + src];
+  sums[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && i < n_out) {
+#pragma unroll
+    for (int w = 1; w < kRedWaves; ++w) s += sums[w][lane];
+    grad[i] = static_cast<float>(s);
+  }
 }
 
 // network input: channel 0 = z, channel 1 = sigma, the rest zero
@@ -656,11 +670,21 @@ __global__ __launch_bounds__(256) void loss_kernel(const float* __restrict__ pil
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__global__ void loss_reduce_kernel(const double* __restrict__ part, int n_part, size_t n, float* __restrict__ loss) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+// one workgroup: thread i adds partials i, i + 256, ..., then a tree over the
+// threads: 4.7 us for 1024 partials (one thread adding all of them, a chain of
+// loads, took 68 us)
+__global__ __launch_bounds__(256) void loss_reduce_kernel(const double* __restrict__ part, int n_part, size_t n,
+                                                          float* __restrict__ loss) {
+  __shared__ double red[256];
   double s = 0.0;
-  for (int i = 0; i < n_part; ++i) s += part[i];
-  *loss = static_cast<float>(s / static_cast<double>(n));
+  for (int i = threadIdx.x; i < n_part; i += 256) s += part[i];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *loss = static_cast<float>(red[0] / static_cast<double>(n));
 }
 
 // packed weights from the float32 master vector: forward [l][t][co][ci],
@@ -757,7 +781,7 @@ hipError_t launch_pilot_conv(int mode, const uint16_t* in, const uint16_t* w, co
 hipError_t launch_pilot_loss(const float* pilot, const float* target, const float* weight, size_t hw, size_t n,
                              uint16_t* g, double* part, int n_part, float* loss, hipStream_t st) {
   hipLaunchKernelGGL(loss_kernel, dim3(n_part), dim3(256), 0, st, pilot, target, weight, hw, n, g, part);
-  hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(64), 0, st, part, n_part, n, loss);
+  hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(256), 0, st, part, n_part, n, loss);
   return hipGetLastError();
 }
 
@@ -766,8 +790,8 @@ hipError_t launch_pilot_wgrad(const uint16_t* x, const uint16_t* g, int N, int H
   hipLaunchKernelGGL(wgrad_kernel, dim3(grid), dim3(256), 0, st, x, g, N, H, W, partial);
   const int ci_n = pilot_cin(layer), co_n = pilot_cout(layer);
   const int n_out = kTaps * ci_n * co_n + co_n;
-  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((n_out + 255) / 256), dim3(256), 0, st, partial, grid, ci_n, co_n,
-                     grad_layer);
+  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((n_out + 63) / 64), dim3(64 * kRedWaves), 0, st, partial, grid, ci_n,
+                     co_n, grad_layer);
   return hipGetLastError();
 }
 
