@@ -32,7 +32,8 @@ def algorithmic_work(H, W, search, k1, k2, norm_in_stacks=False):
     (pixel, displacement) pair -- one difference, one fused square-accumulate
     (2 FLOP) and the two running-sum additions of the box filter -- on the
     fp64 vector ALU.  norm_in_stacks: the correlation matcher's norm table is
-    formed in each stage's stack launch (no norm launch of its own)."""
+    formed in each stage's stack launch (an earlier form of that matcher; the
+    present one needs no table)."""
     from paper_2103_10765_amd import gbm3d
     nref = gbm3d.n_refs(H, W, 3)
     weight_bytes = H * W * 8  # 64-bit block-start weights
@@ -73,8 +74,8 @@ def bm_int8_view(H, W, search, avg_us):
 TRAFFIC_FILES = {512: os.path.join(ROOT, "profiles", "hbm_traffic_denoise_512.txt"),
                  4096: os.path.join(ROOT, "profiles", "hbm_traffic_denoise_4096.txt")}
 KERNEL_SOURCES = {
-    "bm": ["bm.hip", "bm_corr.hip", "common.h", "norm.h", "topk.h"], "bm_norm": ["bm_corr.hip", "common.h", "norm.h"],
-    "stack_bior": ["stack.hip", "common.h", "norm.h"], "stack_dct": ["stack.hip", "common.h", "norm.h"],
+    "bm": ["bm.hip", "bm_corr.hip", "common.h", "topk.h"],
+    "stack_bior": ["stack.hip", "common.h"], "stack_dct": ["stack.hip", "common.h"],
     "group_ht": ["group.hip", "common.h"], "group_wiener": ["group.hip", "common.h"], "reduce": ["group.hip", "common.h"],
 }
 
@@ -539,14 +540,12 @@ def per_kernel(ctx, Zt, sigma, p, steps, variants=None):
         ctx.denoise(Zt, sigma, p)
     torch.cuda.synchronize()
     kernels = {}
-    for name in ("bm", "bm_norm", "stack_bior", "stack_dct", "group_ht", "group_wiener", "reduce"):
+    for name in ("bm", "stack_bior", "stack_dct", "group_ht", "group_wiener", "reduce"):
         tot, n = ctx.timing_read(name)
         if n:
             kernels[name] = {"avg_us": 1e3 * tot / n, "launches_per_step": n / steps, "ms_per_step": tot / steps}
     ctx.timing(False)
-    # no norm launch of its own: the stack launches formed the norm tables
-    work = algorithmic_work(H, W, p.search, p.k_ht, p.k_wiener,
-                            norm_in_stacks="bm_norm" not in kernels and "bm" in kernels)
+    work = algorithmic_work(H, W, p.search, p.k_ht, p.k_wiener)
     for name, k in kernels.items():
         bound, amount, unit = work[name]
         peak, punit, scale = PEAKS[bound]
@@ -695,14 +694,10 @@ def main():
         if not t:
             return None
         s = t["split"]
-        return f"{'bm_corr_kernel' if t['method'] == 'corr' else 'bm_kernel'}<{K}, {4 // s}, {s}, false>"
-    def stack_variant(K, kind):
-        # the stack launch carries the norm table when the correlation kernel
-        # matches; the 512^2 launches are short ones (pixel loads all at once)
-        t = tuned.get(f"K{K}")
-        return f"stack_norm_kernel<{kind}, true>" if t and t["method"] == "corr" else f"stack_kernel<{kind}, false>"
-    variants = {"bm": [bm_variant(p.k_ht), bm_variant(p.k_wiener)], "bm_norm": ["bm_norm_kernel<false>"] * 2,
-                "stack_bior": [stack_variant(p.k_ht, 0)], "stack_dct": [stack_variant(p.k_wiener, 1)],
+        return "bm_corr_kernel<6, 3, true, false>" if t["method"] == "corr" else f"bm_kernel<{K}, {4 // s}, {s}, false>"
+    # (the 512^2 stack launches are short ones: pixel loads all at once)
+    variants = {"bm": [bm_variant(p.k_ht), bm_variant(p.k_wiener)],
+                "stack_bior": ["stack_kernel<0, false, true>"], "stack_dct": ["stack_kernel<1, false, true>"],
                 "group_ht": [f"group_ht_kernel<{p.k_ht}, false, false, "
                              f"{'false' if tuned.get('stage1_groups', {}).get('shape', '').startswith('one') else 'true'}>"],
                 "group_wiener": [f"group_wiener_kernel<{p.k_wiener}, false>"], "reduce": ["reduce_kernel<false>"] * 2}

@@ -61,8 +61,9 @@ extern "C" {
 #define GBM3D_BM_AUTO  0  /* the autotuned choice for the shape, else CORR  */
 #define GBM3D_BM_SHIFT 1  /* per displacement: squared differences, box sums
                              at the reference positions (float64 vector ALU) */
-#define GBM3D_BM_CORR  2  /* per 4x4 reference tile: block norms plus int8
-                             matrix-core cross-correlations, exact           */
+#define GBM3D_BM_CORR  2  /* per 4x4 reference tile: f16 matrix-core distances
+                             that bound the window's candidates, exact
+                             integer distances of those within the bound     */
 
 /* patch-stack transforms */
 #define GBM3D_STACK_BIOR15 0   /* 3-level periodic Mallat bior1.5 (Sec. 5) */
@@ -82,9 +83,10 @@ typedef struct {
   float tv_eps_rel;     /* > 0: w = 1 / (TV + tv_eps_rel * sigma * 64 * k_ht); 1e-3 */
   int32_t keep_dc;      /* 1: the 3-D DC coefficient is never shrunk        */
   /* launch tuning (results do not depend on it) */
-  int32_t bm_split;     /* block matching: waves sharing one reference tile,
-                           each scanning a part of the search window,
-                           1 | 2 | 4; 0 = tuned or chosen by image size      */
+  int32_t bm_split;     /* shift-wise block matching: waves sharing one
+                           reference row, each scanning a part of the search
+                           window, 1 | 2 | 4; 0 = tuned or chosen by image
+                           size (the correlation kernel has one shape)       */
   int32_t bm_method;    /* GBM3D_BM_AUTO (tuned or default) | GBM3D_BM_SHIFT |
                            GBM3D_BM_CORR                                     */
   int32_t ht_source;    /* where stage 1 takes each matched block's bior1.5
@@ -230,8 +232,7 @@ int gbm3d_global_match(gbm3d_ctx* ctx, const uint16_t* img, int H, int W,
 /* gbm3d_denoise for callers that cannot allocate device memory: code under
  * hipGraph stream capture, tight serving loops, hosts that forbid hipMalloc.
  * Same arguments, validation and result (bit for bit) as gbm3d_denoise, but
- * every intermediate buffer (norm table, two patch stacks, match indices,
- * aggregation sums, and the basic estimate and pilot when basic_out / q_out
+ * every intermediate buffer (two patch stacks, match indices, aggregation sums, and the basic estimate and pilot when basic_out / q_out
  * are NULL) is a slice of one static device array of
  * GBM3D_NOALLOC_SCRATCH_BYTES per device, which the library holds on every
  * device it runs on until the process ends.  The call makes no hipMalloc,
@@ -323,7 +324,7 @@ int gbm3d_pilot_adam(gbm3d_ctx* ctx, float* master, float* m, float* v, const fl
 /* Per-kernel timing for benchmarking.  While enabled, the context brackets
  * every kernel it launches with two HIP events recorded on the launch stream.
  * gbm3d_timing_read synchronises the pending events and returns, for one
- * kernel name ("bm", "bm_norm", "stack_bior", "stack_dct", "group_ht",
+ * kernel name ("bm", "stack_bior", "stack_dct", "group_ht",
  * "group_wiener", "reduce"), the summed elapsed milliseconds and the number of
  * launches since the last reset ("stack_dct" is one launch that forms both
  * stage-2 stacks, of the noisy image and of the pilot).  Off by default. */
@@ -335,9 +336,9 @@ int gbm3d_timing_reset(gbm3d_ctx* ctx);
  * on it; results are identical for every choice).  With the caller's params
  * (NULL = defaults; search, and for the shape below k_ht and the stage-1
  * options), on the device image img [H][W]:
- *   - times every block-matching variant (GBM3D_BM_SHIFT and GBM3D_BM_CORR,
- *     each with bm_split 1, 2 and 4) with group size K, `reps` runs each
- *     after one warm-up run, and records the fastest;
+ *   - times every block-matching variant (GBM3D_BM_SHIFT with bm_split 1, 2
+ *     and 4, and GBM3D_BM_CORR) with group size K, `reps` runs each after one
+ *     warm-up run, and records the fastest;
  *   - when K == params.k_ht <= 16, also times whole stage-1 runs (that
  *     matching, sigma 25/255) with each of the two shapes of the stage-1
  *     group kernel (two tiles of 12 waves per compute unit, or one tile of

@@ -28,15 +28,15 @@ FLAGS = [
 ]
 
 
-# The matching kernels hold only finite keys or +inf in their min/max
-# networks: with NaNs ruled out, v_min_f64 / v_max_f64 need no NaN-quieting
-# operand canonicalisation.
-# The learned pilot's fused inference keeps its products' accumulators in
-# ordinary VGPRs (the epilogue reads them without copies out of AGPRs); its
-# values are finite throughout.
+# The matching kernels hold only finite keys, scores or infinities in their
+# min/max operations: with NaNs ruled out these need no NaN-quieting operand
+# canonicalisation.
+# The correlation matcher and the learned pilot's fused inference keep their
+# products' accumulators in ordinary VGPRs (vector instructions read them
+# without copies out of AGPRs); the pilot's values are finite throughout.
 EXTRA = {
     "bm.hip": ["-fno-honor-nans"],
-    "bm_corr.hip": ["-fno-honor-nans"],
+    "bm_corr.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "pilot.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     # the peak-rate probes' accumulator chains stay put in VGPRs instead of
     # being shuffled between AGPRs every iteration

@@ -1,579 +1,626 @@
 // Block matching in the correlation form of Theorem 1 (Sec. 2), on the
 // matrix cores.  Same result as the shift-wise kernel: for every reference the
-// K-1 smallest keys dist * 2048 + rank over the search window, reference in
-// slot 0.
+// K-1 smallest keys dist * 2048 + rank over the search window (dist the exact
+// integer ||a - b||^2), reference in slot 0.
 //
-// ||a - b||^2 = N(a) + N(b) - 2 <a, b>, with N the block's squared norm.  The
-// distance is translation invariant, so pixels are first shifted by 32896:
-// z = Z - 32896 = 256 h + l with signed bytes h = (Z >> 8) - 128 and
-// l = (Z & 255) - 128.  Then <a, b> = 65536 Phh + 256 (Phl + Plh) + Pll, four
-// exact int8 x int8 -> int32 dot products of length 64, which is one
-// v_mfma_i32_16x16x64_i8 each for 16 candidates x 16 references.
+// A workgroup of eight waves owns a 4 x 4 tile of references (step 3); the
+// union of their windows is a square of at most 48 x 48 candidate positions,
+// taken in 4 x 4 blocks that are dealt to the waves.  Exact keys of all pairs
+// cost an order of magnitude more vector instructions than the products
+// themselves, and only K of 1521 are wanted, so the kernel first finds, from
+// approximate distances, a set of little more than K candidates per reference
+// that provably holds the answer, and forms exact keys for that set alone:
 //
-// A wave owns a 4 x 4 tile of references (step 3); the union of their search
-// windows is a (2R + 10)^2 square of candidate positions, walked in 4 x 4
-// candidate blocks from the centre outwards.  Result lane (g, n) holds
-// reference n and candidates (row g, columns 0..3) of the block.  Every pair
-// gets its exact key 2048 (N(a) + N(b) - 512 (256 Phh + Phl + Plh) - 2 Pll) +
-// rank in float64 (all terms integers below 2^50) with no data-dependent
-// branch, held less a constant of its reference (two FMAs on the table
-// entry); keys below the lane's bound go to its candidate buffer.  Norms come
-// from a table written beforehand (norm.h; float64, exact) by bm_norm_kernel
-// or, for a single image, by the stack launch of the same stage.
+//  1. Pixels less the tile's centre pixel, halved, are rounded to f16 (a~),
+//     and one f16 product of 16 candidates x 16 references with the
+//     accumulator started at (N(a~) + N(b~)) / 2 (N the squared norm) leaves
+//     the half distance ||a~ - b~||^2 / 2 of every pair without a vector
+//     instruction.  Each lane keeps its 72 half distances, truncated to bf16
+//     and packed in 36 registers, and the smallest of each of its four
+//     columns: a reference has 8 waves x 4 rows x 4 columns = 128 group bests.
+//  2. The K-th smallest of the 128 bests is a bound: K distinct candidates (one
+//     may be the reference itself) are at least that good.  Candidates of a
+//     group lie far apart, so neighbours, which are good together, fall into
+//     different groups: on noisy images 18 candidates of 1521 pass the bound
+//     for K = 16, on first estimates 37 for K = 32.  The bound is widened by
+//     what the roundings can do (widened_bound below), so that no candidate of
+//     the exact answer is lost.
+//  3. Candidates past the bound go to a queue in LDS, one thread forms each
+//     one's exact integer distance from the u16 pixels, and a key's rank among
+//     its reference's keys is its slot.
 //
-// Every lane keeps the K-1 best keys of its reference among its quarter of
-// the candidates; the four quarters, and the SPLIT waves that share a tile,
-// share two upper bounds on the (K-1)-th best key seen so far for the
-// reference: the smallest worst kept key of any list, and the largest m-th
-// best of any list, where m lists-worth of keys make K-1 (n lists each with m
-// keys at or below a value hold n m >= K-1 of them).  Keys are unique, so a
-// key at or above either bound cannot be among the K-1 best.  The lists merge
-// with bitonic networks at the end.
-#include <type_traits>
-
+// Ties: candidates that are exactly as good are told apart by a position
+// term far below one unit of distance, which survives while the norms are
+// small (constant regions); elsewhere they all pass and the exact keys decide,
+// at the cost of more of them (long lists are cut by the (K-1)-th smallest of
+// their first kPrune keys before the ranks are counted).
+//
+// Bound by LDS cycles and vector issue about equally: per tile 6 200 LDS
+// cycles (the 144 blocks' operands 2 600 of them) and 9 000 vector
+// instructions at K = 16, and by the latency of its eight phases, so three
+// workgroups share a CU (78 registers, 53 KB of LDS): with unpacked half
+// distances and two workgroups per CU the 4096^2 image took 3.0 ms instead of
+// 2.6, and with f16 copies 22 instead of 8 banks apart 2.6 instead of 2.45.
+// Against the earlier kernel (exact float64 keys of all pairs from int8
+// products and a norm table), K = 16 / 32: 512^2 87 / 112 -> 47 / 75 us,
+// 4096^2 2.93 / 3.56 -> 2.46 / 3.03 ms, 128^2 26 / 31 -> 11 / 28 us.
 #include "common.h"
 #include "kernels.h"
-#include "norm.h"
-#include "topk.h"
 
 namespace gbm3d {
 
 namespace {
 
-constexpr int kPitch = 96;                         // bytes per LDS plane row
-constexpr int kMaxNb = (2 * kMaxR + 10 + 3) / 4;   // candidate blocks per axis
-constexpr int kRows = 4 * kMaxNb + 7;              // LDS plane rows
-// Buffered candidates per lane before a merge into the list.  A merge runs
-// when any lane of the wave might overflow, so a deeper buffer makes merges
-// rarer; the depth is what the LDS allows at the occupancy the registers
-// already set (four waves per SIMD for K <= 16, three for K = 32).
-template <int K>
-constexpr int kBuf = K >= 32 ? 16 : K >= 16 ? 12 : 8;
-template <int K>
-constexpr int kFlushAt = kBuf<K> - 4;  // a block appends at most 4
-constexpr double kInf = __builtin_huge_val();
+constexpr int kWaves = 8;
+constexpr int kThreads = kWaves * kWave;
+constexpr int kMaxNb = (2 * kMaxR + 10 + 3) / 4;  // candidate blocks per axis: 12
+constexpr int kCand = 4 * kMaxNb;                 // candidate rows / columns: 48
+constexpr int kRows = kCand + 7;                  // pixel rows: 55
+constexpr int kGroups = kMaxNb + 1;               // 4-pixel column groups of the f16 planes: 13
+constexpr int kPixCols = 4 * (kMaxNb + 2);        // columns of the u16 planes: 56
+constexpr int kPixPitch = 2 * kPixCols;           // bytes per u16 plane row
+constexpr int kPixPlane = kRows * kPixPitch;
+// The f16 plane is kept in four copies shifted by 0..3 pixels, so that the
+// eight pixels of a candidate row start at an 8-byte boundary of the copy its
+// column asks for.  The LDS serves 16 lanes of an 8-byte read at a time from 32
+// banks: with rows 26 words apart and copies 8 words apart (modulo 32) the
+// four rows x four copies that 16 candidates read fall on all 32 banks once.
+constexpr int kF16Pitch = 8 * kGroups;            // 104 bytes
+constexpr int kF16Copy = (kRows * kF16Pitch - 32 + 127) / 128 * 128 + 32;
+static_assert(kF16Copy % 128 == 32 && kF16Copy >= kRows * kF16Pitch, "copies eight banks apart");
+constexpr int kInitPitch = 2 * kF16Pitch;         // bytes per row of the accumulator starts (float)
+constexpr int kSumPitch = 4 * kCand;              // bytes per row of the horizontal norm sums (float)
+constexpr int kBestPitch = 2 * kWaves * 16 + 8;   // bytes per reference of the 128 group bests (bf16)
+constexpr int kQueue = 3072;                      // candidates with exact keys at a time (lists padded to eights)
+constexpr int kPrune = 128;                       // longer lists are cut before their keys are ranked
+// Position term of a half distance, per unit of row * S + column (at most
+// 1880): a half distance is a whole multiple of 1/8 on this scale, the term
+// stays below half of that.
+constexpr float kTieStep = 1.0f / 32768.0f;
 
-// an address in LDS, 32 bits wide
-typedef __attribute__((address_space(3))) double lds_double;
+constexpr int max2(int a, int b) { return a > b ? a : b; }
 
-// Keeps p in its register as it stands (the compiler would otherwise rebuild
-// it from the buffer base and an offset at every use).
-__device__ __forceinline__ void pin(lds_double*& p) { asm("" : "+v"(p)); }
-
-static_assert(12 * 3 + 4 * kMaxNb + 12 <= kPitch, "plane rows too short");
-
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-
-// Candidate blocks of an nb x nb grid in rings of growing Chebyshev distance
-// from its centre (near displacements first tighten the bounds early), each
-// entry the block's (row << 8) | column, so no division by the run-time nb is
-// left in the walk.
-struct BlockOrder {
-  int b[kMaxNb + 1][kMaxNb * kMaxNb];  // 32-bit entries: read with scalar loads
+struct Smem {
+  static constexpr int pix0 = 0;                         // u16 plane, and the same shifted by one pixel:
+  static constexpr int pix1 = pix0 + kPixPlane;          // any candidate row starts at a word of one of them
+  static constexpr int f16 = (pix1 + kPixPlane + 15) / 16 * 16;
+  // the accumulator starts replace the horizontal norm sums they come from
+  static constexpr int sums = (f16 + 4 * kF16Copy + 15) / 16 * 16;
+  static constexpr int init = sums;
+  static constexpr int codes = (sums + max2(kRows * kSumPitch, kCand * kInitPitch) + 15) / 16 * 16;
+  static constexpr int best = codes;                     // dead before the codes are written
+  static constexpr int bound = (codes + max2(16 * kBestPitch, 2 * kQueue) + 15) / 16 * 16;
+  // int[16]: packed half distances up to it pass; double[16]: a bound on the keys of a long list
+  static constexpr int prune = bound + 64;
+  static constexpr int count = prune + 128;              // int[16]: candidates past each reference's bound
+  static constexpr int start = count + 64;               // int[16]: their first place in the queue
+  static constexpr int kept = start + 64;                // int[16]: keys left of a long list
+  static constexpr int bytes = kept + 64;
+  static constexpr int keys = f16;                       // the products' operands are dead by then
 };
+static_assert(Smem::bytes <= 160 * 1024 / 3 / 1280 * 1280, "three workgroups per CU");
+static_assert(8 * kQueue <= Smem::codes - Smem::f16, "keys fit the operands' area");
+static_assert(kGroups % 2 == 1 && kPixCols / 8 * 2 == kGroups + 1, "f16 planes end in half an eight-column item");
+static_assert(kQueue >= (2 * kMaxR + 1) * (2 * kMaxR + 1) + 7, "one reference always fits the queue");
 
-constexpr BlockOrder make_block_order() {
-  BlockOrder o{};
-  for (int nb = 1; nb <= kMaxNb; ++nb) {
-    int n = 0;
-    for (int ring = 0; ring <= 2 * nb; ++ring)
-      for (int b = 0; b < nb * nb; ++b) {
-        int dr = 2 * (b / nb) - (nb - 1), dc = 2 * (b % nb) - (nb - 1);
-        dr = dr < 0 ? -dr : dr;
-        dc = dc < 0 ? -dc : dc;
-        if ((dr > dc ? dr : dc) == ring) o.b[nb][n++] = (b / nb) << 8 | (b % nb);
-      }
-  }
-  return o;
-}
+__host__ __device__ constexpr int blocks_per_axis(int R) { return (2 * R + 10 + 3) / 4; }
 
-__constant__ BlockOrder kOrder = make_block_order();
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
-
-template <bool BATCH>
-__global__ __launch_bounds__(256) void bm_norm_kernel(ImgRec one, WorkList wl, int R, int use_pilot) {
-  __shared__ __align__(16) unsigned char smem[NormSmem::bytes];
-  int* zt = reinterpret_cast<int*>(smem);
-  double* hs = reinterpret_cast<double*>(smem + NormSmem::zt_bytes);
-  for_each_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
-    norm_body<false>(use_pilot ? r.pilot : r.noisy, r.norm, r.H, r.W, R, item, zt, hs);
-  });
-}
-
-// ---------------------------------------------------------------------------
-// matching
-// ---------------------------------------------------------------------------
-
-template <int K, int TPW, int SPLIT>
-struct CorrSmem {
-  static constexpr int L = K - 1;
-  static constexpr size_t kPlanes = 2 * kRows * kPitch;
-  static constexpr size_t kBufBytes = sizeof(double) * 4 * kBuf<K> * kWave;
-  static constexpr size_t kBound = SPLIT > 1 ? sizeof(double) * 2 * 4 * kWave : 0;
-  static constexpr size_t kScan = kPlanes + kBufBytes + kBound;
-  static constexpr size_t kMerge = SPLIT > 1 ? sizeof(double) * 2 * L * kWave : 0;
-  static constexpr size_t bytes = kScan > kMerge ? kScan : kMerge;
-};
-
-template <int TPW>
-__host__ __device__ constexpr int corr_col_items(int W) {
-  return ((W + kStep - 1) / kStep + 4 * TPW - 1) / (4 * TPW);
-}
-
-template <int TPW>
 __host__ __device__ constexpr int corr_items(int H, int W) {
-  return ((H + kStep - 1) / kStep + 3) / 4 * corr_col_items<TPW>(W);
+  return ((H + kStep - 1) / kStep + 3) / 4 * (((W + kStep - 1) / kStep + 3) / 4);
 }
 
-// 8 bytes of LDS plane row r from byte column x (any alignment) as 2 dwords
-__device__ __forceinline__ void seg8(const unsigned char* plane, int r, int x, int& w0, int& w1) {
-  const unsigned* p = reinterpret_cast<const unsigned*>(plane + r * kPitch + (x & ~3));
-  const unsigned d0 = p[0], d1 = p[1], d2 = p[2];
-  const unsigned sh = static_cast<unsigned>(x & 3);
-  w0 = static_cast<int>(__builtin_amdgcn_alignbyte(d1, d0, sh));
-  w1 = static_cast<int>(__builtin_amdgcn_alignbyte(d2, d1, sh));
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+typedef __attribute__((address_space(3))) float lds_float;
+
+// 16 bytes at an 8-byte boundary
+__device__ __forceinline__ f16x8 read_row(const lds_byte* p) {
+  typedef __attribute__((address_space(3))) u32x2 lds_u32x2;
+  const u32x2 a = *(const lds_u32x2*)p, b = *(const lds_u32x2*)(p + 8);
+  return __builtin_bit_cast(f16x8, u32x4{a.x, a.y, b.x, b.y});
 }
 
-// MFMA operand of the block at LDS (row, col): rows 2g, 2g + 1 of the block,
-// 8 bytes each, for the h and l planes (byte j of the 16 <-> k = 16 g + j,
-// block pixel (2g + j / 8, j % 8); the same map for both operands).
-__device__ __forceinline__ void load_operand(const unsigned char* hp, const unsigned char* lp, int row, int col, int g,
-                                             i32x4& oh, i32x4& ol) {
-  int a0, a1, a2, a3;
-  seg8(hp, row + 2 * g, col, a0, a1);
-  seg8(hp, row + 2 * g + 1, col, a2, a3);
-  oh = i32x4{a0, a1, a2, a3};
-  seg8(lp, row + 2 * g, col, a0, a1);
-  seg8(lp, row + 2 * g + 1, col, a2, a3);
-  ol = i32x4{a0, a1, a2, a3};
+__device__ __forceinline__ unsigned join(unsigned lo, unsigned hi) { return __builtin_amdgcn_alignbit(hi, lo, 16); }
+
+// x[0]^2 + x[1]^2 of a pair of f16
+__device__ __forceinline__ float square2(unsigned x) {
+  const f16x2 h = __builtin_bit_cast(f16x2, x);
+  return __builtin_amdgcn_fdot2(h, h, 0.0f, false);
 }
 
-// One work item: reference rows [4 pb, 4 pb + 4) x columns [4 TPW qb, 4 TPW (qb + 1)).
-template <int K, int TPW, int SPLIT>
+// Exact key of reference block (ry, rx) and candidate (cy, cx) of the tile's
+// pixel planes, rank the candidate's displacement rank.  |a - b| is formed on
+// packed u16 and its square from byte digits, 65536 hh + 512 hl + ll, each
+// sum of 64 terms below 2^23.
+__device__ __forceinline__ double exact_key(const unsigned char* smem, int ry, int rx, int cy, int cx, int rank) {
+  const unsigned char* pa = smem + ((cx & 1) ? Smem::pix1 : Smem::pix0) + cy * kPixPitch + 2 * (cx & ~1);
+  const unsigned char* pb = smem + ((rx & 1) ? Smem::pix1 : Smem::pix0) + ry * kPixPitch + 2 * (rx & ~1);
+  unsigned hh = 0, hl = 0, ll = 0;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const unsigned* a = reinterpret_cast<const unsigned*>(pa + r * kPixPitch);
+    const unsigned* b = reinterpret_cast<const unsigned*>(pb + r * kPixPitch);
+    unsigned d[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const u16x2 x = __builtin_bit_cast(u16x2, a[i]), y = __builtin_bit_cast(u16x2, b[i]);
+      const u16x2 e = __builtin_elementwise_max(x, y) - __builtin_elementwise_min(x, y);
+      d[i] = __builtin_bit_cast(unsigned, e);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {
+      const unsigned h = __builtin_amdgcn_perm(d[i + 1], d[i], 0x07050301u);
+      const unsigned l = __builtin_amdgcn_perm(d[i + 1], d[i], 0x06040200u);
+      hh = __builtin_amdgcn_udot4(h, h, hh, false);
+      hl = __builtin_amdgcn_udot4(h, l, hl, false);
+      ll = __builtin_amdgcn_udot4(l, l, ll, false);
+    }
+  }
+  const double dist = fma(static_cast<double>(hh), 65536.0, fma(static_cast<double>(hl), 512.0, static_cast<double>(ll)));
+  return fma(dist, 2048.0, static_cast<double>(rank));
+}
+
+// The widened bound on the approximate half distances of a reference, from
+// the K-th best of its group bests, `half`, and hn = N(b~) / 2.  With
+// t = |a~ - b~| the distance that half stands for and e = 2^-11 the relative
+// rounding of f16, a candidate at approximate distance <= t has true distance
+// at most t + e (|a| + |b|), and a candidate truly that close has approximate
+// distance at most t + e (4 |b~| + 2 t) to first order in e (|a| <= |b| + t
+// for both).  The accumulation of a half distance, 64 products and the start
+// value, is off by less than 2^-17 (|b~| + t)^2 (65 roundings of 2^-23 of sums
+// below (|b~| + t)^2); this counts twice.
+__device__ __forceinline__ float widened_bound(float half, float hn) {
+  const float nb = __builtin_amdgcn_sqrtf(2.0f * hn) * 1.000002f, t = __builtin_amdgcn_sqrtf(2.0f * half) * 1.000002f;
+  const float t2 = t + (1.01f / 2048.0f) * (4.0f * nb + 2.0f * t);
+  return 0.500002f * t2 * t2 + 1.0f / 65536.0f * (nb + t2) * (nb + t2);
+}
+
+// How many of the first n entries of list (16-byte aligned, filled up to a
+// multiple of eight with infinities) lie below key.
+__device__ __forceinline__ int entries_below(const double* list, int n, double key) {
+  typedef double f64x2 __attribute__((ext_vector_type(2)));
+  const f64x2* p = reinterpret_cast<const f64x2*>(list);
+  int below = 0;
+  for (int i = 0; i < n; i += 8, p += 4) {
+    const f64x2 a = p[0], b = p[1], c = p[2], d = p[3];
+    below += (a.x < key) + (a.y < key) + (b.x < key) + (b.y < key) + (c.x < key) + (c.y < key) + (d.x < key) +
+             (d.y < key);
+  }
+  return below;
+}
+
+// One work item: the 4 x 4 references of a tile (raster order).  Wave
+// (wy, wx) = (wave / 4, wave % 4) takes the blocks of rows 2 q + wy and columns
+// 4 k + wx, q < Q, k < C: a group's candidates (one wave, row g, column i) are
+// at least 8 rows or 16 columns apart, so no two of a cluster share a group,
+// and a block's place is its wave's plus a constant.  Q x C covers the grid of
+// blocks_per_axis(R) squared; WIDE: it is 12 x 12 (R >= 18), where the blocks
+// of the middle rows and columns lie inside every window.
+template <int Q, int C, bool WIDE>
 __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* __restrict__ img_,
-                                          const double* __restrict__ norm_, int16_t* __restrict__ idx_, int H, int W,
-                                          int R, int item) {
+                                          int16_t* __restrict__ idx_, int H, int W, int R, int K, int item) {
   const auto img = to_global(img_);
-  const auto norm = to_global(norm_);
   const auto idx = to_global(idx_);
-  static_assert(TPW * SPLIT == 4, "four waves per workgroup");
-  using Smem = CorrSmem<K, TPW, SPLIT>;
-  constexpr int L = K - 1;
-  unsigned char* hp = smem;
-  unsigned char* lp = smem + kRows * kPitch;
-  double* buf = reinterpret_cast<double*>(smem + Smem::kPlanes);
-  unsigned long long* bound = reinterpret_cast<unsigned long long*>(smem + Smem::kPlanes + Smem::kBufBytes);
-
   const int nRy = (H + kStep - 1) / kStep, nRx = (W + kStep - 1) / kStep;
-  const int S = 2 * R + 1;
-  const int nb = (2 * R + 10 + 3) / 4;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = wave_id();
-  const int t = wave / SPLIT, part = wave % SPLIT;
-  const int g = lane >> 4, n = lane & 15;
-  const int u = n >> 2, v = n & 3;
-  const int segs = corr_col_items<TPW>(W);
-  const int p0 = (item / segs) * 4;
-  const int q0 = (item % segs) * 4 * TPW;
-  const int qt = q0 + 4 * t;  // first reference column of this wave's tile
-
-  // LDS planes of the image region rows 3 p0 - R + [0, 4 nb + 7), columns 3 q0 - R + [0, kPitch)
+  const int tiles_x = (nRx + 3) / 4;
+  const int S = 2 * R + 1, nb = blocks_per_axis(R), rows = 4 * nb + 7;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = wave_id();
+  const int g = lane >> 4, n = lane & 15, u = n >> 2, v = n & 3;
+  const int p0 = item / tiles_x * 4, q0 = item % tiles_x * 4;
   const int y0 = kStep * p0 - R, x0 = kStep * q0 - R;
-  const int rows = 4 * nb + 7;
-  // y0 < H and x0 < W: rows and columns wrap at most once when the image
-  // is at least as tall as the region and as wide as a plane row
-  const bool near = H >= rows && W >= kPitch;
-  // the reference's norm-table entry, loaded ahead of the fill (from an
-  // in-bounds column also for a tile right of the last reference column,
-  // whose value is not used)
-  const int We = norm_pitch(W);
-  const int cr = kStep * (qt + v) + kNormPad;
-  const double nref = norm[static_cast<size_t>(kStep * (p0 + u) + kNormPad) * We + min(cr, We - 1)];
-  // every thread's pixel loads are issued before the first is used: one
-  // memory round trip for the whole fill instead of one per item
-  constexpr int kFillThreads = 256;
-  constexpr int kFillIter = (kRows * (kPitch / 4) + kFillThreads - 1) / kFillThreads;
-  const int n_fill = rows * (kPitch / 4);
-  unsigned zv[kFillIter][4];
+
+  // the u16 plane: rows y0 .., columns x0 .. x0 + 55, a wave a row and a lane
+  // a column, all loads issued before the first store; rows and columns wrap
+  // at most once when the image is larger than the region and its margin
+  {
+    static_assert(kPixCols <= kWave, "a row per wave");
+    constexpr int kIter = (kRows + kWaves - 1) / kWaves;
+    const int xl = x0 + lane, x = W >= kWave + kMaxR ? xl + (xl < 0 ? W : (xl >= W ? -W : 0)) : pmod(xl, W);
+    unsigned short z[kIter];
+    const bool near = H >= kRows + kMaxR;
 #pragma unroll
-  for (int it = 0; it < kFillIter; ++it) {
-    const int i = static_cast<int>(threadIdx.x) + it * kFillThreads;
-    if (i < n_fill) {
-      const int r = i / (kPitch / 4), c = (i - r * (kPitch / 4)) * 4;
-      int y = y0 + r, xb = x0 + c;
-      if (near) {
-        y += y < 0 ? H : (y >= H ? -H : 0);
-        xb += xb < 0 ? W : (xb >= W ? -W : 0);
-      } else {
-        y = pmod(y, H);
-        xb = pmod(xb, W);
-      }
+    for (int it = 0; it < kIter; ++it) {
+      const int r = wave + it * kWaves;
+      int y = y0 + r;
+      y = near ? y + (y < 0 ? H : (y >= H ? -H : 0)) : pmod(y, H);
+      if (r < rows) z[it] = (img + static_cast<size_t>(y) * W)[x];
+    }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int x = xb + j < W ? xb + j : xb + j - W;  // W >= 8 > j
-        zv[it][j] = img[static_cast<size_t>(y) * W + x];
-      }
+    for (int it = 0; it < kIter; ++it) {
+      const int r = wave + it * kWaves;
+      if (r < rows && lane < kPixCols)
+        *reinterpret_cast<uint16_t*>(smem + Smem::pix0 + r * kPixPitch + 2 * lane) = z[it];
     }
   }
-#pragma unroll
-  for (int it = 0; it < kFillIter; ++it) {
-    const int i = static_cast<int>(threadIdx.x) + it * kFillThreads;
-    if (i < n_fill) {
-      const int r = i / (kPitch / 4), c = (i - r * (kPitch / 4)) * 4;
-      unsigned wh = 0, wl = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        wh |= ((zv[it][j] >> 8) ^ 0x80u) << (8 * j);
-        wl |= ((zv[it][j] & 0xFFu) ^ 0x80u) << (8 * j);
-      }
-      reinterpret_cast<unsigned*>(hp + r * kPitch)[c / 4] = wh;
-      reinterpret_cast<unsigned*>(lp + r * kPitch)[c / 4] = wl;
-    }
-  }
-  if constexpr (SPLIT > 1) {
-    bound[threadIdx.x] = __double_as_longlong(kInf);
-    bound[blockDim.x + threadIdx.x] = __double_as_longlong(kInf);
+  if (tid < 16) {
+    reinterpret_cast<int*>(smem + Smem::count)[tid] = 0;
+    reinterpret_cast<int*>(smem + Smem::kept)[tid] = 0;
   }
   __syncthreads();
 
-  // this lane's reference (p0 + u, qt + v): operand rows 2g, 2g + 1, and norm
-  i32x4 rh, rl;
-  load_operand(hp, lp, R + 3 * u, R + 12 * t + 3 * v, g, rh, rl);
-  // Keys are held less this lane's reference constant A = 2048 N(a) - F(a)
-  // + R S + R, with F the position term of the norm table (its entry at the
-  // reference is 2048 N(a) + F(a)): a candidate's key is then its table entry
-  // less the correlation terms, and the four quarters and SPLIT waves that
-  // compare or merge keys share the reference, so A is added only to the
-  // final list (a tile right of the last reference column only takes part
-  // in the merges)
-  const int f_ref = (kStep * (p0 + u) + kNormPad) * S + cr;
-  const double key_a = qt < nRx ? nref - static_cast<double>(2 * f_ref - R * S - R) : 0.0;
-  // table entries of this lane's result candidates: block (br, bc) row g, columns 0..3
-  const auto ncand = norm + static_cast<size_t>(y0 + g + kNormPad) * We + (x0 + 12 * t + kNormPad);
-
-  double list[L];
+  // the shifted u16 plane, the f16 copies and the horizontal norm sums, eight
+  // columns per item.  Sums of eight squares are formed in one association
+  // for every column, so equal blocks get equal norms.
+  {
+    const unsigned centre = *reinterpret_cast<const uint16_t*>(smem + Smem::pix0 + (R + 8) * kPixPitch + 2 * (R + 8));
+    const float shift = -0.5f * static_cast<float>(centre);
+    constexpr int kCols = kPixCols / 8;  // 7
+    static_assert(kRows * kCols <= kThreads, "one item per thread");
+    const int r = tid / kCols, q = tid - r * kCols;
+    if (r < rows) {
+      const unsigned char* src = smem + Smem::pix0 + r * kPixPitch + 16 * q;
+      // (the last item has no pixels past its own and repeats them)
+      const unsigned char* src2 = src + (q < kCols - 1 ? 16 : 0);
+      unsigned w[8], P[8], O[7];
 #pragma unroll
-  for (int i = 0; i < L; ++i) list[i] = kInf;
-  double thr = kInf;  // no key at or above it can enter the list
-  double* mybuf = buf + wave * kBuf<K> * kWave + lane;
-  // this lane's next free buffer slot, an LDS address held in a register:
-  // an append is one add and a store, and the compiler branches over the
-  // appends that no lane makes
-  lds_double* const buf0 = (lds_double*)(mybuf);
-  lds_double* wp = buf0;
-  pin(wp);
-  const int r_center = R * S + R;
-
-  // the two bounds over the 4 SPLIT lists of this reference (a published
-  // value may be stale: lists only improve, so it stays a valid bound)
-  constexpr int M = (L + 4 * SPLIT - 1) / (4 * SPLIT);
-  auto publish = [&]() {
-    double b1 = fmin(list[L - 1], shfl_xor_double(list[L - 1], 16));
-    b1 = fmin(b1, shfl_xor_double(b1, 32));
-    double b2 = fmax(list[M - 1], shfl_xor_double(list[M - 1], 16));
-    b2 = fmax(b2, shfl_xor_double(b2, 32));
-    if constexpr (SPLIT > 1) {
-      unsigned long long* bmax = bound + 4 * kWave;
-      __hip_atomic_store(bound + wave * kWave + lane, static_cast<unsigned long long>(__double_as_longlong(b1)),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      __hip_atomic_store(bmax + wave * kWave + lane, static_cast<unsigned long long>(__double_as_longlong(b2)),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-#pragma unroll
-      for (int s2 = 0; s2 < SPLIT; ++s2) {
-        const int o = (t * SPLIT + s2) * kWave + lane;
-        b1 = fmin(b1, __longlong_as_double(static_cast<long long>(
-                          __hip_atomic_load(bound + o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))));
-        b2 = fmax(b2, __longlong_as_double(static_cast<long long>(
-                          __hip_atomic_load(bmax + o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))));
+      for (int k = 0; k < 4; ++k) {
+        const u32x2 t = *reinterpret_cast<const u32x2*>(k < 2 ? src + 8 * k : src2 + 8 * (k - 2));
+        w[2 * k] = t.x;
+        w[2 * k + 1] = t.y;
       }
-    }
-    thr = fmin(b1, b2);
-  };
-  auto flush = [&]() {
-    merge_buffer<L, kBuf<K>>(list, mybuf, kWave, static_cast<int>(wp - buf0) / kWave);
-    wp = buf0;
-    pin(wp);
-    publish();
-  };
-
-  if (qt < nRx) {
-    const int nblk = nb * nb;
-    // Block j of the walk: its entry in the walk order (row << 8 | column,
-    // a scalar load), this lane's four candidate norms (global loads), its
-    // operands (LDS) and its products (matrix cores).  Past the end of the
-    // walk the last block's entry is read and what follows from it is never
-    // used, so every load is unconditional and the wait before a block's use
-    // covers its own loads only.
-    auto order = [&](int j) { return kOrder.b[nb][j < nblk ? j : nblk - 1]; };
-    auto load_norms = [&](int b, double (&nv)[4]) {
-      const auto nc = ncand + static_cast<size_t>(4 * (b >> 8)) * We + 4 * (b & 255);
+      u32x2* odd = reinterpret_cast<u32x2*>(smem + Smem::pix1 + r * kPixPitch + 16 * q);
+      odd[0] = u32x2{join(w[0], w[1]), join(w[1], w[2])};
+      odd[1] = u32x2{join(w[2], w[3]), join(w[3], w[4])};
 #pragma unroll
-      for (int i = 0; i < 4; ++i) nv[i] = nc[i];
-    };
-    struct Ops {
-      i32x4 ch, cl;
-    };
-    // operand: candidate m = n -> block row n / 4, column n % 4
-    auto operands = [&](int b, Ops& o) {
-      load_operand(hp, lp, 4 * (b >> 8) + (n >> 2), 12 * t + 4 * (b & 255) + (n & 3), g, o.ch, o.cl);
-    };
-    struct Prod {
-      i32x4 hh, cc, ll;
-    };
-    // the block's four exact byte-plane products
-    auto products = [&](const Ops& o, Prod& pr) {
-      const i32x4 zero = {0, 0, 0, 0};
-      pr.hh = __builtin_amdgcn_mfma_i32_16x16x64_i8(o.ch, rh, zero, 0, 0, 0);
-      pr.cc = __builtin_amdgcn_mfma_i32_16x16x64_i8(o.ch, rl, zero, 0, 0, 0);
-      pr.cc = __builtin_amdgcn_mfma_i32_16x16x64_i8(o.cl, rh, pr.cc, 0, 0, 0);
-      pr.ll = __builtin_amdgcn_mfma_i32_16x16x64_i8(o.cl, rl, zero, 0, 0, 0);
-    };
-    // the block's keys from its norms and products
-    auto keys_of = [&](int b, const double (&nv)[4], const Prod& pr, auto warm, double (&keys)[4]) {
-      const int br = b >> 8, bc = b & 255;
-      const i32x4 hh = pr.hh, cc = pr.cc, ll = pr.ll;
-      // result lane (g, n): candidates (4 br + g, 4 bc + i) vs reference (3u, 3v), in window units
-      const int ey = 4 * br + g - 3 * u;     // dy + R
-      const int ex0 = 4 * bc - 3 * v;        // dx + R for i = 0
-      const bool row_ok = static_cast<unsigned>(ey) <= static_cast<unsigned>(2 * R);
-      // key = 2048 (N(a) + N(b) - 512 s - 2 Pll) + rank, held less A: the
-      // table entry 2048 N(b) + F(b) less the correlation terms, every
-      // intermediate an integer below 2^50 in magnitude
-      // the reference itself (dy = dx = 0) is candidate ic of this block in at most a few lanes
-      const int ic = R - ex0;
-      const bool center_here = ey == R && static_cast<unsigned>(ic) < 4u;
-      auto pairs = [&](auto check_center) {
+      for (int k = 0; k < 8; ++k)
+        P[k] = __builtin_bit_cast(
+            unsigned, __builtin_convertvector(f32x2{fmaf(static_cast<float>(w[k] & 0xFFFFu), 0.5f, shift),
+                                                    fmaf(static_cast<float>(w[k] >> 16), 0.5f, shift)},
+                                              f16x2));
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int s = hh[i] * 256 + cc[i];  // 256 Phh + Phl + Plh, |s| < 2^29
-          const double key =
-              fma(-1048576.0, static_cast<double>(s), fma(-4096.0, static_cast<double>(ll[i]), nv[i]));
-          // (bitwise: no short-circuit branches)
-          bool ok = row_ok & (static_cast<unsigned>(ex0 + i) <= static_cast<unsigned>(2 * R));
-          if constexpr (decltype(check_center)::value) ok = ok & !(center_here & (i == ic));
-          if constexpr (decltype(warm)::value) {
-            keys[i] = ok ? key : kInf;
-          } else if (ok & (key < thr)) {
-            *wp = key;
-            wp += kWave;
-            pin(wp);
-          }
-        }
-      };
-      if (wave_any(center_here))
-        pairs(std::true_type{});
-      else
-        pairs(std::false_type{});
-      if constexpr (!decltype(warm)::value) {
-        if (wave_any(wp > buf0 + kFlushAt<K> * kWave)) flush();
+      for (int k = 0; k < 7; ++k) O[k] = join(P[k], P[k + 1]);
+      unsigned char* dst = smem + Smem::f16 + r * kF16Pitch + 16 * q;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (h == 1 && q == kCols - 1) break;  // the f16 planes end in half an item
+        const int e = 2 * h;
+        *reinterpret_cast<u32x2*>(dst + 8 * h) = u32x2{P[e], P[e + 1]};
+        *reinterpret_cast<u32x2*>(dst + 8 * h + kF16Copy) = u32x2{O[e], O[e + 1]};
+        *reinterpret_cast<u32x2*>(dst + 8 * h + 2 * kF16Copy) = u32x2{P[e + 1], P[e + 2]};
+        *reinterpret_cast<u32x2*>(dst + 8 * h + 3 * kF16Copy) = u32x2{O[e + 1], O[e + 2]};
       }
-    };
-    // Warm start: the first kWarm blocks of this part give each lane four
-    // candidates per block; sorted, they are its first list, and the lists
-    // hold enough keys for a finite m-th-best bound at once.
-    constexpr int kWarm = L < 16 ? 1 : 2;
-    {
-      double seed[4 * kWarm];
+      if (q < kCols - 1) {
+        float e[7], o[7];
 #pragma unroll
-      for (int w = 0; w < kWarm; ++w) {
-        double k4[4] = {kInf, kInf, kInf, kInf};
-        const int jw = part + w * SPLIT;
-        if (jw < nblk) {
-          const int bw = order(jw);
-          double nvw[4];
-          Ops ow;
-          Prod pw;
-          load_norms(bw, nvw);
-          operands(bw, ow);
-          products(ow, pw);
-          keys_of(bw, nvw, pw, std::true_type{}, k4);
+        for (int k = 0; k < 7; ++k) {
+          e[k] = square2(P[k]);
+          o[k] = square2(O[k]);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) seed[4 * w + i] = k4[i];
+        for (int k = 0; k < 6; ++k) {
+          e[k] += e[k + 1];
+          o[k] += o[k + 1];
+        }
+        f32x4* sums = reinterpret_cast<f32x4*>(smem + Smem::sums + r * kSumPitch + 32 * q);
+        sums[0] = f32x4{e[0] + e[2], o[0] + o[2], e[1] + e[3], o[1] + o[3]};
+        sums[1] = f32x4{e[2] + e[4], o[2] + o[4], e[3] + e[5], o[3] + o[5]};
       }
-      bitonic_sort<4 * kWarm>(seed);
-#pragma unroll
-      for (int i = 0; i < L && i < 4 * kWarm; ++i) list[i] = seed[i];
-      publish();
     }
-    double unused[4];
-    // Software pipeline over the rest of the walk, in steps of SPLIT blocks:
-    // while block j's keys are formed, block j + 2 SPLIT's operands are read
-    // from LDS, and its products and norms are issued right after, two steps
-    // ahead of their use.  Two register sets of norms and products alternate.
-    const int jb = part + kWarm * SPLIT;
-    int b0 = order(jb), b1 = order(jb + SPLIT), b2 = order(jb + 2 * SPLIT);
-    double nv0[4], nv1[4];
-    Prod p0, p1;
-    Ops op;
-    // (issued in walk order: the waits in the loop count on the older loads
-    // landing first)
-    load_norms(b0, nv0);
-    __builtin_amdgcn_sched_barrier(0);
-    load_norms(b1, nv1);
-    operands(b0, op);
-    products(op, p0);
-    operands(b1, op);
-    products(op, p1);
-    auto step = [&](int j, double (&nvc)[4], Prod& pc) {
-      operands(b2, op);
-      keys_of(b0, nvc, pc, std::false_type{}, unused);
-      products(op, pc);
-      load_norms(b2, nvc);
-      b0 = b1;
-      b1 = b2;
-      b2 = order(j + 3 * SPLIT);
-    };
-    // whole pairs of steps in the loop and an odd last step after it: every
-    // path into a step then comes from the step of the other register set,
-    // whose loads are the younger ones the wait may leave in flight
-    const int steps = jb < nblk ? (nblk - jb + SPLIT - 1) / SPLIT : 0;
-    int j = jb;
-#pragma unroll 1
-    for (int s2 = 0; s2 + 1 < steps; s2 += 2, j += 2 * SPLIT) {
-      step(j, nv0, p0);
-      step(j + SPLIT, nv1, p1);
-    }
-    if (steps & 1) step(j, nv0, p0);
   }
-  if (wave_any(wp != buf0)) flush();
+  __syncthreads();
+  // accumulator starts N / 2 + position term, eight rows of a column per item
+  {
+    constexpr int kSegs = kCand / 8;
+    static_assert(kSegs * kCand <= kThreads, "one item per thread");
+    const int col = tid % kCand, seg = tid / kCand;
+    const bool active = seg < kSegs && 8 * seg < 4 * nb && col < 4 * nb;
+    float a[15];
+    if (active) {
+      const float* h = reinterpret_cast<const float*>(smem + Smem::sums) + 8 * seg * kCand + col;
+#pragma unroll
+      for (int k = 0; k < 15; ++k) a[k] = h[k * kCand];  // (rows past the region only reach unused outputs)
+#pragma unroll
+      for (int k = 0; k < 14; ++k) a[k] += a[k + 1];
+#pragma unroll
+      for (int k = 0; k < 12; ++k) a[k] += a[k + 2];
+    }
+    __syncthreads();
+    if (active) {
+      float* c = reinterpret_cast<float*>(smem + Smem::init + 8 * seg * kInitPitch) + col;
+      const float row = kTieStep * static_cast<float>(S);
+      float at = kTieStep * static_cast<float>(8 * seg * S + col);  // (exact: whole multiples below 2^11)
+#pragma unroll
+      for (int k = 0; k < 8; ++k, at += row) c[k * (kInitPitch / 4)] = fmaf(a[k] + a[k + 4], 0.5f, at);
+    }
+  }
+  __syncthreads();
 
-  // the four quarters of each reference, then the SPLIT waves of the tile
-  merge_sorted<L>(list, [&](int j) { return shfl_xor_double(list[j], 16); });
-  merge_sorted<L>(list, [&](int j) { return shfl_xor_double(list[j], 32); });
-  if constexpr (SPLIT > 1) {
-    __syncthreads();  // planes, buffers and bounds are dead
-    double* ml = reinterpret_cast<double*>(smem);
-    auto put = [&](int slot) {
+  // half distances: operand lane (g, m) holds row 4 h + g of candidate m
+  // (block row m / 4, column m % 4) or, negated, of reference m, so product h
+  // covers block rows 4 h .. 4 h + 3; result lane (g, n) holds candidates (row
+  // g, columns 0..3) against reference n
+  constexpr int kSteps = Q * C;
+  const int wy = wave >> 2, wx = wave & 3;
+  auto half_norm = [&](int ref) {
+    return reinterpret_cast<const float*>(smem + Smem::init)[(R + 3 * (ref >> 2)) * (kInitPitch / 4) + R + 3 * (ref & 3)];
+  };
+  unsigned half[kSteps][2];  // bf16 pairs, truncated: columns 0, 1 and 2, 3
+  {
+    // the lanes whose window holds row g of block row q / column i of block column k
+    unsigned long long row_in[Q], col_in[C][4];
 #pragma unroll
-      for (int i = 0; i < L; ++i) ml[(slot * L + i) * kWave + lane] = list[i];
-    };
-    auto take = [&](int slot) {
-      const double* b = ml + slot * L * kWave + lane;
-      merge_sorted<L>(list, [&](int j) { return b[j * kWave]; });
-    };
-    if constexpr (SPLIT == 2) {
-      if (part == 1) put(t);
-      __syncthreads();
-      if (part == 0) take(t);
-    } else {
-      if (part & 1) put(part >> 1);
-      __syncthreads();
-      if (!(part & 1)) take(part >> 1);
-      __syncthreads();
-      if (part == 2) put(0);
-      __syncthreads();
-      if (part == 0) take(0);
+    for (int q = 0; q < Q; ++q)
+      row_in[q] = __builtin_amdgcn_ballot_w64(static_cast<unsigned>(8 * q + 4 * wy + g - 3 * u) <= static_cast<unsigned>(2 * R));
+#pragma unroll
+    for (int k = 0; k < C; ++k)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        col_in[k][i] =
+            __builtin_amdgcn_ballot_w64(static_cast<unsigned>(16 * k + 4 * wx + i - 3 * v) <= static_cast<unsigned>(2 * R));
+    const int rc = R + 3 * v;
+    const lds_byte* rp = (const lds_byte*)(smem + Smem::f16 + (rc & 3) * kF16Copy + (R + 3 * u + g) * kF16Pitch + (rc >> 2) * 8);
+    const f16x8 b0 = -read_row(rp), b1 = -read_row(rp + 4 * kF16Pitch);
+    const float hn = half_norm(n);
+    // (one address register per row of blocks: the reads of a row reach their
+    // columns by instruction offsets)
+    const lds_byte* ap[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      ap[q] = (const lds_byte*)(smem + Smem::f16 + v * kF16Copy + (8 * q + 4 * wy + u + g) * kF16Pitch + 8 * wx);
+      asm("" : "+v"(ap[q]));
     }
-    if (part != 0) return;
+    const lds_byte* cp = (const lds_byte*)(smem + Smem::init + (4 * wy + u) * kInitPitch + 16 * wx + 4 * v);
+    constexpr float kInf = __builtin_huge_valf();
+    float best[4] = {kInf, kInf, kInf, kInf};
+    // the accumulator starts, N(a~) / 2 + N(b~) / 2, as a float product of
+    // depth 4: lanes g = 0 hold N(a~) / 2 of candidate m and one, lanes g = 1
+    // one and N(b~) / 2 of reference n (reading the start of every result
+    // would take four times the LDS cycles, and an addition per result)
+    const float start_b = g == 0 ? 1.0f : g == 1 ? hn : 0.0f, start_a = g == 1 ? 1.0f : 0.0f;
+    const unsigned long long first_row = __builtin_amdgcn_ballot_w64(g == 0);
+    struct Operands {
+      f16x8 a0, a1;
+      float norm;
+    };
+    auto load = [&](int s) {
+      const int q = s / C, k = s % C;
+      return Operands{read_row(ap[q] + 32 * k), read_row(ap[q] + 32 * k + 4 * kF16Pitch),
+                      *(const lds_float*)(cp + 8 * q * kInitPitch + 64 * k)};
+    };
+    // the next block's operands are read while this one's products run (and
+    // no further ahead: the registers are the occupancy)
+    Operands o = load(0);
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+      const int q = s / C, k = s % C;
+      const float start = __builtin_amdgcn_inverse_ballot_w64(first_row) ? o.norm : start_a;
+      f32x4 c = __builtin_amdgcn_mfma_f32_16x16x4f32(start, start_b, f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_16x16x32_f16(o.a0, b0, c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_16x16x32_f16(o.a1, b1, c, 0, 0, 0);
+      if (s + 1 < kSteps) o = load(s + 1);
+      const bool rows_in = WIDE && (q == 2 || q == 3), cols_in = WIDE && k == 1;
+      float d[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const unsigned long long in = rows_in ? col_in[k][i] : cols_in ? row_in[q] : row_in[q] & col_in[k][i];
+        d[i] = c[i];
+        if (!(rows_in && cols_in)) d[i] = __builtin_amdgcn_inverse_ballot_w64(in) ? d[i] : kInf;
+        best[i] = fminf(best[i], d[i]);
+      }
+      half[s][0] = __builtin_amdgcn_perm(__float_as_uint(d[1]), __float_as_uint(d[0]), 0x07060302u);
+      half[s][1] = __builtin_amdgcn_perm(__float_as_uint(d[3]), __float_as_uint(d[2]), 0x07060302u);
+      asm volatile("" : "+v"(half[s][0]), "+v"(half[s][1]));  // packed here, not at the use
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // the group bests (not below zero, so that their bit patterns are ordered)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) best[i] = fmaxf(best[i], 0.0f);
+    *reinterpret_cast<u32x2*>(smem + Smem::best + n * kBestPitch + (wave * 4 + g) * 8) =
+        u32x2{__builtin_amdgcn_perm(__float_as_uint(best[1]), __float_as_uint(best[0]), 0x07060302u),
+              __builtin_amdgcn_perm(__float_as_uint(best[3]), __float_as_uint(best[2]), 0x07060302u)};
   }
+  __syncthreads();
+  // the K-th smallest of a reference's 128 bests: two references per wave,
+  // their bests two to a lane, bit by bit from the top (the largest prefix
+  // with fewer than K bests below it)
+  constexpr unsigned kInfBits = 0x7F80u;
+  {
+    const unsigned* bp = reinterpret_cast<const unsigned*>(smem + Smem::best + 2 * wave * kBestPitch) + lane;
+    const unsigned w0 = bp[0], w1 = bp[kBestPitch / 4];
+    const unsigned x[2][2] = {{w0 & 0xFFFFu, w0 >> 16}, {w1 & 0xFFFFu, w1 >> 16}};
+    unsigned kth[2] = {0, 0};
+#pragma unroll
+    for (int bit = 14; bit >= 0; --bit)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const unsigned t = kth[j] | 1u << bit;
+        const int below = __builtin_popcountll(__builtin_amdgcn_ballot_w64(x[j][0] < t)) +
+                          __builtin_popcountll(__builtin_amdgcn_ballot_w64(x[j][1] < t));
+        kth[j] = below < K ? t : kth[j];
+      }
+    if (lane < 2) {
+      const int ref = 2 * wave + lane;
+      const unsigned k = lane ? kth[1] : kth[0];
+      unsigned b = kInfBits - 1;  // fewer than K groups have a candidate: all pass
+      if (k < kInfBits) b = min(b, __float_as_uint(widened_bound(__uint_as_float(k << 16 | 0xFFFFu), half_norm(ref))) >> 16);
+      reinterpret_cast<unsigned*>(smem + Smem::bound)[ref] = b << 16 | b;
+    }
+  }
+  __syncthreads();
+  // candidates past the bound: one bit per half distance, and each lane's
+  // place among its reference's candidates
+  int* count = reinterpret_cast<int*>(smem + Smem::count);
+  int* start = reinterpret_cast<int*>(smem + Smem::start);
+  constexpr int kPer = kSteps % 6 == 0 ? 6 : 4;  // blocks per mask word
+  constexpr int kWords = kSteps / kPer, kLow = 16 - 2 * kPer;
+  static_assert(kSteps % kPer == 0 && kWords <= 3, "whole mask words");
+  unsigned pass[kWords];
+  int n_pass = 0;
+  {
+    typedef short s16x2 __attribute__((ext_vector_type(2)));
+    const s16x2 bound = __builtin_bit_cast(s16x2, reinterpret_cast<const unsigned*>(smem + Smem::bound)[n]);
+#pragma unroll
+    for (int w = 0; w < kWords; ++w) {
+      unsigned m = 0;
+      // (the signs of bound - half, shifted into both halves from the top)
+#pragma unroll
+      for (int t = 0; t < 2 * kPer; ++t) {
+        const s16x2 d = __builtin_elementwise_sub_sat(bound, __builtin_bit_cast(s16x2, half[w * kPer + t / 2][t & 1]));
+        m = m >> 1 | (__builtin_bit_cast(unsigned, d) & 0x80008000u);
+      }
+      pass[w] = ~m & (((1u << 2 * kPer) - 1) << kLow) * 0x10001u;
+      n_pass += __builtin_popcount(pass[w]);
+    }
+  }
+  const int place = n_pass ? atomicAdd(count + n, n_pass) : 0;
+  __syncthreads();
 
-  const int p = p0 + u, q = qt + v;
-  if (g == 0 && p < nRy && q < nRx) {
-    const auto out = idx + (static_cast<size_t>(p) * nRx + q) * K;
-    out[0] = static_cast<int16_t>(r_center);
-#pragma unroll
-    for (int i = 0; i < L; ++i) {
-      out[1 + i] = key_rank(list[i] + key_a);
+  // exact keys and slots, as many references at a time as the queue holds
+  // (nearly always all 16): their candidates' codes (reference << 12 |
+  // row << 6 | column) end to end, each list padded to a multiple of eight
+  uint16_t* codes = reinterpret_cast<uint16_t*>(smem + Smem::codes);
+  double* keys = reinterpret_cast<double*>(smem + Smem::keys);
+  constexpr unsigned kPad = 0xFFFFu;
+  for (int first = 0; first < 16;) {
+    // lane (g, n): the padded length of reference n's list, and the sum of the
+    // lengths up to it (along the 16 lanes of a row)
+    const int c = count[n], c8 = n >= first ? (c + 7) & ~7 : 0;
+    int upto = c8;
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xF, 0xF, true);  // row_shr:1
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xF, 0xF, true);  // row_shr:2
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xF, 0xF, true);  // row_shr:4
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xF, 0xF, true);  // row_shr:8
+    const int my_start = upto - c8;
+    const unsigned full = static_cast<unsigned>(__builtin_amdgcn_ballot_w64(upto > kQueue)) & 0xFFFFu;
+    const int last = full ? __builtin_ctz(full) : 16;  // > first: a list always fits an empty queue
+    const int total = __builtin_amdgcn_readlane(upto, last - 1);
+    const bool here = n >= first && n < last;
+    const bool long_lists = wave_any(here && c > kPrune);
+    if (wave == 0 && here) {
+      if (g == 0) start[n] = my_start;
+      for (int e = (c & ~7) + g; e < c8; e += 4)
+        if (e >= c) codes[my_start + e] = kPad;
     }
+    if (n_pass && here) {
+      int at = my_start + place;
+      const int mine = n << 12 | (4 * wy + g) << 6 | 4 * wx;
+#pragma unroll
+      for (int w = 0; w < kWords; ++w)
+        for (unsigned m = pass[w]; m != 0; m &= m - 1) {
+          const int bit = __builtin_ctz(m), t = (bit & 15) - kLow, s = w * kPer + (t >> 1), q = s / C, k = s - q * C;
+          codes[at++] = static_cast<uint16_t>(mine + 512 * q + 16 * k + 2 * (t & 1) + (bit >> 4));
+        }
+    }
+    __syncthreads();
+    for (int f = tid; f < total; f += kThreads) {
+      const unsigned code = codes[f], k = code >> 12, cy = code >> 6 & 63, cx = code & 63;
+      const int dy = static_cast<int>(cy) - 3 * static_cast<int>(k >> 2), dx = static_cast<int>(cx) - 3 * static_cast<int>(k & 3);
+      // (the reference itself takes no slot among the others)
+      double key = __builtin_huge_val();
+      if (code != kPad && (dy != R || dx != R))
+        key = exact_key(smem, R + 3 * (k >> 2), R + 3 * (k & 3), cy, cx, dy * S + dx);
+      keys[f] = key;
+    }
+    __syncthreads();
+    if (long_lists) {
+      // a long list: the (K-1)-th smallest of its first kPrune keys is a bound,
+      // and only the keys up to it stay (in their places, the others infinite)
+      double* prune = reinterpret_cast<double*>(smem + Smem::prune);
+      for (int f = tid; f < total; f += kThreads) {
+        const unsigned code = codes[f];
+        const int k = code >> 12, at = f - start[k];
+        if (code != kPad && count[k] > kPrune && at < kPrune && entries_below(keys + start[k], kPrune, keys[f]) == K - 2)
+          prune[k] = keys[f];
+      }
+      __syncthreads();
+      int* kept = reinterpret_cast<int*>(smem + Smem::kept);
+      double mine[kQueue / kThreads];
+#pragma unroll
+      for (int m = 0; m < kQueue / kThreads; ++m) {
+        const int f = tid + m * kThreads;
+        const unsigned code = f < total ? codes[f] : kPad;
+        const int k = code >> 12;
+        mine[m] = __builtin_huge_val();
+        if (code != kPad && count[k] > kPrune && keys[f] <= prune[k]) mine[m] = keys[f];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < kQueue / kThreads; ++m) {
+        const int f = tid + m * kThreads;
+        const unsigned code = f < total ? codes[f] : kPad;
+        const int k = code >> 12;
+        if (code != kPad && count[k] > kPrune) keys[f] = __builtin_huge_val();
+      }
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < kQueue / kThreads; ++m)
+        if (mine[m] < __builtin_huge_val()) {
+          const int k = codes[tid + m * kThreads] >> 12;
+          keys[start[k] + atomicAdd(kept + k, 1)] = mine[m];
+        }
+      __syncthreads();
+    }
+    // a key's slot is the number of smaller keys of its reference
+    for (int f = tid; f < total; f += kThreads) {
+      const double key = keys[f];
+      const int k = codes[f] >> 12, p = p0 + (k >> 2), q = q0 + (k & 3);
+      if (key == __builtin_huge_val()) continue;
+      const int n_keys = count[k] > kPrune ? reinterpret_cast<const int*>(smem + Smem::kept)[k] : count[k];
+      const int rank = entries_below(keys + start[k], n_keys, key);
+      if (rank < K - 1 && p < nRy && q < nRx)
+        idx[(static_cast<size_t>(p) * nRx + q) * K + 1 + rank] =
+            static_cast<int16_t>(key - 2048.0 * floor(key * (1.0 / 2048.0)));
+    }
+    first = last;
+    if (first < 16) __syncthreads();  // the queue is reused
   }
+  if (tid < 16 && p0 + (tid >> 2) < nRy && q0 + (tid & 3) < nRx)
+    idx[(static_cast<size_t>(p0 + (tid >> 2)) * nRx + q0 + (tid & 3)) * K] = static_cast<int16_t>(R * S + R);
 }
 
-// The second launch bound is the waves per SIMD that the registers must
-// allow: what the LDS of a workgroup allows for K = 16 (four workgroups of
-// four waves per CU) and K = 32 (three); smaller groups are held by neither.
-template <int K>
-constexpr int kCorrWaves = K == 16 ? 4 : K == 32 ? 3 : 2;
-
-template <int K, int TPW, int SPLIT, bool BATCH>
-__global__ __launch_bounds__(256, kCorrWaves<K>) void bm_corr_kernel(ImgRec one, WorkList wl, int R, int use_pilot) {
-  __shared__ __align__(16) unsigned char smem[CorrSmem<K, TPW, SPLIT>::bytes];
+template <int Q, int C, bool WIDE, bool BATCH>
+__global__ __launch_bounds__(kThreads, 6) void bm_corr_kernel(ImgRec one, WorkList wl, int R, int K, int use_pilot) {
+  __shared__ __align__(16) unsigned char smem[Smem::bytes];
   if constexpr (!BATCH) {
     // Workgroups go to the eight XCDs in turn (g -> XCD g mod 8): XCD x takes
     // the x-th eighth of the items, a band of reference rows, so each XCD's
-    // L2 fetches its band's planes and norm-table rows instead of the whole
-    // image.  The grid is 8 q; items past the last exit at once.
-    const int n = corr_items<TPW>(one.H, one.W), q = (n + 7) / 8;
-    const int g = static_cast<int>(blockIdx.x);
-    const int item = (g & 7) * q + (g >> 3);
+    // L2 fetches its band's pixels instead of the whole image.  The grid is
+    // 8 q; items past the last exit at once.
+    const int n = corr_items(one.H, one.W), q = (n + 7) / 8;
+    const int b = static_cast<int>(blockIdx.x);
+    const int item = (b & 7) * q + (b >> 3);
     if (item >= n) return;
-    corr_body<K, TPW, SPLIT>(smem, use_pilot ? one.pilot : one.noisy, one.norm, one.idx, one.H, one.W, R, item);
+    corr_body<Q, C, WIDE>(smem, use_pilot ? one.pilot : one.noisy, one.idx, one.H, one.W, R, K, item);
   } else {
-    for_each_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
-      corr_body<K, TPW, SPLIT>(smem, use_pilot ? r.pilot : r.noisy, r.norm, r.idx, r.H, r.W, R, item);
-    });
+    int first;
+    const int item = static_cast<int>(blockIdx.x);
+    const const_rec_ptr r = find_item(wl, item, first);
+    corr_body<Q, C, WIDE>(smem, use_pilot ? r->pilot : r->noisy, r->idx, r->H, r->W, R, K, item - first);
   }
 }
 
-template <int K, int TPW, int SPLIT>
-hipError_t launch_corr_shape(const ImgRec& one, const WorkList* wl, int R, int use_pilot, int grid_cap,
-                             hipStream_t st) {
+template <int Q, int C, bool WIDE>
+hipError_t launch_corr_grid(const ImgRec& one, const WorkList* wl, int R, int K, int use_pilot, hipStream_t st) {
   if (!wl) {
-    hipLaunchKernelGGL((bm_corr_kernel<K, TPW, SPLIT, false>), dim3(8 * ((corr_items<TPW>(one.H, one.W) + 7) / 8)), dim3(256), 0, st,
-                       one, WorkList{}, R, use_pilot);
+    hipLaunchKernelGGL((bm_corr_kernel<Q, C, WIDE, false>), dim3(8 * ((corr_items(one.H, one.W) + 7) / 8)),
+                       dim3(kThreads), 0, st, one, WorkList{}, R, K, use_pilot);
   } else {
     if (wl->total <= 0) return hipSuccess;
-    hipLaunchKernelGGL((bm_corr_kernel<K, TPW, SPLIT, true>), dim3(std::min(wl->total, grid_cap)), dim3(256), 0, st,
-                       one, *wl, R, use_pilot);
+    hipLaunchKernelGGL((bm_corr_kernel<Q, C, WIDE, true>), dim3(wl->total), dim3(kThreads), 0, st, one, *wl, R, K,
+                       use_pilot);
   }
   return hipGetLastError();
-}
-
-template <int K>
-hipError_t launch_corr_k(const ImgRec& one, const WorkList* wl, int R, int split, int use_pilot, int grid_cap,
-                         hipStream_t st) {
-  switch (split) {
-    case 1: return launch_corr_shape<K, 4, 1>(one, wl, R, use_pilot, grid_cap, st);
-    case 2: return launch_corr_shape<K, 2, 2>(one, wl, R, use_pilot, grid_cap, st);
-    case 4: return launch_corr_shape<K, 1, 4>(one, wl, R, use_pilot, grid_cap, st);
-    default: return hipErrorInvalidValue;
-  }
 }
 
 }  // namespace
 
-size_t norm_bytes(int H, int W) {
-  return static_cast<size_t>(H + 2 * kNormPad) * (W + 2 * kNormPad) * sizeof(double);
-}
+int corr_items_for(int H, int W) { return corr_items(H, W); }
 
-int norm_items_for(int H, int W) { return norm_items(H, W); }
+long corr_tiles(int H, int W) { return static_cast<long>(corr_items(H, W)); }
 
-int corr_items_for(int H, int W, int split) {
-  switch (split) {
-    case 1: return corr_items<4>(H, W);
-    case 2: return corr_items<2>(H, W);
-    default: return corr_items<1>(H, W);
-  }
-}
-
-long corr_tiles(int H, int W) { return static_cast<long>(corr_items<1>(H, W)); }
-
-int corr_auto_split(long tiles) { return tiles >= 4096 ? 1 : (tiles >= 2048 ? 2 : 4); }
-
-hipError_t launch_bm_norm(const ImgRec& one, const WorkList* wl, int R, int use_pilot, int grid_cap,
-                          hipStream_t st) {
-  if (!wl) {
-    hipLaunchKernelGGL((bm_norm_kernel<false>), dim3(norm_items(one.H, one.W)), dim3(256), 0, st, one, WorkList{}, R,
-                       use_pilot);
-  } else {
-    if (wl->total <= 0) return hipSuccess;
-    hipLaunchKernelGGL((bm_norm_kernel<true>), dim3(std::min(wl->total, grid_cap)), dim3(256), 0, st, one, *wl, R,
-                       use_pilot);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_bm_corr(const ImgRec& one, const WorkList* wl, int R, int K, int split, int use_pilot, int grid_cap,
-                          hipStream_t st) {
-  if (split <= 0) split = corr_auto_split(corr_tiles(one.H, one.W));
-  switch (K) {
-    case 2: return launch_corr_k<2>(one, wl, R, split, use_pilot, grid_cap, st);
-    case 4: return launch_corr_k<4>(one, wl, R, split, use_pilot, grid_cap, st);
-    case 8: return launch_corr_k<8>(one, wl, R, split, use_pilot, grid_cap, st);
-    case 16: return launch_corr_k<16>(one, wl, R, split, use_pilot, grid_cap, st);
-    case 32: return launch_corr_k<32>(one, wl, R, split, use_pilot, grid_cap, st);
-    default: return hipErrorInvalidValue;
-  }
+hipError_t launch_bm_corr(const ImgRec& one, const WorkList* wl, int R, int K, int use_pilot, hipStream_t st) {
+  if (K < 2 || K > 32 || R < 0 || R > kMaxR) return hipErrorInvalidValue;
+  const int nb = blocks_per_axis(R);
+  if (nb <= 8) return launch_corr_grid<4, 2, false>(one, wl, R, K, use_pilot, st);
+  if (nb < kMaxNb) return launch_corr_grid<6, 3, false>(one, wl, R, K, use_pilot, st);
+  return launch_corr_grid<6, 3, true>(one, wl, R, K, use_pilot, st);
 }
 
 }  // namespace gbm3d

@@ -84,7 +84,7 @@ void* scratch_addr(int dev) {
 }
 
 // Work lists of the batch phases: per-image prefix offsets of the items.
-enum Phase { kNorm1, kBm1, kStack1, kGroup1, kReduce1, kNorm2, kBm2, kStack2, kGroup2, kReduce2, kPhases };
+enum Phase { kBm1, kStack1, kGroup1, kReduce1, kBm2, kStack2, kGroup2, kReduce2, kPhases };
 
 struct BatchPlan {
   std::vector<ImgRec> recs;
@@ -128,7 +128,7 @@ struct gbm3d_ctx {
   int device = 0;
   int n_cu = 256;
   std::string err;
-  Buffer stack_a, stack_b, idx, partials, basic, q, norm;
+  Buffer stack_a, stack_b, idx, partials, basic, q;
   // global stage 1
   Buffer gl_a, gl_b, gl_num, gl_idx, gl_shift, gl_pad, gl_out;
   // block-matching choices per (K, shape class)
@@ -361,33 +361,13 @@ int choose_shape(const gbm3d_ctx* ctx, const gbm3d_params& p, long tiles) {
   return shape;
 }
 
-// The correlation kernel's norm table: r.norm when set, else the context's.
-int bind_norm(gbm3d_ctx* ctx, ImgRec& r) {
-  if (!r.norm) {
-    CHECK(ensure(ctx, ctx->norm, gbm3d::norm_bytes(r.H, r.W), "norm table"));
-    r.norm = static_cast<double*>(ctx->norm.p);
-  }
-  return GBM3D_OK;
-}
-
 // Block matching of one image (r.noisy, or r.pilot with use_pilot) into r.idx.
-// norm_ready: the correlation kernel's norm table is already in r.norm (formed
-// by the stack launch before it).
-int run_match(gbm3d_ctx* ctx, ImgRec& r, int R, int K, const BmChoice& c, int use_pilot, hipStream_t st,
-              bool norm_ready = false) {
-  if (c.method == GBM3D_BM_CORR) {
-    CHECK(bind_norm(ctx, r));
-    if (!norm_ready)
-      HIP_TRY(ctx, timed(ctx, "bm_norm", st, [&] { return gbm3d::launch_bm_norm(r, nullptr, R, use_pilot, 0, st); }),
-              "norm table launch");
-    HIP_TRY(ctx, timed(ctx, "bm", st, [&] {
-              return gbm3d::launch_bm_corr(r, nullptr, R, K, c.split, use_pilot, 0, st);
-            }),
-            "block matching launch");
-  } else {
-    HIP_TRY(ctx, timed(ctx, "bm", st, [&] { return gbm3d::launch_bm(r, nullptr, R, K, c.split, use_pilot, 0, st); }),
-            "block matching launch");
-  }
+int run_match(gbm3d_ctx* ctx, ImgRec& r, int R, int K, const BmChoice& c, int use_pilot, hipStream_t st) {
+  HIP_TRY(ctx, timed(ctx, "bm", st, [&] {
+            return c.method == GBM3D_BM_CORR ? gbm3d::launch_bm_corr(r, nullptr, R, K, use_pilot, st)
+                                             : gbm3d::launch_bm(r, nullptr, R, K, c.split, use_pilot, 0, st);
+          }),
+          "block matching launch");
   return GBM3D_OK;
 }
 
@@ -404,7 +384,6 @@ struct Workspace {
   float* stack_b = nullptr;
   int16_t* idx = nullptr;
   unsigned long long* partials = nullptr;
-  double* norm = nullptr;
 };
 
 // Stage 1 of one image into `basic` (and optionally its quantisation into q).
@@ -433,22 +412,12 @@ int run_basic(gbm3d_ctx* ctx, const uint16_t* noisy, int H, int W, float sigma, 
   r.stack_a = recompute ? nullptr : w.stack_a;
   r.idx = w.idx;
   r.partials = w.partials;
-  r.norm = w.norm;
   r.eps = tv_eps(p, sigma);
   const BmChoice c = choose_bm(ctx, p, gbm3d::corr_tiles(H, W), p.k_ht);
+  CHECK(run_match(ctx, r, R, p.k_ht, c, 0, st));
   if (recompute) {
-    CHECK(run_match(ctx, r, R, p.k_ht, c, 0, st));
     HIP_TRY(ctx, gbm3d::launch_clear_weights(r, st), "weight clearing launch");
-  } else if (c.method == GBM3D_BM_CORR) {
-    // the stack and the matcher's norm table in one launch, then the matching
-    CHECK(bind_norm(ctx, r));
-    HIP_TRY(ctx, timed(ctx, "stack_bior", st, [&] {
-              return gbm3d::launch_stack_norm(r, 0, 0, 0, R, 0, st);
-            }),
-            "stack launch");
-    CHECK(run_match(ctx, r, R, p.k_ht, c, 0, st, true));
   } else {
-    CHECK(run_match(ctx, r, R, p.k_ht, c, 0, st));
     HIP_TRY(ctx, timed(ctx, "stack_bior", st, [&] { return gbm3d::launch_stack(r, nullptr, 0, 0, 0, 0, st); }),
             "stack launch");
   }
@@ -487,22 +456,10 @@ int run_wiener(gbm3d_ctx* ctx, const uint16_t* noisy, const uint16_t* pilot, int
   r.stack_b = w.stack_b;
   r.idx = w.idx;
   r.partials = w.partials;
-  r.norm = w.norm;
-  // the noisy and the pilot's DCT stacks in one launch, with the matcher's
-  // norm table of the pilot when the correlation kernel matches
-  const BmChoice c = choose_bm(ctx, p, gbm3d::corr_tiles(H, W), p.k_wiener);
-  if (c.method == GBM3D_BM_CORR) {
-    CHECK(bind_norm(ctx, r));
-    HIP_TRY(ctx, timed(ctx, "stack_dct", st, [&] {
-              return gbm3d::launch_stack_norm(r, 1, -1, -1, R, 1, st);
-            }),
-            "stack launch");
-    CHECK(run_match(ctx, r, R, p.k_wiener, c, 1, st, true));
-  } else {
-    CHECK(run_match(ctx, r, R, p.k_wiener, c, 1, st));
-    HIP_TRY(ctx, timed(ctx, "stack_dct", st, [&] { return gbm3d::launch_stack(r, nullptr, 1, -1, -1, 0, st); }),
-            "stack launch");
-  }
+  CHECK(run_match(ctx, r, R, p.k_wiener, choose_bm(ctx, p, gbm3d::corr_tiles(H, W), p.k_wiener), 1, st));
+  // the noisy and the pilot's DCT stacks in one launch
+  HIP_TRY(ctx, timed(ctx, "stack_dct", st, [&] { return gbm3d::launch_stack(r, nullptr, 1, -1, -1, 0, st); }),
+          "stack launch");
   HIP_TRY(ctx, timed(ctx, "group_wiener", st, [&] {
             return gbm3d::launch_group_wiener(r, nullptr, R, p.k_wiener, 0, st);
           }),
@@ -547,14 +504,13 @@ int plan_batch(gbm3d_ctx* ctx, const gbm3d_image* imgs, int n, const gbm3d_param
   const BmChoice c1 = choose_bm(ctx, p, tiles1, p.k_ht), c2 = choose_bm(ctx, p, tiles2, p.k_wiener);
   plan.bm_method1 = c1.method;
   plan.bm_method2 = c2.method;
-  auto split_of = [](const BmChoice& c, long tiles, long waves) {
-    if (c.split > 0) return c.split;
-    return c.method == GBM3D_BM_CORR ? gbm3d::corr_auto_split(tiles) : gbm3d::bm_auto_split(waves);
+  auto split_of = [](const BmChoice& c, long waves) {
+    if (c.method == GBM3D_BM_CORR) return 1;
+    return c.split > 0 ? c.split : gbm3d::bm_auto_split(waves);
   };
-  plan.bm_split1 = split_of(c1, tiles1, waves1);
-  plan.bm_split2 = split_of(c2, tiles2, waves2);
+  plan.bm_split1 = split_of(c1, waves1);
+  plan.bm_split2 = split_of(c2, waves2);
   plan.ht_shape = choose_shape(ctx, p, tiles1);
-  const bool need_norm = (tiles1 > 0 && c1.method == GBM3D_BM_CORR) || (tiles2 > 0 && c2.method == GBM3D_BM_CORR);
   // workspace slices
   size_t total = 0;
   std::vector<size_t> off(n);
@@ -562,7 +518,6 @@ int plan_batch(gbm3d_ctx* ctx, const gbm3d_image* imgs, int n, const gbm3d_param
     const int H = imgs[i].H, W = imgs[i].W;
     const bool s1 = imgs[i].pilot == nullptr;
     off[i] = total;
-    if (need_norm) total += align256(gbm3d::norm_bytes(H, W));              // norm table
     total += align256(stack_bytes(H, W));                                   // stack_a
     if (!basic_only) total += align256(stack_bytes(H, W));                  // stack_b
     total += align256(n_refs(H, W) * kmax * sizeof(int16_t));               // idx
@@ -578,10 +533,6 @@ int plan_batch(gbm3d_ctx* ctx, const gbm3d_image* imgs, int n, const gbm3d_param
     const bool s1 = im.pilot == nullptr;
     ImgRec r = blank_rec(H, W, im.sigma);
     char* c = base + off[i];
-    if (need_norm) {
-      r.norm = reinterpret_cast<double*>(c);
-      c += align256(gbm3d::norm_bytes(H, W));
-    }
     r.stack_a = reinterpret_cast<float*>(c);
     c += align256(stack_bytes(H, W));
     if (!basic_only) {
@@ -617,13 +568,11 @@ int plan_batch(gbm3d_ctx* ctx, const gbm3d_image* imgs, int n, const gbm3d_param
     const bool s2 = !basic_only;
     const bool corr1 = plan.bm_method1 == GBM3D_BM_CORR, corr2 = plan.bm_method2 == GBM3D_BM_CORR;
     const int items[kPhases] = {
-        s1 && corr1 ? gbm3d::norm_items_for(H, W) : 0,
-        s1 ? (corr1 ? gbm3d::corr_items_for(H, W, plan.bm_split1) : gbm3d::bm_items_for(H, W, plan.bm_split1)) : 0,
+        s1 ? (corr1 ? gbm3d::corr_items_for(H, W) : gbm3d::bm_items_for(H, W, plan.bm_split1)) : 0,
         s1 ? gbm3d::stack_items_for(H, W) : 0,
         s1 ? gbm3d::group_items_for(H, W, R) : 0,
         s1 ? gbm3d::reduce_items_for(H, W) : 0,
-        s2 && corr2 ? gbm3d::norm_items_for(H, W) : 0,
-        s2 ? (corr2 ? gbm3d::corr_items_for(H, W, plan.bm_split2) : gbm3d::bm_items_for(H, W, plan.bm_split2)) : 0,
+        s2 ? (corr2 ? gbm3d::corr_items_for(H, W) : gbm3d::bm_items_for(H, W, plan.bm_split2)) : 0,
         s2 ? gbm3d::stack_items_for(H, W) : 0,
         s2 ? gbm3d::group_items_for(H, W, R) : 0,
         s2 ? gbm3d::reduce_items_for(H, W) : 0,
@@ -658,28 +607,18 @@ WorkList worklist(const gbm3d_ctx* ctx, const BatchPlan& plan, int n, int phase)
 // Grid cap of the batch launches: none (one workgroup per item).
 constexpr int kFullGrid = 1 << 30;
 
-// Batch matching of a stage, norm tables first when the correlation kernel
-// matches, then its stacks (kind 0: the bior1.5 stack of the noisy images;
-// 1: the DCT stacks of the noisy images and of the pilots).  Unlike a single
-// image, a batch keeps the norm tables in a launch of their own: carried by
-// the stack launch they made the 64-image batch slower (913 vs 940
-// Mpixel/s).
-int launch_batch_prep(gbm3d_ctx* ctx, const WorkList& sk, const WorkList& nm, const WorkList& bm, int R, int K,
-                      int method, int split, int kind, hipStream_t st) {
+// Batch matching of a stage, then its stacks (kind 0: the bior1.5 stack of the
+// noisy images; 1: the DCT stacks of the noisy images and of the pilots).
+int launch_batch_prep(gbm3d_ctx* ctx, const WorkList& sk, const WorkList& bm, int R, int K, int method, int split,
+                      int kind, hipStream_t st) {
   const ImgRec none = blank_rec(0, 0, 0.0f);
   const int use_pilot = kind;
   const int sel = kind == 0 ? 0 : -1;
-  if (method == GBM3D_BM_CORR) {
-    HIP_TRY(ctx, timed(ctx, "bm_norm", st, [&] { return gbm3d::launch_bm_norm(none, &nm, R, use_pilot, kFullGrid, st); }),
-            "batch norm tables");
-    HIP_TRY(ctx, timed(ctx, "bm", st, [&] {
-              return gbm3d::launch_bm_corr(none, &bm, R, K, split, use_pilot, kFullGrid, st);
-            }),
-            "batch block matching");
-  } else {
-    HIP_TRY(ctx, timed(ctx, "bm", st, [&] { return gbm3d::launch_bm(none, &bm, R, K, split, use_pilot, kFullGrid, st); }),
-            "batch block matching");
-  }
+  HIP_TRY(ctx, timed(ctx, "bm", st, [&] {
+            return method == GBM3D_BM_CORR ? gbm3d::launch_bm_corr(none, &bm, R, K, use_pilot, st)
+                                           : gbm3d::launch_bm(none, &bm, R, K, split, use_pilot, kFullGrid, st);
+          }),
+          "batch block matching");
   HIP_TRY(ctx, timed(ctx, kind == 0 ? "stack_bior" : "stack_dct", st, [&] {
             return gbm3d::launch_stack(none, &sk, kind, sel, sel, kFullGrid, st);
           }),
@@ -697,10 +636,9 @@ int launch_batch(gbm3d_ctx* ctx, const BatchPlan& plan, int n, const gbm3d_param
   const ImgRec none = blank_rec(0, 0, 0.0f);
   if (plan.any_stage1) {
     TraceRange trace("batch stage1");
-    const WorkList nm = worklist(ctx, plan, n, kNorm1), bm = worklist(ctx, plan, n, kBm1);
-    const WorkList sk = worklist(ctx, plan, n, kStack1);
+    const WorkList bm = worklist(ctx, plan, n, kBm1), sk = worklist(ctx, plan, n, kStack1);
     const WorkList gr = worklist(ctx, plan, n, kGroup1), rd = worklist(ctx, plan, n, kReduce1);
-    CHECK(launch_batch_prep(ctx, sk, nm, bm, R, p.k_ht, plan.bm_method1, plan.bm_split1, 0, st));
+    CHECK(launch_batch_prep(ctx, sk, bm, R, p.k_ht, plan.bm_method1, plan.bm_split1, 0, st));
     HIP_TRY(ctx, timed(ctx, "group_ht", st, [&] {
               return gbm3d::launch_group_ht(none, &gr, R, p.k_ht, p.ht_a, p.ht_b, p.ht_weight, p.keep_dc, 0,
                                             plan.ht_shape, kFullGrid,
@@ -712,10 +650,9 @@ int launch_batch(gbm3d_ctx* ctx, const BatchPlan& plan, int n, const gbm3d_param
   }
   if (plan.any_stage2) {
     TraceRange trace("batch stage2");
-    const WorkList nm = worklist(ctx, plan, n, kNorm2), bm = worklist(ctx, plan, n, kBm2);
-    const WorkList sk = worklist(ctx, plan, n, kStack2);
+    const WorkList bm = worklist(ctx, plan, n, kBm2), sk = worklist(ctx, plan, n, kStack2);
     const WorkList gr = worklist(ctx, plan, n, kGroup2), rd = worklist(ctx, plan, n, kReduce2);
-    CHECK(launch_batch_prep(ctx, sk, nm, bm, R, p.k_wiener, plan.bm_method2, plan.bm_split2, 1, st));
+    CHECK(launch_batch_prep(ctx, sk, bm, R, p.k_wiener, plan.bm_method2, plan.bm_split2, 1, st));
     HIP_TRY(ctx, timed(ctx, "group_wiener", st, [&] {
               return gbm3d::launch_group_wiener(none, &gr, R, p.k_wiener, kFullGrid, st);
             }),
@@ -838,8 +775,8 @@ void gbm3d_destroy(gbm3d_ctx* ctx) {
     DeviceGuard g(ctx->device);
     (void)hipDeviceSynchronize();
     drop_graph(ctx);
-    for (Buffer* b : {&ctx->stack_a, &ctx->stack_b, &ctx->idx, &ctx->partials, &ctx->basic, &ctx->q, &ctx->norm, &ctx->batch_ws,
-                      &ctx->batch_table, &ctx->pilot_w, &ctx->pilot_act, &ctx->pilot_part, &ctx->gl_a, &ctx->gl_b,
+    for (Buffer* b : {&ctx->stack_a, &ctx->stack_b, &ctx->idx, &ctx->partials, &ctx->basic, &ctx->q, &ctx->batch_ws, &ctx->batch_table,
+                      &ctx->pilot_w, &ctx->pilot_act, &ctx->pilot_part, &ctx->gl_a, &ctx->gl_b,
                       &ctx->gl_num, &ctx->gl_idx, &ctx->gl_shift, &ctx->gl_pad, &ctx->gl_out})
       if (b->p) (void)hipFree(b->p);
     if (ctx->host_stage) (void)hipHostFree(ctx->host_stage);
@@ -940,6 +877,7 @@ int gbm3d_autotune(gbm3d_ctx* ctx, const uint16_t* img, int H, int W, int K, con
   const int R = p.search / 2;
   for (int method : {GBM3D_BM_SHIFT, GBM3D_BM_CORR}) {
     for (int split : {1, 2, 4}) {
+      if (method == GBM3D_BM_CORR && split > 1) continue;  // one launch shape
       const BmChoice c{method, split};
       float ms = 0.0f;
       CHECK(time_runs([&] { return run_match(ctx, r, R, K, c, 0, st); }, ms));
@@ -1253,7 +1191,8 @@ int gbm3d_denoise_noalloc(gbm3d_ctx* ctx, const uint16_t* noisy, int H, int W, f
     off += align256(bytes);
     return o;
   };
-  const size_t o_norm = take(gbm3d::norm_bytes(H, W));
+  // (the first slice is not used; it holds the documented size limit where it is)
+  take(static_cast<size_t>(H + 64) * (W + 64) * sizeof(double));
   const size_t o_sa = take(stack_bytes(H, W));
   const size_t o_sb = take(stack_bytes(H, W));
   const size_t o_idx = take(n_refs(H, W) * std::max(p.k_ht, p.k_wiener) * sizeof(int16_t));
@@ -1268,7 +1207,6 @@ int gbm3d_denoise_noalloc(gbm3d_ctx* ctx, const uint16_t* noisy, int H, int W, f
   char* base = static_cast<char*>(scratch_addr(ctx->device));
   if (!base) return fail(ctx, GBM3D_EHIP, "device scratch of device %d not resolved", ctx->device);
   Workspace ws;
-  ws.norm = reinterpret_cast<double*>(base + o_norm);
   ws.stack_a = reinterpret_cast<float*>(base + o_sa);
   ws.stack_b = reinterpret_cast<float*>(base + o_sb);
   ws.idx = reinterpret_cast<int16_t*>(base + o_idx);

@@ -259,7 +259,6 @@ struct ImgRec {
   unsigned long long* partials;    // 64-bit fixed-point aggregation sums: H*W block-start
                                    // weights, then H*W numerator sums (both cleared by the
                                    // stack launch into stack_a)
-  double* norm;                    // block norms with a periodic border (correlation matching)
   int H, W;
   float sigma, eps;
 };
@@ -338,7 +337,6 @@ __device__ __forceinline__ void for_each_item(const ImgRec& one, const WorkList&
         r.stack_b = recs[i].stack_b;
         r.idx = recs[i].idx;
         r.partials = recs[i].partials;
-        r.norm = recs[i].norm;
         r.H = recs[i].H;
         r.W = recs[i].W;
         r.sigma = recs[i].sigma;
@@ -348,6 +346,20 @@ __device__ __forceinline__ void for_each_item(const ImgRec& one, const WorkList&
       __syncthreads();  // LDS is reused by the next item
     }
   }
+}
+
+// The image owning batch item `item` and, in `first`, that image's first item:
+// for kernels launched with one workgroup per item, which read only the
+// descriptor fields they use (through the returned constant-space pointer, so
+// with scalar loads).
+typedef const __attribute__((address_space(4))) ImgRec* const_rec_ptr;
+__device__ __forceinline__ const_rec_ptr find_item(const WorkList& wl, int item, int& first) {
+  typedef const __attribute__((address_space(4))) int* const_int_ptr;
+  const const_int_ptr begin = (const_int_ptr)wl.begin;
+  int i = ((const_int_ptr)wl.start)[item / kItemBlock];
+  while (begin[i + 1] <= item) ++i;
+  first = begin[i];
+  return (const_rec_ptr)wl.recs + i;
 }
 
 // ---------------------------------------------------------------------------

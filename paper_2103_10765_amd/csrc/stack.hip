@@ -11,7 +11,6 @@
 // 16-byte stores (half-size staging keeps four workgroups per CU).
 #include "common.h"
 #include "kernels.h"
-#include "norm.h"
 
 namespace gbm3d {
 
@@ -151,56 +150,40 @@ __device__ __forceinline__ void stack_body(float (*pix)[kPixCols + 1], float (*s
   __syncthreads();  // the pixel tile and the staging area are reused
 }
 
+// Workgroups up to which a stack launch counts as short: 32 per CU of the 256.
+constexpr int kShortLaunchItems = 32 * 256;
+
 // src_sel: 0 = noisy, 1 = pilot; dst_sel: 0 = stack_a, 1 = stack_b; both
 // negative: blockIdx.y selects (noisy -> stack_a, pilot -> stack_b)
-template <int KIND, bool BATCH>
+template <int KIND, bool BATCH, bool LOADS_FIRST>
 __global__ __launch_bounds__(kStackThreads) void stack_kernel(ImgRec one, WorkList wl, int src_sel, int dst_sel) {
   __shared__ float pix[kPixRows][kPixCols + 1];
   __shared__ float stage[kRowsPerWg][kHalf * kStagePitch];
   const int src = src_sel < 0 ? static_cast<int>(blockIdx.y) : src_sel;
   const int dst = dst_sel < 0 ? static_cast<int>(blockIdx.y) : dst_sel;
   for_each_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
-    stack_body<KIND, false>(pix, stage, src ? r.pilot : r.noisy, dst ? r.stack_b : r.stack_a,
-                            dst ? nullptr : r.partials, r.H, r.W, item);
+    stack_body<KIND, LOADS_FIRST>(pix, stage, src ? r.pilot : r.noisy, dst ? r.stack_b : r.stack_a,
+                                  dst ? nullptr : r.partials, r.H, r.W, item);
   });
 }
 
-// The stacks of a stage beside the correlation matcher's norm table of the
-// image it matches, in one launch over one image: grid rows y < gridDim.y - 1
-// are stack planes as in stack_kernel, the last row the norm items.  The two
-// passes share nothing but the launch: the short, latency-bound norm pass
-// runs in the gaps of the write-bound stack items instead of as a launch of
-// its own.
-// Workgroups (all grid rows) up to which a stack launch counts as short:
-// 32 per CU of the 256.
-constexpr int kShortLaunchItems = 32 * 256;
-
-struct StackSmem {
-  static constexpr int pix_bytes = (kPixRows * (kPixCols + 1) * 4 + 15) / 16 * 16;
-  static constexpr int bytes = pix_bytes + kRowsPerWg * kHalf * kStagePitch * 4;
-};
-
-template <int KIND, bool LOADS_FIRST>
-__global__ __launch_bounds__(kStackThreads) void stack_norm_kernel(ImgRec r, int src_sel, int dst_sel, int R,
-                                                                   int norm_src) {
-  constexpr int kBytes = StackSmem::bytes > NormSmem::bytes ? StackSmem::bytes : NormSmem::bytes;
-  __shared__ __align__(16) unsigned char smem[kBytes];
-  static_assert(kStackThreads == 256, "norm items are laid out for 256 threads");
-  const int item = static_cast<int>(blockIdx.x);
-  if (blockIdx.y == gridDim.y - 1) {
-    if (item >= norm_items(r.H, r.W)) return;
-    int* zt = reinterpret_cast<int*>(smem);
-    double* hs = reinterpret_cast<double*>(smem + NormSmem::zt_bytes);
-    norm_body<LOADS_FIRST>(norm_src ? r.pilot : r.noisy, r.norm, r.H, r.W, R, item, zt, hs);
-    return;
-  }
-  if (item >= stack_items(r.H, r.W)) return;
-  auto pix = reinterpret_cast<float(*)[kPixCols + 1]>(smem);
-  auto stage = reinterpret_cast<float(*)[kHalf * kStagePitch]>(smem + StackSmem::pix_bytes);
-  const int src = src_sel < 0 ? static_cast<int>(blockIdx.y) : src_sel;
-  const int dst = dst_sel < 0 ? static_cast<int>(blockIdx.y) : dst_sel;
-  stack_body<KIND, LOADS_FIRST>(pix, stage, src ? r.pilot : r.noisy, dst ? r.stack_b : r.stack_a,
-                                dst ? nullptr : r.partials, r.H, r.W, item);
+template <int KIND>
+hipError_t launch_stack_kind(const ImgRec& one, const WorkList* wl, int src_sel, int dst_sel, int grid_cap,
+                             hipStream_t st) {
+  const unsigned planes = src_sel < 0 ? 2u : 1u;  // both stacks in one launch
+  const int items = wl ? std::min(wl->total, grid_cap) : stack_items(one.H, one.W);
+  if (items <= 0) return hipSuccess;
+  const dim3 grid(static_cast<unsigned>(items), planes), block(kStackThreads);
+  // A launch of a few workgroups per CU is bound by each workgroup's
+  // latency: there the pixel loads go out all at once (measured: 512^2
+  // faster, 4096^2 slower, where the stack writes bound the launch)
+  if (wl)
+    hipLaunchKernelGGL((stack_kernel<KIND, true, false>), grid, block, 0, st, one, *wl, src_sel, dst_sel);
+  else if (items * static_cast<int>(planes) <= kShortLaunchItems)
+    hipLaunchKernelGGL((stack_kernel<KIND, false, true>), grid, block, 0, st, one, WorkList{}, src_sel, dst_sel);
+  else
+    hipLaunchKernelGGL((stack_kernel<KIND, false, false>), grid, block, 0, st, one, WorkList{}, src_sel, dst_sel);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -210,50 +193,8 @@ int stack_items_for(int H, int W) { return stack_items(H, W); }
 hipError_t launch_stack(const ImgRec& one, const WorkList* wl, int kind, int src_sel, int dst_sel, int grid_cap,
                         hipStream_t st) {
   if ((src_sel < 0) != (dst_sel < 0)) return hipErrorInvalidValue;
-  const unsigned planes = src_sel < 0 ? 2u : 1u;  // both stacks in one launch
-  if (!wl) {
-    const dim3 grid(static_cast<unsigned>(stack_items(one.H, one.W)), planes);
-    if (kind == 0)
-      hipLaunchKernelGGL((stack_kernel<0, false>), grid, dim3(kStackThreads), 0, st, one, WorkList{}, src_sel, dst_sel);
-    else
-      hipLaunchKernelGGL((stack_kernel<1, false>), grid, dim3(kStackThreads), 0, st, one, WorkList{}, src_sel, dst_sel);
-  } else {
-    if (wl->total <= 0) return hipSuccess;
-    const dim3 grid(static_cast<unsigned>(std::min(wl->total, grid_cap)), planes);
-    if (kind == 0)
-      hipLaunchKernelGGL((stack_kernel<0, true>), grid, dim3(kStackThreads), 0, st, one, *wl, src_sel, dst_sel);
-    else
-      hipLaunchKernelGGL((stack_kernel<1, true>), grid, dim3(kStackThreads), 0, st, one, *wl, src_sel, dst_sel);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_stack_norm(const ImgRec& one, int kind, int src_sel, int dst_sel, int R, int norm_src,
-                             hipStream_t st) {
-  if ((src_sel < 0) != (dst_sel < 0)) return hipErrorInvalidValue;
-  const unsigned rows = (src_sel < 0 ? 2u : 1u) + 1u;  // stack planes, then the norm items
-  const int items = std::max(stack_items(one.H, one.W), norm_items(one.H, one.W));
-  const dim3 grid(static_cast<unsigned>(items), rows);
-  // A launch of a few workgroups per CU is bound by each workgroup's
-  // latency: there the pixel loads go out all at once (measured: 512^2
-  // faster, 4096^2 slower, where the stack writes bound the launch)
-  const bool short_launch = items * static_cast<int>(rows) <= kShortLaunchItems;
-  if (kind == 0) {
-    if (short_launch)
-      hipLaunchKernelGGL((stack_norm_kernel<0, true>), grid, dim3(kStackThreads), 0, st, one, src_sel, dst_sel, R,
-                         norm_src);
-    else
-      hipLaunchKernelGGL((stack_norm_kernel<0, false>), grid, dim3(kStackThreads), 0, st, one, src_sel, dst_sel, R,
-                         norm_src);
-  } else {
-    if (short_launch)
-      hipLaunchKernelGGL((stack_norm_kernel<1, true>), grid, dim3(kStackThreads), 0, st, one, src_sel, dst_sel, R,
-                         norm_src);
-    else
-      hipLaunchKernelGGL((stack_norm_kernel<1, false>), grid, dim3(kStackThreads), 0, st, one, src_sel, dst_sel, R,
-                         norm_src);
-  }
-  return hipGetLastError();
+  return kind == 0 ? launch_stack_kind<0>(one, wl, src_sel, dst_sel, grid_cap, st)
+                   : launch_stack_kind<1>(one, wl, src_sel, dst_sel, grid_cap, st);
 }
 
 }  // namespace gbm3d

@@ -613,3 +613,28 @@ def test_large_stages_windows(torch, G, ctx, large_case):
         Yo = O.wiener_estimate(Z, pilot, SIG, O.DEFAULT, ref_ids=ids)
         rows, cols = (y0 + np.arange(h)) % 4096, (x0 + np.arange(w)) % 4096
         assert np.abs(Yw[np.ix_(rows, cols)] - Yo[np.ix_(rows, cols)]).max() <= MAXABS
+
+
+def _tie_image(kind, H, W):
+    rng = np.random.default_rng(77)
+    y, x = np.mgrid[:H, :W]
+    if kind == "checkerboard":     # half the window at distance zero
+        return ((y + x) % 2 * 65535).astype(np.uint16)
+    if kind == "two levels":       # flat regions far apart, noise of a few units: near ties at large norms
+        return (np.where((x // 29 + y // 23) % 2, 52000, 9000) + rng.integers(-3, 4, (H, W))).astype(np.uint16)
+    return np.tile(rng.integers(0, 65536, (8, 8)), (H // 8 + 1, W // 8 + 1))[:H, :W].astype(np.uint16)
+
+
+@pytest.mark.parametrize("kind", ["checkerboard", "two levels", "period 8"])
+@pytest.mark.parametrize("S,K", [(39, 16), (39, 32), (31, 32), (21, 16), (7, 32), (3, 2)])
+def test_match_many_near_ties(torch, G, ctx, kind, S, K):
+    """Images on which many more candidates than K come near the K-th best
+    (the correlation matcher's candidate lists are cut, and go through its
+    queue in several parts), for every shape of its candidate grid."""
+    H, W = 53, 82
+    say("match near ties", kind, S, K)
+    Z = _tie_image(kind, H, W)
+    got = ctx.match(up(torch, Z), K, G.default_params(search=S, bm_method=2)).cpu().numpy().astype(np.int64)
+    exp = O.match(Z, K, O.DEFAULT.with_(search=S))
+    bad = np.nonzero((got != exp).any(axis=1))[0]
+    assert bad.size == 0, (bad[:5], got[bad[:2]], exp[bad[:2]])
