@@ -275,7 +275,7 @@ __device__ __forceinline__ void bm_body(unsigned char* smem, const uint16_t* __r
 template <int K, int RPW, int SPLIT, bool BATCH>
 __global__ __launch_bounds__(256, 2) void bm_kernel(ImgRec one, WorkList wl, int R, int use_pilot) {
   __shared__ __align__(16) unsigned char smem[BmSmem<K, RPW, SPLIT>::bytes];
-  for_each_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
+  for_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
     bm_body<K, RPW, SPLIT>(smem, use_pilot ? r.pilot : r.noisy, r.idx, r.H, r.W, R, item);
   });
 }
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(256, 2) void bm_kernel(ImgRec one, WorkList wl, int
 }  // namespace
 
 template <int K, int RPW, int SPLIT>
-static hipError_t launch_bm_shape(const ImgRec& one, const WorkList* wl, int R, int use_pilot, int grid_cap,
+static hipError_t launch_bm_shape(const ImgRec& one, const WorkList* wl, int R, int use_pilot,
                                   hipStream_t st) {
   if (!wl) {
     const int items = bm_items<RPW>(one.H, one.W);
@@ -291,8 +291,8 @@ static hipError_t launch_bm_shape(const ImgRec& one, const WorkList* wl, int R, 
                        use_pilot);
   } else {
     if (wl->total <= 0) return hipSuccess;
-    const int grid = std::min(wl->total, grid_cap);
-    hipLaunchKernelGGL((bm_kernel<K, RPW, SPLIT, true>), dim3(grid), dim3(256), 0, st, one, *wl, R, use_pilot);
+    hipLaunchKernelGGL((bm_kernel<K, RPW, SPLIT, true>), batch_grid(wl->total), dim3(256), 0, st, one, *wl, R,
+                       use_pilot);
   }
   return hipGetLastError();
 }
@@ -314,25 +314,25 @@ long bm_waves_unsplit(int H, int W) {
 }
 
 template <int K>
-static hipError_t launch_bm_k(const ImgRec& one, const WorkList* wl, int R, int split, int use_pilot, int grid_cap,
+static hipError_t launch_bm_k(const ImgRec& one, const WorkList* wl, int R, int split, int use_pilot,
                               hipStream_t st) {
   switch (split) {
-    case 1: return launch_bm_shape<K, 4, 1>(one, wl, R, use_pilot, grid_cap, st);
-    case 2: return launch_bm_shape<K, 2, 2>(one, wl, R, use_pilot, grid_cap, st);
-    case 4: return launch_bm_shape<K, 1, 4>(one, wl, R, use_pilot, grid_cap, st);
+    case 1: return launch_bm_shape<K, 4, 1>(one, wl, R, use_pilot, st);
+    case 2: return launch_bm_shape<K, 2, 2>(one, wl, R, use_pilot, st);
+    case 4: return launch_bm_shape<K, 1, 4>(one, wl, R, use_pilot, st);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_bm(const ImgRec& one, const WorkList* wl, int R, int K, int split, int use_pilot, int grid_cap,
+hipError_t launch_bm(const ImgRec& one, const WorkList* wl, int R, int K, int split, int use_pilot,
                      hipStream_t st) {
   if (split <= 0) split = bm_auto_split(bm_waves_unsplit(one.H, one.W));
   switch (K) {
-    case 2: return launch_bm_k<2>(one, wl, R, split, use_pilot, grid_cap, st);
-    case 4: return launch_bm_k<4>(one, wl, R, split, use_pilot, grid_cap, st);
-    case 8: return launch_bm_k<8>(one, wl, R, split, use_pilot, grid_cap, st);
-    case 16: return launch_bm_k<16>(one, wl, R, split, use_pilot, grid_cap, st);
-    case 32: return launch_bm_k<32>(one, wl, R, split, use_pilot, grid_cap, st);
+    case 2: return launch_bm_k<2>(one, wl, R, split, use_pilot, st);
+    case 4: return launch_bm_k<4>(one, wl, R, split, use_pilot, st);
+    case 8: return launch_bm_k<8>(one, wl, R, split, use_pilot, st);
+    case 16: return launch_bm_k<16>(one, wl, R, split, use_pilot, st);
+    case 32: return launch_bm_k<32>(one, wl, R, split, use_pilot, st);
     default: return hipErrorInvalidValue;
   }
 }

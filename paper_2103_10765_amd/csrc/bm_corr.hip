@@ -603,7 +603,7 @@ hipError_t launch_corr_grid(const ImgRec& one, const WorkList* wl, int R, int K,
                        dim3(kThreads), 0, st, one, WorkList{}, R, K, use_pilot);
   } else {
     if (wl->total <= 0) return hipSuccess;
-    hipLaunchKernelGGL((bm_corr_kernel<Q, C, WIDE, true>), dim3(wl->total), dim3(kThreads), 0, st, one, *wl, R, K,
+    hipLaunchKernelGGL((bm_corr_kernel<Q, C, WIDE, true>), batch_grid(wl->total), dim3(kThreads), 0, st, one, *wl, R, K,
                        use_pilot);
   }
   return hipGetLastError();

@@ -365,7 +365,7 @@ int choose_shape(const gbm3d_ctx* ctx, const gbm3d_params& p, long tiles) {
 int run_match(gbm3d_ctx* ctx, ImgRec& r, int R, int K, const BmChoice& c, int use_pilot, hipStream_t st) {
   HIP_TRY(ctx, timed(ctx, "bm", st, [&] {
             return c.method == GBM3D_BM_CORR ? gbm3d::launch_bm_corr(r, nullptr, R, K, use_pilot, st)
-                                             : gbm3d::launch_bm(r, nullptr, R, K, c.split, use_pilot, 0, st);
+                                             : gbm3d::launch_bm(r, nullptr, R, K, c.split, use_pilot, st);
           }),
           "block matching launch");
   return GBM3D_OK;
@@ -418,15 +418,15 @@ int run_basic(gbm3d_ctx* ctx, const uint16_t* noisy, int H, int W, float sigma, 
   if (recompute) {
     HIP_TRY(ctx, gbm3d::launch_clear_weights(r, st), "weight clearing launch");
   } else {
-    HIP_TRY(ctx, timed(ctx, "stack_bior", st, [&] { return gbm3d::launch_stack(r, nullptr, 0, 0, 0, 0, st); }),
+    HIP_TRY(ctx, timed(ctx, "stack_bior", st, [&] { return gbm3d::launch_stack(r, nullptr, 0, 0, 0, st); }),
             "stack launch");
   }
   HIP_TRY(ctx, timed(ctx, "group_ht", st, [&] {
             return gbm3d::launch_group_ht(r, nullptr, R, p.k_ht, p.ht_a, p.ht_b, p.ht_weight, p.keep_dc, recompute,
-                                          choose_shape(ctx, p, gbm3d::corr_tiles(H, W)), 0, st);
+                                          choose_shape(ctx, p, gbm3d::corr_tiles(H, W)), st);
           }),
           "hard-threshold group launch");
-  HIP_TRY(ctx, timed(ctx, "reduce", st, [&] { return gbm3d::launch_reduce(r, nullptr, 0, 0, st); }),
+  HIP_TRY(ctx, timed(ctx, "reduce", st, [&] { return gbm3d::launch_reduce(r, nullptr, 0, st); }),
           "aggregation launch");
   return GBM3D_OK;
 }
@@ -458,13 +458,13 @@ int run_wiener(gbm3d_ctx* ctx, const uint16_t* noisy, const uint16_t* pilot, int
   r.partials = w.partials;
   CHECK(run_match(ctx, r, R, p.k_wiener, choose_bm(ctx, p, gbm3d::corr_tiles(H, W), p.k_wiener), 1, st));
   // the noisy and the pilot's DCT stacks in one launch
-  HIP_TRY(ctx, timed(ctx, "stack_dct", st, [&] { return gbm3d::launch_stack(r, nullptr, 1, -1, -1, 0, st); }),
+  HIP_TRY(ctx, timed(ctx, "stack_dct", st, [&] { return gbm3d::launch_stack(r, nullptr, 1, -1, -1, st); }),
           "stack launch");
   HIP_TRY(ctx, timed(ctx, "group_wiener", st, [&] {
-            return gbm3d::launch_group_wiener(r, nullptr, R, p.k_wiener, 0, st);
+            return gbm3d::launch_group_wiener(r, nullptr, R, p.k_wiener, st);
           }),
           "Wiener group launch");
-  HIP_TRY(ctx, timed(ctx, "reduce", st, [&] { return gbm3d::launch_reduce(r, nullptr, 1, 0, st); }),
+  HIP_TRY(ctx, timed(ctx, "reduce", st, [&] { return gbm3d::launch_reduce(r, nullptr, 1, st); }),
           "aggregation launch");
   return GBM3D_OK;
 }
@@ -604,9 +604,6 @@ WorkList worklist(const gbm3d_ctx* ctx, const BatchPlan& plan, int n, int phase)
   return w;
 }
 
-// Grid cap of the batch launches: none (one workgroup per item).
-constexpr int kFullGrid = 1 << 30;
-
 // Batch matching of a stage, then its stacks (kind 0: the bior1.5 stack of the
 // noisy images; 1: the DCT stacks of the noisy images and of the pilots).
 int launch_batch_prep(gbm3d_ctx* ctx, const WorkList& sk, const WorkList& bm, int R, int K, int method, int split,
@@ -616,11 +613,11 @@ int launch_batch_prep(gbm3d_ctx* ctx, const WorkList& sk, const WorkList& bm, in
   const int sel = kind == 0 ? 0 : -1;
   HIP_TRY(ctx, timed(ctx, "bm", st, [&] {
             return method == GBM3D_BM_CORR ? gbm3d::launch_bm_corr(none, &bm, R, K, use_pilot, st)
-                                           : gbm3d::launch_bm(none, &bm, R, K, split, use_pilot, kFullGrid, st);
+                                           : gbm3d::launch_bm(none, &bm, R, K, split, use_pilot, st);
           }),
           "batch block matching");
   HIP_TRY(ctx, timed(ctx, kind == 0 ? "stack_bior" : "stack_dct", st, [&] {
-            return gbm3d::launch_stack(none, &sk, kind, sel, sel, kFullGrid, st);
+            return gbm3d::launch_stack(none, &sk, kind, sel, sel, st);
           }),
           "batch stacks");
   return GBM3D_OK;
@@ -641,11 +638,11 @@ int launch_batch(gbm3d_ctx* ctx, const BatchPlan& plan, int n, const gbm3d_param
     CHECK(launch_batch_prep(ctx, sk, bm, R, p.k_ht, plan.bm_method1, plan.bm_split1, 0, st));
     HIP_TRY(ctx, timed(ctx, "group_ht", st, [&] {
               return gbm3d::launch_group_ht(none, &gr, R, p.k_ht, p.ht_a, p.ht_b, p.ht_weight, p.keep_dc, 0,
-                                            plan.ht_shape, kFullGrid,
+                                            plan.ht_shape,
                                             st);
             }),
             "batch hard-threshold groups");
-    HIP_TRY(ctx, timed(ctx, "reduce", st, [&] { return gbm3d::launch_reduce(none, &rd, 0, kFullGrid, st); }),
+    HIP_TRY(ctx, timed(ctx, "reduce", st, [&] { return gbm3d::launch_reduce(none, &rd, 0, st); }),
             "batch aggregation");
   }
   if (plan.any_stage2) {
@@ -654,10 +651,10 @@ int launch_batch(gbm3d_ctx* ctx, const BatchPlan& plan, int n, const gbm3d_param
     const WorkList gr = worklist(ctx, plan, n, kGroup2), rd = worklist(ctx, plan, n, kReduce2);
     CHECK(launch_batch_prep(ctx, sk, bm, R, p.k_wiener, plan.bm_method2, plan.bm_split2, 1, st));
     HIP_TRY(ctx, timed(ctx, "group_wiener", st, [&] {
-              return gbm3d::launch_group_wiener(none, &gr, R, p.k_wiener, kFullGrid, st);
+              return gbm3d::launch_group_wiener(none, &gr, R, p.k_wiener, st);
             }),
             "batch Wiener groups");
-    HIP_TRY(ctx, timed(ctx, "reduce", st, [&] { return gbm3d::launch_reduce(none, &rd, 1, kFullGrid, st); }),
+    HIP_TRY(ctx, timed(ctx, "reduce", st, [&] { return gbm3d::launch_reduce(none, &rd, 1, st); }),
             "batch aggregation");
   }
   return GBM3D_OK;
@@ -981,7 +978,7 @@ int gbm3d_stack(gbm3d_ctx* ctx, const uint16_t* img, int H, int W, int kind, flo
   ImgRec r = blank_rec(H, W, 1.0f);
   r.noisy = img;
   r.stack_a = out;
-  HIP_TRY(ctx, gbm3d::launch_stack(r, nullptr, kind, 0, 0, 0, static_cast<hipStream_t>(stream)), "stack launch");
+  HIP_TRY(ctx, gbm3d::launch_stack(r, nullptr, kind, 0, 0, static_cast<hipStream_t>(stream)), "stack launch");
   return GBM3D_OK;
 }
 

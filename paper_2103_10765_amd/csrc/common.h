@@ -244,8 +244,8 @@ __device__ __forceinline__ void haar_inv_raw(float* v) {
 
 // ---------------------------------------------------------------------------
 // Per-image descriptor and work lists.  Every kernel is a per-work-item body;
-// for one image the grid enumerates its items, for a batch a persistent grid
-// walks a work list whose per-image prefix offsets are in `begin`.
+// for one image the grid enumerates its items, for a batch the items of a work
+// list whose per-image prefix offsets are in `begin`.
 // ---------------------------------------------------------------------------
 struct ImgRec {
   const uint16_t* noisy;           // u16 [H][W]
@@ -300,58 +300,12 @@ __device__ __forceinline__ global_ptr<T> to_global(T* p) {
   return (global_ptr<T>)p;
 }
 
-// Runs body(rec, local_item) for this workgroup's items: the single image's
-// item blockIdx.x, or every batch item blockIdx.x + k * gridDim.x.  The image
-// owning a batch item is found from the image owning the first item of its
-// block of kItemBlock items (start) by stepping forward through the
-// per-image prefix offsets (begin is non-decreasing, begin[0] = 0,
-// begin[n] = total; wave-uniform scalar loads); the descriptor is reloaded
-// only when the image changes.
-template <bool BATCH, typename F>
-__device__ __forceinline__ void for_each_item(const ImgRec& one, const WorkList& wl, F&& body) {
-  if constexpr (!BATCH) {
-    body(one, static_cast<int>(blockIdx.x));
-  } else {
-    // the work list is read-only for the launch: through constant-space
-    // pointers its uniform loads are scalar loads, which wait on the LDS /
-    // scalar counter and not behind the previous item's global stores
-    typedef const __attribute__((address_space(4))) int* const_int_ptr;
-    typedef const __attribute__((address_space(4))) ImgRec* const_rec_ptr;
-    const const_int_ptr begin = (const_int_ptr)wl.begin;
-    const const_int_ptr start = (const_int_ptr)wl.start;
-    const const_rec_ptr recs = (const_rec_ptr)wl.recs;
-    int i = -1, lo = 0, hi = 0;  // image i owns items [lo, hi)
-    ImgRec r;
-    for (int item = blockIdx.x; item < wl.total; item += gridDim.x) {
-      if (item >= hi) {
-        i = start[item / kItemBlock];
-        while (begin[i + 1] <= item) ++i;
-        lo = begin[i];
-        hi = begin[i + 1];
-        r.noisy = recs[i].noisy;
-        r.pilot = recs[i].pilot;
-        r.out = recs[i].out;
-        r.basic = recs[i].basic;
-        r.q = recs[i].q;
-        r.stack_a = recs[i].stack_a;
-        r.stack_b = recs[i].stack_b;
-        r.idx = recs[i].idx;
-        r.partials = recs[i].partials;
-        r.H = recs[i].H;
-        r.W = recs[i].W;
-        r.sigma = recs[i].sigma;
-        r.eps = recs[i].eps;
-      }
-      body(r, item - lo);
-      __syncthreads();  // LDS is reused by the next item
-    }
-  }
-}
-
 // The image owning batch item `item` and, in `first`, that image's first item:
-// for kernels launched with one workgroup per item, which read only the
-// descriptor fields they use (through the returned constant-space pointer, so
-// with scalar loads).
+// from the image owning the first item of its block of kItemBlock items
+// (start) by stepping forward through the per-image prefix offsets (begin is
+// non-decreasing, begin[0] = 0, begin[n] = total).  The work list is read-only
+// for the launch: through constant-space pointers its uniform loads are scalar
+// loads.
 typedef const __attribute__((address_space(4))) ImgRec* const_rec_ptr;
 __device__ __forceinline__ const_rec_ptr find_item(const WorkList& wl, int item, int& first) {
   typedef const __attribute__((address_space(4))) int* const_int_ptr;
@@ -360,6 +314,45 @@ __device__ __forceinline__ const_rec_ptr find_item(const WorkList& wl, int item,
   while (begin[i + 1] <= item) ++i;
   first = begin[i];
   return (const_rec_ptr)wl.recs + i;
+}
+
+// The grid of a batch launch of `total` items: one workgroup each, in slices of
+// 2^21 along z (a launch may have fewer than 2^32 threads in a direction).
+inline dim3 batch_grid(int total, unsigned planes = 1) {
+  constexpr int kSlice = 1 << 21;
+  return dim3(static_cast<unsigned>(total < kSlice ? total : kSlice), planes,
+              static_cast<unsigned>((total - 1) / kSlice + 1));
+}
+
+// Runs body(rec, local_item) for this workgroup's item: the single image's
+// item blockIdx.x, or the batch item of its place in batch_grid (one workgroup
+// per item; the fields a body does not use are not loaded).
+template <bool BATCH, typename F>
+__device__ __forceinline__ void for_item(const ImgRec& one, const WorkList& wl, F&& body) {
+  if constexpr (!BATCH) {
+    body(one, static_cast<int>(blockIdx.x));
+  } else {
+    const unsigned at = blockIdx.z * gridDim.x + blockIdx.x;
+    if (at >= static_cast<unsigned>(wl.total)) return;
+    const int item = static_cast<int>(at);
+    int first;
+    const const_rec_ptr p = find_item(wl, item, first);
+    ImgRec r;
+    r.noisy = p->noisy;
+    r.pilot = p->pilot;
+    r.out = p->out;
+    r.basic = p->basic;
+    r.q = p->q;
+    r.stack_a = p->stack_a;
+    r.stack_b = p->stack_b;
+    r.idx = p->idx;
+    r.partials = p->partials;
+    r.H = p->H;
+    r.W = p->W;
+    r.sigma = p->sigma;
+    r.eps = p->eps;
+    body(r, item - first);
+  }
 }
 
 // ---------------------------------------------------------------------------

@@ -47,34 +47,25 @@ using acc_t = unsigned long long;
 struct Foot {
   static constexpr int FYmax = kStep * (kTPY - 1) + kPatch + 2 * kMaxR;
   static constexpr int FXmax = kStep * (kTPX - 1) + kPatch + 2 * kMaxR;
-  static constexpr int FXPmax = FXmax + ((8 - FXmax) % 32 + 32) % 32;
-  static constexpr int entries = FYmax * FXPmax;
+  // cells per footprint row of every window (so that the rows of a block are
+  // instruction offsets), 8 modulo 32
+  static constexpr int FXP = FXmax + ((8 - FXmax) % 32 + 32) % 32;
+  static constexpr int entries = FYmax * FXP;
 };
 
-// Launch shape of a group kernel.  The hard-threshold kernel (K <= 16; the
-// WIDE shape, which the autotuner may swap for the one-tile shape below) runs
-// two tiles per CU: 12 waves each (six per SIMD), inverse
-// transforms 8 blocks at a time through each wave's scratch, no prefetch of
-// the next group (the other waves hide the loads).  Otherwise one tile per
-// CU: sixteen waves (four per SIMD) where a 16-block scratch per wave fits
-// beside the footprint accumulator and the filter's registers fit a quarter
-// of the register file, else eight; small groups keep the next group's
-// spectra in flight.  The hard-threshold filter holds all K inverse blocks
-// until its weight is known, which does not fit sixteen waves for K = 32;
-// the batched variant carries more state per wave and keeps one tile per CU.
-template <int K, bool HT, bool BATCH, bool WIDE = true>
+// Launch shape of a group kernel.  Two tiles share a CU: 12 waves each (six
+// per SIMD), inverse transforms 8 blocks at a time through each wave's
+// scratch, no prefetch of the next group (the other waves hide the loads).
+// The hard-threshold kernel has a second shape (WIDE = false; K <= 16, which
+// the autotuner may choose): one tile of sixteen waves that keeps the next
+// group's spectra in flight.  Its filter holds all K inverse blocks until its
+// weight is known, so K = 32 runs one tile of eight waves.
+template <int K, bool HT, bool WIDE = true>
 struct GroupCfg {
-  static constexpr bool two_tiles = HT && K <= 16 && WIDE;
+  static constexpr bool two_tiles = !HT || (K <= 16 && WIDE);
   static constexpr int chunk = two_tiles ? (K > 8 ? 8 : K) : (K > 16 ? 16 : K);
   static constexpr int rank_bytes = kTPY * kTPX * K * 2;  // the tile's ranks (int16)
-  static constexpr int waves =
-      two_tiles ? 12
-      : Foot::entries * static_cast<int>(sizeof(acc_t)) +
-                      16 * chunk * kBlockFloats * static_cast<int>(sizeof(float)) + rank_bytes <=
-                  kLdsBytes &&
-              !(HT && K > 16)
-          ? 16
-          : 8;
+  static constexpr int waves = two_tiles ? 12 : K <= 16 ? 16 : 8;
   static constexpr int tiles = two_tiles ? 2 : 1;
   static constexpr bool prefetch = !two_tiles && K <= 16;
   static constexpr int threads = waves * kWave;
@@ -87,7 +78,7 @@ struct GroupCfg {
 
 struct GroupArgs {
   int H, W, R, S, nRy, nRx, nTx, nTy;
-  int FY, FX, FXP;
+  int FY, FX;
   float invS;  // 1 / S for the rank decode
 };
 
@@ -103,7 +94,6 @@ __host__ __device__ inline GroupArgs make_args(int H, int W, int R) {
   g.nTy = (g.nRy + kTPY - 1) / kTPY;
   g.FY = kStep * (kTPY - 1) + kPatch + 2 * R;
   g.FX = kStep * (kTPX - 1) + kPatch + 2 * R;
-  g.FXP = g.FX + ((8 - g.FX) % 32 + 32) % 32;
   g.invS = 1.0f / static_cast<float>(g.S);
   return g;
 }
@@ -169,15 +159,15 @@ __device__ __forceinline__ void slot_pos(const GroupArgs& g, int r, int p, int q
     const int yw = y < 0 ? y + g.H : (y >= g.H ? y - g.H : y);
     const int xw = x < 0 ? x + g.W : (x >= g.W ? x - g.W : x);
     pos = yw * g.W + xw;
-    fo = (y - fy0) * g.FXP + (x - fx0);
+    fo = (y - fy0) * Foot::FXP + (x - fx0);
   }
 }
 
 // w * u[k] into the footprint for blocks k0 .. k0 + N - 1 (u holds their values)
 template <int N>
-__device__ __forceinline__ void accumulate(acc_t* acc, const GroupArgs& g, int fo_v, int k0, const float (&u)[N],
+__device__ __forceinline__ void accumulate(acc_t* acc, int fo_v, int k0, const float (&u)[N],
                                            float w, int lane) {
-  const int ab = (lane >> 3) * g.FXP + (lane & 7);
+  const int ab = (lane >> 3) * Foot::FXP + (lane & 7);
   const float ws = w * kFixScaleF;
 #pragma unroll
   for (int k = 0; k < N; ++k) {
@@ -225,7 +215,7 @@ __device__ __forceinline__ void flush_acc(const acc_t* acc, const GroupArgs& g, 
     int y = fy0 + fy;
     y = once ? y + (y < 0 ? g.H : (y >= g.H ? -g.H : 0)) : pmod(y, g.H);
     const auto row = gnum + static_cast<size_t>(y) * g.W;
-    const acc_t* cells = acc + fy * g.FXP;
+    const acc_t* cells = acc + fy * Foot::FXP;
 #pragma unroll
     for (int p = 0; p < kPasses; ++p) {
       const int fx = p * kWave + lane;
@@ -390,16 +380,16 @@ __device__ __forceinline__ void for_each_group(const GroupWalk<WAVES>& walk, con
 // One work item = one tile of references: stage-1 groups.  RECOMPUTE: the
 // blocks' spectra are computed here from the image's pixels instead of
 // gathered from the bior1.5 stack.
-template <int K, bool BATCH, bool RECOMPUTE, bool WIDE>
+template <int K, bool RECOMPUTE, bool WIDE>
 __device__ __forceinline__ void group_ht_body(acc_t* acc,
-                                              float (*scratch)[GroupCfg<K, true, BATCH, WIDE>::chunk * kBlockFloats],
+                                              float (*scratch)[GroupCfg<K, true, WIDE>::chunk * kBlockFloats],
                                               int16_t* ranks, const ImgRec& r, int R, const HtParams& hp, int item) {
   const GroupArgs g = make_args(r.H, r.W, R);
   const int tyi = item / g.nTx, txi = item % g.nTx;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = wave_id();
-  const int n_acc = g.FY * g.FXP;
-  load_ranks<K, GroupCfg<K, true, BATCH, WIDE>::threads>(ranks, g, r.idx, tyi, txi);
+  const int n_acc = g.FY * Foot::FXP;
+  load_ranks<K, GroupCfg<K, true, WIDE>::threads>(ranks, g, r.idx, tyi, txi);
   zero_acc(acc, n_acc);
   const int fy0 = kStep * tyi * kTPY - g.R;
   const int fx0 = kStep * txi * kTPX - g.R;
@@ -409,7 +399,7 @@ __device__ __forceinline__ void group_ht_body(acc_t* acc,
   const bool dc_lane = hp.keep_dc && lane == 0;
   acc_t* bw = r.partials;  // block-start weights
 
-  using Cfg = GroupCfg<K, true, BATCH, WIDE>;
+  using Cfg = GroupCfg<K, true, WIDE>;
   const GroupWalk<Cfg::waves> walk{g, ranks, tyi, txi, wave, lane, fy0, fx0};
   const float* const stacks[1] = {r.stack_a};
   auto filter = [&](const float (&cur)[1][K], int fo_v, int pos_v) {
@@ -465,7 +455,7 @@ __device__ __forceinline__ void group_ht_body(acc_t* acc,
     } else {
       w = 1.0f;
     }
-    accumulate<K>(acc, g, fo_v, 0, u, w, lane);
+    accumulate<K>(acc, fo_v, 0, u, w, lane);
     add_block_weights<K>(bw, pos_v, w, lane);
   };
   if constexpr (RECOMPUTE) {
@@ -486,89 +476,161 @@ __device__ __forceinline__ void group_ht_body(acc_t* acc,
   flush_acc(acc, g, fy0, fx0, numerator_sums(r));
 }
 
+// 8-point inverse DCT-II of the coefficients X, all of them scaled by the
+// factor the constants c carry: c[i] = scale cos(i pi / 16) / 2 (i = 1 .. 7;
+// c[4] is also the constant's weight, sqrt(1/8) = cos(pi / 4) / 2).
+__device__ __forceinline__ void dct8_inv_scaled(const float (&c)[8], const float* X, float* x) {
+  const float t = c[4] * X[0], p = fmaf(c[4], X[4], t), m = fmaf(-c[4], X[4], t);
+  const float r = fmaf(c[2], X[2], c[6] * X[6]), q = fmaf(c[6], X[2], -(c[2] * X[6]));
+  const float e[4] = {p + r, m + q, m - q, p - r};
+  float o[4];
+  // cos((2 n + 1) k pi / 16) for k = 1, 3, 5, 7, folded into the first octant
+  o[0] = fmaf(c[1], X[1], fmaf(c[3], X[3], fmaf(c[5], X[5], c[7] * X[7])));
+  o[1] = fmaf(c[3], X[1], fmaf(-c[7], X[3], fmaf(-c[1], X[5], -(c[5] * X[7]))));
+  o[2] = fmaf(c[5], X[1], fmaf(-c[1], X[3], fmaf(c[7], X[5], c[3] * X[7])));
+  o[3] = fmaf(c[7], X[1], fmaf(-c[5], X[3], fmaf(c[3], X[5], -(c[1] * X[7]))));
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    x[n] = e[n] + o[n];
+    x[7 - n] = e[n] - o[n];
+  }
+}
+
+// Unnormalised Haar inverse (haar_inv_raw) of v[k] haar_gain2<K>(k) K: the
+// band [h, 2h) enters with its weight h.
+template <int K>
+__device__ __forceinline__ void haar_inv_banded(float* v) {
+#pragma unroll
+  for (int half = 1; half <= K / 2; half *= 2) {
+    float t[K];
+#pragma unroll
+    for (int j = 0; j < half; ++j) {
+      t[2 * j] = fmaf(static_cast<float>(half), v[half + j], v[j]);
+      t[2 * j + 1] = fmaf(-static_cast<float>(half), v[half + j], v[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 2 * half; ++j) v[j] = t[j];
+  }
+}
+
 // One work item = one tile of references: stage-2 groups.
-template <int K, bool BATCH>
-__device__ __forceinline__ void group_wiener_body(acc_t* acc,
-                                                  float (*scratch)[GroupCfg<K, false, BATCH>::chunk * kBlockFloats],
+// Bound by vector issue and the gathers' latency.  Every multiplication by a
+// factor common to a block or band rides on one that is there anyway: the
+// Haar gains of the Wiener quotient are on the noise variance (sv), those of
+// the inverse on its butterflies, and the aggregation weight and fixed-point
+// scale on the constants of the row transform.  The column transform leaves a
+// lane eight pixels of one column of a block, which it adds into the footprint
+// from there: one address per column, rows by instruction offsets, no trip
+// back through the scratch.  At 80 registers two tiles of twelve waves share a
+// CU (one of sixteen before, each wave with a pixel of every block and an
+// address per block; kernel us before -> now: 512^2 91 -> 76, 1001 x 750
+// 285 -> 242, 4096^2 4837 -> 4270, 64 mixed images 7604 -> 6226).
+template <int K>
+__device__ __forceinline__ void group_wiener_body(acc_t* acc, float (*scratch)[GroupCfg<K, false>::chunk * kBlockFloats],
                                                   int16_t* ranks, const ImgRec& r, int R, int item) {
+  using Cfg = GroupCfg<K, false>;
   const GroupArgs g = make_args(r.H, r.W, R);
   const int tyi = item / g.nTx, txi = item % g.nTx;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = wave_id();
-  const int n_acc = g.FY * g.FXP;
-  load_ranks<K, GroupCfg<K, false, BATCH>::threads>(ranks, g, r.idx, tyi, txi);
-  zero_acc(acc, n_acc);
+  load_ranks<K, Cfg::threads>(ranks, g, r.idx, tyi, txi);
+  zero_acc(acc, g.FY * Foot::FXP);
   const int fy0 = kStep * tyi * kTPY - g.R;
   const int fx0 = kStep * txi * kTPX - g.R;
   float* xw = scratch[wave];
   const int a = lane >> 3, b = lane & 7;
   const float s2 = r.sigma * r.sigma;
   acc_t* bw = r.partials;  // block-start weights
-
-  using Cfg = GroupCfg<K, false, BATCH>;
-  const GroupWalk<Cfg::waves> walk{g, ranks, tyi, txi, wave, lane, fy0, fx0};
-  // the walk gathers the pilot's spectra; the noisy ones are loaded once the
-  // gains are known, so the two groups are never in registers together
-  const float* const stacks[1] = {r.stack_b};
   const float* __restrict__ stack_n = r.stack_a;
-  for_each_group<K, 1, Cfg::prefetch>(walk, stacks, [&](const float (&cur)[1][K], int fo_v, int pos_v) {
-    float vp[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) vp[k] = cur[0][k];
-    // unnormalised Haar (orthonormal coefficient k = haar_gain(k) * raw);
-    // haar_gain^2 is a power of two, so b^2 and the rescaling are exact
-    haar_fwd_raw<K>(vp);
+  const float* __restrict__ stack_p = r.stack_b;
+  constexpr Mat8 D = dct8();
+  constexpr int CH = Cfg::chunk;
+
+  const GroupWalk<Cfg::waves> walk{g, ranks, tyi, txi, wave, lane, fy0, fx0};
+#pragma unroll 1
+  for (int j = 0; j < walk.kGroups; ++j) {
+    int p, q, pos_v, fo_v;
+    if (!walk.ref_of(j, p, q)) continue;
+    slot_pos<K>(g, walk.template rank<K>(j), p, q, fy0, fx0, lane, pos_v, fo_v);
+    // the pilot's spectra, turned into the Wiener gains; the noisy spectra are
+    // loaded after them, so that the two are never in flight together
     float wt[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      wt[k] = load_block_lane(stack_p + static_cast<size_t>(__builtin_amdgcn_readlane(pos_v, k)) * 64, lane);
+    haar_fwd_raw<K>(wt);
     float sw2 = 0.0f;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const float b2 = vp[k] * vp[k] * haar_gain2<K>(k);
-      wt[k] = b2 * __builtin_amdgcn_rcpf(b2 + s2);
+      // b^2 / (b^2 + sigma^2) with b^2 = haar_gain2 x (haar_gain2 is a power of two)
+      const float x = wt[k] * wt[k], sv = s2 * (1.0f / haar_gain2<K>(k));
+      wt[k] = x * __builtin_amdgcn_rcpf(x + sv);
       if (k == 0 && lane == 0) wt[k] = 1.0f;
       sw2 = fmaf(wt[k], wt[k], sw2);
     }
     __builtin_amdgcn_sched_barrier(0);
-    float vn[K];
+    float v[K];
 #pragma unroll
     for (int k = 0; k < K; ++k)
-      vn[k] = load_block_lane(stack_n + static_cast<size_t>(__builtin_amdgcn_readlane(pos_v, k)) * 64, lane);
-    haar_fwd_raw<K>(vn);
-#pragma unroll
-    for (int k = 0; k < K; ++k) vn[k] *= wt[k] * haar_gain2<K>(k);
+      v[k] = load_block_lane(stack_n + static_cast<size_t>(__builtin_amdgcn_readlane(pos_v, k)) * 64, lane);
     const float w = 1.0f / wave_sum(sw2);
-    haar_inv_raw<K>(vn);
-    // the weight is known: each chunk is aggregated as soon as it is back
-    constexpr int CH = Cfg::chunk;
+    haar_fwd_raw<K>(v);
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] *= wt[k];
+    haar_inv_banded<K>(v);
+    float c1[8], c2[8];
+    const float scale = w * (kFixScaleF / static_cast<float>(K));
+#pragma unroll
+    for (int i = 1; i < 8; ++i) {
+      c2[i] = i == 4 ? static_cast<float>(D.m[0][0]) : static_cast<float>(D.m[i][0]);
+      c1[i] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(scale * c2[i])));  // (wave-uniform)
+    }
 #pragma unroll
     for (int c0 = 0; c0 < K; c0 += CH) {
       wave_lds_sync();  // earlier reads of the scratch are done
 #pragma unroll
-      for (int k = 0; k < CH; ++k) xw[k * kBlockFloats + a * kScratchPitch + b] = vn[c0 + k];
+      for (int k = 0; k < CH; ++k) xw[k * kBlockFloats + a * kScratchPitch + b] = v[c0 + k];
       wave_lds_sync();
-      inverse_level<CH, 8>(xw, lane, [&](const float* x, float* y) { dct8_inv(x, y); });
-      float u[CH];
+      // lane (a, b) of the chunk: row b, then column b, of block a
+      if (CH == 8 || a < CH) {
+        float* line = xw + a * kBlockFloats + b * kScratchPitch;
+        float x[8], y[8];
 #pragma unroll
-      for (int k = 0; k < CH; ++k) u[k] = xw[k * kBlockFloats + a * kScratchPitch + b];
-      accumulate<CH>(acc, g, fo_v, c0, u, w, lane);
+        for (int i = 0; i < 8; ++i) x[i] = line[i];
+        dct8_inv_scaled(c1, x, y);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) line[i] = y[i];
+      }
+      wave_lds_sync();
+      const int fo = __shfl(fo_v, c0 + a, kWave);
+      if (CH == 8 || a < CH) {
+        const float* col = xw + a * kBlockFloats + b;
+        float x[8], y[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = col[i * kScratchPitch];
+        dct8_inv_scaled(c2, x, y);
+        acc_t* cell = acc + fo + b;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) atomicAdd(cell + i * Foot::FXP, static_cast<acc_t>(to_fixed_scaled(y[i])));
+      }
     }
     add_block_weights<K>(bw, pos_v, w, lane);
-  });
+  }
   flush_acc(acc, g, fy0, fx0, numerator_sums(r));
 }
 
 // (the second launch bound is the minimum number of waves per SIMD)
 template <int K, bool BATCH, bool RECOMPUTE, bool WIDE>
-__global__ __launch_bounds__((GroupCfg<K, true, BATCH, WIDE>::threads),
-                             (GroupCfg<K, true, BATCH, WIDE>::min_waves_per_simd)) void group_ht_kernel(ImgRec one,
-                                                                                                         WorkList wl,
-                                                                                                         int R,
-                                                                                                         HtParams hp) {
-  using Cfg = GroupCfg<K, true, BATCH, WIDE>;
+__global__ __launch_bounds__((GroupCfg<K, true, WIDE>::threads),
+                             (GroupCfg<K, true, WIDE>::min_waves_per_simd)) void group_ht_kernel(ImgRec one,
+                                                                                                 WorkList wl, int R,
+                                                                                                 HtParams hp) {
+  using Cfg = GroupCfg<K, true, WIDE>;
   __shared__ acc_t acc[Foot::entries];
   __shared__ float scratch[Cfg::waves][Cfg::chunk * kBlockFloats];
   __shared__ int16_t ranks[kTPY * kTPX * K];
-  for_each_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
-    group_ht_body<K, BATCH, RECOMPUTE, WIDE>(acc, scratch, ranks, r, R, hp, item);
+  for_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
+    group_ht_body<K, RECOMPUTE, WIDE>(acc, scratch, ranks, r, R, hp, item);
   });
 }
 
@@ -581,14 +643,15 @@ __global__ void clear_weights_kernel(acc_t* __restrict__ w, size_t n) {
 }
 
 template <int K, bool BATCH>
-__global__ __launch_bounds__((GroupCfg<K, false, BATCH>::threads)) void group_wiener_kernel(ImgRec one, WorkList wl,
-                                                                                             int R) {
-  using Cfg = GroupCfg<K, false, BATCH>;
+__global__ __launch_bounds__((GroupCfg<K, false>::threads),
+                             (GroupCfg<K, false>::min_waves_per_simd)) void group_wiener_kernel(ImgRec one, WorkList wl,
+                                                                                                int R) {
+  using Cfg = GroupCfg<K, false>;
   __shared__ acc_t acc[Foot::entries];
   __shared__ float scratch[Cfg::waves][Cfg::chunk * kBlockFloats];
   __shared__ int16_t ranks[kTPY * kTPX * K];
-  for_each_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
-    group_wiener_body<K, BATCH>(acc, scratch, ranks, r, R, item);
+  for_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
+    group_wiener_body<K>(acc, scratch, ranks, r, R, item);
   });
 }
 
@@ -663,7 +726,7 @@ __device__ __forceinline__ void reduce_body(acc_t* colsum, const ImgRec& r, int 
 template <bool BATCH>
 __global__ __launch_bounds__(kReduceThreads) void reduce_kernel(ImgRec one, WorkList wl, int final_stage) {
   __shared__ acc_t colsum[kReduceThreads + 8];
-  for_each_item<BATCH>(one, wl, [&](const ImgRec& r, int item) { reduce_body(colsum, r, final_stage, item); });
+  for_item<BATCH>(one, wl, [&](const ImgRec& r, int item) { reduce_body(colsum, r, final_stage, item); });
 }
 
 __global__ void quantize_kernel(const float* __restrict__ in, uint16_t* __restrict__ out, size_t n) {
@@ -687,8 +750,8 @@ int reduce_items_for(int H, int W) { return reduce_items(H, W); }
 
 template <int K, bool WIDE>
 static hipError_t launch_ht_shape(const ImgRec& one, const WorkList* wl, int R, const HtParams& hp, int recompute,
-                                  int grid_cap, hipStream_t st) {
-  using Cfg = GroupCfg<K, true, false, WIDE>;
+                                  hipStream_t st) {
+  using Cfg = GroupCfg<K, true, WIDE>;
   if (!wl) {
     if (recompute)
       hipLaunchKernelGGL((group_ht_kernel<K, false, true, WIDE>), dim3(group_items_for(one.H, one.W, R)),
@@ -699,30 +762,28 @@ static hipError_t launch_ht_shape(const ImgRec& one, const WorkList* wl, int R, 
   } else {
     if (recompute) return hipErrorInvalidValue;  // batches read the stack
     if (wl->total <= 0) return hipSuccess;
-    hipLaunchKernelGGL((group_ht_kernel<K, true, false, WIDE>), dim3(std::min(wl->total, grid_cap)),
-                       dim3(GroupCfg<K, true, true, WIDE>::threads), 0, st, one, *wl, R, hp);
+    hipLaunchKernelGGL((group_ht_kernel<K, true, false, WIDE>), batch_grid(wl->total),
+                       dim3(Cfg::threads), 0, st, one, *wl, R, hp);
   }
   return hipGetLastError();
 }
 
 template <int K>
 static hipError_t launch_ht_k(const ImgRec& one, const WorkList* wl, int R, const HtParams& hp, int recompute,
-                              int shape, int grid_cap, hipStream_t st) {
-  if (K <= 16 && shape == 1) return launch_ht_shape<K, false>(one, wl, R, hp, recompute, grid_cap, st);
-  return launch_ht_shape<K, true>(one, wl, R, hp, recompute, grid_cap, st);
+                              int shape, hipStream_t st) {
+  if (K <= 16 && shape == 1) return launch_ht_shape<K, false>(one, wl, R, hp, recompute, st);
+  return launch_ht_shape<K, true>(one, wl, R, hp, recompute, st);
 }
 
-int group_ht_tiles_per_cu(int K, int shape) { return K <= 16 && shape == 0 ? 2 : 1; }
-
 hipError_t launch_group_ht(const ImgRec& one, const WorkList* wl, int R, int K, float ht_a, float ht_b,
-                           int weight_mode, int keep_dc, int recompute, int shape, int grid_cap, hipStream_t st) {
+                           int weight_mode, int keep_dc, int recompute, int shape, hipStream_t st) {
   const HtParams hp{ht_a, ht_b, weight_mode, keep_dc};
   switch (K) {
-    case 2: return launch_ht_k<2>(one, wl, R, hp, recompute, shape, grid_cap, st);
-    case 4: return launch_ht_k<4>(one, wl, R, hp, recompute, shape, grid_cap, st);
-    case 8: return launch_ht_k<8>(one, wl, R, hp, recompute, shape, grid_cap, st);
-    case 16: return launch_ht_k<16>(one, wl, R, hp, recompute, shape, grid_cap, st);
-    case 32: return launch_ht_k<32>(one, wl, R, hp, recompute, shape, grid_cap, st);
+    case 2: return launch_ht_k<2>(one, wl, R, hp, recompute, shape, st);
+    case 4: return launch_ht_k<4>(one, wl, R, hp, recompute, shape, st);
+    case 8: return launch_ht_k<8>(one, wl, R, hp, recompute, shape, st);
+    case 16: return launch_ht_k<16>(one, wl, R, hp, recompute, shape, st);
+    case 32: return launch_ht_k<32>(one, wl, R, hp, recompute, shape, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -735,37 +796,36 @@ hipError_t launch_clear_weights(const ImgRec& one, hipStream_t st) {
 }
 
 template <int K>
-static hipError_t launch_wiener_k(const ImgRec& one, const WorkList* wl, int R, int grid_cap, hipStream_t st) {
+static hipError_t launch_wiener_k(const ImgRec& one, const WorkList* wl, int R, hipStream_t st) {
   if (!wl) {
     hipLaunchKernelGGL((group_wiener_kernel<K, false>), dim3(group_items_for(one.H, one.W, R)),
-                       dim3(GroupCfg<K, false, false>::threads), 0, st, one, WorkList{}, R);
+                       dim3(GroupCfg<K, false>::threads), 0, st, one, WorkList{}, R);
   } else {
     if (wl->total <= 0) return hipSuccess;
-    hipLaunchKernelGGL((group_wiener_kernel<K, true>), dim3(std::min(wl->total, grid_cap)),
-                       dim3(GroupCfg<K, false, true>::threads), 0, st, one, *wl, R);
+    hipLaunchKernelGGL((group_wiener_kernel<K, true>), batch_grid(wl->total),
+                       dim3(GroupCfg<K, false>::threads), 0, st, one, *wl, R);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_group_wiener(const ImgRec& one, const WorkList* wl, int R, int K, int grid_cap, hipStream_t st) {
+hipError_t launch_group_wiener(const ImgRec& one, const WorkList* wl, int R, int K, hipStream_t st) {
   switch (K) {
-    case 2: return launch_wiener_k<2>(one, wl, R, grid_cap, st);
-    case 4: return launch_wiener_k<4>(one, wl, R, grid_cap, st);
-    case 8: return launch_wiener_k<8>(one, wl, R, grid_cap, st);
-    case 16: return launch_wiener_k<16>(one, wl, R, grid_cap, st);
-    case 32: return launch_wiener_k<32>(one, wl, R, grid_cap, st);
+    case 2: return launch_wiener_k<2>(one, wl, R, st);
+    case 4: return launch_wiener_k<4>(one, wl, R, st);
+    case 8: return launch_wiener_k<8>(one, wl, R, st);
+    case 16: return launch_wiener_k<16>(one, wl, R, st);
+    case 32: return launch_wiener_k<32>(one, wl, R, st);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_reduce(const ImgRec& one, const WorkList* wl, int final_stage, int grid_cap,
-                         hipStream_t st) {
+hipError_t launch_reduce(const ImgRec& one, const WorkList* wl, int final_stage, hipStream_t st) {
   if (!wl) {
     hipLaunchKernelGGL((reduce_kernel<false>), dim3(reduce_items(one.H, one.W)), dim3(kReduceThreads), 0, st, one,
                        WorkList{}, final_stage);
   } else {
     if (wl->total <= 0) return hipSuccess;
-    hipLaunchKernelGGL((reduce_kernel<true>), dim3(std::min(wl->total, grid_cap)), dim3(kReduceThreads), 0, st,
+    hipLaunchKernelGGL((reduce_kernel<true>), batch_grid(wl->total), dim3(kReduceThreads), 0, st,
                        one, *wl, final_stage);
   }
   return hipGetLastError();

@@ -2,8 +2,7 @@
 //
 // Each launcher runs either one image (`wl` == nullptr: the grid enumerates
 // the image's work items, the descriptor `one` is passed by value) or a batch
-// (`wl` != nullptr: a persistent grid of at most `grid_cap` workgroups walks
-// the work list).  The *_items_for functions give an image's item count for
+// (`wl` != nullptr: the grid enumerates the work list's items).  The *_items_for functions give an image's item count for
 // each kernel, used to build work lists.
 #pragma once
 
@@ -18,7 +17,7 @@ namespace gbm3d {
 // Block matching of one image's noisy (use_pilot = 0) or pilot (1) image into
 // rec.idx[n_refs][K] (slot 0 = reference).  split: parts of the displacement
 // rows per reference row (1, 2, 4; 0 = by image size).
-hipError_t launch_bm(const ImgRec& one, const WorkList* wl, int R, int K, int split, int use_pilot, int grid_cap,
+hipError_t launch_bm(const ImgRec& one, const WorkList* wl, int R, int K, int split, int use_pilot,
                      hipStream_t st);
 int bm_auto_split(long total_waves_unsplit);
 long bm_waves_unsplit(int H, int W);
@@ -35,7 +34,7 @@ long corr_tiles(int H, int W);
 // src_sel = dst_sel = -1: noisy -> stack_a and pilot -> stack_b in one launch.
 // The launch into stack_a clears the aggregation sums of rec.partials (when
 // set).
-hipError_t launch_stack(const ImgRec& one, const WorkList* wl, int kind, int src_sel, int dst_sel, int grid_cap,
+hipError_t launch_stack(const ImgRec& one, const WorkList* wl, int kind, int src_sel, int dst_sel,
                         hipStream_t st);
 int stack_items_for(int H, int W);
 // bytes of the aggregation buffer (64-bit fixed point) of the group kernels:
@@ -47,21 +46,19 @@ int group_items_for(int H, int W, int R);
 // recompute (one image only): the blocks' spectra from rec.noisy's pixels
 // instead of stack_a.  shape (K <= 16): 0 = two tiles of 12 waves per CU,
 // 1 = one tile of 16 waves with the next group's spectra prefetched; the
-// same result either way.  group_ht_tiles_per_cu: the persistent-grid
-// multiplier of a shape.
+// same result either way.
 hipError_t launch_group_ht(const ImgRec& one, const WorkList* wl, int R, int K, float ht_a, float ht_b,
-                           int weight_mode, int keep_dc, int recompute, int shape, int grid_cap, hipStream_t st);
-int group_ht_tiles_per_cu(int K, int shape);
+                           int weight_mode, int keep_dc, int recompute, int shape, hipStream_t st);
 // zeroes the block-start weights and numerator sums of rec.partials (what the
 // bior1.5 stack launch does when the stage-1 groups read the stack)
 hipError_t launch_clear_weights(const ImgRec& one, hipStream_t st);
 
 // stage-2 groups: stack_a (noisy DCT) + stack_b (pilot DCT) + idx -> partials
-hipError_t launch_group_wiener(const ImgRec& one, const WorkList* wl, int R, int K, int grid_cap, hipStream_t st);
+hipError_t launch_group_wiener(const ImgRec& one, const WorkList* wl, int R, int K, hipStream_t st);
 
 // numerator sum / 8 x 8 box sum of the block-start weights into rec.basic
 // (+ its quantisation into rec.q when set) or, with final_stage, rec.out
-hipError_t launch_reduce(const ImgRec& one, const WorkList* wl, int final_stage, int grid_cap,
+hipError_t launch_reduce(const ImgRec& one, const WorkList* wl, int final_stage,
                          hipStream_t st);
 int reduce_items_for(int H, int W);
 

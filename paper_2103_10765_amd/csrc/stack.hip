@@ -153,6 +153,16 @@ __device__ __forceinline__ void stack_body(float (*pix)[kPixCols + 1], float (*s
 // Workgroups up to which a stack launch counts as short: 32 per CU of the 256.
 constexpr int kShortLaunchItems = 32 * 256;
 
+// Workgroups beyond which a batch launch runs three per CU instead of the four
+// that fit, by unused LDS: its write streams then go to several images of
+// uneven widths at once, and fewer of them write faster.  Both DCT stacks, three
+// against four per CU: 64 images of 256 to 1024 pixels a side (207k workgroups)
+// 2438 against 2740 us; 32 images of 512^2 (65k) 760 against 735 us, 8 of 256^2
+// 51 against 49 us.  One image of any size is faster with four (4096^2: 1554
+// against 1475 us).
+constexpr int kLongBatchItems = 512 * 256;
+constexpr unsigned kLongBatchPad = 8192;
+
 // src_sel: 0 = noisy, 1 = pilot; dst_sel: 0 = stack_a, 1 = stack_b; both
 // negative: blockIdx.y selects (noisy -> stack_a, pilot -> stack_b)
 template <int KIND, bool BATCH, bool LOADS_FIRST>
@@ -161,25 +171,29 @@ __global__ __launch_bounds__(kStackThreads) void stack_kernel(ImgRec one, WorkLi
   __shared__ float stage[kRowsPerWg][kHalf * kStagePitch];
   const int src = src_sel < 0 ? static_cast<int>(blockIdx.y) : src_sel;
   const int dst = dst_sel < 0 ? static_cast<int>(blockIdx.y) : dst_sel;
-  for_each_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
+  for_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
     stack_body<KIND, LOADS_FIRST>(pix, stage, src ? r.pilot : r.noisy, dst ? r.stack_b : r.stack_a,
                                   dst ? nullptr : r.partials, r.H, r.W, item);
   });
 }
 
 template <int KIND>
-hipError_t launch_stack_kind(const ImgRec& one, const WorkList* wl, int src_sel, int dst_sel, int grid_cap,
+hipError_t launch_stack_kind(const ImgRec& one, const WorkList* wl, int src_sel, int dst_sel,
                              hipStream_t st) {
   const unsigned planes = src_sel < 0 ? 2u : 1u;  // both stacks in one launch
-  const int items = wl ? std::min(wl->total, grid_cap) : stack_items(one.H, one.W);
+  const int items = wl ? wl->total : stack_items(one.H, one.W);
   if (items <= 0) return hipSuccess;
-  const dim3 grid(static_cast<unsigned>(items), planes), block(kStackThreads);
+  const dim3 grid = wl ? batch_grid(items, planes) : dim3(static_cast<unsigned>(items), planes);
+  const dim3 block(kStackThreads);
   // A launch of a few workgroups per CU is bound by each workgroup's
   // latency: there the pixel loads go out all at once (measured: 512^2
   // faster, 4096^2 slower, where the stack writes bound the launch)
+  const long long wgs = static_cast<long long>(items) * planes;
+  const bool short_launch = wgs <= kShortLaunchItems;
   if (wl)
-    hipLaunchKernelGGL((stack_kernel<KIND, true, false>), grid, block, 0, st, one, *wl, src_sel, dst_sel);
-  else if (items * static_cast<int>(planes) <= kShortLaunchItems)
+    hipLaunchKernelGGL((stack_kernel<KIND, true, false>), grid, block,
+                       wgs > kLongBatchItems ? kLongBatchPad : 0, st, one, *wl, src_sel, dst_sel);
+  else if (short_launch)
     hipLaunchKernelGGL((stack_kernel<KIND, false, true>), grid, block, 0, st, one, WorkList{}, src_sel, dst_sel);
   else
     hipLaunchKernelGGL((stack_kernel<KIND, false, false>), grid, block, 0, st, one, WorkList{}, src_sel, dst_sel);
@@ -190,11 +204,11 @@ hipError_t launch_stack_kind(const ImgRec& one, const WorkList* wl, int src_sel,
 
 int stack_items_for(int H, int W) { return stack_items(H, W); }
 
-hipError_t launch_stack(const ImgRec& one, const WorkList* wl, int kind, int src_sel, int dst_sel, int grid_cap,
+hipError_t launch_stack(const ImgRec& one, const WorkList* wl, int kind, int src_sel, int dst_sel,
                         hipStream_t st) {
   if ((src_sel < 0) != (dst_sel < 0)) return hipErrorInvalidValue;
-  return kind == 0 ? launch_stack_kind<0>(one, wl, src_sel, dst_sel, grid_cap, st)
-                   : launch_stack_kind<1>(one, wl, src_sel, dst_sel, grid_cap, st);
+  return kind == 0 ? launch_stack_kind<0>(one, wl, src_sel, dst_sel, st)
+                   : launch_stack_kind<1>(one, wl, src_sel, dst_sel, st);
 }
 
 }  // namespace gbm3d

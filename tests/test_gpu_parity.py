@@ -314,6 +314,21 @@ def test_wiener_parity(torch, G, ctx, H, W, S, sigma, seed):
     assert abs(O.psnr(Yg, clean) - O.psnr(Yo, clean)) <= PSNR_TOL
 
 
+@pytest.mark.parametrize("k", [2, 4, 8, 16, 32])
+@pytest.mark.parametrize("H,W,S", [(22, 25, 15), (24, 21, 7), (46, 49, 39)])
+def test_wiener_group_sizes_at_tile_edges(torch, G, ctx, k, H, W, S):
+    """Stage 2 at every group size, on images of eight references a side and of
+    one more (a tile that is full, or holds a single row or column of groups),
+    with windows of a fraction and of the whole footprint; the sums are rounded
+    to 2^-40 and the transforms are float32, far inside MAXABS."""
+    say("wiener group sizes", k, H, W, S)
+    _, Z = synth.make_case(H, W, SIG, 19)
+    gp = G.default_params(search=S, k_wiener=k)
+    pilot = O.quantize(synth.make_case(H, W, SIG / 5, 19)[1] / 65535.0)
+    Yg = ctx.wiener(up(torch, Z), up(torch, pilot), SIG, gp).cpu().numpy().astype(np.float64)
+    assert np.abs(Yg - O.wiener_estimate(Z, pilot, SIG, oparams(G, gp))).max() <= MAXABS
+
+
 def test_wiener_full_size_windows(torch, G, ctx):
     """512 x 512: pilot = the clean image quantised (an input both sides take)."""
     clean, Z = synth.single_image_case(512, SIG, 2)
