@@ -46,6 +46,7 @@
 // 4096^2 2.93 / 3.56 -> 2.46 / 3.03 ms, 128^2 26 / 31 -> 11 / 28 us.
 #include "common.h"
 #include "kernels.h"
+#include "stack_body.h"
 
 namespace gbm3d {
 
@@ -575,38 +576,98 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
     idx[(static_cast<size_t>(p0 + (tid >> 2)) * nRx + q0 + (tid & 3)) * K] = static_cast<int16_t>(R * S + R);
 }
 
-template <int Q, int C, bool WIDE, bool BATCH>
-__global__ __launch_bounds__(kThreads, 6) void bm_corr_kernel(ImgRec one, WorkList wl, int R, int K, int use_pilot) {
+// Stack work beside the matching: `pairs` workgroups of two stack items each,
+// spread evenly over the launch.  Workgroups come in groups of eight (one per
+// XCD); group g holds stack items where floor(g * share / 2^32) steps,
+// share / 2^32 just above their part of all groups.
+struct StackShare {
+  int pairs = 0, per_plane = 0;  // workgroups of stack items; of one of its planes
+  unsigned share = 0;
+};
+
+template <int Q, int C, bool WIDE, bool BATCH, int KIND>
+__global__ __launch_bounds__(kThreads, 6) void bm_corr_kernel(ImgRec one, WorkList wl, WorkList stack_wl,
+                                                              StackShare ss, int R, int K, int use_pilot) {
   __shared__ __align__(16) unsigned char smem[Smem::bytes];
+  unsigned b = blockIdx.z * gridDim.x + blockIdx.x;
+  if constexpr (KIND >= 0) {
+    const unsigned g = b >> 3, sg = __umulhi(g, ss.share);
+    if (__umulhi(g + 1, ss.share) != sg) {
+      using Lds = StackLds<4>;
+      static_assert(2 * sizeof(Lds) <= Smem::bytes, "two stack items fit the matcher's LDS");
+      const int s = static_cast<int>(sg * 8 + (b & 7));
+      if (s >= ss.pairs) return;
+      const int plane = s >= ss.per_plane ? 1 : 0;
+      const int half = wave_id() / kStackRows;
+      Lds& lds = reinterpret_cast<Lds*>(smem)[half];
+      const int t = static_cast<int>(threadIdx.x) & (kStackThreads - 1);
+      int item = 2 * (s - plane * ss.per_plane) + half;
+      if constexpr (!BATCH) {
+        if (item >= stack_items(one.H, one.W)) item = -1;
+        stack_body<KIND, 4, true>(lds, t, plane ? one.pilot : one.noisy, plane ? one.stack_b : one.stack_a,
+                                  plane ? nullptr : one.partials, one.H, one.W, item);
+      } else {
+        int first = item + 1;
+        const bool any = item < stack_wl.total;
+        const const_rec_ptr r = find_item(stack_wl, any ? item : 0, first);
+        stack_body<KIND, 4, true>(lds, t, plane ? r->pilot : r->noisy, plane ? r->stack_b : r->stack_a,
+                                  plane ? nullptr : r->partials, r->H, r->W, any ? item - first : -1);
+      }
+      return;
+    }
+    b -= sg * 8;
+  }
   if constexpr (!BATCH) {
     // Workgroups go to the eight XCDs in turn (g -> XCD g mod 8): XCD x takes
     // the x-th eighth of the items, a band of reference rows, so each XCD's
     // L2 fetches its band's pixels instead of the whole image.  The grid is
     // 8 q; items past the last exit at once.
     const int n = corr_items(one.H, one.W), q = (n + 7) / 8;
-    const int b = static_cast<int>(blockIdx.x);
-    const int item = (b & 7) * q + (b >> 3);
-    if (item >= n) return;
+    const int item = static_cast<int>((b & 7) * q + (b >> 3));
+    if (static_cast<int>(b >> 3) >= q || item >= n) return;
     corr_body<Q, C, WIDE>(smem, use_pilot ? one.pilot : one.noisy, one.idx, one.H, one.W, R, K, item);
   } else {
+    if (b >= static_cast<unsigned>(wl.total)) return;
     int first;
-    const int item = static_cast<int>(blockIdx.x);
+    const int item = static_cast<int>(b);
     const const_rec_ptr r = find_item(wl, item, first);
     corr_body<Q, C, WIDE>(smem, use_pilot ? r->pilot : r->noisy, r->idx, r->H, r->W, R, K, item - first);
   }
 }
 
-template <int Q, int C, bool WIDE>
-hipError_t launch_corr_grid(const ImgRec& one, const WorkList* wl, int R, int K, int use_pilot, hipStream_t st) {
-  if (!wl) {
-    hipLaunchKernelGGL((bm_corr_kernel<Q, C, WIDE, false>), dim3(8 * ((corr_items(one.H, one.W) + 7) / 8)),
-                       dim3(kThreads), 0, st, one, WorkList{}, R, K, use_pilot);
-  } else {
-    if (wl->total <= 0) return hipSuccess;
-    hipLaunchKernelGGL((bm_corr_kernel<Q, C, WIDE, true>), batch_grid(wl->total), dim3(kThreads), 0, st, one, *wl, R, K,
-                       use_pilot);
+// kind < 0: matching only; else the stacks of stack_wl (or of the image) beside it
+template <int Q, int C, bool WIDE, int KIND>
+hipError_t launch_corr_kind(const ImgRec& one, const WorkList* wl, const WorkList* stack_wl, int R, int K,
+                            int use_pilot, hipStream_t st) {
+  const int n = wl ? wl->total : corr_items(one.H, one.W);
+  if (n <= 0) return hipSuccess;
+  const int match_groups = (n + 7) / 8;
+  int groups = match_groups;
+  StackShare ss;
+  if constexpr (KIND >= 0) {
+    const int planes = KIND == 0 ? 1 : 2;
+    ss.per_plane = ((wl ? stack_wl->total : stack_items(one.H, one.W)) + 1) / 2;
+    ss.pairs = planes * ss.per_plane;
+    const int stack_groups = (ss.pairs + 7) / 8;
+    groups += stack_groups;
+    ss.share = static_cast<unsigned>(((static_cast<unsigned long long>(stack_groups) << 32) + groups - 1) / groups);
   }
+  const dim3 grid = batch_grid(8 * groups);
+  if (wl)
+    hipLaunchKernelGGL((bm_corr_kernel<Q, C, WIDE, true, KIND>), grid, dim3(kThreads), 0, st, one, *wl,
+                       stack_wl ? *stack_wl : WorkList{}, ss, R, K, use_pilot);
+  else
+    hipLaunchKernelGGL((bm_corr_kernel<Q, C, WIDE, false, KIND>), grid, dim3(kThreads), 0, st, one, WorkList{},
+                       WorkList{}, ss, R, K, use_pilot);
   return hipGetLastError();
+}
+
+template <int Q, int C, bool WIDE>
+hipError_t launch_corr_grid(const ImgRec& one, const WorkList* wl, const WorkList* stack_wl, int R, int K,
+                            int use_pilot, int stack_kind, hipStream_t st) {
+  if (stack_kind < 0) return launch_corr_kind<Q, C, WIDE, -1>(one, wl, stack_wl, R, K, use_pilot, st);
+  return stack_kind == 0 ? launch_corr_kind<Q, C, WIDE, 0>(one, wl, stack_wl, R, K, use_pilot, st)
+                         : launch_corr_kind<Q, C, WIDE, 1>(one, wl, stack_wl, R, K, use_pilot, st);
 }
 
 }  // namespace
@@ -615,12 +676,13 @@ int corr_items_for(int H, int W) { return corr_items(H, W); }
 
 long corr_tiles(int H, int W) { return static_cast<long>(corr_items(H, W)); }
 
-hipError_t launch_bm_corr(const ImgRec& one, const WorkList* wl, int R, int K, int use_pilot, hipStream_t st) {
-  if (K < 2 || K > 32 || R < 0 || R > kMaxR) return hipErrorInvalidValue;
+hipError_t launch_bm_corr(const ImgRec& one, const WorkList* wl, const WorkList* stack_wl, int R, int K, int use_pilot,
+                          int stack_kind, hipStream_t st) {
+  if (K < 2 || K > 32 || R < 0 || R > kMaxR || (wl && stack_kind >= 0 && !stack_wl)) return hipErrorInvalidValue;
   const int nb = blocks_per_axis(R);
-  if (nb <= 8) return launch_corr_grid<4, 2, false>(one, wl, R, K, use_pilot, st);
-  if (nb < kMaxNb) return launch_corr_grid<6, 3, false>(one, wl, R, K, use_pilot, st);
-  return launch_corr_grid<6, 3, true>(one, wl, R, K, use_pilot, st);
+  if (nb <= 8) return launch_corr_grid<4, 2, false>(one, wl, stack_wl, R, K, use_pilot, stack_kind, st);
+  if (nb < kMaxNb) return launch_corr_grid<6, 3, false>(one, wl, stack_wl, R, K, use_pilot, stack_kind, st);
+  return launch_corr_grid<6, 3, true>(one, wl, stack_wl, R, K, use_pilot, stack_kind, st);
 }
 
 }  // namespace gbm3d

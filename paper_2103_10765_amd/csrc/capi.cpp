@@ -364,7 +364,7 @@ int choose_shape(const gbm3d_ctx* ctx, const gbm3d_params& p, long tiles) {
 // Block matching of one image (r.noisy, or r.pilot with use_pilot) into r.idx.
 int run_match(gbm3d_ctx* ctx, ImgRec& r, int R, int K, const BmChoice& c, int use_pilot, hipStream_t st) {
   HIP_TRY(ctx, timed(ctx, "bm", st, [&] {
-            return c.method == GBM3D_BM_CORR ? gbm3d::launch_bm_corr(r, nullptr, R, K, use_pilot, st)
+            return c.method == GBM3D_BM_CORR ? gbm3d::launch_bm_corr(r, nullptr, nullptr, R, K, use_pilot, -1, st)
                                              : gbm3d::launch_bm(r, nullptr, R, K, c.split, use_pilot, st);
           }),
           "block matching launch");
@@ -373,6 +373,28 @@ int run_match(gbm3d_ctx* ctx, ImgRec& r, int R, int K, const BmChoice& c, int us
 
 int run_match(gbm3d_ctx* ctx, ImgRec& r, int R, int K, const gbm3d_params& p, int use_pilot, hipStream_t st) {
   return run_match(ctx, r, R, K, choose_bm(ctx, p, gbm3d::corr_tiles(r.H, r.W), K), use_pilot, st);
+}
+
+// True if a stage's matching launch also writes its stacks: the matcher is
+// bound by vector issue and LDS, the stacks by memory writes.  While launches
+// are timed, each kernel is launched, and recorded, by itself.
+bool match_with_stacks(const gbm3d_ctx* ctx, int method) { return method == GBM3D_BM_CORR && !ctx->timing; }
+
+// A stage's matching and stacks (kind 0: the bior1.5 stack of the noisy image
+// into stack_a, 1: the DCT stacks of the noisy image and the pilot).
+int run_match_stacks(gbm3d_ctx* ctx, ImgRec& r, int R, int K, const BmChoice& c, int use_pilot, int kind,
+                     hipStream_t st) {
+  if (match_with_stacks(ctx, c.method)) {
+    HIP_TRY(ctx, gbm3d::launch_bm_corr(r, nullptr, nullptr, R, K, use_pilot, kind, st), "block matching launch");
+    return GBM3D_OK;
+  }
+  CHECK(run_match(ctx, r, R, K, c, use_pilot, st));
+  const int sel = kind == 0 ? 0 : -1;
+  HIP_TRY(ctx, timed(ctx, kind == 0 ? "stack_bior" : "stack_dct", st, [&] {
+            return gbm3d::launch_stack(r, nullptr, kind, sel, sel, st);
+          }),
+          "stack launch");
+  return GBM3D_OK;
 }
 
 float tv_eps(const gbm3d_params& p, float sigma) { return p.tv_eps_rel * sigma * 64.0f * static_cast<float>(p.k_ht); }
@@ -414,12 +436,11 @@ int run_basic(gbm3d_ctx* ctx, const uint16_t* noisy, int H, int W, float sigma, 
   r.partials = w.partials;
   r.eps = tv_eps(p, sigma);
   const BmChoice c = choose_bm(ctx, p, gbm3d::corr_tiles(H, W), p.k_ht);
-  CHECK(run_match(ctx, r, R, p.k_ht, c, 0, st));
   if (recompute) {
+    CHECK(run_match(ctx, r, R, p.k_ht, c, 0, st));
     HIP_TRY(ctx, gbm3d::launch_clear_weights(r, st), "weight clearing launch");
   } else {
-    HIP_TRY(ctx, timed(ctx, "stack_bior", st, [&] { return gbm3d::launch_stack(r, nullptr, 0, 0, 0, st); }),
-            "stack launch");
+    CHECK(run_match_stacks(ctx, r, R, p.k_ht, c, 0, 0, st));
   }
   HIP_TRY(ctx, timed(ctx, "group_ht", st, [&] {
             return gbm3d::launch_group_ht(r, nullptr, R, p.k_ht, p.ht_a, p.ht_b, p.ht_weight, p.keep_dc, recompute,
@@ -456,10 +477,7 @@ int run_wiener(gbm3d_ctx* ctx, const uint16_t* noisy, const uint16_t* pilot, int
   r.stack_b = w.stack_b;
   r.idx = w.idx;
   r.partials = w.partials;
-  CHECK(run_match(ctx, r, R, p.k_wiener, choose_bm(ctx, p, gbm3d::corr_tiles(H, W), p.k_wiener), 1, st));
-  // the noisy and the pilot's DCT stacks in one launch
-  HIP_TRY(ctx, timed(ctx, "stack_dct", st, [&] { return gbm3d::launch_stack(r, nullptr, 1, -1, -1, st); }),
-          "stack launch");
+  CHECK(run_match_stacks(ctx, r, R, p.k_wiener, choose_bm(ctx, p, gbm3d::corr_tiles(H, W), p.k_wiener), 1, 1, st));
   HIP_TRY(ctx, timed(ctx, "group_wiener", st, [&] {
             return gbm3d::launch_group_wiener(r, nullptr, R, p.k_wiener, st);
           }),
@@ -611,8 +629,12 @@ int launch_batch_prep(gbm3d_ctx* ctx, const WorkList& sk, const WorkList& bm, in
   const ImgRec none = blank_rec(0, 0, 0.0f);
   const int use_pilot = kind;
   const int sel = kind == 0 ? 0 : -1;
+  if (match_with_stacks(ctx, method)) {
+    HIP_TRY(ctx, gbm3d::launch_bm_corr(none, &bm, &sk, R, K, use_pilot, kind, st), "batch block matching");
+    return GBM3D_OK;
+  }
   HIP_TRY(ctx, timed(ctx, "bm", st, [&] {
-            return method == GBM3D_BM_CORR ? gbm3d::launch_bm_corr(none, &bm, R, K, use_pilot, st)
+            return method == GBM3D_BM_CORR ? gbm3d::launch_bm_corr(none, &bm, nullptr, R, K, use_pilot, -1, st)
                                            : gbm3d::launch_bm(none, &bm, R, K, split, use_pilot, st);
           }),
           "batch block matching");

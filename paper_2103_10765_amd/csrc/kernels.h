@@ -24,8 +24,11 @@ long bm_waves_unsplit(int H, int W);
 int bm_items_for(int H, int W, int split);
 
 // Correlation-form matching (Theorem 1, f16 matrix cores, exact keys for the
-// candidates that can matter): the same indices.
-hipError_t launch_bm_corr(const ImgRec& one, const WorkList* wl, int R, int K, int use_pilot, hipStream_t st);
+// candidates that can matter): the same indices.  stack_kind 0 or 1: the
+// launch also does the work of launch_stack(one, stack_wl, 0, 0, 0) or
+// launch_stack(one, stack_wl, 1, -1, -1); -1: matching only.
+hipError_t launch_bm_corr(const ImgRec& one, const WorkList* wl, const WorkList* stack_wl, int R, int K, int use_pilot,
+                          int stack_kind, hipStream_t st);
 int corr_items_for(int H, int W);
 long corr_tiles(int H, int W);
 
