@@ -503,7 +503,6 @@ size_t table_bytes(const BatchPlan& plan, int n) {
 }
 
 int plan_batch(gbm3d_ctx* ctx, const gbm3d_image* imgs, int n, const gbm3d_params& p, int flags, BatchPlan& plan) {
-  const int R = p.search / 2;
   const bool basic_only = (flags & GBM3D_BATCH_BASIC_ONLY) != 0;
   const int kmax = std::max(p.k_ht, p.k_wiener);
   // matching kernels of the two stages, from the tiles of all their images
@@ -588,11 +587,11 @@ int plan_batch(gbm3d_ctx* ctx, const gbm3d_image* imgs, int n, const gbm3d_param
     const int items[kPhases] = {
         s1 ? (corr1 ? gbm3d::corr_items_for(H, W) : gbm3d::bm_items_for(H, W, plan.bm_split1)) : 0,
         s1 ? gbm3d::stack_items_for(H, W) : 0,
-        s1 ? gbm3d::group_items_for(H, W, R) : 0,
+        s1 ? gbm3d::group_items_for(H, W) : 0,
         s1 ? gbm3d::reduce_items_for(H, W) : 0,
         s2 ? (corr2 ? gbm3d::corr_items_for(H, W) : gbm3d::bm_items_for(H, W, plan.bm_split2)) : 0,
         s2 ? gbm3d::stack_items_for(H, W) : 0,
-        s2 ? gbm3d::group_items_for(H, W, R) : 0,
+        s2 ? gbm3d::group_items_for(H, W) : 0,
         s2 ? gbm3d::reduce_items_for(H, W) : 0,
     };
     for (int ph = 0; ph < kPhases; ++ph) plan.begin[ph][i + 1] = plan.begin[ph][i] + items[ph];

@@ -1,6 +1,6 @@
 // Collaborative filtering of matched groups and their aggregation.
 //
-// A workgroup of 8 to 16 waves owns a tile of 8 x 8 references; each wave
+// A workgroup of 8 to 16 waves owns a tile of 8 to 64 references; each wave
 // filters one group at a time with lane = 2-D coefficient index (64 lanes =
 // 8x8 coefficients) and the group axis in registers:
 //   decode the K block positions (lane k decodes slot k, the values are
@@ -32,45 +32,58 @@
 #include "common.h"
 #include "kernels.h"
 
+#include <type_traits>
+
 namespace gbm3d {
 
 namespace {
 
 constexpr int kScratchPitch = 9;                  // LDS row pitch of a parked 8x8 block
 constexpr int kBlockFloats = 8 * kScratchPitch;   // 72
-constexpr int kTPY = 8, kTPX = 8;                 // references per tile
 constexpr int kReduceThreads = 256;
 constexpr int kLdsBytes = 160 * 1024;             // LDS of one workgroup
 
 using acc_t = unsigned long long;
 
-struct Foot {
-  static constexpr int FYmax = kStep * (kTPY - 1) + kPatch + 2 * kMaxR;
-  static constexpr int FXmax = kStep * (kTPX - 1) + kPatch + 2 * kMaxR;
+// The reference tile of a workgroup and its footprint.
+template <int PY, int PX>
+struct Tile {
+  static constexpr int refs = PY * PX, py = PY, px = PX;
+  static constexpr int FYmax = kStep * (PY - 1) + kPatch + 2 * kMaxR;
+  static constexpr int FXmax = kStep * (PX - 1) + kPatch + 2 * kMaxR;
   // cells per footprint row of every window (so that the rows of a block are
   // instruction offsets), 8 modulo 32
   static constexpr int FXP = FXmax + ((8 - FXmax) % 32 + 32) % 32;
   static constexpr int entries = FYmax * FXP;
 };
 
-// Launch shape of a group kernel.  Two tiles share a CU: 12 waves each (six
-// per SIMD), inverse transforms 8 blocks at a time through each wave's
-// scratch, no prefetch of the next group (the other waves hide the loads).
-// The hard-threshold kernel has a second shape (WIDE = false; K <= 16, which
-// the autotuner may choose): one tile of sixteen waves that keeps the next
-// group's spectra in flight.  Its filter holds all K inverse blocks until its
-// weight is known, so K = 32 runs one tile of eight waves.
-template <int K, bool HT, bool WIDE = true>
+// Shapes of the group kernels.
+enum GroupShape {
+  kTwoTiles,  // 8 x 8 references by 12 waves, two tiles per CU
+  kOneTile,   // 8 x 8 references by 16 waves, one tile per CU, the next group's spectra in flight
+  kSmall,     // 4 x 4 references by 8 waves
+  kTiny,      // 2 x 4 references by 8 waves
+};
+
+// Launch shape of a group kernel.  Tiles share a CU so that it has 24 waves
+// (six per SIMD); inverse transforms go 8 blocks at a time through each wave's
+// scratch, without a prefetch of the next group (the other waves hide the
+// loads).  kOneTile is a choice of the autotuner for the hard-threshold kernel
+// (K <= 16).  That kernel's filter holds all K inverse blocks until its weight
+// is known, so K = 32 runs eight waves and one tile per CU.
+template <int K, bool HT, int SHAPE>
 struct GroupCfg {
-  static constexpr bool two_tiles = !HT || (K <= 16 && WIDE);
-  static constexpr int chunk = two_tiles ? (K > 8 ? 8 : K) : (K > 16 ? 16 : K);
-  static constexpr int rank_bytes = kTPY * kTPX * K * 2;  // the tile's ranks (int16)
-  static constexpr int waves = two_tiles ? 12 : K <= 16 ? 16 : 8;
-  static constexpr int tiles = two_tiles ? 2 : 1;
-  static constexpr bool prefetch = !two_tiles && K <= 16;
+  static constexpr bool large = HT && K > 16;
+  using T = std::conditional_t<SHAPE == kTiny, Tile<2, 4>, std::conditional_t<SHAPE == kSmall, Tile<4, 4>, Tile<8, 8>>>;
+  static constexpr bool prefetch = SHAPE == kOneTile;
+  static constexpr int chunk = SHAPE == kOneTile || large ? (K > 16 ? 16 : K) : (K > 8 ? 8 : K);
+  static constexpr int rank_bytes = T::refs * K * 2;  // the tile's ranks (int16)
+  static constexpr int waves = SHAPE == kOneTile ? 16 : large || SHAPE != kTwoTiles ? 8 : 12;
+  static constexpr int tiles = SHAPE == kOneTile || large ? 1 : 24 / waves;
   static constexpr int threads = waves * kWave;
   static constexpr int min_waves_per_simd = waves * tiles / 4;
-  static_assert(tiles * (Foot::entries * static_cast<int>(sizeof(acc_t)) +
+  static_assert(SHAPE != kOneTile || (HT && K <= 16), "only the hard-threshold kernel of small groups prefetches");
+  static_assert(tiles * (T::entries * static_cast<int>(sizeof(acc_t)) +
                          waves * chunk * kBlockFloats * static_cast<int>(sizeof(float)) + rank_bytes) <=
                     kLdsBytes,
                 "LDS of the tiles sharing a CU");
@@ -82,6 +95,7 @@ struct GroupArgs {
   float invS;  // 1 / S for the rank decode
 };
 
+template <typename T>
 __host__ __device__ inline GroupArgs make_args(int H, int W, int R) {
   GroupArgs g;
   g.H = H;
@@ -90,10 +104,10 @@ __host__ __device__ inline GroupArgs make_args(int H, int W, int R) {
   g.S = 2 * R + 1;
   g.nRy = (H + kStep - 1) / kStep;
   g.nRx = (W + kStep - 1) / kStep;
-  g.nTx = (g.nRx + kTPX - 1) / kTPX;
-  g.nTy = (g.nRy + kTPY - 1) / kTPY;
-  g.FY = kStep * (kTPY - 1) + kPatch + 2 * R;
-  g.FX = kStep * (kTPX - 1) + kPatch + 2 * R;
+  g.nTx = (g.nRx + T::px - 1) / T::px;
+  g.nTy = (g.nRy + T::py - 1) / T::py;
+  g.FY = kStep * (T::py - 1) + kPatch + 2 * R;
+  g.FX = kStep * (T::px - 1) + kPatch + 2 * R;
   g.invS = 1.0f / static_cast<float>(g.S);
   return g;
 }
@@ -145,7 +159,7 @@ __device__ __forceinline__ void inverse_level(float* xw, int lane, F&& line) {
 // Block positions of the group of reference (p, q): lane k < K decodes the
 // rank r of slot k into a stack position (pixel index) and the offset of the
 // block's top-left in the tile's footprint.
-template <int K>
+template <int K, typename T>
 __device__ __forceinline__ void slot_pos(const GroupArgs& g, int r, int p, int q, int fy0, int fx0, int lane, int& pos,
                                          int& fo) {
   pos = 0;
@@ -159,15 +173,15 @@ __device__ __forceinline__ void slot_pos(const GroupArgs& g, int r, int p, int q
     const int yw = y < 0 ? y + g.H : (y >= g.H ? y - g.H : y);
     const int xw = x < 0 ? x + g.W : (x >= g.W ? x - g.W : x);
     pos = yw * g.W + xw;
-    fo = (y - fy0) * Foot::FXP + (x - fx0);
+    fo = (y - fy0) * T::FXP + (x - fx0);
   }
 }
 
 // w * u[k] into the footprint for blocks k0 .. k0 + N - 1 (u holds their values)
-template <int N>
+template <int N, typename T>
 __device__ __forceinline__ void accumulate(acc_t* acc, int fo_v, int k0, const float (&u)[N],
                                            float w, int lane) {
-  const int ab = (lane >> 3) * Foot::FXP + (lane & 7);
+  const int ab = (lane >> 3) * T::FXP + (lane & 7);
   const float ws = w * kFixScaleF;
 #pragma unroll
   for (int k = 0; k < N; ++k) {
@@ -195,6 +209,7 @@ __device__ __forceinline__ void zero_acc(acc_t* acc, int n) {
 // agent-scope integer atomic per nonzero cell: integer addition, so the sums
 // do not depend on the order in which tiles arrive.  A wave takes whole
 // footprint rows, a lane the same columns of each.
+template <typename T>
 __device__ __forceinline__ void flush_acc(const acc_t* acc, const GroupArgs& g, int fy0, int fx0,
                                           acc_t* __restrict__ num) {
   __syncthreads();
@@ -204,7 +219,7 @@ __device__ __forceinline__ void flush_acc(const acc_t* acc, const GroupArgs& g, 
   // -R <= fy0 and fy0 + FY <= H + FY - R + 1: with H > FY every footprint row
   // is at most one period away (same for the columns)
   const bool once = g.H > g.FY && g.W > g.FX;
-  constexpr int kPasses = (Foot::FXmax + kWave - 1) / kWave;
+  constexpr int kPasses = (T::FXmax + kWave - 1) / kWave;
   int xs[kPasses];
 #pragma unroll
   for (int p = 0; p < kPasses; ++p) {
@@ -215,7 +230,7 @@ __device__ __forceinline__ void flush_acc(const acc_t* acc, const GroupArgs& g, 
     int y = fy0 + fy;
     y = once ? y + (y < 0 ? g.H : (y >= g.H ? -g.H : 0)) : pmod(y, g.H);
     const auto row = gnum + static_cast<size_t>(y) * g.W;
-    const acc_t* cells = acc + fy * Foot::FXP;
+    const acc_t* cells = acc + fy * T::FXP;
 #pragma unroll
     for (int p = 0; p < kPasses; ++p) {
       const int fx = p * kWave + lane;
@@ -226,23 +241,23 @@ __device__ __forceinline__ void flush_acc(const acc_t* acc, const GroupArgs& g, 
   __syncthreads();  // the accumulator is reused by the next item
 }
 
-// The tile's match ranks [reference t][K] into LDS (t = 8 * row + column of
-// the tile's 8 x 8 references; references past the image's last row or
+// The tile's match ranks [reference t][K] into LDS (t = row-major place
+// among the tile's references; references past the image's last row or
 // column read a clamped in-bounds entry that no group uses), every thread's
 // loads issued before the first is stored: one memory round trip per tile
 // instead of one per group.  The caller's next barrier publishes them.
-template <int K, int THREADS>
+template <int K, typename T, int THREADS>
 __device__ __forceinline__ void load_ranks(int16_t* ranks, const GroupArgs& g, const int16_t* idx_, int tyi,
                                            int txi) {
   const auto idx = to_global(idx_);
-  constexpr int n = kTPY * kTPX * K;
+  constexpr int n = T::refs * K;
   constexpr int iters = (n + THREADS - 1) / THREADS;
   int v[iters];
 #pragma unroll
   for (int it = 0; it < iters; ++it) {
     const int e = min(static_cast<int>(threadIdx.x) + it * THREADS, n - 1);
     const int t = e / K, k = e % K;
-    const int p = min(tyi * kTPY + t / kTPX, g.nRy - 1), q = min(txi * kTPX + t % kTPX, g.nRx - 1);
+    const int p = min(tyi * T::py + t / T::px, g.nRy - 1), q = min(txi * T::px + t % T::px, g.nRx - 1);
     v[it] = idx[(static_cast<size_t>(p) * g.nRx + q) * K + k];
   }
 #pragma unroll
@@ -254,25 +269,25 @@ __device__ __forceinline__ void load_ranks(int16_t* ranks, const GroupArgs& g, c
 
 // The groups a wave filters in a tile: reference t = wave + j * WAVES,
 // j < kGroups.
-template <int WAVES>
+template <typename T, int WAVES>
 struct GroupWalk {
-  static constexpr int kGroups = (kTPY * kTPX + WAVES - 1) / WAVES;
+  static constexpr int kGroups = (T::refs + WAVES - 1) / WAVES;
   const GroupArgs& g;
   const int16_t* ranks;  // the tile's match ranks in LDS [reference t][K]
   int tyi, txi, wave, lane, fy0, fx0;
 
   __device__ __forceinline__ bool ref_of(int j, int& p, int& q) const {
     const int t = wave + j * WAVES;
-    p = tyi * kTPY + t / kTPX;
-    q = txi * kTPX + t % kTPX;
-    return j < kGroups && t < kTPY * kTPX && p < g.nRy && q < g.nRx;
+    p = tyi * T::py + t / T::px;
+    q = txi * T::px + t % T::px;
+    return j < kGroups && t < T::refs && p < g.nRy && q < g.nRx;
   }
   // rank of slot `lane` of group j, for lanes below K of a group that exists
   // (gather reads nothing else)
   template <int K>
   __device__ __forceinline__ int rank(int j) const {
     const int t = wave + j * WAVES;
-    return t < kTPY * kTPX ? ranks[t * K + (lane & (K - 1))] : 0;
+    return t < T::refs ? ranks[t * K + (lane & (K - 1))] : 0;
   }
   // stack rows of group j from its ranks: v[k] = stack[pos_k * 64 + lane];
   // lane k < K returns slot k's pixel index and footprint offset
@@ -281,7 +296,7 @@ struct GroupWalk {
                                          int& pos_v) const {
     int p, q;
     if (!ref_of(j, p, q)) return false;
-    slot_pos<K>(g, r, p, q, fy0, fx0, lane, pos_v, fo);
+    slot_pos<K, T>(g, r, p, q, fy0, fx0, lane, pos_v, fo);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       // the block's base address is uniform: it goes into a buffer resource
@@ -300,7 +315,7 @@ struct GroupWalk {
                                                 int& fo, int& pos_v) const {
     int p, q;
     if (!ref_of(j, p, q)) return false;
-    slot_pos<K>(g, r, p, q, fy0, fx0, lane, pos_v, fo);
+    slot_pos<K, T>(g, r, p, q, fy0, fx0, lane, pos_v, fo);
     const int a = lane >> 3, b = lane & 7;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -342,8 +357,8 @@ __device__ __forceinline__ void forward_blocks(float* xw, int lane, float (&v)[K
 // gathered spectra.  Small groups also keep the next group's spectra in
 // flight; large ones leave the registers to the filter (sixteen waves per
 // tile hide the loads instead).
-template <int K, int NS, bool PREFETCH, int WAVES, typename F>
-__device__ __forceinline__ void for_each_group(const GroupWalk<WAVES>& walk, const float* const (&stacks)[NS],
+template <int K, int NS, bool PREFETCH, typename W, typename F>
+__device__ __forceinline__ void for_each_group(const W& walk, const float* const (&stacks)[NS],
                                                F&& filter) {
   if constexpr (PREFETCH) {
     int r1 = walk.template rank<K>(1);
@@ -380,27 +395,27 @@ __device__ __forceinline__ void for_each_group(const GroupWalk<WAVES>& walk, con
 // One work item = one tile of references: stage-1 groups.  RECOMPUTE: the
 // blocks' spectra are computed here from the image's pixels instead of
 // gathered from the bior1.5 stack.
-template <int K, bool RECOMPUTE, bool WIDE>
+template <int K, bool RECOMPUTE, int SHAPE>
 __device__ __forceinline__ void group_ht_body(acc_t* acc,
-                                              float (*scratch)[GroupCfg<K, true, WIDE>::chunk * kBlockFloats],
+                                              float (*scratch)[GroupCfg<K, true, SHAPE>::chunk * kBlockFloats],
                                               int16_t* ranks, const ImgRec& r, int R, const HtParams& hp, int item) {
-  const GroupArgs g = make_args(r.H, r.W, R);
+  using Cfg = GroupCfg<K, true, SHAPE>;
+  using T = typename Cfg::T;
+  const GroupArgs g = make_args<T>(r.H, r.W, R);
   const int tyi = item / g.nTx, txi = item % g.nTx;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = wave_id();
-  const int n_acc = g.FY * Foot::FXP;
-  load_ranks<K, GroupCfg<K, true, WIDE>::threads>(ranks, g, r.idx, tyi, txi);
-  zero_acc(acc, n_acc);
-  const int fy0 = kStep * tyi * kTPY - g.R;
-  const int fx0 = kStep * txi * kTPX - g.R;
+  load_ranks<K, T, Cfg::threads>(ranks, g, r.idx, tyi, txi);
+  zero_acc(acc, g.FY * T::FXP);
+  const int fy0 = kStep * tyi * T::py - g.R;
+  const int fx0 = kStep * txi * T::px - g.R;
   float* xw = scratch[wave];
   const int a = lane >> 3, b = lane & 7;
   const float tau = r.sigma * (hp.ht_a - hp.ht_b * static_cast<float>(bior_level(lane)));
   const bool dc_lane = hp.keep_dc && lane == 0;
   acc_t* bw = r.partials;  // block-start weights
 
-  using Cfg = GroupCfg<K, true, WIDE>;
-  const GroupWalk<Cfg::waves> walk{g, ranks, tyi, txi, wave, lane, fy0, fx0};
+  const GroupWalk<T, Cfg::waves> walk{g, ranks, tyi, txi, wave, lane, fy0, fx0};
   const float* const stacks[1] = {r.stack_a};
   auto filter = [&](const float (&cur)[1][K], int fo_v, int pos_v) {
     float v[K];
@@ -455,7 +470,7 @@ __device__ __forceinline__ void group_ht_body(acc_t* acc,
     } else {
       w = 1.0f;
     }
-    accumulate<K>(acc, fo_v, 0, u, w, lane);
+    accumulate<K, T>(acc, fo_v, 0, u, w, lane);
     add_block_weights<K>(bw, pos_v, w, lane);
   };
   if constexpr (RECOMPUTE) {
@@ -473,13 +488,14 @@ __device__ __forceinline__ void group_ht_body(acc_t* acc,
   } else {
     for_each_group<K, 1, Cfg::prefetch>(walk, stacks, filter);
   }
-  flush_acc(acc, g, fy0, fx0, numerator_sums(r));
+  flush_acc<T>(acc, g, fy0, fx0, numerator_sums(r));
 }
 
 // 8-point inverse DCT-II of the coefficients X, all of them scaled by the
 // factor the constants c carry: c[i] = scale cos(i pi / 16) / 2 (i = 1 .. 7;
 // c[4] is also the constant's weight, sqrt(1/8) = cos(pi / 4) / 2).
 __device__ __forceinline__ void dct8_inv_scaled(const float (&c)[8], const float* X, float* x) {
+#pragma clang fp contract(off)
   const float t = c[4] * X[0], p = fmaf(c[4], X[4], t), m = fmaf(-c[4], X[4], t);
   const float r = fmaf(c[2], X[2], c[6] * X[6]), q = fmaf(c[6], X[2], -(c[2] * X[6]));
   const float e[4] = {p + r, m + q, m - q, p - r};
@@ -500,6 +516,7 @@ __device__ __forceinline__ void dct8_inv_scaled(const float (&c)[8], const float
 // band [h, 2h) enters with its weight h.
 template <int K>
 __device__ __forceinline__ void haar_inv_banded(float* v) {
+#pragma clang fp contract(off)
 #pragma unroll
   for (int half = 1; half <= K / 2; half *= 2) {
     float t[K];
@@ -525,18 +542,21 @@ __device__ __forceinline__ void haar_inv_banded(float* v) {
 // CU (one of sixteen before, each wave with a pixel of every block and an
 // address per block; kernel us before -> now: 512^2 91 -> 76, 1001 x 750
 // 285 -> 242, 4096^2 4837 -> 4270, 64 mixed images 7604 -> 6226).
-template <int K>
-__device__ __forceinline__ void group_wiener_body(acc_t* acc, float (*scratch)[GroupCfg<K, false>::chunk * kBlockFloats],
+template <int K, int SHAPE>
+__device__ __forceinline__ void group_wiener_body(acc_t* acc,
+                                                  float (*scratch)[GroupCfg<K, false, SHAPE>::chunk * kBlockFloats],
                                                   int16_t* ranks, const ImgRec& r, int R, int item) {
-  using Cfg = GroupCfg<K, false>;
-  const GroupArgs g = make_args(r.H, r.W, R);
+#pragma clang fp contract(off)  // the same roundings in every shape
+  using Cfg = GroupCfg<K, false, SHAPE>;
+  using T = typename Cfg::T;
+  const GroupArgs g = make_args<T>(r.H, r.W, R);
   const int tyi = item / g.nTx, txi = item % g.nTx;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = wave_id();
-  load_ranks<K, Cfg::threads>(ranks, g, r.idx, tyi, txi);
-  zero_acc(acc, g.FY * Foot::FXP);
-  const int fy0 = kStep * tyi * kTPY - g.R;
-  const int fx0 = kStep * txi * kTPX - g.R;
+  load_ranks<K, T, Cfg::threads>(ranks, g, r.idx, tyi, txi);
+  zero_acc(acc, g.FY * T::FXP);
+  const int fy0 = kStep * tyi * T::py - g.R;
+  const int fx0 = kStep * txi * T::px - g.R;
   float* xw = scratch[wave];
   const int a = lane >> 3, b = lane & 7;
   const float s2 = r.sigma * r.sigma;
@@ -546,12 +566,12 @@ __device__ __forceinline__ void group_wiener_body(acc_t* acc, float (*scratch)[G
   constexpr Mat8 D = dct8();
   constexpr int CH = Cfg::chunk;
 
-  const GroupWalk<Cfg::waves> walk{g, ranks, tyi, txi, wave, lane, fy0, fx0};
+  const GroupWalk<T, Cfg::waves> walk{g, ranks, tyi, txi, wave, lane, fy0, fx0};
 #pragma unroll 1
   for (int j = 0; j < walk.kGroups; ++j) {
     int p, q, pos_v, fo_v;
     if (!walk.ref_of(j, p, q)) continue;
-    slot_pos<K>(g, walk.template rank<K>(j), p, q, fy0, fx0, lane, pos_v, fo_v);
+    slot_pos<K, T>(g, walk.template rank<K>(j), p, q, fy0, fx0, lane, pos_v, fo_v);
     // the pilot's spectra, turned into the Wiener gains; the noisy spectra are
     // loaded after them, so that the two are never in flight together
     float wt[K];
@@ -611,26 +631,26 @@ __device__ __forceinline__ void group_wiener_body(acc_t* acc, float (*scratch)[G
         dct8_inv_scaled(c2, x, y);
         acc_t* cell = acc + fo + b;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) atomicAdd(cell + i * Foot::FXP, static_cast<acc_t>(to_fixed_scaled(y[i])));
+        for (int i = 0; i < 8; ++i) atomicAdd(cell + i * T::FXP, static_cast<acc_t>(to_fixed_scaled(y[i])));
       }
     }
     add_block_weights<K>(bw, pos_v, w, lane);
   }
-  flush_acc(acc, g, fy0, fx0, numerator_sums(r));
+  flush_acc<T>(acc, g, fy0, fx0, numerator_sums(r));
 }
 
 // (the second launch bound is the minimum number of waves per SIMD)
-template <int K, bool BATCH, bool RECOMPUTE, bool WIDE>
-__global__ __launch_bounds__((GroupCfg<K, true, WIDE>::threads),
-                             (GroupCfg<K, true, WIDE>::min_waves_per_simd)) void group_ht_kernel(ImgRec one,
-                                                                                                 WorkList wl, int R,
-                                                                                                 HtParams hp) {
-  using Cfg = GroupCfg<K, true, WIDE>;
-  __shared__ acc_t acc[Foot::entries];
+template <int K, bool BATCH, bool RECOMPUTE, int SHAPE>
+__global__ __launch_bounds__((GroupCfg<K, true, SHAPE>::threads),
+                             (GroupCfg<K, true, SHAPE>::min_waves_per_simd)) void group_ht_kernel(ImgRec one,
+                                                                                                  WorkList wl, int R,
+                                                                                                  HtParams hp) {
+  using Cfg = GroupCfg<K, true, SHAPE>;
+  __shared__ acc_t acc[Cfg::T::entries];
   __shared__ float scratch[Cfg::waves][Cfg::chunk * kBlockFloats];
-  __shared__ int16_t ranks[kTPY * kTPX * K];
+  __shared__ int16_t ranks[Cfg::T::refs * K];
   for_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
-    group_ht_body<K, RECOMPUTE, WIDE>(acc, scratch, ranks, r, R, hp, item);
+    group_ht_body<K, RECOMPUTE, SHAPE>(acc, scratch, ranks, r, R, hp, item);
   });
 }
 
@@ -642,16 +662,17 @@ __global__ void clear_weights_kernel(acc_t* __restrict__ w, size_t n) {
     w[i] = 0;
 }
 
-template <int K, bool BATCH>
-__global__ __launch_bounds__((GroupCfg<K, false>::threads),
-                             (GroupCfg<K, false>::min_waves_per_simd)) void group_wiener_kernel(ImgRec one, WorkList wl,
-                                                                                                int R) {
-  using Cfg = GroupCfg<K, false>;
-  __shared__ acc_t acc[Foot::entries];
+template <int K, bool BATCH, int SHAPE>
+__global__ __launch_bounds__((GroupCfg<K, false, SHAPE>::threads),
+                             (GroupCfg<K, false, SHAPE>::min_waves_per_simd)) void group_wiener_kernel(ImgRec one,
+                                                                                                       WorkList wl,
+                                                                                                       int R) {
+  using Cfg = GroupCfg<K, false, SHAPE>;
+  __shared__ acc_t acc[Cfg::T::entries];
   __shared__ float scratch[Cfg::waves][Cfg::chunk * kBlockFloats];
-  __shared__ int16_t ranks[kTPY * kTPX * K];
+  __shared__ int16_t ranks[Cfg::T::refs * K];
   for_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
-    group_wiener_body<K>(acc, scratch, ranks, r, R, item);
+    group_wiener_body<K, SHAPE>(acc, scratch, ranks, r, R, item);
   });
 }
 
@@ -741,29 +762,58 @@ __global__ void quantize_kernel(const float* __restrict__ in, uint16_t* __restri
 
 size_t partials_bytes(int H, int W) { return aggregation_entries(H, W) * sizeof(acc_t); }
 
-int group_items_for(int H, int W, int R) {
-  const GroupArgs g = make_args(H, W, R);
+template <typename T>
+static int tiles_of(int H, int W) {
+  const GroupArgs g = make_args<T>(H, W, 0);
   return g.nTy * g.nTx;
 }
 
+// items of the batch launches (two-tile shape)
+int group_items_for(int H, int W) { return tiles_of<Tile<8, 8>>(H, W); }
+
 int reduce_items_for(int H, int W) { return reduce_items(H, W); }
 
-template <int K, bool WIDE>
+// The shapes of a single image's launches, by its tiles of 8 x 8 references.
+// Two tiles per CU are 512 of them: below that CUs idle, or hold one tile while
+// others work on two, unless the tiles are smaller; small tiles pay for it with
+// more footprint cells to clear and add per reference.  Whole first stage, us,
+// 8 x 8 | 4 x 4 | 2 x 4 references: 36 tiles (128^2) 44 | 27 | 24; 64 (192^2)
+// 50 | 35 | 33; 121 (256^2) 57 | 45 | 49; 256 (384^2, one per CU) 71 | 73 | 75;
+// 294 (321 x 481) 88 | 77 | 79; 361 (448^2) 96 | 90 | 94; 484 (512^2)
+// 108 | 110 | 113; 1344 (1001 x 750) 280 | 266 | 279; 29241 (4096^2)
+// 5300 | 5476 | 5788.
+static GroupShape ht_shape_for(int H, int W) {
+  const int t = tiles_of<Tile<8, 8>>(H, W);
+  if (t <= 64) return kTiny;
+  return t <= 192 || (t > 256 && t <= 420) ? kSmall : kTwoTiles;
+}
+
+// The Wiener kernel also gains from a loop of one group per wave (no register
+// spills), which pays for the cells much further.  Whole second stage, us,
+// 8 x 8 | 4 x 4 | 2 x 4 references: 128^2 60 | 37 | 31; 256^2 72 | 58 | 55;
+// 384^2 99 | 101 | 92; 321 x 481 119 | 106 | 98; 512^2 149 | 160 | 146;
+// 640^2 224 | 234 | 218; 1001 x 750 415 | 424 | 387; 2048^2 2092 | 2202 | 2101.
+static GroupShape wiener_shape_for(int H, int W) {
+  return tiles_of<Tile<8, 8>>(H, W) <= 4096 ? kTiny : kTwoTiles;
+}
+
+template <int K, int SHAPE>
 static hipError_t launch_ht_shape(const ImgRec& one, const WorkList* wl, int R, const HtParams& hp, int recompute,
                                   hipStream_t st) {
-  using Cfg = GroupCfg<K, true, WIDE>;
+  using Cfg = GroupCfg<K, true, SHAPE>;
   if (!wl) {
+    const dim3 grid(tiles_of<typename Cfg::T>(one.H, one.W));
     if (recompute)
-      hipLaunchKernelGGL((group_ht_kernel<K, false, true, WIDE>), dim3(group_items_for(one.H, one.W, R)),
-                         dim3(Cfg::threads), 0, st, one, WorkList{}, R, hp);
+      hipLaunchKernelGGL((group_ht_kernel<K, false, true, SHAPE>), grid, dim3(Cfg::threads), 0, st, one, WorkList{}, R,
+                         hp);
     else
-      hipLaunchKernelGGL((group_ht_kernel<K, false, false, WIDE>), dim3(group_items_for(one.H, one.W, R)),
-                         dim3(Cfg::threads), 0, st, one, WorkList{}, R, hp);
-  } else {
+      hipLaunchKernelGGL((group_ht_kernel<K, false, false, SHAPE>), grid, dim3(Cfg::threads), 0, st, one, WorkList{},
+                         R, hp);
+  } else if constexpr (SHAPE <= kOneTile) {
     if (recompute) return hipErrorInvalidValue;  // batches read the stack
     if (wl->total <= 0) return hipSuccess;
-    hipLaunchKernelGGL((group_ht_kernel<K, true, false, WIDE>), batch_grid(wl->total),
-                       dim3(Cfg::threads), 0, st, one, *wl, R, hp);
+    hipLaunchKernelGGL((group_ht_kernel<K, true, false, SHAPE>), batch_grid(wl->total), dim3(Cfg::threads), 0, st, one,
+                       *wl, R, hp);
   }
   return hipGetLastError();
 }
@@ -771,8 +821,13 @@ static hipError_t launch_ht_shape(const ImgRec& one, const WorkList* wl, int R, 
 template <int K>
 static hipError_t launch_ht_k(const ImgRec& one, const WorkList* wl, int R, const HtParams& hp, int recompute,
                               int shape, hipStream_t st) {
-  if (K <= 16 && shape == 1) return launch_ht_shape<K, false>(one, wl, R, hp, recompute, st);
-  return launch_ht_shape<K, true>(one, wl, R, hp, recompute, st);
+  if constexpr (K <= 16)
+    if (shape == 1) return launch_ht_shape<K, kOneTile>(one, wl, R, hp, recompute, st);
+  switch (wl ? kTwoTiles : ht_shape_for(one.H, one.W)) {
+    case kTiny: return launch_ht_shape<K, kTiny>(one, wl, R, hp, recompute, st);
+    case kSmall: return launch_ht_shape<K, kSmall>(one, wl, R, hp, recompute, st);
+    default: return launch_ht_shape<K, kTwoTiles>(one, wl, R, hp, recompute, st);
+  }
 }
 
 hipError_t launch_group_ht(const ImgRec& one, const WorkList* wl, int R, int K, float ht_a, float ht_b,
@@ -795,17 +850,24 @@ hipError_t launch_clear_weights(const ImgRec& one, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int K>
-static hipError_t launch_wiener_k(const ImgRec& one, const WorkList* wl, int R, hipStream_t st) {
+template <int K, int SHAPE>
+static hipError_t launch_wiener_shape(const ImgRec& one, const WorkList* wl, int R, hipStream_t st) {
+  using Cfg = GroupCfg<K, false, SHAPE>;
   if (!wl) {
-    hipLaunchKernelGGL((group_wiener_kernel<K, false>), dim3(group_items_for(one.H, one.W, R)),
-                       dim3(GroupCfg<K, false>::threads), 0, st, one, WorkList{}, R);
-  } else {
+    hipLaunchKernelGGL((group_wiener_kernel<K, false, SHAPE>), dim3(tiles_of<typename Cfg::T>(one.H, one.W)),
+                       dim3(Cfg::threads), 0, st, one, WorkList{}, R);
+  } else if constexpr (SHAPE == kTwoTiles) {
     if (wl->total <= 0) return hipSuccess;
-    hipLaunchKernelGGL((group_wiener_kernel<K, true>), batch_grid(wl->total),
-                       dim3(GroupCfg<K, false>::threads), 0, st, one, *wl, R);
+    hipLaunchKernelGGL((group_wiener_kernel<K, true, SHAPE>), batch_grid(wl->total), dim3(Cfg::threads), 0, st, one,
+                       *wl, R);
   }
   return hipGetLastError();
+}
+
+template <int K>
+static hipError_t launch_wiener_k(const ImgRec& one, const WorkList* wl, int R, hipStream_t st) {
+  if (!wl && wiener_shape_for(one.H, one.W) == kTiny) return launch_wiener_shape<K, kTiny>(one, wl, R, st);
+  return launch_wiener_shape<K, kTwoTiles>(one, wl, R, st);
 }
 
 hipError_t launch_group_wiener(const ImgRec& one, const WorkList* wl, int R, int K, hipStream_t st) {

@@ -43,7 +43,7 @@ int stack_items_for(int H, int W);
 // bytes of the aggregation buffer (64-bit fixed point) of the group kernels:
 // block-start weights of the image, then its numerator sums
 size_t partials_bytes(int H, int W);
-int group_items_for(int H, int W, int R);
+int group_items_for(int H, int W);
 
 // stage-1 groups: stack_a (bior) + idx -> partials (weights scaled by rec.eps);
 // recompute (one image only): the blocks' spectra from rec.noisy's pixels

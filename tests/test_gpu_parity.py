@@ -516,6 +516,18 @@ def test_batch_equals_single_calls(torch, G, ctx):
         assert np.array_equal(basic[i].cpu().numpy(), ctx.basic(imgs[i], sig[i]).cpu().numpy())
 
 
+@pytest.mark.parametrize("k", [2, 4, 8, 16, 32])
+@pytest.mark.parametrize("H,W", [(24, 25), (190, 196), (200, 211)])
+def test_single_image_tiles_equal_batch_tiles(torch, G, ctx, k, H, W):
+    """A single image's group launches take smaller reference tiles than a
+    batch's where the image has few; the sums are integers, so both give the
+    same bits (sizes on both sides of a rule's line and at ragged tile edges)."""
+    say("tile shapes", k, H, W)
+    gp = G.default_params(search=15, k_ht=k, k_wiener=k)
+    x = up(torch, synth.make_case(H, W, SIG, 23)[1])
+    assert torch.equal(ctx.denoise_batch([x], [SIG], params=gp)[0], ctx.denoise(x, SIG, gp))
+
+
 def test_batch_many_small_images_equal_single_calls(torch, G, ctx):
     """Many images of 39..64 px (several images share each 64-item block of
     every phase's item -> image table) around two larger ones, some with a
