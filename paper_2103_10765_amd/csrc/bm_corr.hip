@@ -605,13 +605,14 @@ __global__ __launch_bounds__(kThreads, 6) void bm_corr_kernel(ImgRec one, WorkLi
       if constexpr (!BATCH) {
         if (item >= stack_items(one.H, one.W)) item = -1;
         stack_body<KIND, 4, true>(lds, t, plane ? one.pilot : one.noisy, plane ? one.stack_b : one.stack_a,
-                                  plane ? nullptr : one.partials, one.H, one.W, item);
+                                  plane ? nullptr : one.partials, plane == 0, one.H, one.W, item);
       } else {
         int first = item + 1;
         const bool any = item < stack_wl.total;
         const const_rec_ptr r = find_item(stack_wl, any ? item : 0, first);
         stack_body<KIND, 4, true>(lds, t, plane ? r->pilot : r->noisy, plane ? r->stack_b : r->stack_a,
-                                  plane ? nullptr : r->partials, r->H, r->W, any ? item - first : -1);
+                                  plane ? nullptr : r->partials, plane == 0, r->H, r->W,
+                                  any ? item - first : -1);
       }
       return;
     }
@@ -667,7 +668,7 @@ hipError_t launch_corr_grid(const ImgRec& one, const WorkList* wl, const WorkLis
                             int use_pilot, int stack_kind, hipStream_t st) {
   if (stack_kind < 0) return launch_corr_kind<Q, C, WIDE, -1>(one, wl, stack_wl, R, K, use_pilot, st);
   return stack_kind == 0 ? launch_corr_kind<Q, C, WIDE, 0>(one, wl, stack_wl, R, K, use_pilot, st)
-                         : launch_corr_kind<Q, C, WIDE, 1>(one, wl, stack_wl, R, K, use_pilot, st);
+                         : launch_corr_kind<Q, C, WIDE, 2>(one, wl, stack_wl, R, K, use_pilot, st);
 }
 
 }  // namespace
@@ -678,7 +679,8 @@ long corr_tiles(int H, int W) { return static_cast<long>(corr_items(H, W)); }
 
 hipError_t launch_bm_corr(const ImgRec& one, const WorkList* wl, const WorkList* stack_wl, int R, int K, int use_pilot,
                           int stack_kind, hipStream_t st) {
-  if (K < 2 || K > 32 || R < 0 || R > kMaxR || (wl && stack_kind >= 0 && !stack_wl)) return hipErrorInvalidValue;
+  if (K < 2 || K > 32 || R < 0 || R > kMaxR || stack_kind == 1 ||
+      (wl && stack_kind >= 0 && !stack_wl)) return hipErrorInvalidValue;
   const int nb = blocks_per_axis(R);
   if (nb <= 8) return launch_corr_grid<4, 2, false>(one, wl, stack_wl, R, K, use_pilot, stack_kind, st);
   if (nb < kMaxNb) return launch_corr_grid<6, 3, false>(one, wl, stack_wl, R, K, use_pilot, stack_kind, st);

@@ -381,9 +381,9 @@ int run_match(gbm3d_ctx* ctx, ImgRec& r, int R, int K, const gbm3d_params& p, in
 bool match_with_stacks(const gbm3d_ctx* ctx, int method) { return method == GBM3D_BM_CORR && !ctx->timing; }
 
 // A stage's matching and stacks (kind 0: the bior1.5 stack of the noisy image
-// into stack_a, 1: the DCT stacks of the noisy image and the pilot).
-int run_match_stacks(gbm3d_ctx* ctx, ImgRec& r, int R, int K, const BmChoice& c, int use_pilot, int kind,
-                     hipStream_t st) {
+// into stack_a, 2: the DCT stacks of the noisy image and the pilot).
+int run_match_stacks(gbm3d_ctx* ctx, ImgRec& r, int R, int K, const BmChoice& c, int kind, hipStream_t st) {
+  const int use_pilot = kind == 0 ? 0 : 1;
   if (match_with_stacks(ctx, c.method)) {
     HIP_TRY(ctx, gbm3d::launch_bm_corr(r, nullptr, nullptr, R, K, use_pilot, kind, st), "block matching launch");
     return GBM3D_OK;
@@ -440,7 +440,7 @@ int run_basic(gbm3d_ctx* ctx, const uint16_t* noisy, int H, int W, float sigma, 
     CHECK(run_match(ctx, r, R, p.k_ht, c, 0, st));
     HIP_TRY(ctx, gbm3d::launch_clear_weights(r, st), "weight clearing launch");
   } else {
-    CHECK(run_match_stacks(ctx, r, R, p.k_ht, c, 0, 0, st));
+    CHECK(run_match_stacks(ctx, r, R, p.k_ht, c, 0, st));
   }
   HIP_TRY(ctx, timed(ctx, "group_ht", st, [&] {
             return gbm3d::launch_group_ht(r, nullptr, R, p.k_ht, p.ht_a, p.ht_b, p.ht_weight, p.keep_dc, recompute,
@@ -477,7 +477,7 @@ int run_wiener(gbm3d_ctx* ctx, const uint16_t* noisy, const uint16_t* pilot, int
   r.stack_b = w.stack_b;
   r.idx = w.idx;
   r.partials = w.partials;
-  CHECK(run_match_stacks(ctx, r, R, p.k_wiener, choose_bm(ctx, p, gbm3d::corr_tiles(H, W), p.k_wiener), 1, 1, st));
+  CHECK(run_match_stacks(ctx, r, R, p.k_wiener, choose_bm(ctx, p, gbm3d::corr_tiles(H, W), p.k_wiener), 2, st));
   HIP_TRY(ctx, timed(ctx, "group_wiener", st, [&] {
             return gbm3d::launch_group_wiener(r, nullptr, R, p.k_wiener, st);
           }),
@@ -622,11 +622,11 @@ WorkList worklist(const gbm3d_ctx* ctx, const BatchPlan& plan, int n, int phase)
 }
 
 // Batch matching of a stage, then its stacks (kind 0: the bior1.5 stack of the
-// noisy images; 1: the DCT stacks of the noisy images and of the pilots).
+// noisy images; 2: the DCT stacks of the noisy images and of the pilots).
 int launch_batch_prep(gbm3d_ctx* ctx, const WorkList& sk, const WorkList& bm, int R, int K, int method, int split,
                       int kind, hipStream_t st) {
   const ImgRec none = blank_rec(0, 0, 0.0f);
-  const int use_pilot = kind;
+  const int use_pilot = kind == 0 ? 0 : 1;
   const int sel = kind == 0 ? 0 : -1;
   if (match_with_stacks(ctx, method)) {
     HIP_TRY(ctx, gbm3d::launch_bm_corr(none, &bm, &sk, R, K, use_pilot, kind, st), "batch block matching");
@@ -670,7 +670,7 @@ int launch_batch(gbm3d_ctx* ctx, const BatchPlan& plan, int n, const gbm3d_param
     TraceRange trace("batch stage2");
     const WorkList bm = worklist(ctx, plan, n, kBm2), sk = worklist(ctx, plan, n, kStack2);
     const WorkList gr = worklist(ctx, plan, n, kGroup2), rd = worklist(ctx, plan, n, kReduce2);
-    CHECK(launch_batch_prep(ctx, sk, bm, R, p.k_wiener, plan.bm_method2, plan.bm_split2, 1, st));
+    CHECK(launch_batch_prep(ctx, sk, bm, R, p.k_wiener, plan.bm_method2, plan.bm_split2, 2, st));
     HIP_TRY(ctx, timed(ctx, "group_wiener", st, [&] {
               return gbm3d::launch_group_wiener(none, &gr, R, p.k_wiener, st);
             }),

@@ -121,7 +121,7 @@ __device__ __forceinline__ void apply_mat(const Mat8& M, const float* x, float* 
   }
 }
 
-// 8-point DCT-II and its inverse by the even/odd symmetry of the basis,
+// 8-point DCT-II by the even/odd symmetry of the basis,
 // C[k][7-n] = (-1)^k C[k][n]: 40 operations instead of 64.
 __device__ __forceinline__ void dct8_fwd(const float* x, float* y) {
   constexpr Mat8 C = dct8();
@@ -141,18 +141,62 @@ __device__ __forceinline__ void dct8_fwd(const float* x, float* y) {
   }
 }
 
-__device__ __forceinline__ void dct8_inv(const float* X, float* x) {
-  constexpr Mat8 C = dct8();
+// The same transform with its output factors left out: C = S F with
+// S = diag(dct8_scale), 26 operations for F (rotations by pi/8, 3 pi/16 and
+// pi/16 in tangent form, the last two's common factor in the sums after them).
+constexpr double dct8_scale(int k) {
+  return k % 4 == 0             ? 0.35355339059327376  // sqrt(1/8)
+         : k % 2 == 0           ? 0.46193976625564337  // cos(pi/8) / 2
+         : k == 1 || k == 7     ? 0.29396890060483970  // cos(3 pi/16) / sqrt(8)
+                                : 0.41573480615127262; // cos(3 pi/16) / 2
+}
+constexpr float kTan2 = 0.41421356237309503f;              // tan(pi/8)
+constexpr float kTan3 = 0.66817863791929892f;              // tan(3 pi/16)
+constexpr float kTan1 = 0.19891236737965800f;              // tan(pi/16)
+constexpr float kRot = 1.1795805980838893f;                // cos(pi/16) / cos(3 pi/16)
+
+// y = F x
+__device__ __forceinline__ void dct8_fwd_raw(const float* x, float* y) {
+#pragma clang fp contract(off)
+  float s[4], d[4];
 #pragma unroll
   for (int n = 0; n < 4; ++n) {
-    float e = 0.0f, o = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 8; k += 2) e = fmaf(static_cast<float>(C.m[k][n]), X[k], e);
-#pragma unroll
-    for (int k = 1; k < 8; k += 2) o = fmaf(static_cast<float>(C.m[k][n]), X[k], o);
-    x[n] = e + o;
-    x[7 - n] = e - o;
+    s[n] = x[n] + x[7 - n];
+    d[n] = x[n] - x[7 - n];
   }
+  const float a0 = s[0] + s[3], a1 = s[1] + s[2], b0 = s[0] - s[3], b1 = s[1] - s[2];
+  y[0] = a0 + a1;
+  y[4] = a0 - a1;
+  y[2] = fmaf(kTan2, b1, b0);
+  y[6] = fmaf(kTan2, b0, -b1);
+  const float u4 = fmaf(kTan3, d[0], d[3]), u7 = fmaf(-kTan3, d[3], d[0]);
+  const float u5 = fmaf(kTan1, d[1], d[2]), u6 = fmaf(-kTan1, d[2], d[1]);
+  const float e4 = fmaf(kRot, u6, u4), e6 = fmaf(-kRot, u6, u4);
+  const float e7 = fmaf(kRot, u5, u7), e5 = fmaf(-kRot, u5, u7);
+  y[1] = e7 + e4;
+  y[7] = e7 - e4;
+  y[3] = e5;
+  y[5] = e6;
+}
+
+// x = F^T z: the inverse DCT of coefficients z / dct8_scale
+__device__ __forceinline__ void dct8_inv_raw(const float* z, float* x) {
+#pragma clang fp contract(off)
+  const float a0 = z[0] + z[4], a1 = z[0] - z[4];
+  const float b0 = fmaf(kTan2, z[6], z[2]), b1 = fmaf(kTan2, z[2], -z[6]);
+  const float s[4] = {a0 + b0, a1 + b1, a1 - b1, a0 - b0};
+  const float e4 = z[1] - z[7], e7 = z[1] + z[7];
+  const float u4 = e4 + z[5], u6 = e4 - z[5], u7 = e7 + z[3], u5 = e7 - z[3];
+  const float d3 = fmaf(-kTan3, u7, u4), d0 = fmaf(kTan3, u4, u7);
+  const float d2 = fmaf(-kTan1, u6, u5), d1 = fmaf(kTan1, u5, u6);  // (times kRot)
+  x[0] = s[0] + d0;
+  x[7] = s[0] - d0;
+  x[1] = fmaf(kRot, d1, s[1]);
+  x[6] = fmaf(-kRot, d1, s[1]);
+  x[2] = fmaf(kRot, d2, s[2]);
+  x[5] = fmaf(-kRot, d2, s[2]);
+  x[3] = s[3] + d3;
+  x[4] = s[3] - d3;
 }
 
 // Element `lane` of the 64 floats at `blk` (a wave-uniform address) by a raw
@@ -176,6 +220,11 @@ constexpr double kFixMagic = 6755399441055744.0;  // 1.5 * 2^52: adding it round
 __device__ __forceinline__ long long to_fixed(float x) {
   const double y = fma(static_cast<double>(x), kFixScale, kFixMagic);
   return __double_as_longlong(y) - __double_as_longlong(kFixMagic);
+}
+
+// The same with x = w y, w as w * 2^40 in double (the product is exact).
+__device__ __forceinline__ long long to_fixed_product(float y, double w_scaled) {
+  return __double_as_longlong(fma(static_cast<double>(y), w_scaled, kFixMagic)) - __double_as_longlong(kFixMagic);
 }
 
 // The same for xs = x * 2^40 already formed in float (scaling by a power of

@@ -491,39 +491,18 @@ __device__ __forceinline__ void group_ht_body(acc_t* acc,
   flush_acc<T>(acc, g, fy0, fx0, numerator_sums(r));
 }
 
-// 8-point inverse DCT-II of the coefficients X, all of them scaled by the
-// factor the constants c carry: c[i] = scale cos(i pi / 16) / 2 (i = 1 .. 7;
-// c[4] is also the constant's weight, sqrt(1/8) = cos(pi / 4) / 2).
-__device__ __forceinline__ void dct8_inv_scaled(const float (&c)[8], const float* X, float* x) {
-#pragma clang fp contract(off)
-  const float t = c[4] * X[0], p = fmaf(c[4], X[4], t), m = fmaf(-c[4], X[4], t);
-  const float r = fmaf(c[2], X[2], c[6] * X[6]), q = fmaf(c[6], X[2], -(c[2] * X[6]));
-  const float e[4] = {p + r, m + q, m - q, p - r};
-  float o[4];
-  // cos((2 n + 1) k pi / 16) for k = 1, 3, 5, 7, folded into the first octant
-  o[0] = fmaf(c[1], X[1], fmaf(c[3], X[3], fmaf(c[5], X[5], c[7] * X[7])));
-  o[1] = fmaf(c[3], X[1], fmaf(-c[7], X[3], fmaf(-c[1], X[5], -(c[5] * X[7]))));
-  o[2] = fmaf(c[5], X[1], fmaf(-c[1], X[3], fmaf(c[7], X[5], c[3] * X[7])));
-  o[3] = fmaf(c[7], X[1], fmaf(-c[5], X[3], fmaf(c[3], X[5], -(c[1] * X[7]))));
-#pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    x[n] = e[n] + o[n];
-    x[7 - n] = e[n] - o[n];
-  }
-}
-
-// Unnormalised Haar inverse (haar_inv_raw) of v[k] haar_gain2<K>(k) K: the
-// band [h, 2h) enters with its weight h.
+// Unnormalised Haar inverse (haar_inv_raw) of v[k] wt[k], in place of v.
 template <int K>
-__device__ __forceinline__ void haar_inv_banded(float* v) {
+__device__ __forceinline__ void haar_inv_weighted(float* v, const float* wt) {
 #pragma clang fp contract(off)
+  v[0] *= wt[0];
 #pragma unroll
   for (int half = 1; half <= K / 2; half *= 2) {
     float t[K];
 #pragma unroll
     for (int j = 0; j < half; ++j) {
-      t[2 * j] = fmaf(static_cast<float>(half), v[half + j], v[j]);
-      t[2 * j + 1] = fmaf(-static_cast<float>(half), v[half + j], v[j]);
+      t[2 * j] = fmaf(v[half + j], wt[half + j], v[j]);
+      t[2 * j + 1] = fmaf(-v[half + j], wt[half + j], v[j]);
     }
 #pragma unroll
     for (int j = 0; j < 2 * half; ++j) v[j] = t[j];
@@ -531,17 +510,21 @@ __device__ __forceinline__ void haar_inv_banded(float* v) {
 }
 
 // One work item = one tile of references: stage-2 groups.
-// Bound by vector issue and the gathers' latency.  Every multiplication by a
-// factor common to a block or band rides on one that is there anyway: the
-// Haar gains of the Wiener quotient are on the noise variance (sv), those of
-// the inverse on its butterflies, and the aggregation weight and fixed-point
-// scale on the constants of the row transform.  The column transform leaves a
-// lane eight pixels of one column of a block, which it adds into the footprint
-// from there: one address per column, rows by instruction offsets, no trip
-// back through the scratch.  At 80 registers two tiles of twelve waves share a
-// CU (one of sixteen before, each wave with a pixel of every block and an
-// address per block; kernel us before -> now: 512^2 91 -> 76, 1001 x 750
-// 285 -> 242, 4096^2 4837 -> 4270, 64 mixed images 7604 -> 6226).
+// Bound by vector issue.  No factor common to a block, band or coefficient is
+// multiplied in by itself: the DCT's output factors s = dct8_scale(a)
+// dct8_scale(b) are left out of the pilot's stack and squared in the noisy one
+// (as the inverse without its input factors wants them), and with the Haar
+// gains they are on the noise variance; the inverse Haar's band weights h are
+// on the gains, which enter its butterflies as FMAs; the aggregation weight is
+// on the conversion to fixed point.  The column transform leaves a lane eight
+// pixels of one column of a block, which it adds into the footprint from
+// there: one address per column, rows by instruction offsets, no trip back
+// through the scratch.
+// At 80 registers two tiles of twelve waves share a CU (before: one of sixteen,
+// a pixel of every block per lane and an address per block).  Kernel us, before
+// -> two tiles -> scale-free transforms: 512^2 91 -> 76 -> 71, 1001 x 750
+// 285 -> 242 -> 217, 4096^2 4837 -> 4270 -> 3760, 64 mixed images
+// 7604 -> 6226 -> 5670.
 template <int K, int SHAPE>
 __device__ __forceinline__ void group_wiener_body(acc_t* acc,
                                                   float (*scratch)[GroupCfg<K, false, SHAPE>::chunk * kBlockFloats],
@@ -551,26 +534,36 @@ __device__ __forceinline__ void group_wiener_body(acc_t* acc,
   using T = typename Cfg::T;
   const GroupArgs g = make_args<T>(r.H, r.W, R);
   const int tyi = item / g.nTx, txi = item % g.nTx;
-  const int lane = threadIdx.x & (kWave - 1);
+  const int lane0 = threadIdx.x & (kWave - 1);
   const int wave = wave_id();
   load_ranks<K, T, Cfg::threads>(ranks, g, r.idx, tyi, txi);
   zero_acc(acc, g.FY * T::FXP);
   const int fy0 = kStep * tyi * T::py - g.R;
   const int fx0 = kStep * txi * T::px - g.R;
-  float* xw = scratch[wave];
-  const int a = lane >> 3, b = lane & 7;
-  const float s2 = r.sigma * r.sigma;
+  // noise variance in the units of the lane's squared pilot coefficients
+  float s2 = r.sigma * r.sigma;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float inv = static_cast<float>(1.0 / (dct8_scale(i) * dct8_scale(i)));
+    s2 *= (lane0 / 8 == i ? inv : 1.0f) * (lane0 % 8 == i ? inv : 1.0f);
+  }
   acc_t* bw = r.partials;  // block-start weights
   const float* __restrict__ stack_n = r.stack_a;
   const float* __restrict__ stack_p = r.stack_b;
-  constexpr Mat8 D = dct8();
   constexpr int CH = Cfg::chunk;
 
-  const GroupWalk<T, Cfg::waves> walk{g, ranks, tyi, txi, wave, lane, fy0, fx0};
+  const GroupWalk<T, Cfg::waves> walk{g, ranks, tyi, txi, wave, lane0, fy0, fx0};
 #pragma unroll 1
   for (int j = 0; j < walk.kGroups; ++j) {
     int p, q, pos_v, fo_v;
     if (!walk.ref_of(j, p, q)) continue;
+    // what follows from the lane is formed again for each group: kept through
+    // the loop it would not fit the registers
+    int lane = lane0;
+    float sv = s2;
+    asm volatile("" : "+v"(lane), "+v"(sv));
+    float* xw = scratch[wave];
+    const int a = lane >> 3, b = lane & 7;
     slot_pos<K, T>(g, walk.template rank<K>(j), p, q, fy0, fx0, lane, pos_v, fo_v);
     // the pilot's spectra, turned into the Wiener gains; the noisy spectra are
     // loaded after them, so that the two are never in flight together
@@ -579,14 +572,19 @@ __device__ __forceinline__ void group_wiener_body(acc_t* acc,
     for (int k = 0; k < K; ++k)
       wt[k] = load_block_lane(stack_p + static_cast<size_t>(__builtin_amdgcn_readlane(pos_v, k)) * 64, lane);
     haar_fwd_raw<K>(wt);
-    float sw2 = 0.0f;
+    // h b^2 / (b^2 + sigma^2), b^2 = haar_gain2 x and h = K haar_gain2 >= 1 the
+    // band's weight (both powers of two); their squares' sum without h
+    float sw2 = 0.0f, band = 0.0f;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      // b^2 / (b^2 + sigma^2) with b^2 = haar_gain2 x (haar_gain2 is a power of two)
-      const float x = wt[k] * wt[k], sv = s2 * (1.0f / haar_gain2<K>(k));
-      wt[k] = x * __builtin_amdgcn_rcpf(x + sv);
+      const float h = K * haar_gain2<K>(k), x = wt[k] * wt[k];
+      wt[k] = x * __builtin_amdgcn_rcpf(fmaf(x, 1.0f / h, sv * (K / (h * h))));
       if (k == 0 && lane == 0) wt[k] = 1.0f;
-      sw2 = fmaf(wt[k], wt[k], sw2);
+      band = fmaf(wt[k], wt[k], band);
+      if (k == 0 || k + 1 == K || haar_gain2<K>(k + 1) != haar_gain2<K>(k)) {
+        sw2 = fmaf(band, 1.0f / (h * h), sw2);
+        band = 0.0f;
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
     float v[K];
@@ -595,16 +593,8 @@ __device__ __forceinline__ void group_wiener_body(acc_t* acc,
       v[k] = load_block_lane(stack_n + static_cast<size_t>(__builtin_amdgcn_readlane(pos_v, k)) * 64, lane);
     const float w = 1.0f / wave_sum(sw2);
     haar_fwd_raw<K>(v);
-#pragma unroll
-    for (int k = 0; k < K; ++k) v[k] *= wt[k];
-    haar_inv_banded<K>(v);
-    float c1[8], c2[8];
-    const float scale = w * (kFixScaleF / static_cast<float>(K));
-#pragma unroll
-    for (int i = 1; i < 8; ++i) {
-      c2[i] = i == 4 ? static_cast<float>(D.m[0][0]) : static_cast<float>(D.m[i][0]);
-      c1[i] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(scale * c2[i])));  // (wave-uniform)
-    }
+    haar_inv_weighted<K>(v, wt);
+    const double w_scaled = static_cast<double>(w) * (kFixScale / K);
 #pragma unroll
     for (int c0 = 0; c0 < K; c0 += CH) {
       wave_lds_sync();  // earlier reads of the scratch are done
@@ -617,7 +607,7 @@ __device__ __forceinline__ void group_wiener_body(acc_t* acc,
         float x[8], y[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = line[i];
-        dct8_inv_scaled(c1, x, y);
+        dct8_inv_raw(x, y);
 #pragma unroll
         for (int i = 0; i < 8; ++i) line[i] = y[i];
       }
@@ -628,10 +618,10 @@ __device__ __forceinline__ void group_wiener_body(acc_t* acc,
         float x[8], y[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = col[i * kScratchPitch];
-        dct8_inv_scaled(c2, x, y);
+        dct8_inv_raw(x, y);
         acc_t* cell = acc + fo + b;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) atomicAdd(cell + i * T::FXP, static_cast<acc_t>(to_fixed_scaled(y[i])));
+        for (int i = 0; i < 8; ++i) atomicAdd(cell + i * T::FXP, static_cast<acc_t>(to_fixed_product(y[i], w_scaled)));
       }
     }
     add_block_weights<K>(bw, pos_v, w, lane);
@@ -788,14 +778,14 @@ static GroupShape ht_shape_for(int H, int W) {
   return t <= 192 || (t > 256 && t <= 420) ? kSmall : kTwoTiles;
 }
 
-// The Wiener kernel also gains from a loop of one group per wave (no register
-// spills), which pays for the cells much further.  Whole second stage, us,
-// 8 x 8 | 4 x 4 | 2 x 4 references: 128^2 60 | 37 | 31; 256^2 72 | 58 | 55;
-// 384^2 99 | 101 | 92; 321 x 481 119 | 106 | 98; 512^2 149 | 160 | 146;
-// 640^2 224 | 234 | 218; 1001 x 750 415 | 424 | 387; 2048^2 2092 | 2202 | 2101.
-static GroupShape wiener_shape_for(int H, int W) {
-  return tiles_of<Tile<8, 8>>(H, W) <= 4096 ? kTiny : kTwoTiles;
-}
+// The Wiener kernel (more arithmetic per footprint cell) takes the
+// smallest tile up to the same size.  Whole second stage, us, 8 x 8 | 4 x 4 |
+// 2 x 4 references: 128^2 57 | 36 | 30; 192^2 63 | 43 | 38; 256^2 70 | 53 | 52;
+// 384^2 93 | 90 | 85; 321 x 481 113 | 98 | 92; 448^2 124 | 115 | 111.  Beyond,
+// the order depends on the image; kernel alone on photograph-like images:
+// 512^2 71 | 75 | 71; 1001 x 750 217 | 213 | 225; whole stage 4096^2
+// 8243 | 8586 | 8392.
+static GroupShape wiener_shape_for(int H, int W) { return tiles_of<Tile<8, 8>>(H, W) <= 420 ? kTiny : kTwoTiles; }
 
 template <int K, int SHAPE>
 static hipError_t launch_ht_shape(const ImgRec& one, const WorkList* wl, int R, const HtParams& hp, int recompute,

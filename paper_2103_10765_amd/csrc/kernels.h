@@ -24,17 +24,19 @@ long bm_waves_unsplit(int H, int W);
 int bm_items_for(int H, int W, int split);
 
 // Correlation-form matching (Theorem 1, f16 matrix cores, exact keys for the
-// candidates that can matter): the same indices.  stack_kind 0 or 1: the
+// candidates that can matter): the same indices.  stack_kind 0 or 2: the
 // launch also does the work of launch_stack(one, stack_wl, 0, 0, 0) or
-// launch_stack(one, stack_wl, 1, -1, -1); -1: matching only.
+// launch_stack(one, stack_wl, 2, -1, -1); -1: matching only.
 hipError_t launch_bm_corr(const ImgRec& one, const WorkList* wl, const WorkList* stack_wl, int R, int K, int use_pilot,
                           int stack_kind, hipStream_t st);
 int corr_items_for(int H, int W);
 long corr_tiles(int H, int W);
 
 // 2-D transform (kind 0 = bior1.5 Mallat, 1 = DCT) of every block of noisy
-// (src_sel 0) or pilot (1) into stack_a (dst_sel 0) or stack_b (1), [H*W][64];
-// src_sel = dst_sel = -1: noisy -> stack_a and pilot -> stack_b in one launch.
+// (src_sel 0) or pilot (1) into stack_a (dst_sel 0) or stack_b (1), [H*W][64].
+// Kind 2, src_sel = dst_sel = -1: the DCTs of noisy -> stack_a and pilot ->
+// stack_b in one launch, scaled as launch_group_wiener wants them (the pilot's
+// without the transform's output factors, the noisy one's with their squares).
 // The launch into stack_a clears the aggregation sums of rec.partials (when
 // set).
 hipError_t launch_stack(const ImgRec& one, const WorkList* wl, int kind, int src_sel, int dst_sel,

@@ -39,7 +39,8 @@ __global__ __launch_bounds__(kStackThreads) void stack_kernel(ImgRec one, WorkLi
   const int dst = dst_sel < 0 ? static_cast<int>(blockIdx.y) : dst_sel;
   for_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
     stack_body<KIND, 2, LOADS_FIRST>(lds, static_cast<int>(threadIdx.x), src ? r.pilot : r.noisy,
-                                     dst ? r.stack_b : r.stack_a, dst ? nullptr : r.partials, r.H, r.W, item);
+                                     dst ? r.stack_b : r.stack_a, dst ? nullptr : r.partials, dst == 0, r.H, r.W,
+                                     item);
   });
 }
 
@@ -72,9 +73,10 @@ int stack_items_for(int H, int W) { return stack_items(H, W); }
 
 hipError_t launch_stack(const ImgRec& one, const WorkList* wl, int kind, int src_sel, int dst_sel,
                         hipStream_t st) {
-  if ((src_sel < 0) != (dst_sel < 0)) return hipErrorInvalidValue;
-  return kind == 0 ? launch_stack_kind<0>(one, wl, src_sel, dst_sel, st)
-                   : launch_stack_kind<1>(one, wl, src_sel, dst_sel, st);
+  if ((src_sel < 0) != (dst_sel < 0) || (kind == 2) != (src_sel < 0)) return hipErrorInvalidValue;
+  return kind == 0   ? launch_stack_kind<0>(one, wl, src_sel, dst_sel, st)
+         : kind == 1 ? launch_stack_kind<1>(one, wl, src_sel, dst_sel, st)
+                     : launch_stack_kind<2>(one, wl, src_sel, dst_sel, st);
 }
 
 }  // namespace gbm3d

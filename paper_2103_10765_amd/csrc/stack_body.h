@@ -51,8 +51,10 @@ __device__ __forceinline__ void forward2d(float (&x)[8][8]) {
     rows_cols<8>(x, [&](const float* i, float* o) { apply_mat<8>(A8, i, o); });
     rows_cols<4>(x, [&](const float* i, float* o) { apply_mat<4>(A4, i, o); });
     rows_cols<2>(x, [&](const float* i, float* o) { apply_mat<2>(A2, i, o); });
-  } else {
+  } else if constexpr (KIND == 1) {
     rows_cols<8>(x, [&](const float* i, float* o) { dct8_fwd(i, o); });
+  } else {
+    rows_cols<8>(x, [&](const float* i, float* o) { dct8_fwd_raw(i, o); });
   }
 }
 
@@ -63,12 +65,16 @@ __host__ __device__ constexpr int stack_items(int H, int W) {
 // One item by the four waves of threads t = 0 .. 255; every thread of the
 // workgroup has to come here (barriers), those of a half without an item with
 // item < 0.
+// KIND 0: bior1.5; 1: DCT; 2: DCT as the Wiener groups want it, without its
+// output factors dct8_scale(a) dct8_scale(b) for the pilot, with their squares
+// for the noisy image (no multiplications for the first, and 26 instead of 40
+// operations per line).
 // LOADS_FIRST: every thread's pixel loads are issued before the first is
 // used (one memory round trip for the tile); otherwise one item at a time.
 template <int KIND, int PARTS, bool LOADS_FIRST>
 __device__ __forceinline__ void stack_body(StackLds<PARTS>& lds, int t, const uint16_t* __restrict__ img_,
                                            float* __restrict__ out_, unsigned long long* __restrict__ block_weights_,
-                                           int H, int W, int item) {
+                                           bool noisy, int H, int W, int item) {
   constexpr int kPart = kWave / PARTS;
   auto& pix = lds.pix;
   auto& stage = lds.stage;
@@ -125,6 +131,15 @@ __device__ __forceinline__ void stack_body(StackLds<PARTS>& lds, int t, const ui
 #pragma unroll
     for (int b = 0; b < 8; ++b) x[a][b] = pix[w + a][lane + b];
   forward2d<KIND>(x);
+  if (KIND == 2 && noisy) {
+#pragma unroll
+    for (int a = 0; a < 8; ++a)
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        const double s = dct8_scale(a) * dct8_scale(b);
+        x[a][b] *= static_cast<float>(s * s);
+      }
+  }
   const int y = y0 + w;
   const int n_pos = min(kWave, W - x0);  // positions of this row in the tile
   // the aggregation that follows adds into the block-start weights and the
