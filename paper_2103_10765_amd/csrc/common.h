@@ -3,6 +3,8 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 #include <stdint.h>
 
 namespace gbm3d {
@@ -423,9 +425,26 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Sum over the wave, every lane's: the butterfly v += v(lane ^ 32), ^ 16, .. ^ 1
+// on register moves (a swap of halves gives both summands, addition commutes).
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
+  typedef unsigned u32x2s __attribute__((ext_vector_type(2)));
+  auto add = [](u32x2s p) { return __uint_as_float(p.x) + __uint_as_float(p.y); };
+  auto dpp = [](float old, float x, auto ctrl, auto banks) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(x), decltype(ctrl)::value, 0xf,
+                                                      decltype(banks)::value, false));
+  };
+  using All = std::integral_constant<int, 0xf>;
+  unsigned b = __float_as_uint(v);
+  v = add(__builtin_bit_cast(u32x2s, __builtin_amdgcn_permlane32_swap(b, b, false, false)));
+  b = __float_as_uint(v);
+  v = add(__builtin_bit_cast(u32x2s, __builtin_amdgcn_permlane16_swap(b, b, false, false)));
+  v += dpp(v, v, std::integral_constant<int, 0x128>{}, All{});  // rotate the row of 16 by 8
+  // lanes of even banks of four take lane + 4, the others lane - 4
+  const float up = dpp(v, v, std::integral_constant<int, 0x104>{}, std::integral_constant<int, 0x5>{});
+  v += dpp(up, v, std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xa>{});
+  v += dpp(v, v, std::integral_constant<int, 0x4e>{}, All{});  // quads: 2 3 0 1
+  v += dpp(v, v, std::integral_constant<int, 0xb1>{}, All{});  // quads: 1 0 3 2
   return v;
 }
 

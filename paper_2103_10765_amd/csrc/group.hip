@@ -32,7 +32,6 @@
 #include "common.h"
 #include "kernels.h"
 
-#include <type_traits>
 
 namespace gbm3d {
 
@@ -55,38 +54,6 @@ struct Tile {
   // instruction offsets), 8 modulo 32
   static constexpr int FXP = FXmax + ((8 - FXmax) % 32 + 32) % 32;
   static constexpr int entries = FYmax * FXP;
-};
-
-// Shapes of the group kernels.
-enum GroupShape {
-  kTwoTiles,  // 8 x 8 references by 12 waves, two tiles per CU
-  kOneTile,   // 8 x 8 references by 16 waves, one tile per CU, the next group's spectra in flight
-  kSmall,     // 4 x 4 references by 8 waves
-  kTiny,      // 2 x 4 references by 8 waves
-};
-
-// Launch shape of a group kernel.  Tiles share a CU so that it has 24 waves
-// (six per SIMD); inverse transforms go 8 blocks at a time through each wave's
-// scratch, without a prefetch of the next group (the other waves hide the
-// loads).  kOneTile is a choice of the autotuner for the hard-threshold kernel
-// (K <= 16).  That kernel's filter holds all K inverse blocks until its weight
-// is known, so K = 32 runs eight waves and one tile per CU.
-template <int K, bool HT, int SHAPE>
-struct GroupCfg {
-  static constexpr bool large = HT && K > 16;
-  using T = std::conditional_t<SHAPE == kTiny, Tile<2, 4>, std::conditional_t<SHAPE == kSmall, Tile<4, 4>, Tile<8, 8>>>;
-  static constexpr bool prefetch = SHAPE == kOneTile;
-  static constexpr int chunk = SHAPE == kOneTile || large ? (K > 16 ? 16 : K) : (K > 8 ? 8 : K);
-  static constexpr int rank_bytes = T::refs * K * 2;  // the tile's ranks (int16)
-  static constexpr int waves = SHAPE == kOneTile ? 16 : large || SHAPE != kTwoTiles ? 8 : 12;
-  static constexpr int tiles = SHAPE == kOneTile || large ? 1 : 24 / waves;
-  static constexpr int threads = waves * kWave;
-  static constexpr int min_waves_per_simd = waves * tiles / 4;
-  static_assert(SHAPE != kOneTile || (HT && K <= 16), "only the hard-threshold kernel of small groups prefetches");
-  static_assert(tiles * (T::entries * static_cast<int>(sizeof(acc_t)) +
-                         waves * chunk * kBlockFloats * static_cast<int>(sizeof(float)) + rank_bytes) <=
-                    kLdsBytes,
-                "LDS of the tiles sharing a CU");
 };
 
 struct GroupArgs {
@@ -112,6 +79,88 @@ __host__ __device__ inline GroupArgs make_args(int H, int W, int R) {
   return g;
 }
 
+// The tile's matched blocks, [reference t][K] (t = row-major place among the
+// tile's references): stack position (pixel index) and first footprint cell
+// (its byte offset).
+// They are decoded from the ranks once, by all threads (per group and wave it
+// would be 25 instructions for K active lanes).
+template <int K, typename T>
+struct Slots {
+  alignas(16) int pos[T::refs * K];
+  alignas(16) uint16_t fo[T::refs * K];
+
+  // every thread's rank loads are issued before the first is used: one memory
+  // round trip per tile.  References past the image's last row or column get a
+  // clamped in-bounds entry that no group uses.  The caller's next barrier
+  // publishes the slots.
+  template <int THREADS>
+  __device__ __forceinline__ void load(const GroupArgs& g, const int16_t* idx_, int tyi, int txi) {
+    const auto idx = to_global(idx_);
+    constexpr int n = T::refs * K;
+    constexpr int iters = (n + THREADS - 1) / THREADS;
+    int v[iters];
+#pragma unroll
+    for (int it = 0; it < iters; ++it) {
+      const int e = min(static_cast<int>(threadIdx.x) + it * THREADS, n - 1);
+      const int t = e / K, k = e % K;
+      const int p = min(tyi * T::py + t / T::px, g.nRy - 1), q = min(txi * T::px + t % T::px, g.nRx - 1);
+      v[it] = idx[(static_cast<size_t>(p) * g.nRx + q) * K + k];
+    }
+#pragma unroll
+    for (int it = 0; it < iters; ++it) {
+      const int e = static_cast<int>(threadIdx.x) + it * THREADS;
+      if (e >= n) break;
+      const int t = e / K, r = v[it];
+      const int p = min(tyi * T::py + t / T::px, g.nRy - 1), q = min(txi * T::px + t % T::px, g.nRx - 1);
+      // r / S in float: r + 1/2 lies at least 1/(2S) from a multiple of S and
+      // r < S^2 <= 1521, far inside float's exact range
+      const int dyi = static_cast<int>((static_cast<float>(r) + 0.5f) * g.invS), dxi = r - dyi * g.S;
+      const int y = kStep * p + dyi - g.R, x = kStep * q + dxi - g.R;
+      // -R <= y < H + R and H >= S > R + 1: at most one period away (same for x)
+      const int yw = y < 0 ? y + g.H : (y >= g.H ? y - g.H : y);
+      const int xw = x < 0 ? x + g.W : (x >= g.W ? x - g.W : x);
+      pos[e] = yw * g.W + xw;
+      const int cell = (kStep * (p - tyi * T::py) + dyi) * T::FXP + kStep * (q - txi * T::px) + dxi;
+      fo[e] = static_cast<uint16_t>(cell * static_cast<int>(sizeof(acc_t)));
+    }
+  }
+};
+
+// Shapes of the group kernels.
+enum GroupShape {
+  kTwoTiles,  // 8 x 8 references by 12 waves (hard threshold: 16), two tiles per CU
+  kOneTile,   // 8 x 8 references by 16 waves, one tile per CU, the next group's spectra in flight
+  kSmall,     // 4 x 4 references by 8 waves
+  kTiny,      // 2 x 4 references by 8 waves
+};
+
+// Launch shape of a group kernel.  Tiles share a CU so that it has 24 waves
+// (six per SIMD; two of sixteen for the hard-threshold kernel at 54 registers,
+// an even four groups per wave); inverse transforms go 8 blocks at a time
+// through each wave's scratch, without a prefetch of the next group (the other
+// waves hide the loads).  kOneTile is a choice of the autotuner for the
+// hard-threshold kernel (K <= 16).  That kernel's filter holds all K inverse
+// blocks until its weight is known, so K = 32 runs eight waves and one tile per
+// CU.
+template <int K, bool HT, int SHAPE>
+struct GroupCfg {
+  static constexpr bool large = HT && K > 16;
+  using T = std::conditional_t<SHAPE == kTiny, Tile<2, 4>, std::conditional_t<SHAPE == kSmall, Tile<4, 4>, Tile<8, 8>>>;
+  static constexpr bool prefetch = SHAPE == kOneTile;
+  static constexpr int chunk = SHAPE == kOneTile || large ? (K > 16 ? 16 : K) : (K > 8 ? 8 : K);
+  using SlotTable = Slots<K, T>;
+  static constexpr int waves = SHAPE == kOneTile ? 16 : large || SHAPE != kTwoTiles ? 8 : HT ? 16 : 12;
+  static constexpr int tiles = SHAPE == kOneTile || large ? 1 : SHAPE == kTwoTiles ? 2 : 3;
+  static constexpr int threads = waves * kWave;
+  static constexpr int min_waves_per_simd = waves * tiles / 4;
+  static_assert(SHAPE != kOneTile || (HT && K <= 16), "only the hard-threshold kernel of small groups prefetches");
+  static_assert(tiles * (T::entries * static_cast<int>(sizeof(acc_t)) +
+                         waves * chunk * kBlockFloats * static_cast<int>(sizeof(float)) +
+                         static_cast<int>(sizeof(SlotTable))) <=
+                    kLdsBytes,
+                "LDS of the tiles sharing a CU");
+};
+
 __host__ __device__ inline int reduce_items(int H, int W) { return H * ((W + kReduceThreads - 1) / kReduceThreads); }
 
 struct HtParams {
@@ -119,17 +168,16 @@ struct HtParams {
   int weight_mode, keep_dc;
 };
 
-// Inverse of one separable level on the leading L x L block of each of the K
-// blocks parked at xw[k*72 + a*9 + b]: rows, then columns.
-template <int K, int L, typename F>
-__device__ __forceinline__ void inverse_level(float* xw, int lane, F&& line) {
+// Lines of the leading L x L block of each of K blocks parked at
+// xw[k * BLOCK + a * PITCH + b], one line per lane: every row in place.
+template <int K, int L, int BLOCK, int PITCH, typename F>
+__device__ __forceinline__ void transform_rows(float* xw, int lane, F&& line) {
   constexpr int items = K * L;
 #pragma unroll
   for (int it0 = 0; it0 < items; it0 += kWave) {
     const int it = it0 + lane;
     if (it < items) {
-      const int k = it / L, i = it % L;
-      float* row = xw + k * kBlockFloats + i * kScratchPitch;
+      float* row = xw + it / L * BLOCK + it % L * PITCH;
       float x[8], y[8];
 #pragma unroll
       for (int j = 0; j < L; ++j) x[j] = row[j];
@@ -139,54 +187,52 @@ __device__ __forceinline__ void inverse_level(float* xw, int lane, F&& line) {
     }
   }
   wave_lds_sync();
+}
+
+// Every column: put(pass, k, j, y), y the transformed column j of block k.
+template <int K, int L, int BLOCK, int PITCH, typename F, typename P>
+__device__ __forceinline__ void transform_columns(const float* xw, int lane, F&& line, P&& put) {
+  constexpr int items = K * L;
 #pragma unroll
   for (int it0 = 0; it0 < items; it0 += kWave) {
     const int it = it0 + lane;
     if (it < items) {
-      const int k = it / L, j = it % L;
-      float* col = xw + k * kBlockFloats + j;
+      const float* col = xw + it / L * BLOCK + it % L;
       float x[8], y[8];
 #pragma unroll
-      for (int i = 0; i < L; ++i) x[i] = col[i * kScratchPitch];
+      for (int i = 0; i < L; ++i) x[i] = col[i * PITCH];
       line(x, y);
-#pragma unroll
-      for (int i = 0; i < L; ++i) col[i * kScratchPitch] = y[i];
+      put(it0 / kWave, it / L, it % L, y);
     }
   }
+}
+
+// One separable level in place: rows, then columns.
+template <int K, int L, int BLOCK = kBlockFloats, int PITCH = kScratchPitch, typename F>
+__device__ __forceinline__ void transform_level(float* xw, int lane, F&& line) {
+  transform_rows<K, L, BLOCK, PITCH>(xw, lane, line);
+  transform_columns<K, L, BLOCK, PITCH>(xw, lane, line, [&](int, int k, int j, const float (&y)[8]) {
+#pragma unroll
+    for (int i = 0; i < L; ++i) xw[k * BLOCK + i * PITCH + j] = y[i];
+  });
   wave_lds_sync();
 }
 
-// Block positions of the group of reference (p, q): lane k < K decodes the
-// rank r of slot k into a stack position (pixel index) and the offset of the
-// block's top-left in the tile's footprint.
-template <int K, typename T>
-__device__ __forceinline__ void slot_pos(const GroupArgs& g, int r, int p, int q, int fy0, int fx0, int lane, int& pos,
-                                         int& fo) {
-  pos = 0;
-  fo = 0;
-  if (lane < K) {
-    // r / S in float: r + 1/2 lies at least 1/(2S) from a multiple of S and
-    // r < S^2 <= 1521, far inside float's exact range
-    const int dyi = static_cast<int>((static_cast<float>(r) + 0.5f) * g.invS), dxi = r - dyi * g.S;
-    const int y = kStep * p + dyi - g.R, x = kStep * q + dxi - g.R;
-    // -R <= y < H + R and H >= S > R + 1: at most one period away (same for x)
-    const int yw = y < 0 ? y + g.H : (y >= g.H ? y - g.H : y);
-    const int xw = x < 0 ? x + g.W : (x >= g.W ? x - g.W : x);
-    pos = yw * g.W + xw;
-    fo = (y - fy0) * T::FXP + (x - fx0);
-  }
+// The footprint cell at a byte offset.
+__device__ __forceinline__ acc_t* cell_at(acc_t* acc, unsigned bytes) {
+  return reinterpret_cast<acc_t*>(reinterpret_cast<char*>(acc) + bytes);
 }
 
-// w * u[k] into the footprint for blocks k0 .. k0 + N - 1 (u holds their values)
-template <int N, typename T>
-__device__ __forceinline__ void accumulate(acc_t* acc, int fo_v, int k0, const float (&u)[N],
-                                           float w, int lane) {
-  const int ab = (lane >> 3) * T::FXP + (lane & 7);
-  const float ws = w * kFixScaleF;
+// ws * u[k] (fixed point) into the footprint, block k at byte offset fo[k] (two
+// to a word)
+template <int K, typename T>
+__device__ __forceinline__ void accumulate(acc_t* acc, const uint16_t* fo, const float (&u)[K], float ws, int lane) {
+  const unsigned ab = ((lane >> 3) * T::FXP + (lane & 7)) * sizeof(acc_t);
+  const unsigned* pairs = reinterpret_cast<const unsigned*>(fo);
 #pragma unroll
-  for (int k = 0; k < N; ++k) {
-    const int o = __builtin_amdgcn_readlane(fo_v, k0 + k) + ab;
-    atomicAdd(acc + o, static_cast<acc_t>(to_fixed_scaled(ws * u[k])));
+  for (int k = 0; k < K; ++k) {
+    const unsigned o = k % 2 ? pairs[k / 2] >> 16 : pairs[k / 2] & 0xffffu;
+    atomicAdd(cell_at(acc, o + ab), static_cast<acc_t>(to_fixed_scaled(ws * u[k])));
   }
 }
 
@@ -241,62 +287,30 @@ __device__ __forceinline__ void flush_acc(const acc_t* acc, const GroupArgs& g, 
   __syncthreads();  // the accumulator is reused by the next item
 }
 
-// The tile's match ranks [reference t][K] into LDS (t = row-major place
-// among the tile's references; references past the image's last row or
-// column read a clamped in-bounds entry that no group uses), every thread's
-// loads issued before the first is stored: one memory round trip per tile
-// instead of one per group.  The caller's next barrier publishes them.
-template <int K, typename T, int THREADS>
-__device__ __forceinline__ void load_ranks(int16_t* ranks, const GroupArgs& g, const int16_t* idx_, int tyi,
-                                           int txi) {
-  const auto idx = to_global(idx_);
-  constexpr int n = T::refs * K;
-  constexpr int iters = (n + THREADS - 1) / THREADS;
-  int v[iters];
-#pragma unroll
-  for (int it = 0; it < iters; ++it) {
-    const int e = min(static_cast<int>(threadIdx.x) + it * THREADS, n - 1);
-    const int t = e / K, k = e % K;
-    const int p = min(tyi * T::py + t / T::px, g.nRy - 1), q = min(txi * T::px + t % T::px, g.nRx - 1);
-    v[it] = idx[(static_cast<size_t>(p) * g.nRx + q) * K + k];
-  }
-#pragma unroll
-  for (int it = 0; it < iters; ++it) {
-    const int e = static_cast<int>(threadIdx.x) + it * THREADS;
-    if (e < n) ranks[e] = static_cast<int16_t>(v[it]);
-  }
-}
-
 // The groups a wave filters in a tile: reference t = wave + j * WAVES,
 // j < kGroups.
 template <typename T, int WAVES>
 struct GroupWalk {
   static constexpr int kGroups = (T::refs + WAVES - 1) / WAVES;
   const GroupArgs& g;
-  const int16_t* ranks;  // the tile's match ranks in LDS [reference t][K]
-  int tyi, txi, wave, lane, fy0, fx0;
+  const int* pos;  // the tile's block positions in LDS [reference t][K]
+  int tyi, txi, wave, lane;
 
-  __device__ __forceinline__ bool ref_of(int j, int& p, int& q) const {
-    const int t = wave + j * WAVES;
-    p = tyi * T::py + t / T::px;
-    q = txi * T::px + t % T::px;
-    return j < kGroups && t < T::refs && p < g.nRy && q < g.nRx;
+  __device__ __forceinline__ int ref(int j) const { return wave + j * WAVES; }
+  __device__ __forceinline__ bool exists(int j) const {
+    const int t = ref(j);
+    return j < kGroups && t < T::refs && tyi * T::py + t / T::px < g.nRy && txi * T::px + t % T::px < g.nRx;
   }
-  // rank of slot `lane` of group j, for lanes below K of a group that exists
-  // (gather reads nothing else)
+  // position of slot lane % K of group j (0 past the last)
   template <int K>
-  __device__ __forceinline__ int rank(int j) const {
-    const int t = wave + j * WAVES;
-    return t < T::refs ? ranks[t * K + (lane & (K - 1))] : 0;
+  __device__ __forceinline__ int slot(int j) const {
+    const int t = ref(j);
+    return t < T::refs ? pos[t * K + (lane & (K - 1))] : 0;
   }
-  // stack rows of group j from its ranks: v[k] = stack[pos_k * 64 + lane];
-  // lane k < K returns slot k's pixel index and footprint offset
+  // stack rows of the group whose slots' positions the lanes hold:
+  // v[k] = stack[pos_k * 64 + lane]
   template <int K, int NS>
-  __device__ __forceinline__ bool gather(int j, int r, const float* const (&stacks)[NS], float (&v)[NS][K], int& fo,
-                                         int& pos_v) const {
-    int p, q;
-    if (!ref_of(j, p, q)) return false;
-    slot_pos<K, T>(g, r, p, q, fy0, fx0, lane, pos_v, fo);
+  __device__ __forceinline__ void gather(int pos_v, const float* const (&stacks)[NS], float (&v)[NS][K]) const {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       // the block's base address is uniform: it goes into a buffer resource
@@ -305,17 +319,12 @@ struct GroupWalk {
 #pragma unroll
       for (int s = 0; s < NS; ++s) v[s][k] = load_block_lane(stacks[s] + blk, lane);
     }
-    return true;
   }
-  // the pixels of group j's blocks instead of their spectra: v[k] = z at
+  // the pixels of the group's blocks instead of their spectra: v[k] = z at
   // (row lane / 8, column lane % 8) of slot k's block (periodic),
   // z = Z / 65535 as the stack kernel reads it
   template <int K>
-  __device__ __forceinline__ bool gather_pixels(int j, int r, const uint16_t* __restrict__ img, float (&v)[1][K],
-                                                int& fo, int& pos_v) const {
-    int p, q;
-    if (!ref_of(j, p, q)) return false;
-    slot_pos<K, T>(g, r, p, q, fy0, fx0, lane, pos_v, fo);
+  __device__ __forceinline__ void gather_pixels(int pos_v, const uint16_t* __restrict__ img, float (&v)[1][K]) const {
     const int a = lane >> 3, b = lane & 7;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -324,7 +333,6 @@ struct GroupWalk {
       const int yy = y + a >= g.H ? y + a - g.H : y + a, xx = x + b >= g.W ? x + b - g.W : x + b;
       v[0][k] = static_cast<float>(to_global(img)[static_cast<size_t>(yy) * g.W + xx]) * (1.0f / 65535.0f);
     }
-    return true;
   }
 };
 
@@ -345,67 +353,128 @@ __device__ __forceinline__ void forward_blocks(float* xw, int lane, float (&v)[K
 #pragma unroll
     for (int k = 0; k < CH; ++k) xw[k * kBlockFloats + a * kScratchPitch + b] = v[c0 + k];
     wave_lds_sync();
-    inverse_level<CH, 8>(xw, lane, [&](const float* x, float* y) { apply_mat<8>(A8, x, y); });
-    inverse_level<CH, 4>(xw, lane, [&](const float* x, float* y) { apply_mat<4>(A4, x, y); });
-    inverse_level<CH, 2>(xw, lane, [&](const float* x, float* y) { apply_mat<2>(A2, x, y); });
+    transform_level<CH, 8>(xw, lane, [&](const float* x, float* y) { apply_mat<8>(A8, x, y); });
+    transform_level<CH, 4>(xw, lane, [&](const float* x, float* y) { apply_mat<4>(A4, x, y); });
+    transform_level<CH, 2>(xw, lane, [&](const float* x, float* y) { apply_mat<2>(A2, x, y); });
 #pragma unroll
     for (int k = 0; k < CH; ++k) v[c0 + k] = xw[k * kBlockFloats + a * kScratchPitch + b];
   }
 }
 
-// Runs filter(v, fo_v, pos_v) on every group of this wave in the tile, v the
-// gathered spectra.  Small groups also keep the next group's spectra in
-// flight; large ones leave the registers to the filter (sixteen waves per
-// tile hide the loads instead).
+// Runs filter(v, j, pos_v) on every group j of this wave in the tile, v the
+// gathered spectra, lane k < K's pos_v slot k's position.  PREFETCH also keeps
+// the next group's spectra in flight (otherwise the CU's other waves hide the
+// loads).
 template <int K, int NS, bool PREFETCH, typename W, typename F>
-__device__ __forceinline__ void for_each_group(const W& walk, const float* const (&stacks)[NS],
-                                               F&& filter) {
+__device__ __forceinline__ void for_each_group(const W& walk, const float* const (&stacks)[NS], F&& filter) {
   if constexpr (PREFETCH) {
-    int r1 = walk.template rank<K>(1);
+    int pos_c = walk.template slot<K>(0), pos_n = walk.template slot<K>(1);
     float cur[NS][K];
-    int fo_c = 0, pos_c = 0;
-    bool ok_c = walk.template gather<K, NS>(0, walk.template rank<K>(0), stacks, cur, fo_c, pos_c);
+    bool ok_c = walk.exists(0);
+    if (ok_c) walk.template gather<K, NS>(pos_c, stacks, cur);
     for (int j = 0; j < walk.kGroups; ++j) {
-      const int r2 = walk.template rank<K>(j + 2);
+      const int pos_2 = walk.template slot<K>(j + 2);
       float nxt[NS][K];
-      int fo_n = 0, pos_n = 0;
-      const bool ok_n = walk.template gather<K, NS>(j + 1, r1, stacks, nxt, fo_n, pos_n);
-      if (ok_c) filter(cur, fo_c, pos_c);
+      const bool ok_n = walk.exists(j + 1);
+      if (ok_n) walk.template gather<K, NS>(pos_n, stacks, nxt);
+      if (ok_c) filter(cur, j, pos_c);
 #pragma unroll
       for (int s = 0; s < NS; ++s)
 #pragma unroll
         for (int k = 0; k < K; ++k) cur[s][k] = nxt[s][k];
-      fo_c = fo_n;
       pos_c = pos_n;
+      pos_n = pos_2;
       ok_c = ok_n;
-      r1 = r2;
     }
   } else {
-    int r0 = walk.template rank<K>(0);
+    int pos_v = walk.template slot<K>(0);
     for (int j = 0; j < walk.kGroups; ++j) {
-      const int r1 = walk.template rank<K>(j + 1);
-      float cur[NS][K];
-      int fo = 0, pos = 0;
-      if (walk.template gather<K, NS>(j, r0, stacks, cur, fo, pos)) filter(cur, fo, pos);
-      r0 = r1;
+      const int pos_n = walk.template slot<K>(j + 1);
+      if (walk.exists(j)) {
+        float cur[NS][K];
+        walk.template gather<K, NS>(pos_v, stacks, cur);
+        filter(cur, j, pos_v);
+      }
+      pos_v = pos_n;
     }
   }
+}
+
+// |v| * haar_gain(k) >= tau, a float product, as |v| >= a threshold: haar_gain
+// is 2^-m, or sqrt(1/2) 2^-m for which the smallest t with t sqrt(1/2) >= tau
+// (rounded) lies within two units of the last place of tau sqrt(2).
+constexpr float kSqrtHalf = static_cast<float>(kInvSqrt2);
+__device__ __forceinline__ float smallest_kept(float tau) {
+  const float t0 = tau * static_cast<float>(2 * kInvSqrt2);
+  float t = __int_as_float(__float_as_int(t0) + 2);
+#pragma unroll
+  for (int d = 1; d >= -2; --d) {
+    const float c = __int_as_float(__float_as_int(t0) + d);
+    t = c * kSqrtHalf >= tau ? c : t;
+  }
+  return t;
+}
+// e of haar_gain2<K>(k) = 2^-e
+template <int K>
+__host__ __device__ constexpr int gain2_log(int k) {
+  int e = 0;
+  for (float g = haar_gain2<K>(k); g < 1.0f; g *= 2.0f) ++e;
+  return e;
+}
+template <int K>
+constexpr bool gains_are_scaled() {
+  for (int k = 0; k < K; ++k) {
+    const int e = gain2_log<K>(k);
+    if (haar_gain<K>(k) * static_cast<float>(1 << (e / 2)) != (e % 2 ? kSqrtHalf : 1.0f)) return false;
+  }
+  return true;
+}
+
+// Unnormalised Haar inverse (haar_inv_raw) of v[k] haar_gain2<K>(k) K: the
+// band [h, 2h) enters with its weight h (a power of two: an exact product).
+template <int K>
+__device__ __forceinline__ void haar_inv_banded(float* v) {
+#pragma unroll
+  for (int half = 1; half <= K / 2; half *= 2) {
+    float t[K];
+#pragma unroll
+    for (int j = 0; j < half; ++j) {
+      t[2 * j] = fmaf(static_cast<float>(half), v[half + j], v[j]);
+      t[2 * j + 1] = fmaf(-static_cast<float>(half), v[half + j], v[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 2 * half; ++j) v[j] = t[j];
+  }
+}
+
+// The next lane's value (lanes 15, 31, ..: 0).
+__device__ __forceinline__ float next_lane(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x101, 0xf, 0xf, true));
 }
 
 // One work item = one tile of references: stage-1 groups.  RECOMPUTE: the
 // blocks' spectra are computed here from the image's pixels instead of
 // gathered from the bior1.5 stack.
+// Bound by vector issue and LDS cycles (80 and 60 % of the kernel's).  What is
+// the same for a band or a chunk is taken out of the group's arithmetic where
+// the result stays the same to the bit: thresholds on unscaled coefficients,
+// powers of two kept until the weight, the coarse transform levels of all K
+// blocks at once, neighbours from the next lane's register, block positions
+// decoded once per tile.  580 -> 480 vector and 130 -> 100 LDS instructions per
+// group of 16; kernel us: 512^2 58 -> 50, 4096^2 2535 -> 2130, 64 mixed images
+// 3760 -> 3110.
 template <int K, bool RECOMPUTE, int SHAPE>
 __device__ __forceinline__ void group_ht_body(acc_t* acc,
                                               float (*scratch)[GroupCfg<K, true, SHAPE>::chunk * kBlockFloats],
-                                              int16_t* ranks, const ImgRec& r, int R, const HtParams& hp, int item) {
+                                              typename GroupCfg<K, true, SHAPE>::SlotTable& slots, const ImgRec& r,
+                                              int R, const HtParams& hp, int item) {
   using Cfg = GroupCfg<K, true, SHAPE>;
   using T = typename Cfg::T;
   const GroupArgs g = make_args<T>(r.H, r.W, R);
   const int tyi = item / g.nTx, txi = item % g.nTx;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = wave_id();
-  load_ranks<K, T, Cfg::threads>(ranks, g, r.idx, tyi, txi);
+  slots.template load<Cfg::threads>(g, r.idx, tyi, txi);
   zero_acc(acc, g.FY * T::FXP);
   const int fy0 = kStep * tyi * T::py - g.R;
   const int fx0 = kStep * txi * T::px - g.R;
@@ -413,50 +482,100 @@ __device__ __forceinline__ void group_ht_body(acc_t* acc,
   const int a = lane >> 3, b = lane & 7;
   const float tau = r.sigma * (hp.ht_a - hp.ht_b * static_cast<float>(bior_level(lane)));
   const bool dc_lane = hp.keep_dc && lane == 0;
+  // |v[k]| from which coefficient k is kept: k = 0, then by band
+  constexpr int kBands = __builtin_ctz(K);
+  const float tau_sqrt = smallest_kept(tau);
+  static_assert(gains_are_scaled<K>(), "a power of two, or times sqrt(1/2)");
+  auto kept_from = [&](int k) {
+    const int e = gain2_log<K>(k);
+    return (e % 2 ? tau_sqrt : tau) * static_cast<float>(1 << (e / 2));
+  };
+  const float kept_dc = dc_lane ? 0.0f : kept_from(0);
+  float kept[kBands];
+#pragma unroll
+  for (int i = 0; i < kBands; ++i) kept[i] = kept_from(1 << i);
   acc_t* bw = r.partials;  // block-start weights
+  float* own = xw + a * kScratchPitch + b;
+  const float* below = own + (a < 7 ? kScratchPitch : 0);
+  const float has_right = b < 7 ? 1.0f : 0.0f;
 
-  const GroupWalk<T, Cfg::waves> walk{g, ranks, tyi, txi, wave, lane, fy0, fx0};
+  const GroupWalk<T, Cfg::waves> walk{g, slots.pos, tyi, txi, wave, lane};
   const float* const stacks[1] = {r.stack_a};
-  auto filter = [&](const float (&cur)[1][K], int fo_v, int pos_v) {
+  auto filter = [&](const float (&cur)[1][K], int j, int pos_v) {
     float v[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) v[k] = cur[0][k];
     // unnormalised Haar: coefficient k of the orthonormal transform is
-    // haar_gain(k) * v[k]; the kept ones are scaled by haar_gain^2 (a power of
-    // two) for the unnormalised inverse
+    // haar_gain(k) * v[k]; the thresholds are on v[k], and the inverse takes
+    // the bands with their weights h = K haar_gain^2: from here to the
+    // weight, values are K times the orthonormal ones (exactly)
     haar_fwd_raw<K>(v);
+    auto keep = [&](int k, float x) { return fabsf(x) >= (k == 0 ? kept_dc : kept[k == 0 ? 0 : 31 - __builtin_clz(k)]); };
     int nnz = 0;
+    if (hp.weight_mode == 1) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const bool keep = fabsf(v[k]) * haar_gain<K>(k) >= tau || (k == 0 && dc_lane);
-      v[k] = keep ? v[k] * haar_gain2<K>(k) : 0.0f;
-      nnz += keep ? 1 : 0;
+      for (int k = 0; k < K; ++k) {
+        float x = v[k];
+        asm volatile("" : "+v"(x));  // (apart from the selection below, which then folds |x| into its comparison)
+        nnz += keep(k, x) ? 1 : 0;
+      }
     }
-    haar_inv_raw<K>(v);
-    // inverse 2-D transform, kChunk blocks at a time through the scratch; the
-    // spatial total-variation terms are read while a chunk is parked there
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = keep(k, v[k]) ? v[k] : 0.0f;
+    haar_inv_banded<K>(v);
+    // inverse 2-D transform.  The two coarse levels are a 4 x 4 corner: all K
+    // blocks' corners go through the scratch together (fuller waves than a
+    // chunk's), and come back in the registers ll, a column per lane.
     constexpr int CH = Cfg::chunk;
     constexpr Mat8 S2 = bior_synthesis(2);
     constexpr Mat8 S4 = bior_synthesis(4);
     constexpr Mat8 S8 = bior_synthesis(8);
+    constexpr int kCorner = 20, kCornerPitch = 5;  // conflict-free rows and columns
+    constexpr int kPasses = (K * 4 + kWave - 1) / kWave;
+    static_assert(K * kCorner <= CH * kBlockFloats, "the corners fit the scratch");
+    float ll[kPasses][4];
+    wave_lds_sync();  // earlier reads of the scratch are done
+    if (a < 4 && b < 4) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) xw[k * kCorner + a * kCornerPitch + b] = v[k];
+    }
+    wave_lds_sync();
+    auto line4 = [&](const float* x, float* y) { apply_mat<4>(S4, x, y); };
+    transform_level<K, 2, kCorner, kCornerPitch>(xw, lane, [&](const float* x, float* y) { apply_mat<2>(S2, x, y); });
+    transform_rows<K, 4, kCorner, kCornerPitch>(xw, lane, line4);
+    transform_columns<K, 4, kCorner, kCornerPitch>(xw, lane, line4, [&](int pass, int, int, const float (&y)[8]) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ll[pass][i] = y[i];
+    });
+    // the fine level, kChunk blocks at a time; the spatial total-variation
+    // terms are read while a chunk is parked there
     float u[K];
     float tv = 0.0f;
 #pragma unroll
     for (int c0 = 0; c0 < K; c0 += CH) {
       wave_lds_sync();  // earlier reads of the scratch are done
 #pragma unroll
-      for (int k = 0; k < CH; ++k) xw[k * kBlockFloats + a * kScratchPitch + b] = v[c0 + k];
+      for (int k = 0; k < CH; ++k) own[k * kBlockFloats] = v[c0 + k];
       wave_lds_sync();
-      inverse_level<CH, 2>(xw, lane, [&](const float* x, float* y) { apply_mat<2>(S2, x, y); });
-      inverse_level<CH, 4>(xw, lane, [&](const float* x, float* y) { apply_mat<4>(S4, x, y); });
-      inverse_level<CH, 8>(xw, lane, [&](const float* x, float* y) { apply_mat<8>(S8, x, y); });
 #pragma unroll
-      for (int k = 0; k < CH; ++k) u[c0 + k] = xw[k * kBlockFloats + a * kScratchPitch + b];
+      for (int pass = 0; pass < kPasses; ++pass) {
+        const int it = pass * kWave + lane - 4 * c0;  // corner column it % 4 of the chunk's block it / 4
+        if (it >= 0 && it < 4 * CH) {
+          float* col = xw + it / 4 * kBlockFloats + it % 4;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) col[i * kScratchPitch] = ll[pass][i];
+        }
+      }
+      wave_lds_sync();
+      transform_level<CH, 8>(xw, lane, [&](const float* x, float* y) { apply_mat<8>(S8, x, y); });
+#pragma unroll
+      for (int k = 0; k < CH; ++k) u[c0 + k] = own[k * kBlockFloats];
       if (hp.weight_mode == 0) {
+        // (lanes without a neighbour add 0)
 #pragma unroll
         for (int k = 0; k < CH; ++k) {
-          if (b < 7) tv += fabsf(xw[k * kBlockFloats + a * kScratchPitch + b + 1] - u[c0 + k]);
-          if (a < 7) tv += fabsf(xw[k * kBlockFloats + (a + 1) * kScratchPitch + b] - u[c0 + k]);
+          tv = fmaf(fabsf(next_lane(u[c0 + k]) - u[c0 + k]), has_right, tv);
+          tv += fabsf(below[k * kBlockFloats] - u[c0 + k]);
         }
       }
     }
@@ -464,26 +583,23 @@ __device__ __forceinline__ void group_ht_body(acc_t* acc,
     if (hp.weight_mode == 0) {
 #pragma unroll
       for (int k = 0; k + 1 < K; ++k) tv += fabsf(u[k + 1] - u[k]);
-      w = r.eps / (wave_sum(tv) + r.eps);
+      w = r.eps / fmaf(wave_sum(tv), 1.0f / K, r.eps);
     } else if (hp.weight_mode == 1) {
       w = 1.0f / static_cast<float>(max(wave_sum_int(nnz), 1));
     } else {
       w = 1.0f;
     }
-    accumulate<K, T>(acc, fo_v, 0, u, w, lane);
+    accumulate<K, T>(acc, slots.fo + walk.ref(j) * K, u, w * (kFixScaleF / K), lane);
     add_block_weights<K>(bw, pos_v, w, lane);
   };
   if constexpr (RECOMPUTE) {
-    int r0 = walk.template rank<K>(0);
     for (int j = 0; j < walk.kGroups; ++j) {
-      const int r1 = walk.template rank<K>(j + 1);
+      if (!walk.exists(j)) continue;
+      const int pos_v = walk.template slot<K>(j);
       float cur[1][K];
-      int fo = 0, pos = 0;
-      if (walk.template gather_pixels<K>(j, r0, r.noisy, cur, fo, pos)) {
-        forward_blocks<K, Cfg::chunk>(xw, lane, cur[0]);
-        filter(cur, fo, pos);
-      }
-      r0 = r1;
+      walk.template gather_pixels<K>(pos_v, r.noisy, cur);
+      forward_blocks<K, Cfg::chunk>(xw, lane, cur[0]);
+      filter(cur, j, pos_v);
     }
   } else {
     for_each_group<K, 1, Cfg::prefetch>(walk, stacks, filter);
@@ -520,15 +636,15 @@ __device__ __forceinline__ void haar_inv_weighted(float* v, const float* wt) {
 // pixels of one column of a block, which it adds into the footprint from
 // there: one address per column, rows by instruction offsets, no trip back
 // through the scratch.
-// At 80 registers two tiles of twelve waves share a CU (before: one of sixteen,
-// a pixel of every block per lane and an address per block).  Kernel us, before
-// -> two tiles -> scale-free transforms: 512^2 91 -> 76 -> 71, 1001 x 750
-// 285 -> 242 -> 217, 4096^2 4837 -> 4270 -> 3760, 64 mixed images
-// 7604 -> 6226 -> 5670.
+// At 80 registers two tiles of twelve waves share a CU.  Against one tile of
+// sixteen waves with scaled transforms, a pixel of every block per lane and an
+// address per block, kernel us: 512^2 91 -> 67, 1001 x 750 285 -> 205, 4096^2
+// 4837 -> 3420, 64 mixed images 7604 -> 5110.
 template <int K, int SHAPE>
 __device__ __forceinline__ void group_wiener_body(acc_t* acc,
                                                   float (*scratch)[GroupCfg<K, false, SHAPE>::chunk * kBlockFloats],
-                                                  int16_t* ranks, const ImgRec& r, int R, int item) {
+                                                  typename GroupCfg<K, false, SHAPE>::SlotTable& slots,
+                                                  const ImgRec& r, int R, int item) {
 #pragma clang fp contract(off)  // the same roundings in every shape
   using Cfg = GroupCfg<K, false, SHAPE>;
   using T = typename Cfg::T;
@@ -536,7 +652,7 @@ __device__ __forceinline__ void group_wiener_body(acc_t* acc,
   const int tyi = item / g.nTx, txi = item % g.nTx;
   const int lane0 = threadIdx.x & (kWave - 1);
   const int wave = wave_id();
-  load_ranks<K, T, Cfg::threads>(ranks, g, r.idx, tyi, txi);
+  slots.template load<Cfg::threads>(g, r.idx, tyi, txi);
   zero_acc(acc, g.FY * T::FXP);
   const int fy0 = kStep * tyi * T::py - g.R;
   const int fx0 = kStep * txi * T::px - g.R;
@@ -552,11 +668,11 @@ __device__ __forceinline__ void group_wiener_body(acc_t* acc,
   const float* __restrict__ stack_p = r.stack_b;
   constexpr int CH = Cfg::chunk;
 
-  const GroupWalk<T, Cfg::waves> walk{g, ranks, tyi, txi, wave, lane0, fy0, fx0};
+  const GroupWalk<T, Cfg::waves> walk{g, slots.pos, tyi, txi, wave, lane0};
 #pragma unroll 1
   for (int j = 0; j < walk.kGroups; ++j) {
-    int p, q, pos_v, fo_v;
-    if (!walk.ref_of(j, p, q)) continue;
+    if (!walk.exists(j)) continue;
+    const int pos_v = walk.template slot<K>(j);
     // what follows from the lane is formed again for each group: kept through
     // the loop it would not fit the registers
     int lane = lane0;
@@ -564,7 +680,6 @@ __device__ __forceinline__ void group_wiener_body(acc_t* acc,
     asm volatile("" : "+v"(lane), "+v"(sv));
     float* xw = scratch[wave];
     const int a = lane >> 3, b = lane & 7;
-    slot_pos<K, T>(g, walk.template rank<K>(j), p, q, fy0, fx0, lane, pos_v, fo_v);
     // the pilot's spectra, turned into the Wiener gains; the noisy spectra are
     // loaded after them, so that the two are never in flight together
     float wt[K];
@@ -612,14 +727,13 @@ __device__ __forceinline__ void group_wiener_body(acc_t* acc,
         for (int i = 0; i < 8; ++i) line[i] = y[i];
       }
       wave_lds_sync();
-      const int fo = __shfl(fo_v, c0 + a, kWave);
       if (CH == 8 || a < CH) {
         const float* col = xw + a * kBlockFloats + b;
         float x[8], y[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = col[i * kScratchPitch];
         dct8_inv_raw(x, y);
-        acc_t* cell = acc + fo + b;
+        acc_t* cell = cell_at(acc, slots.fo[walk.ref(j) * K + c0 + a]) + b;
 #pragma unroll
         for (int i = 0; i < 8; ++i) atomicAdd(cell + i * T::FXP, static_cast<acc_t>(to_fixed_product(y[i], w_scaled)));
       }
@@ -638,9 +752,9 @@ __global__ __launch_bounds__((GroupCfg<K, true, SHAPE>::threads),
   using Cfg = GroupCfg<K, true, SHAPE>;
   __shared__ acc_t acc[Cfg::T::entries];
   __shared__ float scratch[Cfg::waves][Cfg::chunk * kBlockFloats];
-  __shared__ int16_t ranks[Cfg::T::refs * K];
+  __shared__ typename Cfg::SlotTable slots;
   for_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
-    group_ht_body<K, RECOMPUTE, SHAPE>(acc, scratch, ranks, r, R, hp, item);
+    group_ht_body<K, RECOMPUTE, SHAPE>(acc, scratch, slots, r, R, hp, item);
   });
 }
 
@@ -660,9 +774,9 @@ __global__ __launch_bounds__((GroupCfg<K, false, SHAPE>::threads),
   using Cfg = GroupCfg<K, false, SHAPE>;
   __shared__ acc_t acc[Cfg::T::entries];
   __shared__ float scratch[Cfg::waves][Cfg::chunk * kBlockFloats];
-  __shared__ int16_t ranks[Cfg::T::refs * K];
+  __shared__ typename Cfg::SlotTable slots;
   for_item<BATCH>(one, wl, [&](const ImgRec& r, int item) {
-    group_wiener_body<K, SHAPE>(acc, scratch, ranks, r, R, item);
+    group_wiener_body<K, SHAPE>(acc, scratch, slots, r, R, item);
   });
 }
 
@@ -767,24 +881,23 @@ int reduce_items_for(int H, int W) { return reduce_items(H, W); }
 // Two tiles per CU are 512 of them: below that CUs idle, or hold one tile while
 // others work on two, unless the tiles are smaller; small tiles pay for it with
 // more footprint cells to clear and add per reference.  Whole first stage, us,
-// 8 x 8 | 4 x 4 | 2 x 4 references: 36 tiles (128^2) 44 | 27 | 24; 64 (192^2)
-// 50 | 35 | 33; 121 (256^2) 57 | 45 | 49; 256 (384^2, one per CU) 71 | 73 | 75;
-// 294 (321 x 481) 88 | 77 | 79; 361 (448^2) 96 | 90 | 94; 484 (512^2)
-// 108 | 110 | 113; 1344 (1001 x 750) 280 | 266 | 279; 29241 (4096^2)
-// 5300 | 5476 | 5788.
+// 8 x 8 | 4 x 4 | 2 x 4 references: 36 tiles (128^2) 38 | 25 | 23; 64 (192^2)
+// 44 | 33 | 32; 121 (256^2) 52 | 45 | 46; 256 (384^2, one per CU) 66 | 68 | 70;
+// 294 (321 x 481) 81 | 73 | 75; 361 (448^2) 89 | 86 | 90; 484 (512^2)
+// 102 | 105 | 109; 1344 (1001 x 750) 262 | 255 | 274; 29241 (4096^2)
+// 4899 | 5342 | 5418.
 static GroupShape ht_shape_for(int H, int W) {
   const int t = tiles_of<Tile<8, 8>>(H, W);
   if (t <= 64) return kTiny;
   return t <= 192 || (t > 256 && t <= 420) ? kSmall : kTwoTiles;
 }
 
-// The Wiener kernel (more arithmetic per footprint cell) takes the
-// smallest tile up to the same size.  Whole second stage, us, 8 x 8 | 4 x 4 |
-// 2 x 4 references: 128^2 57 | 36 | 30; 192^2 63 | 43 | 38; 256^2 70 | 53 | 52;
-// 384^2 93 | 90 | 85; 321 x 481 113 | 98 | 92; 448^2 124 | 115 | 111.  Beyond,
-// the order depends on the image; kernel alone on photograph-like images:
-// 512^2 71 | 75 | 71; 1001 x 750 217 | 213 | 225; whole stage 4096^2
-// 8243 | 8586 | 8392.
+// The Wiener kernel (more arithmetic per footprint cell) takes the smallest
+// tile up to the same size.  Whole second stage, us, 8 x 8 | 4 x 4 | 2 x 4
+// references: 128^2 54 | 35 | 31; 192^2 59 | 41 | 38; 256^2 66 | 51 | 52; 384^2
+// 89 | 86 | 85; 321 x 481 106 | 93 | 92; 448^2 119 | 112 | 112; 512^2
+// 141 | 136 | 137 (other images 67 | 70 | 71 for the kernel alone); 1001 x 750
+// 372 | 365 | 368; 4096^2 8051 | 8200 | 8398.
 static GroupShape wiener_shape_for(int H, int W) { return tiles_of<Tile<8, 8>>(H, W) <= 420 ? kTiny : kTwoTiles; }
 
 template <int K, int SHAPE>
