@@ -501,12 +501,46 @@ __global__ __launch_bounds__(kFThreads) void fused_infer_kernel(const uint16_t* 
 // ---------------------------------------------------------------------------
 // weight gradient: dW[t][ci][co] = sum_p x[p + off_t][ci] g[p][co], db[co] = sum_p g[p][co]
 // per-workgroup partials [grid][kWmat + kC]
+//
+// The products run over pixels, so both tensors are needed channel-major; a
+// thread loads eight channels of eight pixels of a row, transposes them in
+// registers (32 byte permutes) and stores eight 16-byte runs of pixels.  A wave
+// owns 16 x 16 channels of all nine taps.  It goes down the tile's rows: an
+// operand of x (eight pixels from column 8 grp on, and two more) gives the
+// three column shifts in registers and meets the operands of the three rows of
+// g it is a tap of, so a row is read from LDS once.  A tile's loads are in
+// flight during the products of the one before.  64 images of 128^2, us per
+// layer: 86 with 2-byte stores into three shifted copies and two operand reads
+// per product, 45 transposed, 38 with the loads ahead; both tensors once at the
+// rate of a large copy are 28.
 // ---------------------------------------------------------------------------
+constexpr int kXGroups = (kTileX + 2 + 7) / 8;          // eights of columns x0 - 1 .. : 5
+constexpr int kXRow = 8 * kXGroups;
+// channel pitches of 12 and 4 words modulo 32: eight lanes' 16-byte reads of
+// eight channels fall on all banks; every eight channels start 8 words later,
+// so that the stores of four lanes' eights of channels do too
+constexpr int kXCh = (kTileY + 2) * kXRow + 8, kGCh = kTileY * kTileX + 8;
+constexpr int kEights = 16;
+static_assert(kXCh * 2 / 4 % 32 == 12 && kGCh * 2 / 4 % 32 == 4, "conflict-free channel pitches");
+
+__device__ __forceinline__ int channel_at(int ch, int pitch) { return ch * pitch + (ch >> 3) * kEights; }
+
+// v[k] = channels 8 c8 .. 8 c8 + 7 of pixel k, to dst[channel * pitch + k]
+__device__ __forceinline__ void store_transposed(uint16_t* dst, int pitch, const uint4 (&v)[8]) {
+  auto word = [&](int k, int j) { return j == 0 ? v[k].x : j == 1 ? v[k].y : j == 2 ? v[k].z : v[k].w; };
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    auto even = [&](int k) { return __builtin_amdgcn_perm(word(k + 1, j), word(k, j), 0x05040100u); };
+    auto odd = [&](int k) { return __builtin_amdgcn_perm(word(k + 1, j), word(k, j), 0x07060302u); };
+    *reinterpret_cast<uint4*>(dst + 2 * j * pitch) = make_uint4(even(0), even(2), even(4), even(6));
+    *reinterpret_cast<uint4*>(dst + (2 * j + 1) * pitch) = make_uint4(odd(0), odd(2), odd(4), odd(6));
+  }
+}
+
 __global__ __launch_bounds__(256) void wgrad_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ g,
                                                     int N, int H, int W, float* __restrict__ partial) {
-  // channel-major tiles; xs[kx] holds x shifted by kx - 1 columns
-  __shared__ __align__(16) uint16_t xs[3][kC][kTileY + 2][kTileX];
-  __shared__ __align__(16) uint16_t gs[kC][kTileY][kTileX];
+  __shared__ __align__(16) uint16_t xs[kC * kXCh + 4 * kEights];  // column 0 is x0 - 1, row 0 y0 - 1
+  __shared__ __align__(16) uint16_t gs[kC * kGCh + 4 * kEights];
   const int tx_n = (W + kTileX - 1) / kTileX, ty_n = (H + kTileY - 1) / kTileY;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 15, grp = lane >> 4;
@@ -517,59 +551,88 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const uint16_t* __restrict__
   float db = 0.0f;  // bias-gradient partial of channel tid % 32 over tile rows tid / 32
 
   const int total = conv_items(N, H, W);
-  for (int item = blockIdx.x; item < total; item += gridDim.x) {
+  // eights of pixels of x, then of g; four threads take the channels of one
+  constexpr int kXUnits = (kTileY + 2) * kXGroups, kUnits = kXUnits + kTileY * (kTileX / 8);
+  constexpr int kPasses = (4 * kUnits + 255) / 256;
+  uint4 v[kPasses][8];
+  // unit of pass p: its row and first column in its tile
+  struct Unit {
+    bool of_x;
+    int r, c;
+  };
+  const int c8 = threadIdx.x & 3;
+  auto unit = [&](int p) {
+    const int u = (static_cast<int>(threadIdx.x) + 256 * p) >> 2, ug = u - kXUnits;
+    const bool of_x = u < kXUnits;
+    const int r = of_x ? u / kXGroups : ug / (kTileX / 8);
+    return Unit{of_x, r, 8 * (of_x ? u - r * kXGroups : ug - r * (kTileX / 8))};
+  };
+  auto active = [&](int p) { return p + 1 < kPasses || static_cast<int>(threadIdx.x) + 256 * p < 4 * kUnits; };
+  auto load = [&](int item) {
     const int n = item / (tx_n * ty_n);
     const int rem = item - n * tx_n * ty_n;
     const int y0 = (rem / tx_n) * kTileY, x0 = (rem % tx_n) * kTileX;
-    const uint16_t* xn = x + static_cast<size_t>(n) * H * W * kC;
-    const uint16_t* gn = g + static_cast<size_t>(n) * H * W * kC;
-    // x: rows y0-1 .. y0+8, columns x0-1 .. x0+32 (34), scattered into the
-    // three shifted copies; a thread moves 8 channels of one pixel, consecutive
-    // threads take consecutive pixels (conflict-free LDS stores)
-    constexpr int kXPix = (kTileY + 2) * (kTileX + 2);
-    for (int i = threadIdx.x; i < kXPix * 4; i += blockDim.x) {
-      const int c8 = i / kXPix, pix = i - c8 * kXPix;
-      const int r = pix / (kTileX + 2), c = pix - r * (kTileX + 2);
-      const int y = y0 - 1 + r, xx = x0 - 1 + c;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (y >= 0 && y < H && xx >= 0 && xx < W) v = *reinterpret_cast<const uint4*>(xn + (static_cast<size_t>(y) * W + xx) * kC + 8 * c8);
-      const uint16_t* vv = reinterpret_cast<const uint16_t*>(&v);
 #pragma unroll
-      for (int kx = 0; kx < 3; ++kx) {
-        const int cc = c - kx;  // xs[kx][..][cc] = x[column x0 + cc + kx - 1]
-        if (cc >= 0 && cc < kTileX) {
+    for (int p = 0; p < kPasses; ++p) {
+      const Unit u = unit(p);
+      const int y = u.of_x ? y0 - 1 + u.r : y0 + u.r, xx = u.of_x ? x0 - 1 + u.c : x0 + u.c;
+      const int cols = u.of_x ? kTileX + 2 - u.c : kTileX;  // columns of the eight that are used
+      const uint16_t* src =
+          (u.of_x ? x : g) + (static_cast<ptrdiff_t>(n) * H * W + static_cast<ptrdiff_t>(y) * W + xx) * kC + 8 * c8;
 #pragma unroll
-          for (int j = 0; j < 8; ++j) xs[kx][8 * c8 + j][r][cc] = vv[j];
-        }
+      for (int k = 0; k < 8; ++k) {
+        v[p][k] = make_uint4(0, 0, 0, 0);
+        if (active(p) && y >= 0 && y < H && xx + k >= 0 && xx + k < W && k < cols)
+          v[p][k] = *reinterpret_cast<const uint4*>(src + k * kC);
       }
     }
-    constexpr int kGPix = kTileY * kTileX;
-    for (int i = threadIdx.x; i < kGPix * 4; i += blockDim.x) {
-      const int c8 = i / kGPix, pix = i - c8 * kGPix;
-      const int r = pix / kTileX, c = pix - r * kTileX;
-      const int y = y0 + r, xx = x0 + c;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (y < H && xx < W) v = *reinterpret_cast<const uint4*>(gn + (static_cast<size_t>(y) * W + xx) * kC + 8 * c8);
-      const uint16_t* vv = reinterpret_cast<const uint16_t*>(&v);
+  };
+  if (static_cast<int>(blockIdx.x) < total) load(blockIdx.x);
+  for (int item = blockIdx.x; item < total; item += gridDim.x) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) gs[8 * c8 + j][r][c] = vv[j];
+    for (int p = 0; p < kPasses; ++p) {
+      const Unit u = unit(p);
+      if (!active(p)) continue;
+      if (u.of_x)
+        store_transposed(xs + channel_at(8 * c8, kXCh) + u.r * kXRow + u.c, kXCh, v[p]);
+      else
+        store_transposed(gs + channel_at(8 * c8, kGCh) + u.r * kTileX + u.c, kGCh, v[p]);
     }
+    // the next tile's loads are in flight during this one's products
+    if (item + static_cast<int>(gridDim.x) < total) load(item + gridDim.x);
     __syncthreads();
+    const uint16_t* xrow = xs + channel_at(ci_t * 16 + col, kXCh) + 8 * grp;
+    const uint16_t* grow = gs + channel_at(co_t * 16 + col, kGCh) + 8 * grp;
+    bf16x8 A[3];  // rows xr, xr - 1, xr - 2 of g
 #pragma unroll
-    for (int t = 0; t < kTaps; ++t) {
-      const int ky = t / 3, kx = t % 3;
+    for (int xr = 0; xr < kTileY + 2; ++xr) {
+      A[2] = A[1];
+      A[1] = A[0];
+      if (xr < kTileY) A[0] = as_bf16x8(*reinterpret_cast<const uint4*>(grow + xr * kTileX));
+      const uint4 q = *reinterpret_cast<const uint4*>(xrow + xr * kXRow);
+      const unsigned e = *reinterpret_cast<const unsigned*>(xrow + xr * kXRow + 8);
+      const bf16x8 B[3] = {as_bf16x8(q),
+                           as_bf16x8(make_uint4(__builtin_amdgcn_alignbit(q.y, q.x, 16), __builtin_amdgcn_alignbit(q.z, q.y, 16),
+                                                __builtin_amdgcn_alignbit(q.w, q.z, 16), __builtin_amdgcn_alignbit(e, q.w, 16))),
+                           as_bf16x8(make_uint4(q.y, q.z, q.w, e))};
 #pragma unroll
-      for (int r = 0; r < kTileY; ++r) {
-        const bf16x8 Aop = as_bf16x8(*reinterpret_cast<const uint4*>(&gs[co_t * 16 + col][r][8 * grp]));
-        const bf16x8 Bop = as_bf16x8(*reinterpret_cast<const uint4*>(&xs[kx][ci_t * 16 + col][r + ky][8 * grp]));
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Aop, Bop, acc[t], 0, 0, 0);
-      }
+      for (int ky = 0; ky < 3; ++ky)
+        if (xr >= ky && xr - ky < kTileY) {
+#pragma unroll
+          for (int kx = 0; kx < 3; ++kx)
+            acc[3 * ky + kx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[ky], B[kx], acc[3 * ky + kx], 0, 0, 0);
+        }
     }
     {  // bias gradient: thread (channel tid % 32, row tid / 32) sums one tile row
-      const int ch = threadIdx.x & (kC - 1), r = threadIdx.x >> 5;
+      const uint16_t* row = gs + channel_at(threadIdx.x & (kC - 1), kGCh) + (threadIdx.x >> 5) * kTileX;
       float s = 0.0f;
-#pragma unroll 8
-      for (int c = 0; c < kTileX; ++c) s += bf2f(gs[ch][r][c]);
+#pragma unroll
+      for (int c = 0; c < kTileX; c += 8) {
+        const uint4 q = *reinterpret_cast<const uint4*>(row + c);
+        const uint16_t* v = reinterpret_cast<const uint16_t*>(&q);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += bf2f(v[k]);
+      }
       db += s;
     }
     __syncthreads();

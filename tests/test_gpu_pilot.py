@@ -168,6 +168,28 @@ def test_pilot_gradient_parity(torch, G, ctx, weight):
         o += n
 
 
+@pytest.mark.parametrize("shape", [(1, 7, 5), (2, 19, 67), (90, 8, 200)])
+def test_pilot_gradient_at_tile_edges(torch, G, ctx, shape):
+    """Images smaller than a tile, tiles with one row or three columns of
+    pixels, and more tiles than workgroups; the bounds of the test above."""
+    B, H, W = shape
+    say("pilot gradient", shape)
+    theta = _theta(2)
+    ctx.pilot_load(torch.from_numpy(theta).cuda())
+    Z, sig = _batch(B, H, W, 31)
+    target = np.random.default_rng(4).random((B, H, W)).astype(np.float32)
+    grad, loss = ctx.pilot_grad(torch.from_numpy(Z).cuda(), torch.from_numpy(target).cuda(), torch.from_numpy(sig).cuda())
+    lo, go = P.loss_and_grad(theta.astype(np.float64), Z / 65535.0, sig, target, bf16=True)
+    assert abs(loss.item() - lo) <= 1e-2 * lo
+    g = grad.cpu().numpy().astype(np.float64)
+    o = 0
+    for l, (ci, co) in enumerate(P.LAYERS):
+        n = 9 * ci * co + co
+        rel = np.linalg.norm(g[o:o + n] - go[o:o + n]) / max(np.linalg.norm(go[o:o + n]), 1e-30)
+        assert rel <= 5e-2, (l, rel)
+        o += n
+
+
 def test_pilot_training_reduces_loss(torch, G, ctx):
     B, H, W = 4, 32, 32
     theta = torch.from_numpy(_theta(4, scale=0.5)).cuda()
