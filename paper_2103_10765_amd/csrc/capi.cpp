@@ -1367,15 +1367,13 @@ int pilot_forward(gbm3d_ctx* ctx, const uint16_t* noisy, int B, int H, int W, co
   const size_t ab = act_bytes(B, H, W);
   const PilotWeights pw = pilot_weights(ctx);
   char* act = static_cast<char*>(ctx->pilot_act.p);
-  auto buf = [&](int l) { return reinterpret_cast<uint16_t*>(act + l * ab); };
+  auto buf = [&](int l) { return reinterpret_cast<uint16_t*>(act + (l - 1) * ab); };
   const int cap = 4 * ctx->n_cu;
-  HIP_TRY(ctx, timed(ctx, "pilot_prep", st, [&] { return gbm3d::launch_pilot_prep(noisy, sigma, B, H, W, buf(0), st); }),
-          "pilot input");
   for (int l = 0; l < gbm3d::kPilotLayers; ++l) {
     const bool last = l == gbm3d::kPilotLayers - 1;
     const uint16_t* w = pw.wf + static_cast<size_t>(l) * 9 * kPilotC * kPilotC;
     HIP_TRY(ctx, timed(ctx, "pilot_conv", st, [&] {
-              return gbm3d::launch_pilot_conv(last ? 1 : 0, buf(l), w, pw.bias + l * kPilotC, nullptr,
+              return gbm3d::launch_pilot_conv(l, l ? buf(l) : noisy, sigma, w, pw.bias + l * kPilotC,
                                               last ? nullptr : buf(l + 1), noisy, pilot_f32, pilot_u16, B, H, W, cap,
                                               st);
             }),
@@ -1431,18 +1429,18 @@ int gbm3d_pilot_grad(gbm3d_ctx* ctx, const uint16_t* noisy, const float* target,
   hipStream_t st = static_cast<hipStream_t>(stream);
   const size_t ab = act_bytes(B, H, W);
   const size_t npix = static_cast<size_t>(B) * H * W;
-  // layout: layer inputs x0 .. x(L-1) | grad ping-pong g0, g1 | pilot f32
+  // layout: layer inputs x1 .. x(L-1) | grad ping-pong g0, g1 | pilot f32
   constexpr int L = gbm3d::kPilotLayers;
-  CHECK(ensure(ctx, ctx->pilot_act, (L + 2) * ab + align256(npix * sizeof(float)), "pilot training activations"));
+  CHECK(ensure(ctx, ctx->pilot_act, (L + 1) * ab + align256(npix * sizeof(float)), "pilot training activations"));
   const int wg_grid = 2 * ctx->n_cu;
   const int loss_blocks = 1024;
   CHECK(ensure(ctx, ctx->pilot_part,
                gbm3d::pilot_wgrad_partial_floats(wg_grid) * sizeof(float) + loss_blocks * sizeof(double),
                "pilot partial sums"));
   char* act = static_cast<char*>(ctx->pilot_act.p);
-  auto x = [&](int l) { return reinterpret_cast<uint16_t*>(act + l * ab); };
-  uint16_t* gbuf[2] = {reinterpret_cast<uint16_t*>(act + L * ab), reinterpret_cast<uint16_t*>(act + (L + 1) * ab)};
-  float* pil = reinterpret_cast<float*>(act + (L + 2) * ab);
+  auto x = [&](int l) { return l ? reinterpret_cast<const uint16_t*>(act + (l - 1) * ab) : noisy; };
+  uint16_t* gbuf[2] = {reinterpret_cast<uint16_t*>(act + (L - 1) * ab), reinterpret_cast<uint16_t*>(act + L * ab)};
+  float* pil = reinterpret_cast<float*>(act + (L + 1) * ab);
   float* wpart = static_cast<float*>(ctx->pilot_part.p);
   double* lpart = reinterpret_cast<double*>(reinterpret_cast<char*>(ctx->pilot_part.p) +
                                             gbm3d::pilot_wgrad_partial_floats(wg_grid) * sizeof(float));
@@ -1457,15 +1455,14 @@ int gbm3d_pilot_grad(gbm3d_ctx* ctx, const uint16_t* noisy, const float* target,
   int cur = 0;
   for (int l = gbm3d::kPilotLayers - 1; l >= 0; --l) {
     HIP_TRY(ctx, timed(ctx, "pilot_wgrad", st, [&] {
-              return gbm3d::launch_pilot_wgrad(x(l), gbuf[cur], B, H, W, wg_grid, wpart, l,
+              return gbm3d::launch_pilot_wgrad(x(l), sigma, gbuf[cur], B, H, W, wg_grid, wpart, l,
                                                grad + gbm3d::pilot_layer_offset(l), st);
             }),
             "pilot weight gradient");
     if (l > 0) {
       const uint16_t* w = pw.wb + static_cast<size_t>(l) * 9 * kPilotC * kPilotC;
       HIP_TRY(ctx, timed(ctx, "pilot_dgrad", st, [&] {
-                return gbm3d::launch_pilot_conv(2, gbuf[cur], w, nullptr, x(l), gbuf[cur ^ 1], nullptr, nullptr,
-                                                nullptr, B, H, W, cap, st);
+                return gbm3d::launch_pilot_dgrad(l, gbuf[cur], w, x(l), gbuf[cur ^ 1], B, H, W, cap, st);
               }),
               "pilot input gradient");
       cur ^= 1;

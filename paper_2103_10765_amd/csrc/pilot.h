@@ -27,12 +27,15 @@ size_t pilot_packed_bytes();                 // forward + backward bf16 weight s
 size_t pilot_wgrad_partial_floats(int grid);
 
 hipError_t launch_pilot_pack(const float* master, uint16_t* wf, uint16_t* wb, float* bias, hipStream_t st);
-hipError_t launch_pilot_prep(const uint16_t* noisy, const float* sigma, int N, int H, int W, uint16_t* x0,
-                             hipStream_t st);
-// mode 0: forward + bias + ReLU; 1: last layer -> pilot; 2: input gradient with ReLU mask
-hipError_t launch_pilot_conv(int mode, const uint16_t* in, const uint16_t* w, const float* bias, const uint16_t* mask,
+// forward of one layer; layer 0 reads the u16 images and sigma, the last one
+// gives the pilot
+hipError_t launch_pilot_conv(int layer, const uint16_t* in, const float* sigma, const uint16_t* w, const float* bias,
                              uint16_t* out, const uint16_t* noisy, float* pilot_f32, uint16_t* pilot_u16, int N,
                              int H, int W, int grid_cap, hipStream_t st);
+// input gradient of layer > 0 with the ReLU mask of its input; g of the last
+// layer is the loss gradient
+hipError_t launch_pilot_dgrad(int layer, const uint16_t* g, const uint16_t* w, const uint16_t* mask, uint16_t* out,
+                              int N, int H, int W, int grid_cap, hipStream_t st);
 // inference of all six layers in one launch (one 16 x 32 output tile per
 // workgroup at a time, activations in LDS); grid_cap bounds the persistent grid
 int pilot_fused_tiles(int N, int H, int W);
@@ -40,10 +43,12 @@ hipError_t launch_pilot_infer_fused(const uint16_t* noisy, const float* sigma, c
                                     int N, int H, int W, float* pilot_f32, uint16_t* pilot_u16, int grid_cap,
                                     hipStream_t st);
 // loss = sum_p weight[p / hw] (pilot - target)^2 / n (weight NULL: 1), and dL/df
+// (g, one bf16 per pixel)
 hipError_t launch_pilot_loss(const float* pilot, const float* target, const float* weight, size_t hw, size_t n,
                              uint16_t* g, double* part, int n_part, float* loss, hipStream_t st);
-hipError_t launch_pilot_wgrad(const uint16_t* x, const uint16_t* g, int N, int H, int W, int grid, float* partial,
-                              int layer, float* grad_layer, hipStream_t st);
+// x and g of the layer as for the two passes above
+hipError_t launch_pilot_wgrad(const uint16_t* x, const float* sigma, const uint16_t* g, int N, int H, int W, int grid,
+                              float* partial, int layer, float* grad_layer, hipStream_t st);
 hipError_t launch_pilot_adam(float* w, float* m, float* v, const float* g, int n, float lr, float b1, float b2,
                              float eps, int step, hipStream_t st);
 

@@ -43,14 +43,39 @@ __host__ __device__ inline int conv_items(int N, int H, int W) {
   return N * ((H + kTileY - 1) / kTileY) * ((W + kTileX - 1) / kTileX);
 }
 
+// What a layer reads: an activation tensor, the network's input (channel 0 = z
+// of the u16 image, channel 1 = sigma) or the loss gradient (channel 0, one bf16
+// per pixel).  The last two are expanded to the eights of channels of an
+// activation tensor where a kernel loads them; as such tensors they were 64 MB
+// each for 64 images of 128^2, written once and read twice (95 us of 749 in a
+// gradient step).
+enum Source { kAct, kInput, kLossGrad };
+
+// Channels 8 c8 .. 8 c8 + 7 of pixel `pix` as they lie in memory, and from that
+// as activations of an image of noise level sigma (apart, so that loads can be
+// in flight).
+template <Source SRC>
+__device__ __forceinline__ uint4 load_channels(const uint16_t* __restrict__ p, size_t pix, int c8) {
+  if constexpr (SRC == kAct) return *reinterpret_cast<const uint4*>(p + pix * kC + 8 * c8);
+  return make_uint4(c8 == 0 ? p[pix] : 0, 0, 0, 0);
+}
+template <Source SRC>
+__device__ __forceinline__ uint4 as_activations(uint4 v, float sigma, int c8) {
+  if constexpr (SRC == kInput) {
+    if (c8 == 0) v.x = f2bf(static_cast<float>(v.x) * (1.0f / 65535.0f)) | (static_cast<uint32_t>(f2bf(sigma)) << 16);
+  }
+  return v;
+}
+
 // ---------------------------------------------------------------------------
 // convolution 32 -> 32, 3x3, zero "same" padding
 // MODE 0: forward, + bias, ReLU, bf16 out
 // MODE 1: forward last layer: f = channel 0 + bias; pilot = z - f (fp32 / u16)
 // MODE 2: input gradient: out = conv * (mask > 0), bf16 out
 // ---------------------------------------------------------------------------
-template <int MODE>
-__global__ __launch_bounds__(256) void conv_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ wpk,
+template <int MODE, Source SRC>
+__global__ __launch_bounds__(256) void conv_kernel(const uint16_t* __restrict__ in, const float* __restrict__ sigma,
+                                                   const uint16_t* __restrict__ wpk,
                                                    const float* __restrict__ bias, const uint16_t* __restrict__ mask,
                                                    uint16_t* __restrict__ out, const uint16_t* __restrict__ noisy,
                                                    float* __restrict__ pilot_f32, uint16_t* __restrict__ pilot_u16,
@@ -79,14 +104,15 @@ __global__ __launch_bounds__(256) void conv_kernel(const uint16_t* __restrict__ 
     const int n = item / (tx_n * ty_n);
     const int rem = item - n * tx_n * ty_n;
     const int y0 = (rem / tx_n) * kTileY, x0 = (rem % tx_n) * kTileX;
-    const uint4* src = reinterpret_cast<const uint4*>(in) + static_cast<size_t>(n) * H * W * 4;
     uint4* dst_t = reinterpret_cast<uint4*>(&tile[0][0][0]);
     for (int i = threadIdx.x; i < (kTileY + 2) * (kTileX + 2) * 4; i += blockDim.x) {
       const int pix = i >> 2, part = i & 3;
       const int r = pix / (kTileX + 2), c = pix - r * (kTileX + 2);
       const int y = y0 - 1 + r, x = x0 - 1 + c;
       uint4 v = make_uint4(0, 0, 0, 0);
-      if (y >= 0 && y < H && x >= 0 && x < W) v = src[(static_cast<size_t>(y) * W + x) * 4 + part];
+      if (y >= 0 && y < H && x >= 0 && x < W)
+        v = as_activations<SRC>(load_channels<SRC>(in, (static_cast<size_t>(n) * H + y) * W + x, part),
+                                SRC == kInput ? sigma[n] : 0.0f, part);
       dst_t[i] = v;
     }
     __syncthreads();
@@ -537,8 +563,10 @@ __device__ __forceinline__ void store_transposed(uint16_t* dst, int pitch, const
   }
 }
 
-__global__ __launch_bounds__(256) void wgrad_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ g,
-                                                    int N, int H, int W, float* __restrict__ partial) {
+template <Source XS, Source GS>
+__global__ __launch_bounds__(256) void wgrad_kernel(const uint16_t* __restrict__ x, const float* __restrict__ sigma,
+                                                    const uint16_t* __restrict__ g, int N, int H, int W,
+                                                    float* __restrict__ partial) {
   __shared__ __align__(16) uint16_t xs[kC * kXCh + 4 * kEights];  // column 0 is x0 - 1, row 0 y0 - 1
   __shared__ __align__(16) uint16_t gs[kC * kGCh + 4 * kEights];
   const int tx_n = (W + kTileX - 1) / kTileX, ty_n = (H + kTileY - 1) / kTileY;
@@ -551,84 +579,85 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const uint16_t* __restrict__
   float db = 0.0f;  // bias-gradient partial of channel tid % 32 over tile rows tid / 32
 
   const int total = conv_items(N, H, W);
-  // eights of pixels of x, then of g; four threads take the channels of one
-  constexpr int kXUnits = (kTileY + 2) * kXGroups, kUnits = kXUnits + kTileY * (kTileX / 8);
-  constexpr int kPasses = (4 * kUnits + 255) / 256;
-  uint4 v[kPasses][8];
-  // unit of pass p: its row and first column in its tile
-  struct Unit {
-    bool of_x;
-    int r, c;
-  };
-  const int c8 = threadIdx.x & 3;
-  auto unit = [&](int p) {
-    const int u = (static_cast<int>(threadIdx.x) + 256 * p) >> 2, ug = u - kXUnits;
-    const bool of_x = u < kXUnits;
-    const int r = of_x ? u / kXGroups : ug / (kTileX / 8);
-    return Unit{of_x, r, 8 * (of_x ? u - r * kXGroups : ug - r * (kTileX / 8))};
-  };
-  auto active = [&](int p) { return p + 1 < kPasses || static_cast<int>(threadIdx.x) + 256 * p < 4 * kUnits; };
+  // eights of pixels of x and of g; four threads take the channels of one
+  constexpr int kXUnits = (kTileY + 2) * kXGroups, kGGroups = kTileX / 8, kGUnits = kTileY * kGGroups;
+  static_assert(4 * kXUnits <= 256 && 4 * kGUnits <= 256, "one eight of pixels per thread");
+  uint4 vx[8], vg[8];
+  const int c8 = threadIdx.x & 3, u = threadIdx.x >> 2;
+  const int xr = u / kXGroups, xc = 8 * (u - xr * kXGroups), gr = u / kGGroups, gc = 8 * (u - gr * kGGroups);
+  unsigned in_x = 0;       // the pixels of vx inside the image
+  float sigma_n = 0.0f;
   auto load = [&](int item) {
     const int n = item / (tx_n * ty_n);
     const int rem = item - n * tx_n * ty_n;
     const int y0 = (rem / tx_n) * kTileY, x0 = (rem % tx_n) * kTileX;
-#pragma unroll
-    for (int p = 0; p < kPasses; ++p) {
-      const Unit u = unit(p);
-      const int y = u.of_x ? y0 - 1 + u.r : y0 + u.r, xx = u.of_x ? x0 - 1 + u.c : x0 + u.c;
-      const int cols = u.of_x ? kTileX + 2 - u.c : kTileX;  // columns of the eight that are used
-      const uint16_t* src =
-          (u.of_x ? x : g) + (static_cast<ptrdiff_t>(n) * H * W + static_cast<ptrdiff_t>(y) * W + xx) * kC + 8 * c8;
+    if constexpr (XS == kInput) sigma_n = sigma[n];
+    {
+      const int y = y0 - 1 + xr, xx = x0 - 1 + xc;
+      const bool row = u < kXUnits && y >= 0 && y < H;
+      const size_t pix = (static_cast<size_t>(n) * H + y) * W + xx;
+      in_x = 0;
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        v[p][k] = make_uint4(0, 0, 0, 0);
-        if (active(p) && y >= 0 && y < H && xx + k >= 0 && xx + k < W && k < cols)
-          v[p][k] = *reinterpret_cast<const uint4*>(src + k * kC);
+        vx[k] = make_uint4(0, 0, 0, 0);
+        // (columns past the 34th are not used)
+        if (row && xx + k >= 0 && xx + k < W && xc + k < kTileX + 2) {
+          vx[k] = load_channels<XS>(x, pix + k, c8);
+          in_x |= 1u << k;
+        }
+      }
+    }
+    {
+      const int y = y0 + gr, xx = x0 + gc;
+      const bool row = u < kGUnits && y < H;
+      const size_t pix = (static_cast<size_t>(n) * H + y) * W + xx;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        vg[k] = make_uint4(0, 0, 0, 0);
+        if (row && xx + k < W) vg[k] = load_channels<GS>(g, pix + k, c8);
       }
     }
   };
   if (static_cast<int>(blockIdx.x) < total) load(blockIdx.x);
   for (int item = blockIdx.x; item < total; item += gridDim.x) {
+    if constexpr (XS == kInput) {
 #pragma unroll
-    for (int p = 0; p < kPasses; ++p) {
-      const Unit u = unit(p);
-      if (!active(p)) continue;
-      if (u.of_x)
-        store_transposed(xs + channel_at(8 * c8, kXCh) + u.r * kXRow + u.c, kXCh, v[p]);
-      else
-        store_transposed(gs + channel_at(8 * c8, kGCh) + u.r * kTileX + u.c, kGCh, v[p]);
+      for (int k = 0; k < 8; ++k)
+        if (in_x >> k & 1) vx[k] = as_activations<XS>(vx[k], sigma_n, c8);
     }
+    if (u < kXUnits) store_transposed(xs + channel_at(8 * c8, kXCh) + xr * kXRow + xc, kXCh, vx);
+    if (u < kGUnits) store_transposed(gs + channel_at(8 * c8, kGCh) + gr * kTileX + gc, kGCh, vg);
     // the next tile's loads are in flight during this one's products
     if (item + static_cast<int>(gridDim.x) < total) load(item + gridDim.x);
     __syncthreads();
     const uint16_t* xrow = xs + channel_at(ci_t * 16 + col, kXCh) + 8 * grp;
     const uint16_t* grow = gs + channel_at(co_t * 16 + col, kGCh) + 8 * grp;
-    bf16x8 A[3];  // rows xr, xr - 1, xr - 2 of g
+    bf16x8 A[3];  // rows row, row - 1, row - 2 of g
 #pragma unroll
-    for (int xr = 0; xr < kTileY + 2; ++xr) {
+    for (int row = 0; row < kTileY + 2; ++row) {
       A[2] = A[1];
       A[1] = A[0];
-      if (xr < kTileY) A[0] = as_bf16x8(*reinterpret_cast<const uint4*>(grow + xr * kTileX));
-      const uint4 q = *reinterpret_cast<const uint4*>(xrow + xr * kXRow);
-      const unsigned e = *reinterpret_cast<const unsigned*>(xrow + xr * kXRow + 8);
+      if (row < kTileY) A[0] = as_bf16x8(*reinterpret_cast<const uint4*>(grow + row * kTileX));
+      const uint4 q = *reinterpret_cast<const uint4*>(xrow + row * kXRow);
+      const unsigned e = *reinterpret_cast<const unsigned*>(xrow + row * kXRow + 8);
       const bf16x8 B[3] = {as_bf16x8(q),
                            as_bf16x8(make_uint4(__builtin_amdgcn_alignbit(q.y, q.x, 16), __builtin_amdgcn_alignbit(q.z, q.y, 16),
                                                 __builtin_amdgcn_alignbit(q.w, q.z, 16), __builtin_amdgcn_alignbit(e, q.w, 16))),
                            as_bf16x8(make_uint4(q.y, q.z, q.w, e))};
 #pragma unroll
       for (int ky = 0; ky < 3; ++ky)
-        if (xr >= ky && xr - ky < kTileY) {
+        if (row >= ky && row - ky < kTileY) {
 #pragma unroll
           for (int kx = 0; kx < 3; ++kx)
             acc[3 * ky + kx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[ky], B[kx], acc[3 * ky + kx], 0, 0, 0);
         }
     }
     {  // bias gradient: thread (channel tid % 32, row tid / 32) sums one tile row
-      const uint16_t* row = gs + channel_at(threadIdx.x & (kC - 1), kGCh) + (threadIdx.x >> 5) * kTileX;
+      const uint16_t* line = gs + channel_at(threadIdx.x & (kC - 1), kGCh) + (threadIdx.x >> 5) * kTileX;
       float s = 0.0f;
 #pragma unroll
       for (int c = 0; c < kTileX; c += 8) {
-        const uint4 q = *reinterpret_cast<const uint4*>(row + c);
+        const uint4 q = *reinterpret_cast<const uint4*>(line + c);
         const uint16_t* v = reinterpret_cast<const uint16_t*>(&q);
 #pragma unroll
         for (int k = 0; k < 8; ++k) s += bf2f(v[k]);
@@ -686,27 +715,10 @@ __global__ __launch_bounds__(64 * kRedWaves) void wgrad_reduce_kernel(const floa
   }
 }
 
-// network input: channel 0 = z, channel 1 = sigma, the rest zero
-__global__ void prep_kernel(const uint16_t* __restrict__ noisy, const float* __restrict__ sigma, int N, int HW,
-                            uint16_t* __restrict__ x0) {
-  const size_t total = static_cast<size_t>(N) * HW;
-  for (size_t p = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; p < total;
-       p += static_cast<size_t>(gridDim.x) * blockDim.x) {
-    const int n = static_cast<int>(p / HW);
-    uint4* d = reinterpret_cast<uint4*>(x0 + p * kC);
-    const uint32_t z = f2bf(static_cast<float>(noisy[p]) * (1.0f / 65535.0f));
-    const uint32_t s = f2bf(sigma[n]);
-    d[0] = make_uint4(z | (s << 16), 0, 0, 0);
-    d[1] = make_uint4(0, 0, 0, 0);
-    d[2] = make_uint4(0, 0, 0, 0);
-    d[3] = make_uint4(0, 0, 0, 0);
-  }
-}
-
 // loss gradient of the (per-image weighted) mean squared error:
 // dL/df = -2 w_b (pilot - target) / n with w_b = weight[pixel / hw] (1 if no
-// weights), written as channel 0 of a 32-channel bf16 tensor; per-block
-// partial sums of the weighted squared error in double.
+// weights), one bf16 per pixel; per-block partial sums of the weighted squared
+// error in double.
 __global__ __launch_bounds__(256) void loss_kernel(const float* __restrict__ pilot, const float* __restrict__ target,
                                                    const float* __restrict__ weight, size_t hw, size_t n,
                                                    uint16_t* __restrict__ g, double* __restrict__ part) {
@@ -718,11 +730,7 @@ __global__ __launch_bounds__(256) void loss_kernel(const float* __restrict__ pil
     const float w = weight ? weight[p / hw] : 1.0f;
     const float d = pilot[p] - target[p];
     s += static_cast<double>(w) * d * d;
-    uint4* dst = reinterpret_cast<uint4*>(g + p * kC);
-    dst[0] = make_uint4(f2bf(scale * w * d), 0, 0, 0);
-    dst[1] = make_uint4(0, 0, 0, 0);
-    dst[2] = make_uint4(0, 0, 0, 0);
-    dst[3] = make_uint4(0, 0, 0, 0);
+    g[p] = f2bf(scale * w * d);
   }
   red[threadIdx.x] = s;
   __syncthreads();
@@ -798,14 +806,6 @@ hipError_t launch_pilot_pack(const float* master, uint16_t* wf, uint16_t* wb, fl
   return hipGetLastError();
 }
 
-hipError_t launch_pilot_prep(const uint16_t* noisy, const float* sigma, int N, int H, int W, uint16_t* x0,
-                             hipStream_t st) {
-  const size_t total = static_cast<size_t>(N) * H * W;
-  const unsigned blocks = static_cast<unsigned>(std::min<size_t>((total + 255) / 256, 16384));
-  hipLaunchKernelGGL(prep_kernel, dim3(blocks), dim3(256), 0, st, noisy, sigma, N, H * W, x0);
-  return hipGetLastError();
-}
-
 int pilot_fused_tiles(int N, int H, int W) { return fused_tiles(N, H, W); }
 
 hipError_t launch_pilot_infer_fused(const uint16_t* noisy, const float* sigma, const uint16_t* wf, const float* bias,
@@ -817,27 +817,31 @@ hipError_t launch_pilot_infer_fused(const uint16_t* noisy, const float* sigma, c
   return hipGetLastError();
 }
 
-hipError_t launch_pilot_conv(int mode, const uint16_t* in, const uint16_t* w, const float* bias, const uint16_t* mask,
+hipError_t launch_pilot_conv(int layer, const uint16_t* in, const float* sigma, const uint16_t* w, const float* bias,
                              uint16_t* out, const uint16_t* noisy, float* pilot_f32, uint16_t* pilot_u16, int N,
                              int H, int W, int grid_cap, hipStream_t st) {
-  const int items = conv_items(N, H, W);
-  const int grid = std::max(1, std::min(items, grid_cap));
-  switch (mode) {
-    case 0:
-      hipLaunchKernelGGL(conv_kernel<0>, dim3(grid), dim3(256), 0, st, in, w, bias, mask, out, noisy, pilot_f32,
-                         pilot_u16, N, H, W);
-      break;
-    case 1:
-      hipLaunchKernelGGL(conv_kernel<1>, dim3(grid), dim3(256), 0, st, in, w, bias, mask, out, noisy, pilot_f32,
-                         pilot_u16, N, H, W);
-      break;
-    case 2:
-      hipLaunchKernelGGL(conv_kernel<2>, dim3(grid), dim3(256), 0, st, in, w, bias, mask, out, noisy, pilot_f32,
-                         pilot_u16, N, H, W);
-      break;
-    default:
-      return hipErrorInvalidValue;
-  }
+  const int grid = std::max(1, std::min(conv_items(N, H, W), grid_cap));
+  if (layer == 0)
+    hipLaunchKernelGGL((conv_kernel<0, kInput>), dim3(grid), dim3(256), 0, st, in, sigma, w, bias, nullptr, out, noisy,
+                       pilot_f32, pilot_u16, N, H, W);
+  else if (layer < kPilotLayers - 1)
+    hipLaunchKernelGGL((conv_kernel<0, kAct>), dim3(grid), dim3(256), 0, st, in, sigma, w, bias, nullptr, out, noisy,
+                       pilot_f32, pilot_u16, N, H, W);
+  else
+    hipLaunchKernelGGL((conv_kernel<1, kAct>), dim3(grid), dim3(256), 0, st, in, sigma, w, bias, nullptr, out, noisy,
+                       pilot_f32, pilot_u16, N, H, W);
+  return hipGetLastError();
+}
+
+hipError_t launch_pilot_dgrad(int layer, const uint16_t* g, const uint16_t* w, const uint16_t* mask, uint16_t* out,
+                              int N, int H, int W, int grid_cap, hipStream_t st) {
+  const int grid = std::max(1, std::min(conv_items(N, H, W), grid_cap));
+  if (layer == kPilotLayers - 1)
+    hipLaunchKernelGGL((conv_kernel<2, kLossGrad>), dim3(grid), dim3(256), 0, st, g, nullptr, w, nullptr, mask, out,
+                       nullptr, nullptr, nullptr, N, H, W);
+  else
+    hipLaunchKernelGGL((conv_kernel<2, kAct>), dim3(grid), dim3(256), 0, st, g, nullptr, w, nullptr, mask, out, nullptr,
+                       nullptr, nullptr, N, H, W);
   return hipGetLastError();
 }
 
@@ -848,9 +852,14 @@ hipError_t launch_pilot_loss(const float* pilot, const float* target, const floa
   return hipGetLastError();
 }
 
-hipError_t launch_pilot_wgrad(const uint16_t* x, const uint16_t* g, int N, int H, int W, int grid, float* partial,
-                              int layer, float* grad_layer, hipStream_t st) {
-  hipLaunchKernelGGL(wgrad_kernel, dim3(grid), dim3(256), 0, st, x, g, N, H, W, partial);
+hipError_t launch_pilot_wgrad(const uint16_t* x, const float* sigma, const uint16_t* g, int N, int H, int W, int grid,
+                              float* partial, int layer, float* grad_layer, hipStream_t st) {
+  if (layer == 0)
+    hipLaunchKernelGGL((wgrad_kernel<kInput, kAct>), dim3(grid), dim3(256), 0, st, x, sigma, g, N, H, W, partial);
+  else if (layer < kPilotLayers - 1)
+    hipLaunchKernelGGL((wgrad_kernel<kAct, kAct>), dim3(grid), dim3(256), 0, st, x, sigma, g, N, H, W, partial);
+  else
+    hipLaunchKernelGGL((wgrad_kernel<kAct, kLossGrad>), dim3(grid), dim3(256), 0, st, x, sigma, g, N, H, W, partial);
   const int ci_n = pilot_cin(layer), co_n = pilot_cout(layer);
   const int n_out = kTaps * ci_n * co_n + co_n;
   hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((n_out + 63) / 64), dim3(64 * kRedWaves), 0, st, partial, grid, ci_n,
