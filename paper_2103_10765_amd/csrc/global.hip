@@ -32,6 +32,7 @@ namespace gbm3d {
 namespace {
 
 constexpr int kGlThreads = 256;
+constexpr int kAggThreads = 512;
 constexpr int kMaxSearch = 39;
 constexpr double kKeyInfG = __builtin_huge_val();
 
@@ -62,11 +63,14 @@ struct TileSmem {
   double reg[kRegion * kPitch];          // search region, pixel values
   double keys[kMaxSearch * kMaxSearch];  // dist * 2048 + rank (+inf for the reference)
   double part[kGlThreads / kWave];       // per-wave partial sums of the reference norm
+  double least[kGlThreads];              // smallest key of each thread, then of each of 64 groups
+  double bound;
+  int count;                             // keys up to the bound
 };
 
 template <int N, int K>
 // grid: (tiles, translations)
-__global__ __launch_bounds__(kGlThreads) void gl_match_kernel(const uint16_t* __restrict__ noisy,
+__global__ __launch_bounds__(kGlThreads, 4) void gl_match_kernel(const uint16_t* __restrict__ noisy,
                                                               const uint16_t* __restrict__ shifted, Shifts sh, int H,
                                                               int W, int S, int16_t* __restrict__ idx) {
   using Sm = TileSmem<N>;
@@ -137,29 +141,25 @@ __global__ __launch_bounds__(kGlThreads) void gl_match_kernel(const uint16_t* __
     double d[kDx];
 #pragma unroll
     for (int c = 0; c < kDx; ++c) d[c] = 0.0;
+    double col[kSeg];  // column sums of squares over the same rows, for the candidates' norms
+#pragma unroll
+    for (int b = 0; b < kSeg; ++b) col[b] = 0.0;
 #pragma unroll 1
     for (int a = 0; a < N; ++a) {
       const double* cr = sm.reg + (dy + a) * P + dx0;
       const double* rr = sm.reg + (R + a) * P + R;
       double seg[kSeg];
 #pragma unroll
-      for (int b = 0; b < kSeg; ++b) seg[b] = cr[b];
+      for (int b = 0; b < kSeg; ++b) {
+        seg[b] = cr[b];
+        col[b] = fma(seg[b], seg[b], col[b]);
+      }
 #pragma unroll
       for (int b = 0; b < N; ++b) {
         const double rv = rr[b];
 #pragma unroll
         for (int c = 0; c < kDx; ++c) d[c] = fma(rv, seg[b + c], d[c]);
       }
-    }
-    // the candidates' norms: column sums of squares over the same rows
-    double col[kSeg];
-#pragma unroll
-    for (int b = 0; b < kSeg; ++b) col[b] = 0.0;
-#pragma unroll 1
-    for (int a = 0; a < N; ++a) {
-      const double* cr = sm.reg + (dy + a) * P + dx0;
-#pragma unroll
-      for (int b = 0; b < kSeg; ++b) col[b] = fma(cr[b], cr[b], col[b]);
     }
     double cn = 0.0;
 #pragma unroll
@@ -176,45 +176,53 @@ __global__ __launch_bounds__(kGlThreads) void gl_match_kernel(const uint16_t* __
     }
   }
   __syncthreads();
-  // the K-1 smallest keys (keys are unique): each lane sorts its own keys,
-  // the lanes of a wave merge their lists pairwise along a butterfly (every
-  // lane ends with the wave's K-1 smallest), and wave 0 merges the four
-  // waves' lists the same way
+  // The K-1 smallest keys (keys are unique).  Of 64 groups of keys (lane l of
+  // every wave: displacements 64 apart) the (K-1)-th smallest group minimum
+  // bounds them; the few keys up to it are ranked by counting.  (Sorted lists
+  // merged along a butterfly took more vector instructions than the
+  // distances.)
   constexpr int kPer = (kMaxSearch * kMaxSearch + kGlThreads - 1) / kGlThreads;
-  constexpr int kSort = pow2_ceil(kPer);
-  double list[L];
-  {
-    double mine[kSort];
+  double mine[kPer];
+  double least = kKeyInfG;
 #pragma unroll
-    for (int m = 0; m < kSort; ++m) {
-      const int r = threadIdx.x + m * kGlThreads;
-      mine[m] = (m < kPer && r < S2) ? sm.keys[r] : kKeyInfG;
-    }
-    bitonic_sort<kSort>(mine);
-#pragma unroll
-    for (int i = 0; i < L; ++i) list[i] = i < kSort ? mine[i] : kKeyInfG;
+  for (int m = 0; m < kPer; ++m) {
+    const int r = threadIdx.x + m * kGlThreads;
+    mine[m] = r < S2 ? sm.keys[r] : kKeyInfG;
+    least = fmin(least, mine[m]);
   }
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) merge_sorted<L>(list, [&](int j) { return shfl_xor_double(list[j], off); });
+  sm.least[threadIdx.x] = least;
+  if (threadIdx.x == 0) sm.count = 0;
   __syncthreads();  // every key has been read; the key array is reused below
-  double* wl = sm.keys;  // [4][L]
-  if (lane == 0) {
-#pragma unroll
-    for (int i = 0; i < L; ++i) wl[wave * L + i] = list[i];
-  }
-  __syncthreads();
   if (wave == 0) {
 #pragma unroll
-    for (int i = 0; i < L; ++i) list[i] = lane < kGlThreads / kWave ? wl[lane * L + i] : kKeyInfG;
-#pragma unroll
-    for (int off = 1; off < kGlThreads / kWave; off <<= 1)
-      merge_sorted<L>(list, [&](int j) { return shfl_xor_double(list[j], off); });
-    if (lane == 0) {
-      int16_t* out = idx + static_cast<size_t>(g) * K;
-      out[0] = static_cast<int16_t>(S2 / 2);
-#pragma unroll
-      for (int i = 0; i < L; ++i) out[i + 1] = key_rank(list[i]);
+    for (int w = 1; w < kGlThreads / kWave; ++w) least = fmin(least, sm.least[w * kWave + lane]);
+    wave_lds_sync();
+    sm.least[lane] = least;
+    wave_lds_sync();
+    int below = 0;
+#pragma unroll 8
+    for (int j = 0; j < kWave; ++j) {
+      const double o = sm.least[j];
+      below += o < least || (o == least && j < lane) ? 1 : 0;
     }
+    if (below == L - 1) sm.bound = least;
+  }
+  __syncthreads();
+  const double bound = sm.bound;
+  double* near = sm.keys;
+#pragma unroll
+  for (int m = 0; m < kPer; ++m)
+    if (mine[m] <= bound && mine[m] < kKeyInfG) near[atomicAdd(&sm.count, 1)] = mine[m];
+  __syncthreads();
+  const int n_near = sm.count;
+  int16_t* out = idx + static_cast<size_t>(g) * K;
+  if (threadIdx.x == 0) out[0] = static_cast<int16_t>(S2 / 2);
+  for (int f = threadIdx.x; f < n_near; f += kGlThreads) {
+    const double key = near[f];
+    int below = 0;
+#pragma unroll 4
+    for (int j = 0; j < n_near; ++j) below += near[j] < key ? 1 : 0;
+    if (below < L) out[1 + below] = key_rank(key);
   }
 }
 
@@ -243,16 +251,20 @@ __global__ void gl_mirror_pad_kernel(const uint16_t* __restrict__ img, int H, in
   }
 }
 
-// slice ti of shifted: S_t of the image, img[(y - t) mod H][(x - t) mod W],
-// for every translation t = sh.t[ti] other than 0; grid (g, translations)
-__global__ void gl_roll_kernel(const uint16_t* __restrict__ img, int H, int W, Shifts sh,
-                               uint16_t* __restrict__ shifted) {
+// What the launches after it need: slice ti of shifted, S_t of the image
+// (img[(y - t) mod H][(x - t) mod W]), for every translation t = sh.t[ti] other
+// than 0, and the translation's aggregation sums cleared; grid (g, translations)
+__global__ void gl_prepare_kernel(const uint16_t* __restrict__ img, int H, int W, Shifts sh,
+                                  uint16_t* __restrict__ shifted, unsigned long long* __restrict__ sums) {
   const int t = sh.t[blockIdx.y];
-  if (t == 0) return;
   const size_t n = static_cast<size_t>(H) * W;
   uint16_t* out = shifted + blockIdx.y * n;
+  unsigned long long* zero = sums + blockIdx.y * 2 * n;
   for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n;
        i += static_cast<size_t>(gridDim.x) * blockDim.x) {
+    zero[i] = 0;
+    zero[n + i] = 0;
+    if (t == 0) continue;
     const int y = static_cast<int>(i / W), x = static_cast<int>(i - static_cast<size_t>(y) * W);
     out[i] = img[static_cast<size_t>(pmod(y - t, H)) * W + pmod(x - t, W)];
   }
@@ -288,12 +300,12 @@ __device__ __forceinline__ int wrap1(int j, int L) { return j < 0 ? j + L : (j >
 // Coefficient tiles of a workgroup: TY x TX per band of y and x, one pair of
 // slices along k.  The finest level takes 16 x 32; the coarser levels, whose
 // regions are 8 and 64 times smaller, take 8 x 16 to keep enough workgroups.
-template <int TY, int TX>
+template <int TY, int TX, int THREADS>
 struct LevelTile {
   static constexpr int kFwdRows = 2 * TY + 8, kFwdCols = 2 * TX + 8;  // forward input window
   static constexpr int kInvRows = 2 * TY + 4, kInvCols = 2 * TX + 4;  // inverse input window
-  static constexpr int kFwdIters = (kFwdRows * kFwdCols + kGlThreads - 1) / kGlThreads;
-  static constexpr int kInvIters = (kInvRows * kInvCols + kGlThreads - 1) / kGlThreads;
+  static constexpr int kFwdIters = (kFwdRows * kFwdCols + THREADS - 1) / THREADS;
+  static constexpr int kInvIters = (kInvRows * kInvCols + THREADS - 1) / THREADS;
 };
 
 // One forward level over the region [0, Lk) x [0, Ly) x [0, Lx) of a
@@ -306,14 +318,14 @@ struct LevelTile {
 // Every (translation ti, cycle spin h) has its own pair of volumes, volume
 // v = ti spins + h at v K H W elements into src and dst.
 // grid: (ceil(Lx / 2 / TX), ceil(Ly / 2 / TY), Lk / 2 * volumes), z = v Lk / 2 + kp
-template <int N, int K, bool GATHER, int TY, int TX>
-__global__ __launch_bounds__(kGlThreads) void gl_forward_kernel(const float* __restrict__ src,
+template <int N, int K, bool GATHER, int TY, int TX, int THREADS>
+__global__ __launch_bounds__(THREADS) void gl_forward_kernel(const float* __restrict__ src,
                                                                  const uint16_t* __restrict__ noisy,
                                                                  const uint16_t* __restrict__ shifted, Shifts sh,
                                                                  int spins, const int16_t* __restrict__ idx, int S,
                                                                  float* __restrict__ dst, int H, int W, int Lk, int Ly,
                                                                  int Lx, float tau) {
-  using T = LevelTile<TY, TX>;
+  using T = LevelTile<TY, TX, THREADS>;
   // input window: rows 2 cy0 - 4 .. 2 cy0 + 2 TY + 3, the same for columns;
   // columns stored split by parity so the strided filter taps read
   // consecutive LDS words
@@ -323,7 +335,7 @@ __global__ __launch_bounds__(kGlThreads) void gl_forward_kernel(const float* __r
   // per window row / column: the volume coordinate (with GATHER: of the
   // unspun volume V, and which of the window's tile rows / columns holds it)
   constexpr int kTileRows = (kRows + 2 * N - 2) / N, kTileCols = (kCols + 2 * N - 2) / N;
-  static_assert(kRows + kCols + 2 * kTileRows * kTileCols <= kGlThreads, "one table entry per thread");
+  static_assert(kRows + kCols + 2 * kTileRows * kTileCols <= THREADS, "one table entry per thread");
   __shared__ int row_at[kRows], col_at[kCols], row_lt[GATHER ? kRows : 1], col_lt[GATHER ? kCols : 1];
   // with GATHER: the match displacement (dy, dx) of slices 2 kp + j of every
   // tile the window touches
@@ -376,7 +388,7 @@ __global__ __launch_bounds__(kGlThreads) void gl_forward_kernel(const float* __r
     // V[k'][ys][xs] = z at (ys, xs) + the k'-th match displacement of its tile
 #pragma unroll
     for (int it = 0; it < T::kFwdIters; ++it) {
-      const int e = tid + it * kGlThreads;
+      const int e = tid + it * THREADS;
       if (e < kRows * kCols) {
         const int r = e / kCols, col = e - r * kCols;
         const int ys = row_at[r], xs = col_at[col], lr = row_lt[r], lc = col_lt[col];
@@ -391,7 +403,7 @@ __global__ __launch_bounds__(kGlThreads) void gl_forward_kernel(const float* __r
     const float* s1 = s0 + hw;
 #pragma unroll
     for (int it = 0; it < T::kFwdIters; ++it) {
-      const int e = tid + it * kGlThreads;
+      const int e = tid + it * THREADS;
       if (e < kRows * kCols) {
         const int r = e / kCols, col = e - r * kCols;
         const size_t o = static_cast<size_t>(row_at[r]) * W + col_at[col];
@@ -402,7 +414,7 @@ __global__ __launch_bounds__(kGlThreads) void gl_forward_kernel(const float* __r
   }
 #pragma unroll
   for (int it = 0; it < T::kFwdIters; ++it) {
-    const int e = tid + it * kGlThreads;
+    const int e = tid + it * THREADS;
     if (e < kRows * kCols) {
       const int r = e / kCols, col = e - r * kCols;
       in_s[0][r][col & 1][col >> 1] = (v0[it] + v1[it]) * c;
@@ -411,7 +423,7 @@ __global__ __launch_bounds__(kGlThreads) void gl_forward_kernel(const float* __r
   }
   __syncthreads();
   // along x: window column 2 j + i is even[j + i/2] or odd[j + (i-1)/2]
-  for (int e = tid; e < 2 * kRows * TX; e += kGlThreads) {
+  for (int e = tid; e < 2 * kRows * TX; e += THREADS) {
     const int j = e % TX, r = (e / TX) % kRows, kb = e / (TX * kRows);
     const float* ev = in_s[kb][r][0];
     const float* od = in_s[kb][r][1];
@@ -426,7 +438,7 @@ __global__ __launch_bounds__(kGlThreads) void gl_forward_kernel(const float* __r
   }
   __syncthreads();
   // along y, then out to the bands
-  for (int e = tid; e < 2 * TY * 2 * TX; e += kGlThreads) {
+  for (int e = tid; e < 2 * TY * 2 * TX; e += THREADS) {
     const int cc = e % (2 * TX), i = (e / (2 * TX)) % TY, kb = e / (2 * TX * TY);
     const int xb = cc >= TX ? 1 : 0;
     const int cy = cy0 + i, cx = cx0 + cc - xb * TX;
@@ -448,11 +460,11 @@ __global__ __launch_bounds__(kGlThreads) void gl_forward_kernel(const float* __r
 // (synthesis along x, then y, then the Haar pair along k) at the same
 // positions of dst.  Volumes and grid as in the forward kernel (z = v Lk / 2
 // + kp over every volume v).
-template <int K, int TY, int TX>
-__global__ __launch_bounds__(kGlThreads) void gl_inverse_kernel(const float* __restrict__ src,
+template <int K, int TY, int TX, int THREADS>
+__global__ __launch_bounds__(THREADS) void gl_inverse_kernel(const float* __restrict__ src,
                                                                  float* __restrict__ dst, int H, int W, int Lk, int Ly,
                                                                  int Lx) {
-  using T = LevelTile<TY, TX>;
+  using T = LevelTile<TY, TX, THREADS>;
   // window rows: low band cy0 .. cy0 + TY - 1, then high band cy0 - 2 ..
   // cy0 + TY + 1 (the synthesis taps reach two coefficients either side);
   // the same for columns
@@ -481,7 +493,7 @@ __global__ __launch_bounds__(kGlThreads) void gl_inverse_kernel(const float* __r
     float v0[T::kInvIters], v1[T::kInvIters];
 #pragma unroll
     for (int it = 0; it < T::kInvIters; ++it) {
-      const int e = tid + it * kGlThreads;
+      const int e = tid + it * THREADS;
       if (e < kRows * kCols) {
         const int r = e / kCols, col = e - r * kCols;
         const size_t o = static_cast<size_t>(row_at[r]) * W + col_at[col];
@@ -491,7 +503,7 @@ __global__ __launch_bounds__(kGlThreads) void gl_inverse_kernel(const float* __r
     }
 #pragma unroll
     for (int it = 0; it < T::kInvIters; ++it) {
-      const int e = tid + it * kGlThreads;
+      const int e = tid + it * THREADS;
       if (e < kRows * kCols) {
         const int r = e / kCols, col = e - r * kCols;
         in_s[0][r][col] = v0[it];
@@ -500,7 +512,7 @@ __global__ __launch_bounds__(kGlThreads) void gl_inverse_kernel(const float* __r
     }
   }
   __syncthreads();
-  for (int e = tid; e < 2 * kRows * TX; e += kGlThreads) {
+  for (int e = tid; e < 2 * kRows * TX; e += THREADS) {
     const int j = e % TX, r = (e / TX) % kRows, kb = e / (TX * kRows);
     const float* row = in_s[kb][r];
     const float a = c * row[j];
@@ -515,7 +527,7 @@ __global__ __launch_bounds__(kGlThreads) void gl_inverse_kernel(const float* __r
     xs[kb][r][2 * j + 1] = od;
   }
   __syncthreads();
-  for (int e = tid; e < TY * 2 * TX; e += kGlThreads) {
+  for (int e = tid; e < TY * 2 * TX; e += THREADS) {
     const int cc = e % (2 * TX), i = e / (2 * TX);
     const int y = 2 * (cy0 + i), x = 2 * cx0 + cc;
     if (y >= Ly || x >= Lx) continue;
@@ -541,12 +553,6 @@ __global__ __launch_bounds__(kGlThreads) void gl_inverse_kernel(const float* __r
   }
 }
 
-__global__ void gl_zero_kernel(unsigned long long* __restrict__ p, size_t n) {
-  for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<size_t>(gridDim.x) * blockDim.x)
-    p[i] = 0;
-}
-
 // One workgroup per tile.  u is the average over the cycle spins h of the
 // filtered spun volumes (spin h at vol + h K H W) with each spin undone:
 // u[k][y][x] = (1 / spins) sum_h vol_h[(k + h) mod K][(y + h) mod H][(x + h) mod W].
@@ -560,15 +566,19 @@ template <int N, int K>
 // grid: (tiles, translations); translation ti reads volumes ti spins ..
 // ti spins + spins - 1, its matches and its sums (numerators then
 // denominators, 2 H W words per translation).
-__global__ __launch_bounds__(kGlThreads) void gl_aggregate_kernel(const float* __restrict__ vol, int spins,
-                                                                   const int16_t* __restrict__ idx, int H, int W,
-                                                                   int S, float eps,
-                                                                   unsigned long long* __restrict__ sums) {
+__global__ __launch_bounds__(kAggThreads) void gl_aggregate_kernel(const float* __restrict__ vol, int spins,
+                                                                    const int16_t* __restrict__ idx, int H, int W,
+                                                                    int S, float eps,
+                                                                    unsigned long long* __restrict__ sums) {
   constexpr int kVals = N * N * K;
   constexpr int kFoot = (kMaxSearch + N - 1) * (kMaxSearch + N - 1);
+  constexpr int kWaves = kAggThreads / kWave;
   __shared__ float blk[kVals];
-  __shared__ double part[kGlThreads];
-  __shared__ unsigned long long fnum[kFoot], fden[kFoot];
+  __shared__ double part[kWaves];
+  // a cell's denominator is w times the blocks over it
+  __shared__ unsigned long long fnum[kFoot];
+  __shared__ unsigned fcount[kFoot];
+  __shared__ int corner[K];  // first footprint cell of the k-th block
   const size_t hw = static_cast<size_t>(H) * W;
   const int tiles_x = W / N;
   const int g = blockIdx.x;
@@ -579,17 +589,21 @@ __global__ __launch_bounds__(kGlThreads) void gl_aggregate_kernel(const float* _
   idx += static_cast<size_t>(ti) * gridDim.x * K;
   unsigned long long* num = sums + static_cast<size_t>(ti) * 2 * hw;
   unsigned long long* den = num + hw;
-  for (int i = threadIdx.x; i < side * side; i += blockDim.x) {
+  for (int i = threadIdx.x; i < side * side; i += kAggThreads) {
     fnum[i] = 0;
-    fden[i] = 0;
+    fcount[i] = 0;
   }
+  if (threadIdx.x < K) {
+    const int r = idx[static_cast<size_t>(g) * K + threadIdx.x];
+    corner[threadIdx.x] = r / S * side + r % S;
+  }
+  // all of a spin's loads in flight at once (kVals is a multiple of the
+  // block size)
+  static_assert(kVals % kAggThreads == 0, "whole rounds of the block");
+  constexpr int kIt = kVals / kAggThreads;
+  float acc[kIt];
   {
-    // all of a spin's loads in flight at once (kVals is a multiple of the
-    // block size)
-    static_assert(kVals % kGlThreads == 0, "whole rounds of the block");
-    constexpr int kIt = kVals / kGlThreads;
     const float scale = 1.0f / static_cast<float>(spins);
-    float acc[kIt];
 #pragma unroll
     for (int it = 0; it < kIt; ++it) acc[it] = 0.0f;
     for (int h = 0; h < spins; ++h) {
@@ -597,7 +611,7 @@ __global__ __launch_bounds__(kGlThreads) void gl_aggregate_kernel(const float* _
       float v[kIt];
 #pragma unroll
       for (int it = 0; it < kIt; ++it) {
-        const int i = threadIdx.x + it * kGlThreads;
+        const int i = threadIdx.x + it * kAggThreads;
         const int k = i / (N * N), a = (i / N) % N, b = i % N;
         v[it] = vh[static_cast<size_t>(wrap1(k + h, K)) * hw + static_cast<size_t>(wrap1(y0 + a + h, H)) * W +
                    wrap1(x0 + b + h, W)];
@@ -606,42 +620,46 @@ __global__ __launch_bounds__(kGlThreads) void gl_aggregate_kernel(const float* _
       for (int it = 0; it < kIt; ++it) acc[it] += scale * v[it];
     }
 #pragma unroll
-    for (int it = 0; it < kIt; ++it) blk[threadIdx.x + it * kGlThreads] = acc[it];
+    for (int it = 0; it < kIt; ++it) blk[threadIdx.x + it * kAggThreads] = acc[it];
   }
   __syncthreads();
   double tv = 0.0;
-  for (int i = threadIdx.x; i < kVals; i += blockDim.x) {
+#pragma unroll
+  for (int it = 0; it < kIt; ++it) {
+    const int i = threadIdx.x + it * kAggThreads;
     const int k = i / (N * N), a = (i / N) % N, b = i % N;
-    const float v = blk[i];
     float s = 0.0f;
-    if (k + 1 < K) s += fabsf(blk[i + N * N] - v);
-    if (a + 1 < N) s += fabsf(blk[i + N] - v);
-    if (b + 1 < N) s += fabsf(blk[i + 1] - v);
+    if (k + 1 < K) s += fabsf(blk[i + N * N] - acc[it]);
+    if (a + 1 < N) s += fabsf(blk[i + N] - acc[it]);
+    if (b + 1 < N) s += fabsf(blk[i + 1] - acc[it]);
     tv += s;
   }
-  part[threadIdx.x] = tv;
+#pragma unroll
+  for (int off = kWave / 2; off >= 1; off >>= 1) tv += shfl_xor_double(tv, off);
+  if (threadIdx.x % kWave == 0) part[threadIdx.x / kWave] = tv;
   __syncthreads();
-  for (int s = kGlThreads / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
-    __syncthreads();
-  }
-  const float w = eps / (static_cast<float>(part[0]) + eps);
+  tv = part[0];
+#pragma unroll
+  for (int i = 1; i < kWaves; ++i) tv += part[i];
+  const float w = eps / (static_cast<float>(tv) + eps);
   const unsigned long long wf = static_cast<unsigned long long>(to_fixed(w));
-  for (int i = threadIdx.x; i < kVals; i += blockDim.x) {
+#pragma unroll
+  for (int it = 0; it < kIt; ++it) {
+    const int i = threadIdx.x + it * kAggThreads;
     const int k = i / (N * N), a = (i / N) % N, b = i % N;
-    const int r = idx[static_cast<size_t>(g) * K + k];
-    const int f = (r / S + a) * side + r % S + b;  // footprint cell of (dy + R + a, dx + R + b)
-    atomicAdd(fnum + f, static_cast<unsigned long long>(to_fixed(w * blk[i])));
-    atomicAdd(fden + f, wf);
+    const int f = corner[k] + a * side + b;  // footprint cell of (dy + R + a, dx + R + b)
+    atomicAdd(fnum + f, static_cast<unsigned long long>(to_fixed(w * acc[it])));
+    atomicAdd(fcount + f, 1u);
   }
   __syncthreads();
   const int R = S / 2;
-  for (int i = threadIdx.x; i < side * side; i += blockDim.x) {
-    if (fden[i] == 0) continue;
+  for (int i = threadIdx.x; i < side * side; i += kAggThreads) {
+    const unsigned c = fcount[i];
+    if (c == 0) continue;
     const int fy = i / side, fx = i - fy * side;
-    const size_t o = static_cast<size_t>(wrap(y0 - R + fy, H)) * W + wrap(x0 - R + fx, W);
+    const size_t o = static_cast<size_t>(wrap1(y0 - R + fy, H)) * W + wrap1(x0 - R + fx, W);
     __hip_atomic_fetch_add(num + o, fnum[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_fetch_add(den + o, fden[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(den + o, wf * c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -688,7 +706,8 @@ hipError_t global_nk(const GlobalJob& j, hipStream_t st) {
   for (int i = 0; i < 4; ++i) sh.t[i] = i < j.n_shifts ? j.shifts[i] : 0;
   const int T = j.n_shifts, C = j.cycles, V = T * C;
   // every translation and cycle spin in the same launches
-  hipLaunchKernelGGL(gl_roll_kernel, dim3(grid_for(hw), T), dim3(kGlThreads), 0, st, j.noisy, H, W, sh, j.shifted);
+  hipLaunchKernelGGL(gl_prepare_kernel, dim3(grid_for(hw), T), dim3(kGlThreads), 0, st, j.noisy, H, W, sh, j.shifted,
+                     j.num);
   hipLaunchKernelGGL((gl_match_kernel<N, K>), dim3(tiles, T), dim3(kGlThreads), 0, st, j.noisy, j.shifted, sh, H, W,
                      j.search, j.idx);
   // forward level l writes buf[l & 1]; the next level reads only the
@@ -700,24 +719,23 @@ hipError_t global_nk(const GlobalJob& j, hipStream_t st) {
     const int Lk = K >> l, Ly = H >> l, Lx = W >> l;
     const float tau = j.sigma * (j.ht_a - j.ht_b * static_cast<float>(l + 1));
     if (l == 0)
-      hipLaunchKernelGGL((gl_forward_kernel<N, K, true, 16, 32>), level_grid(Lk, Ly, Lx, 16, 32, V), dim3(kGlThreads),
+      hipLaunchKernelGGL((gl_forward_kernel<N, K, true, 16, 32, 512>), level_grid(Lk, Ly, Lx, 16, 32, V), dim3(512),
                          0, st, nullptr, j.noisy, j.shifted, sh, C, j.idx, j.search, buf[0], H, W, Lk, Ly, Lx, tau);
     else
-      hipLaunchKernelGGL((gl_forward_kernel<N, K, false, 8, 16>), level_grid(Lk, Ly, Lx, 8, 16, V), dim3(kGlThreads),
+      hipLaunchKernelGGL((gl_forward_kernel<N, K, false, 8, 16, 256>), level_grid(Lk, Ly, Lx, 8, 16, V), dim3(256),
                          0, st, buf[(l - 1) & 1], nullptr, nullptr, sh, C, nullptr, j.search, buf[l & 1], H, W, Lk, Ly,
                          Lx, tau);
   }
   for (int l = j.levels - 1; l >= 0; --l) {
     const int Lk = K >> l, Ly = H >> l, Lx = W >> l;
     if (l == 0)
-      hipLaunchKernelGGL((gl_inverse_kernel<K, 16, 32>), level_grid(Lk, Ly, Lx, 16, 32, V), dim3(kGlThreads), 0, st,
+      hipLaunchKernelGGL((gl_inverse_kernel<K, 16, 32, 512>), level_grid(Lk, Ly, Lx, 16, 32, V), dim3(512), 0, st,
                          buf[0], j.vol_a, H, W, Lk, Ly, Lx);
     else
-      hipLaunchKernelGGL((gl_inverse_kernel<K, 8, 16>), level_grid(Lk, Ly, Lx, 8, 16, V), dim3(kGlThreads), 0, st,
+      hipLaunchKernelGGL((gl_inverse_kernel<K, 8, 16, 256>), level_grid(Lk, Ly, Lx, 8, 16, V), dim3(256), 0, st,
                          buf[l & 1], buf[(l - 1) & 1], H, W, Lk, Ly, Lx);
   }
-  hipLaunchKernelGGL(gl_zero_kernel, dim3(grid_for(2 * hw * T)), dim3(kGlThreads), 0, st, j.num, 2 * hw * T);
-  hipLaunchKernelGGL((gl_aggregate_kernel<N, K>), dim3(tiles, T), dim3(kGlThreads), 0, st, j.vol_a, C, j.idx, H, W,
+  hipLaunchKernelGGL((gl_aggregate_kernel<N, K>), dim3(tiles, T), dim3(kAggThreads), 0, st, j.vol_a, C, j.idx, H, W,
                      j.search, eps, j.num);
   hipLaunchKernelGGL(gl_normalize_kernel, dim3(grid_for(hw)), dim3(kGlThreads), 0, st, j.num, H, W, sh, j.out);
   return hipGetLastError();
