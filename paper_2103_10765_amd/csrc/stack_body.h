@@ -150,29 +150,37 @@ __device__ __forceinline__ void stack_body(StackLds<PARTS>& lds, int t, const ui
     block_weights[block_weight_entries(H, W) + o] = 0;
   }
   typedef float f32x4v __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) float lds_f32;
   const auto dst = (global_ptr<f32x4v>)(out + (static_cast<size_t>(y) * W + x0) * 64);
+  // (addresses in registers of their own: as sums with the tile's place in LDS
+  // every pair of accesses would have an addition)
+  lds_f32* park = (lds_f32*)(stage[w] + (lane % kPart) * kStagePitch);
+  const lds_f32* from = (const lds_f32*)(stage[w] + (lane >> 4) * kStagePitch + (lane & 15) * 4);
+  asm volatile("" : "+v"(park), "+v"(from));
+  const bool whole = y < H && n_pos == kWave;
 #pragma unroll
   for (int part = 0; part < PARTS; ++part) {
     wave_lds_sync();  // the previous part's reads are done
     if (lane / kPart == part) {
-      float* st = stage[w] + (lane % kPart) * kStagePitch;
 #pragma unroll
       for (int a = 0; a < 8; ++a)
 #pragma unroll
-        for (int b = 0; b < 8; ++b) st[a * 8 + b] = x[a][b];
+        for (int b = 0; b < 8; ++b) park[a * 8 + b] = x[a][b];
     }
     wave_lds_sync();
-    if (y < H) {
-      // in round i lane l stores float4 g = i*64 + l of the part's run
+    // in round i lane l stores float4 i * 64 + l of the part's run, of its
+    // position 4 i + l / 16
+    auto store = [&](int i) {
+      const lds_f32* s = from + i * 4 * kStagePitch;
+      dst[(part * kPart + i * 4) * 16 + lane] = f32x4v{s[0], s[1], s[2], s[3]};
+    };
+    if (whole) {
 #pragma unroll
-      for (int i = 0; i < kPart / 4; ++i) {
-        const int g = i * kWave + lane;
-        const int blk = g >> 4, c = (g & 15) * 4;
-        if (part * kPart + blk < n_pos) {
-          const float* s = stage[w] + blk * kStagePitch + c;
-          dst[part * kPart * 16 + g] = f32x4v{s[0], s[1], s[2], s[3]};
-        }
-      }
+      for (int i = 0; i < kPart / 4; ++i) store(i);
+    } else if (y < H) {
+#pragma unroll
+      for (int i = 0; i < kPart / 4; ++i)
+        if (part * kPart + i * 4 + (lane >> 4) < n_pos) store(i);
     }
   }
 }
