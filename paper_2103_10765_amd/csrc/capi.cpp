@@ -1451,22 +1451,15 @@ int gbm3d_pilot_grad(gbm3d_ctx* ctx, const uint16_t* noisy, const float* target,
           }),
           "pilot loss");
   const PilotWeights pw = pilot_weights(ctx);
-  const int cap = 4 * ctx->n_cu;
   int cur = 0;
   for (int l = gbm3d::kPilotLayers - 1; l >= 0; --l) {
-    HIP_TRY(ctx, timed(ctx, "pilot_wgrad", st, [&] {
-              return gbm3d::launch_pilot_wgrad(x(l), sigma, gbuf[cur], B, H, W, wg_grid, wpart, l,
-                                               grad + gbm3d::pilot_layer_offset(l), st);
+    const uint16_t* w = pw.wb + static_cast<size_t>(l) * 9 * kPilotC * kPilotC;
+    HIP_TRY(ctx, timed(ctx, "pilot_backward", st, [&] {
+              return gbm3d::launch_pilot_backward(l, x(l), sigma, gbuf[cur], w, B, H, W, wg_grid, wpart,
+                                                  grad + gbm3d::pilot_layer_offset(l), gbuf[cur ^ 1], st);
             }),
-            "pilot weight gradient");
-    if (l > 0) {
-      const uint16_t* w = pw.wb + static_cast<size_t>(l) * 9 * kPilotC * kPilotC;
-      HIP_TRY(ctx, timed(ctx, "pilot_dgrad", st, [&] {
-                return gbm3d::launch_pilot_dgrad(l, gbuf[cur], w, x(l), gbuf[cur ^ 1], B, H, W, cap, st);
-              }),
-              "pilot input gradient");
-      cur ^= 1;
-    }
+            "pilot backward");
+    cur ^= 1;
   }
   return GBM3D_OK;
 }

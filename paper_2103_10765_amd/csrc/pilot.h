@@ -32,10 +32,6 @@ hipError_t launch_pilot_pack(const float* master, uint16_t* wf, uint16_t* wb, fl
 hipError_t launch_pilot_conv(int layer, const uint16_t* in, const float* sigma, const uint16_t* w, const float* bias,
                              uint16_t* out, const uint16_t* noisy, float* pilot_f32, uint16_t* pilot_u16, int N,
                              int H, int W, int grid_cap, hipStream_t st);
-// input gradient of layer > 0 with the ReLU mask of its input; g of the last
-// layer is the loss gradient
-hipError_t launch_pilot_dgrad(int layer, const uint16_t* g, const uint16_t* w, const uint16_t* mask, uint16_t* out,
-                              int N, int H, int W, int grid_cap, hipStream_t st);
 // inference of all six layers in one launch (one 16 x 32 output tile per
 // workgroup at a time, activations in LDS); grid_cap bounds the persistent grid
 int pilot_fused_tiles(int N, int H, int W);
@@ -46,9 +42,12 @@ hipError_t launch_pilot_infer_fused(const uint16_t* noisy, const float* sigma, c
 // (g, one bf16 per pixel)
 hipError_t launch_pilot_loss(const float* pilot, const float* target, const float* weight, size_t hw, size_t n,
                              uint16_t* g, double* part, int n_part, float* loss, hipStream_t st);
-// x and g of the layer as for the two passes above
-hipError_t launch_pilot_wgrad(const uint16_t* x, const float* sigma, const uint16_t* g, int N, int H, int W, int grid,
-                              float* partial, int layer, float* grad_layer, hipStream_t st);
+// weight and bias gradient of a layer and, for layer > 0, its input gradient dx
+// with the ReLU mask of its input; x as for the forward pass, g of the last layer
+// the loss gradient
+hipError_t launch_pilot_backward(int layer, const uint16_t* x, const float* sigma, const uint16_t* g,
+                                 const uint16_t* w, int N, int H, int W, int grid, float* partial, float* grad_layer,
+                                 uint16_t* dx, hipStream_t st);
 hipError_t launch_pilot_adam(float* w, float* m, float* v, const float* g, int n, float lr, float b1, float b2,
                              float eps, int step, hipStream_t st);
 

@@ -9,10 +9,10 @@
 // taps, D[out channel][pixel] += W_tap[out][in] * X[in][pixel shifted by the
 // tap] with v_mfma_f32_16x16x32_bf16 (K = the 32 input channels of one tap),
 // fp32 accumulation, and a fused epilogue (bias + ReLU, or the residual
-// output, or the ReLU mask of the backward pass).  The input-gradient pass is
-// the same kernel with flipped, transposed weights.  The weight gradient is a
-// GEMM over pixels (K = 32 pixels of a tile row per MFMA) into per-workgroup
-// partial sums that a second kernel adds in a fixed order.
+// output).  A layer's backward pass is one kernel: the input gradient is the same
+// convolution with flipped, transposed weights and the ReLU mask, the weight
+// gradient a GEMM over pixels (K = 32 pixels of a tile row per MFMA) into
+// per-workgroup partial sums that a second kernel adds in a fixed order.
 #include <hip/hip_runtime.h>
 
 #include "common.h"
@@ -47,7 +47,7 @@ __host__ __device__ inline int conv_items(int N, int H, int W) {
 // of the u16 image, channel 1 = sigma) or the loss gradient (channel 0, one bf16
 // per pixel).  The last two are expanded to the eights of channels of an
 // activation tensor where a kernel loads them; as such tensors they were 64 MB
-// each for 64 images of 128^2, written once and read twice (95 us of 749 in a
+// each for 64 images of 128^2, written once and read twice (77 us of 749 in a
 // gradient step).
 enum Source { kAct, kInput, kLossGrad };
 
@@ -67,16 +67,22 @@ __device__ __forceinline__ uint4 as_activations(uint4 v, float sigma, int c8) {
   return v;
 }
 
+// v0 as bf16 to out[0 .. 3], v1 to out[16 .. 19]
+__device__ __forceinline__ void store_channels(uint16_t* __restrict__ out, const float (&v0)[4], const float (&v1)[4]) {
+  auto pair = [](float a, float b) { return f2bf(a) | (static_cast<uint32_t>(f2bf(b)) << 16); };
+  *reinterpret_cast<uint2*>(out) = make_uint2(pair(v0[0], v0[1]), pair(v0[2], v0[3]));
+  *reinterpret_cast<uint2*>(out + 16) = make_uint2(pair(v1[0], v1[1]), pair(v1[2], v1[3]));
+}
+
 // ---------------------------------------------------------------------------
 // convolution 32 -> 32, 3x3, zero "same" padding
 // MODE 0: forward, + bias, ReLU, bf16 out
 // MODE 1: forward last layer: f = channel 0 + bias; pilot = z - f (fp32 / u16)
-// MODE 2: input gradient: out = conv * (mask > 0), bf16 out
 // ---------------------------------------------------------------------------
 template <int MODE, Source SRC>
 __global__ __launch_bounds__(256) void conv_kernel(const uint16_t* __restrict__ in, const float* __restrict__ sigma,
                                                    const uint16_t* __restrict__ wpk,
-                                                   const float* __restrict__ bias, const uint16_t* __restrict__ mask,
+                                                   const float* __restrict__ bias,
                                                    uint16_t* __restrict__ out, const uint16_t* __restrict__ noisy,
                                                    float* __restrict__ pilot_f32, uint16_t* __restrict__ pilot_u16,
                                                    int N, int H, int W) {
@@ -132,37 +138,14 @@ __global__ __launch_bounds__(256) void conv_kernel(const uint16_t* __restrict__ 
       const int y = y0 + row, x = x0 + xoff + col;
       if (y < H && x < W) {
         const size_t p = (static_cast<size_t>(n) * H + y) * W + x;
-        if constexpr (MODE == 0 || MODE == 2) {
+        if constexpr (MODE == 0) {
           float v0[4], v1[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            v0[i] = acc0[i];
-            v1[i] = acc1[i];
+            v0[i] = fmaxf(acc0[i] + b0[i], 0.0f);
+            v1[i] = fmaxf(acc1[i] + b1[i], 0.0f);
           }
-          if constexpr (MODE == 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              v0[i] = fmaxf(v0[i] + b0[i], 0.0f);
-              v1[i] = fmaxf(v1[i] + b1[i], 0.0f);
-            }
-          } else {
-            const uint2 m0 = *reinterpret_cast<const uint2*>(mask + p * kC + 4 * grp);
-            const uint2 m1 = *reinterpret_cast<const uint2*>(mask + p * kC + 16 + 4 * grp);
-            const uint16_t* mm0 = reinterpret_cast<const uint16_t*>(&m0);
-            const uint16_t* mm1 = reinterpret_cast<const uint16_t*>(&m1);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              v0[i] = bf2f(mm0[i]) > 0.0f ? v0[i] : 0.0f;
-              v1[i] = bf2f(mm1[i]) > 0.0f ? v1[i] : 0.0f;
-            }
-          }
-          uint2 o0, o1;
-          o0.x = f2bf(v0[0]) | (static_cast<uint32_t>(f2bf(v0[1])) << 16);
-          o0.y = f2bf(v0[2]) | (static_cast<uint32_t>(f2bf(v0[3])) << 16);
-          o1.x = f2bf(v1[0]) | (static_cast<uint32_t>(f2bf(v1[1])) << 16);
-          o1.y = f2bf(v1[2]) | (static_cast<uint32_t>(f2bf(v1[3])) << 16);
-          *reinterpret_cast<uint2*>(out + p * kC + 4 * grp) = o0;
-          *reinterpret_cast<uint2*>(out + p * kC + 16 + 4 * grp) = o1;
+          store_channels(out + p * kC + 4 * grp, v0, v1);
         } else {
           if (grp == 0) {  // channel 0 sits in acc0[0] of lanes 0..15
             const float f = acc0[0] + b0[0];
@@ -525,29 +508,38 @@ __global__ __launch_bounds__(kFThreads) void fused_infer_kernel(const uint16_t* 
 }
 
 // ---------------------------------------------------------------------------
-// weight gradient: dW[t][ci][co] = sum_p x[p + off_t][ci] g[p][co], db[co] = sum_p g[p][co]
-// per-workgroup partials [grid][kWmat + kC]
+// backward pass of a layer
+// weight gradient: dW[t][ci][co] = sum_p x[p + off_t][ci] g[p][co], db[co] = sum_p g[p][co],
+// as per-workgroup partials [grid][kWmat + kC]; with DX also the input gradient
+// dx = (g convolved with the flipped, transposed weights) * (x > 0).
 //
-// The products run over pixels, so both tensors are needed channel-major; a
-// thread loads eight channels of eight pixels of a row, transposes them in
-// registers (32 byte permutes) and stores eight 16-byte runs of pixels.  A wave
-// owns 16 x 16 channels of all nine taps.  It goes down the tile's rows: an
-// operand of x (eight pixels from column 8 grp on, and two more) gives the
-// three column shifts in registers and meets the operands of the three rows of
-// g it is a tap of, so a row is read from LDS once.  A tile's loads are in
-// flight during the products of the one before.  64 images of 128^2, us per
-// layer: 86 with 2-byte stores into three shifted copies and two operand reads
-// per product, 45 transposed, 38 with the loads ahead; both tensors once at the
-// rate of a large copy are 28.
+// The products of the weight gradient run over pixels, so both tensors are
+// needed channel-major; a thread loads eight channels of eight pixels of a row,
+// transposes them in registers (32 byte permutes) and stores eight 16-byte runs
+// of pixels.  A wave owns 16 x 16 channels of all nine taps.  It goes down the
+// tile's rows: an operand of x (eight pixels from column 8 grp on, and two more)
+// gives the three column shifts in registers and meets the operands of the three
+// rows of g it is a tap of, so a row is read from LDS once.  For the input
+// gradient g's pixels are kept as they are too, each pixel's four 16-byte pieces
+// permuted by its column so that eight lanes' reads of eight pixels fall on all
+// banks, and a bit of every x for the mask (read from memory again, it would
+// wait for the loads ahead).
+// A tile's loads are in flight during the products of the one before.
+// Bound by memory (both tensors with a tile's borders, and dx) and by the latency
+// of eight waves per CU.  64 images of 128^2, us per 32 -> 32 layer: the weight
+// gradient alone 86 with 2-byte stores into three shifted copies and two operand
+// reads per product, 38 like this, and 43 for an input-gradient kernel beside it;
+// together 71.  Both tensors read and one written once take 42 at the rate of a
+// large copy.
 // ---------------------------------------------------------------------------
 constexpr int kXGroups = (kTileX + 2 + 7) / 8;          // eights of columns x0 - 1 .. : 5
 constexpr int kXRow = 8 * kXGroups;
-// channel pitches of 12 and 4 words modulo 32: eight lanes' 16-byte reads of
-// eight channels fall on all banks; every eight channels start 8 words later,
-// so that the stores of four lanes' eights of channels do too
-constexpr int kXCh = (kTileY + 2) * kXRow + 8, kGCh = kTileY * kTileX + 8;
+// channel pitch of 12 words modulo 32: eight lanes' 16-byte reads of eight
+// channels fall on all banks; every eight channels start 8 words later, so that
+// the stores of four lanes' eights of channels do too
+constexpr int kXCh = (kTileY + 2) * kXRow + 8;
 constexpr int kEights = 16;
-static_assert(kXCh * 2 / 4 % 32 == 12 && kGCh * 2 / 4 % 32 == 4, "conflict-free channel pitches");
+static_assert(kXCh * 2 / 4 % 32 == 12, "conflict-free channel pitch");
 
 __device__ __forceinline__ int channel_at(int ch, int pitch) { return ch * pitch + (ch >> 3) * kEights; }
 
@@ -563,12 +555,22 @@ __device__ __forceinline__ void store_transposed(uint16_t* dst, int pitch, const
   }
 }
 
-template <Source XS, Source GS>
-__global__ __launch_bounds__(256) void wgrad_kernel(const uint16_t* __restrict__ x, const float* __restrict__ sigma,
-                                                    const uint16_t* __restrict__ g, int N, int H, int W,
-                                                    float* __restrict__ partial) {
-  __shared__ __align__(16) uint16_t xs[kC * kXCh + 4 * kEights];  // column 0 is x0 - 1, row 0 y0 - 1
-  __shared__ __align__(16) uint16_t gs[kC * kGCh + 4 * kEights];
+// sixteen bits (one pixel) further along a row: q, then e
+__device__ __forceinline__ bf16x8 shifted_by_one(uint4 q, unsigned e) {
+  return as_bf16x8(make_uint4(__builtin_amdgcn_alignbit(q.y, q.x, 16), __builtin_amdgcn_alignbit(q.z, q.y, 16),
+                              __builtin_amdgcn_alignbit(q.w, q.z, 16), __builtin_amdgcn_alignbit(e, q.w, 16)));
+}
+
+template <Source XS, Source GS, bool DX>
+__global__ __launch_bounds__(256, 2) void backward_kernel(const uint16_t* __restrict__ x,
+                                                          const float* __restrict__ sigma,
+                                                          const uint16_t* __restrict__ g,
+                                                          const uint16_t* __restrict__ wpk, int N, int H, int W,
+                                                          float* __restrict__ partial, uint16_t* __restrict__ dx) {
+  // column 0 is x0 - 1, row 0 y0 - 1
+  __shared__ __align__(16) uint16_t xs[kC * kXCh + 4 * kEights], gs[kC * kXCh + 4 * kEights];
+  __shared__ __align__(16) uint16_t gp[DX ? kTileY + 2 : 1][kTileX + 2][kC];
+  __shared__ __align__(4) uint8_t positive[DX ? kTileY + 2 : 1][kTileX + 2][4];  // x's channels, a bit each
   const int tx_n = (W + kTileX - 1) / kTileX, ty_n = (H + kTileY - 1) / kTileY;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 15, grp = lane >> 4;
@@ -577,44 +579,42 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const uint16_t* __restrict__
 #pragma unroll
   for (int t = 0; t < kTaps; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
   float db = 0.0f;  // bias-gradient partial of channel tid % 32 over tile rows tid / 32
+  bf16x8 wt[DX ? kTaps : 1][2];
+  if constexpr (DX) {
+#pragma unroll
+    for (int t = 0; t < kTaps; ++t)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        wt[t][h] = as_bf16x8(*reinterpret_cast<const uint4*>(wpk + (t * kC + h * 16 + col) * kC + 8 * grp));
+  }
+  auto piece = [](int c, int c8) { return 8 * (c8 ^ ((c >> 1) & 3)); };  // of the pixel of tile column c
 
   const int total = conv_items(N, H, W);
-  // eights of pixels of x and of g; four threads take the channels of one
-  constexpr int kXUnits = (kTileY + 2) * kXGroups, kGGroups = kTileX / 8, kGUnits = kTileY * kGGroups;
-  static_assert(4 * kXUnits <= 256 && 4 * kGUnits <= 256, "one eight of pixels per thread");
+  // eights of pixels; four threads take the channels of one
+  constexpr int kUnits = (kTileY + 2) * kXGroups;
+  static_assert(4 * kUnits <= 256, "one eight of pixels per thread");
   uint4 vx[8], vg[8];
   const int c8 = threadIdx.x & 3, u = threadIdx.x >> 2;
-  const int xr = u / kXGroups, xc = 8 * (u - xr * kXGroups), gr = u / kGGroups, gc = 8 * (u - gr * kGGroups);
-  unsigned in_x = 0;       // the pixels of vx inside the image
+  const int ur = u / kXGroups, uc = 8 * (u - ur * kXGroups);
+  unsigned inside = 0;  // the pixels of the eight that lie in the image
   float sigma_n = 0.0f;
   auto load = [&](int item) {
     const int n = item / (tx_n * ty_n);
     const int rem = item - n * tx_n * ty_n;
-    const int y0 = (rem / tx_n) * kTileY, x0 = (rem % tx_n) * kTileX;
+    const int y = (rem / tx_n) * kTileY - 1 + ur, xx = (rem % tx_n) * kTileX - 1 + uc;
     if constexpr (XS == kInput) sigma_n = sigma[n];
-    {
-      const int y = y0 - 1 + xr, xx = x0 - 1 + xc;
-      const bool row = u < kXUnits && y >= 0 && y < H;
-      const size_t pix = (static_cast<size_t>(n) * H + y) * W + xx;
-      in_x = 0;
+    const bool row = u < kUnits && y >= 0 && y < H;
+    const size_t pix = (static_cast<size_t>(n) * H + y) * W + xx;
+    inside = 0;
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        vx[k] = make_uint4(0, 0, 0, 0);
-        // (columns past the 34th are not used)
-        if (row && xx + k >= 0 && xx + k < W && xc + k < kTileX + 2) {
-          vx[k] = load_channels<XS>(x, pix + k, c8);
-          in_x |= 1u << k;
-        }
-      }
-    }
-    {
-      const int y = y0 + gr, xx = x0 + gc;
-      const bool row = u < kGUnits && y < H;
-      const size_t pix = (static_cast<size_t>(n) * H + y) * W + xx;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        vg[k] = make_uint4(0, 0, 0, 0);
-        if (row && xx + k < W) vg[k] = load_channels<GS>(g, pix + k, c8);
+    for (int k = 0; k < 8; ++k) {
+      vx[k] = make_uint4(0, 0, 0, 0);
+      vg[k] = make_uint4(0, 0, 0, 0);
+      // (columns past the 34th are not used)
+      if (row && xx + k >= 0 && xx + k < W && uc + k < kTileX + 2) {
+        vx[k] = load_channels<XS>(x, pix + k, c8);
+        vg[k] = load_channels<GS>(g, pix + k, c8);
+        inside |= 1u << k;
       }
     }
   };
@@ -623,27 +623,44 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const uint16_t* __restrict__
     if constexpr (XS == kInput) {
 #pragma unroll
       for (int k = 0; k < 8; ++k)
-        if (in_x >> k & 1) vx[k] = as_activations<XS>(vx[k], sigma_n, c8);
+        if (inside >> k & 1) vx[k] = as_activations<XS>(vx[k], sigma_n, c8);
     }
-    if (u < kXUnits) store_transposed(xs + channel_at(8 * c8, kXCh) + xr * kXRow + xc, kXCh, vx);
-    if (u < kGUnits) store_transposed(gs + channel_at(8 * c8, kGCh) + gr * kTileX + gc, kGCh, vg);
+    if (u < kUnits) {
+      const int at = channel_at(8 * c8, kXCh) + ur * kXRow + uc;
+      store_transposed(xs + at, kXCh, vx);
+      store_transposed(gs + at, kXCh, vg);
+      if constexpr (DX) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (uc + k < kTileX + 2) {
+            *reinterpret_cast<uint4*>(&gp[ur][uc + k][piece(uc + k, c8)]) = vg[k];
+            const unsigned m[4] = {vx[k].x, vx[k].y, vx[k].z, vx[k].w};
+            unsigned bits = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              bits |= (static_cast<int>(m[j] << 16) > 0 ? 1u << (2 * j) : 0u) |
+                      (static_cast<int>(m[j]) > 0xffff ? 2u << (2 * j) : 0u);
+            positive[ur][uc + k][c8] = static_cast<uint8_t>(bits);
+          }
+      }
+    }
     // the next tile's loads are in flight during this one's products
     if (item + static_cast<int>(gridDim.x) < total) load(item + gridDim.x);
     __syncthreads();
     const uint16_t* xrow = xs + channel_at(ci_t * 16 + col, kXCh) + 8 * grp;
-    const uint16_t* grow = gs + channel_at(co_t * 16 + col, kGCh) + 8 * grp;
-    bf16x8 A[3];  // rows row, row - 1, row - 2 of g
+    const uint16_t* grow = gs + channel_at(co_t * 16 + col, kXCh) + 8 * grp;
+    bf16x8 A[3];  // rows row, row - 1, row - 2 of the tile's g
 #pragma unroll
     for (int row = 0; row < kTileY + 2; ++row) {
       A[2] = A[1];
       A[1] = A[0];
-      if (row < kTileY) A[0] = as_bf16x8(*reinterpret_cast<const uint4*>(grow + row * kTileX));
+      if (row < kTileY) {
+        const uint16_t* p = grow + (row + 1) * kXRow;
+        A[0] = shifted_by_one(*reinterpret_cast<const uint4*>(p), *reinterpret_cast<const unsigned*>(p + 8));
+      }
       const uint4 q = *reinterpret_cast<const uint4*>(xrow + row * kXRow);
       const unsigned e = *reinterpret_cast<const unsigned*>(xrow + row * kXRow + 8);
-      const bf16x8 B[3] = {as_bf16x8(q),
-                           as_bf16x8(make_uint4(__builtin_amdgcn_alignbit(q.y, q.x, 16), __builtin_amdgcn_alignbit(q.z, q.y, 16),
-                                                __builtin_amdgcn_alignbit(q.w, q.z, 16), __builtin_amdgcn_alignbit(e, q.w, 16))),
-                           as_bf16x8(make_uint4(q.y, q.z, q.w, e))};
+      const bf16x8 B[3] = {as_bf16x8(q), shifted_by_one(q, e), as_bf16x8(make_uint4(q.y, q.z, q.w, e))};
 #pragma unroll
       for (int ky = 0; ky < 3; ++ky)
         if (row >= ky && row - ky < kTileY) {
@@ -653,16 +670,47 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const uint16_t* __restrict__
         }
     }
     {  // bias gradient: thread (channel tid % 32, row tid / 32) sums one tile row
-      const uint16_t* line = gs + channel_at(threadIdx.x & (kC - 1), kGCh) + (threadIdx.x >> 5) * kTileX;
+      const uint16_t* line = gs + channel_at(threadIdx.x & (kC - 1), kXCh) + ((threadIdx.x >> 5) + 1) * kXRow;
       float s = 0.0f;
 #pragma unroll
-      for (int c = 0; c < kTileX; c += 8) {
+      for (int c = 0; c < kXRow; c += 8) {
         const uint4 q = *reinterpret_cast<const uint4*>(line + c);
-        const uint16_t* v = reinterpret_cast<const uint16_t*>(&q);
+        const unsigned v[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-        for (int k = 0; k < 8; ++k) s += bf2f(v[k]);
+        for (int k = 0; k < 8; ++k)
+          if (c + k >= 1 && c + k <= kTileX) s += bf2f(static_cast<uint16_t>(v[k / 2] >> (16 * (k % 2))));
       }
       db += s;
+    }
+    if constexpr (DX) {
+      const int n = item / (tx_n * ty_n);
+      const int rem = item - n * tx_n * ty_n;
+      const int y0 = (rem / tx_n) * kTileY, x0 = (rem % tx_n) * kTileX;
+#pragma unroll
+      for (int bi = 0; bi < 4; ++bi) {
+        const int row = 2 * wave + (bi >> 1), xoff = (bi & 1) * 16;
+        f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < kTaps; ++t) {
+          const int c = xoff + col + t % 3;
+          const bf16x8 B = as_bf16x8(*reinterpret_cast<const uint4*>(&gp[row + t / 3][c][piece(c, grp)]));
+          acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[t][0], B, acc0, 0, 0, 0);
+          acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[t][1], B, acc1, 0, 0, 0);
+        }
+        // lane holds channels 4*grp + i (acc0) and 16 + 4*grp + i (acc1) of pixel (y, xx)
+        const int y = y0 + row, xx = x0 + xoff + col;
+        if (y < H && xx < W) {
+          const size_t p = ((static_cast<size_t>(n) * H + y) * W + xx) * kC + 4 * grp;
+          const unsigned m = *reinterpret_cast<const unsigned*>(positive[row + 1][xoff + col + 1]) >> (4 * grp);
+          float v0[4], v1[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            v0[i] = m >> i & 1 ? acc0[i] : 0.0f;
+            v1[i] = m >> (16 + i) & 1 ? acc1[i] : 0.0f;
+          }
+          store_channels(dx + p, v0, v1);
+        }
+      }
     }
     __syncthreads();
   }
@@ -822,26 +870,14 @@ hipError_t launch_pilot_conv(int layer, const uint16_t* in, const float* sigma, 
                              int H, int W, int grid_cap, hipStream_t st) {
   const int grid = std::max(1, std::min(conv_items(N, H, W), grid_cap));
   if (layer == 0)
-    hipLaunchKernelGGL((conv_kernel<0, kInput>), dim3(grid), dim3(256), 0, st, in, sigma, w, bias, nullptr, out, noisy,
+    hipLaunchKernelGGL((conv_kernel<0, kInput>), dim3(grid), dim3(256), 0, st, in, sigma, w, bias, out, noisy,
                        pilot_f32, pilot_u16, N, H, W);
   else if (layer < kPilotLayers - 1)
-    hipLaunchKernelGGL((conv_kernel<0, kAct>), dim3(grid), dim3(256), 0, st, in, sigma, w, bias, nullptr, out, noisy,
+    hipLaunchKernelGGL((conv_kernel<0, kAct>), dim3(grid), dim3(256), 0, st, in, sigma, w, bias, out, noisy,
                        pilot_f32, pilot_u16, N, H, W);
   else
-    hipLaunchKernelGGL((conv_kernel<1, kAct>), dim3(grid), dim3(256), 0, st, in, sigma, w, bias, nullptr, out, noisy,
+    hipLaunchKernelGGL((conv_kernel<1, kAct>), dim3(grid), dim3(256), 0, st, in, sigma, w, bias, out, noisy,
                        pilot_f32, pilot_u16, N, H, W);
-  return hipGetLastError();
-}
-
-hipError_t launch_pilot_dgrad(int layer, const uint16_t* g, const uint16_t* w, const uint16_t* mask, uint16_t* out,
-                              int N, int H, int W, int grid_cap, hipStream_t st) {
-  const int grid = std::max(1, std::min(conv_items(N, H, W), grid_cap));
-  if (layer == kPilotLayers - 1)
-    hipLaunchKernelGGL((conv_kernel<2, kLossGrad>), dim3(grid), dim3(256), 0, st, g, nullptr, w, nullptr, mask, out,
-                       nullptr, nullptr, nullptr, N, H, W);
-  else
-    hipLaunchKernelGGL((conv_kernel<2, kAct>), dim3(grid), dim3(256), 0, st, g, nullptr, w, nullptr, mask, out, nullptr,
-                       nullptr, nullptr, N, H, W);
   return hipGetLastError();
 }
 
@@ -852,14 +888,18 @@ hipError_t launch_pilot_loss(const float* pilot, const float* target, const floa
   return hipGetLastError();
 }
 
-hipError_t launch_pilot_wgrad(const uint16_t* x, const float* sigma, const uint16_t* g, int N, int H, int W, int grid,
-                              float* partial, int layer, float* grad_layer, hipStream_t st) {
+hipError_t launch_pilot_backward(int layer, const uint16_t* x, const float* sigma, const uint16_t* g,
+                                 const uint16_t* w, int N, int H, int W, int grid, float* partial, float* grad_layer,
+                                 uint16_t* dx, hipStream_t st) {
   if (layer == 0)
-    hipLaunchKernelGGL((wgrad_kernel<kInput, kAct>), dim3(grid), dim3(256), 0, st, x, sigma, g, N, H, W, partial);
+    hipLaunchKernelGGL((backward_kernel<kInput, kAct, false>), dim3(grid), dim3(256), 0, st, x, sigma, g, w, N, H, W,
+                       partial, dx);
   else if (layer < kPilotLayers - 1)
-    hipLaunchKernelGGL((wgrad_kernel<kAct, kAct>), dim3(grid), dim3(256), 0, st, x, sigma, g, N, H, W, partial);
+    hipLaunchKernelGGL((backward_kernel<kAct, kAct, true>), dim3(grid), dim3(256), 0, st, x, sigma, g, w, N, H, W,
+                       partial, dx);
   else
-    hipLaunchKernelGGL((wgrad_kernel<kAct, kLossGrad>), dim3(grid), dim3(256), 0, st, x, sigma, g, N, H, W, partial);
+    hipLaunchKernelGGL((backward_kernel<kAct, kLossGrad, true>), dim3(grid), dim3(256), 0, st, x, sigma, g, w, N, H, W,
+                       partial, dx);
   const int ci_n = pilot_cin(layer), co_n = pilot_cout(layer);
   const int n_out = kTaps * ci_n * co_n + co_n;
   hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((n_out + 63) / 64), dim3(64 * kRedWaves), 0, st, partial, grid, ci_n,
