@@ -292,6 +292,18 @@ __device__ __forceinline__ float bior_syn_odd(int i) {
   return t[i];
 }
 
+// four floats at 16 bytes of LDS
+__device__ __forceinline__ void load4(const float* p, float* v) {
+  const float4 q = *reinterpret_cast<const float4*>(p);
+  v[0] = q.x;
+  v[1] = q.y;
+  v[2] = q.z;
+  v[3] = q.w;
+}
+__device__ __forceinline__ void store4(float* p, const float* v) {
+  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+}
+
 __device__ __forceinline__ float hard_threshold(float v, float tau) { return fabsf(v) >= tau ? v : 0.0f; }
 
 // j folded into [0, L) when it lies within one period of it
@@ -330,8 +342,9 @@ __global__ __launch_bounds__(THREADS) void gl_forward_kernel(const float* __rest
   // columns stored split by parity so the strided filter taps read
   // consecutive LDS words
   constexpr int kRows = T::kFwdRows, kCols = T::kFwdCols, kHalfCols = kCols / 2;
-  __shared__ float in_s[2][kRows][2][kHalfCols];
-  __shared__ float xs[2][kRows][2 * TX];
+  __shared__ __align__(16) float in_s[2][kRows][2][kHalfCols];
+  __shared__ __align__(16) float xs[2][kRows][2 * TX];
+  static_assert(kHalfCols % 4 == 0 && TX % 4 == 0, "four columns start at 16 bytes");
   // per window row / column: the volume coordinate (with GATHER: of the
   // unspun volume V, and which of the window's tile rows / columns holds it)
   constexpr int kTileRows = (kRows + 2 * N - 2) / N, kTileCols = (kCols + 2 * N - 2) / N;
@@ -422,35 +435,53 @@ __global__ __launch_bounds__(THREADS) void gl_forward_kernel(const float* __rest
     }
   }
   __syncthreads();
-  // along x: window column 2 j + i is even[j + i/2] or odd[j + (i-1)/2]
-  for (int e = tid; e < 2 * kRows * TX; e += THREADS) {
-    const int j = e % TX, r = (e / TX) % kRows, kb = e / (TX * kRows);
-    const float* ev = in_s[kb][r][0];
-    const float* od = in_s[kb][r][1];
-    float lo = 0.0f;
+  // along x: window column 2 j + i is even[j + i/2] or odd[j + (i-1)/2]; four
+  // consecutive j per thread, whose taps are two runs of eight values
+  for (int e = tid; e < 2 * kRows * (TX / 4); e += THREADS) {
+    const int j = 4 * (e % (TX / 4)), r = (e / (TX / 4)) % kRows, kb = e / (TX / 4 * kRows);
+    float ev[8], od[8];
+    load4(in_s[kb][r][0] + j, ev);
+    load4(in_s[kb][r][0] + j + 4, ev + 4);
+    load4(in_s[kb][r][1] + j, od);
+    load4(in_s[kb][r][1] + j + 4, od + 4);
+    float lo[4], hi[4];
 #pragma unroll
-    for (int u = 0; u < 5; ++u) {
-      lo = fmaf(bior_lo_tap(2 * u), ev[j + u], lo);
-      lo = fmaf(bior_lo_tap(2 * u + 1), od[j + u], lo);
+    for (int q = 0; q < 4; ++q) {
+      lo[q] = 0.0f;
+#pragma unroll
+      for (int u = 0; u < 5; ++u) {
+        lo[q] = fmaf(bior_lo_tap(2 * u), ev[q + u], lo[q]);
+        lo[q] = fmaf(bior_lo_tap(2 * u + 1), od[q + u], lo[q]);
+      }
+      hi[q] = (od[q + 2] - ev[q + 2]) * c;
     }
-    xs[kb][r][j] = lo;
-    xs[kb][r][TX + j] = (od[j + 2] - ev[j + 2]) * c;
+    store4(xs[kb][r] + j, lo);
+    store4(xs[kb][r] + TX + j, hi);
   }
   __syncthreads();
-  // along y, then out to the bands
-  for (int e = tid; e < 2 * TY * 2 * TX; e += THREADS) {
-    const int cc = e % (2 * TX), i = (e / (2 * TX)) % TY, kb = e / (2 * TX * TY);
+  // along y, then out to the bands; consecutive rows of a column per thread
+  constexpr int kStrip = 4 * TY * TX / THREADS;
+  static_assert(kStrip * THREADS == 4 * TY * TX && TY % kStrip == 0, "one strip per thread");
+  {
+    const int cc = tid % (2 * TX), i0 = (tid / (2 * TX)) % (TY / kStrip) * kStrip, kb = tid / (2 * TX * (TY / kStrip));
     const int xb = cc >= TX ? 1 : 0;
-    const int cy = cy0 + i, cx = cx0 + cc - xb * TX;
-    if (cy >= hy || cx >= hx) continue;
-    float lo = 0.0f;
+    const int cx = cx0 + cc - xb * TX;
+    float v[2 * kStrip + 8];
 #pragma unroll
-    for (int t = 0; t < 10; ++t) lo = fmaf(bior_lo_tap(t), xs[kb][2 * i + t][cc], lo);
-    const float hi = hard_threshold((xs[kb][2 * i + 5][cc] - xs[kb][2 * i + 4][cc]) * c, tau);
-    if (kb | xb) lo = hard_threshold(lo, tau);
+    for (int t = 0; t < 2 * kStrip + 8; ++t) v[t] = xs[kb][2 * i0 + t][cc];
     float* o = dst + static_cast<size_t>(kb ? hk + kp : kp) * hw + (xb ? hx + cx : cx);
-    o[static_cast<size_t>(cy) * W] = lo;
-    o[static_cast<size_t>(hy + cy) * W] = hi;
+#pragma unroll
+    for (int q = 0; q < kStrip; ++q) {
+      const int cy = cy0 + i0 + q;
+      if (cy >= hy || cx >= hx) continue;
+      float lo = 0.0f;
+#pragma unroll
+      for (int t = 0; t < 10; ++t) lo = fmaf(bior_lo_tap(t), v[2 * q + t], lo);
+      const float hi = hard_threshold((v[2 * q + 5] - v[2 * q + 4]) * c, tau);
+      if (kb | xb) lo = hard_threshold(lo, tau);
+      o[static_cast<size_t>(cy) * W] = lo;
+      o[static_cast<size_t>(hy + cy) * W] = hi;
+    }
   }
 }
 
@@ -469,8 +500,9 @@ __global__ __launch_bounds__(THREADS) void gl_inverse_kernel(const float* __rest
   // cy0 + TY + 1 (the synthesis taps reach two coefficients either side);
   // the same for columns
   constexpr int kRows = T::kInvRows, kCols = T::kInvCols;
-  __shared__ float in_s[2][kRows][kCols];
-  __shared__ float xs[2][kRows][2 * TX];
+  __shared__ __align__(16) float in_s[2][kRows][kCols];
+  __shared__ __align__(16) float xs[2][kRows][2 * TX];
+  static_assert(kCols % 4 == 0 && TX % 4 == 0, "four columns start at 16 bytes");
   __shared__ int row_at[kRows], col_at[kCols];
   const int hy = Ly >> 1, hx = Lx >> 1, hk = Lk >> 1;
   const int h = blockIdx.z / hk, kp = blockIdx.z - h * hk;
@@ -512,43 +544,61 @@ __global__ __launch_bounds__(THREADS) void gl_inverse_kernel(const float* __rest
     }
   }
   __syncthreads();
-  for (int e = tid; e < 2 * kRows * TX; e += THREADS) {
-    const int j = e % TX, r = (e / TX) % kRows, kb = e / (TX * kRows);
+  for (int e = tid; e < 2 * kRows * (TX / 4); e += THREADS) {
+    const int j = 4 * (e % (TX / 4)), r = (e / (TX / 4)) % kRows, kb = e / (TX / 4 * kRows);
     const float* row = in_s[kb][r];
-    const float a = c * row[j];
-    float ev = a, od = a;
+    float a[4], d[8], out[8];
+    load4(row + j, a);
+    load4(row + TX + j, d);
+    load4(row + TX + j + 4, d + 4);
 #pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      const float d = row[TX + j + i];
-      ev = fmaf(bior_syn_even(i), d, ev);
-      od = fmaf(bior_syn_odd(i), d, od);
+    for (int q = 0; q < 4; ++q) {
+      float ev = c * a[q], od = ev;
+#pragma unroll
+      for (int i = 0; i < 5; ++i) {
+        ev = fmaf(bior_syn_even(i), d[q + i], ev);
+        od = fmaf(bior_syn_odd(i), d[q + i], od);
+      }
+      out[2 * q] = ev;
+      out[2 * q + 1] = od;
     }
-    xs[kb][r][2 * j] = ev;
-    xs[kb][r][2 * j + 1] = od;
+    store4(xs[kb][r] + 2 * j, out);
+    store4(xs[kb][r] + 2 * j + 4, out + 4);
   }
   __syncthreads();
-  for (int e = tid; e < TY * 2 * TX; e += THREADS) {
-    const int cc = e % (2 * TX), i = e / (2 * TX);
-    const int y = 2 * (cy0 + i), x = 2 * cx0 + cc;
-    if (y >= Ly || x >= Lx) continue;
-    float ev[2], od[2];
+  constexpr int kStrip = 2 * TY * TX >= 2 * THREADS ? 2 * TY * TX / THREADS : 1;
+  static_assert(TY % kStrip == 0, "whole strips");
+  for (int e = tid; e < TY / kStrip * 2 * TX; e += THREADS) {
+    const int cc = e % (2 * TX), i0 = e / (2 * TX) * kStrip;
+    const int x = 2 * cx0 + cc;
+    float ev[2][kStrip], od[2][kStrip];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
-      const float a = c * xs[kb][i][cc];
-      ev[kb] = a;
-      od[kb] = a;
+      float d[kStrip + 4];
 #pragma unroll
-      for (int u = 0; u < 5; ++u) {
-        const float d = xs[kb][TY + i + u][cc];
-        ev[kb] = fmaf(bior_syn_even(u), d, ev[kb]);
-        od[kb] = fmaf(bior_syn_odd(u), d, od[kb]);
+      for (int u = 0; u < kStrip + 4; ++u) d[u] = xs[kb][TY + i0 + u][cc];
+#pragma unroll
+      for (int q = 0; q < kStrip; ++q) {
+        ev[kb][q] = od[kb][q] = c * xs[kb][i0 + q][cc];
+#pragma unroll
+        for (int u = 0; u < 5; ++u) {
+          ev[kb][q] = fmaf(bior_syn_even(u), d[q + u], ev[kb][q]);
+          od[kb][q] = fmaf(bior_syn_odd(u), d[q + u], od[kb][q]);
+        }
       }
     }
-    const float v[2][2] = {{(ev[0] + ev[1]) * c, (od[0] + od[1]) * c}, {(ev[0] - ev[1]) * c, (od[0] - od[1]) * c}};
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
+    for (int q = 0; q < kStrip; ++q) {
+      const int y = 2 * (cy0 + i0 + q);
+      if (y >= Ly || x >= Lx) continue;
+      const float v[2][2] = {{(ev[0][q] + ev[1][q]) * c, (od[0][q] + od[1][q]) * c},
+                             {(ev[0][q] - ev[1][q]) * c, (od[0][q] - od[1][q]) * c}};
 #pragma unroll
-      for (int p = 0; p < 2; ++p) dst[static_cast<size_t>(2 * kp + s) * hw + static_cast<size_t>(y + p) * W + x] = v[s][p];
+      for (int s = 0; s < 2; ++s) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+          dst[static_cast<size_t>(2 * kp + s) * hw + static_cast<size_t>(y + p) * W + x] = v[s][p];
+      }
     }
   }
 }
