@@ -74,8 +74,8 @@ def bm_int8_view(H, W, search, avg_us):
 TRAFFIC_FILES = {512: os.path.join(ROOT, "profiles", "hbm_traffic_denoise_512.txt"),
                  4096: os.path.join(ROOT, "profiles", "hbm_traffic_denoise_4096.txt")}
 KERNEL_SOURCES = {
-    "bm": ["bm.hip", "bm_corr.hip", "common.h", "topk.h"],
-    "stack_bior": ["stack.hip", "common.h"], "stack_dct": ["stack.hip", "common.h"],
+    "bm": ["bm.hip", "bm_corr.hip", "stack_body.h", "common.h", "topk.h"],
+    "stack_bior": ["stack.hip", "stack_body.h", "common.h"], "stack_dct": ["stack.hip", "stack_body.h", "common.h"],
     "group_ht": ["group.hip", "common.h"], "group_wiener": ["group.hip", "common.h"], "reduce": ["group.hip", "common.h"],
 }
 
@@ -565,8 +565,6 @@ def per_kernel(ctx, Zt, sigma, p, steps, variants=None):
             # what the counters saw leave and enter HBM, over the same time
             k["hbm_counted_GBps"] = tb / (k["avg_us"] * 1e-6) / 1e9
             k["hbm_counted_frac"] = k["hbm_counted_GBps"] / HBM_PEAK_GBS
-        if name == "bm":
-            k["int8_view"] = bm_int8_view(H, W, p.search, k["avg_us"])
         if variants:
             # vector-instruction issue: committed SQ_INSTS_VALU of the same
             # variants x 4 cycles over every SIMD's cycles of the measured time
@@ -663,7 +661,7 @@ def main():
             for ln in open(os.path.join(td, "tune.txt")):
                 f = ln.split()
                 if f[0] == "ht" and int(f[1]) == p.k_ht and int(f[2]) == p.search:
-                    tuned["stage1_groups"] = {"shape": ["two tiles of 12 waves per CU",
+                    tuned["stage1_groups"] = {"shape": ["tiles sharing a CU",
                                                         "one tile of 16 waves, prefetch"][int(f[4])],
                                               "ms_stage1": float(f[5])}
     else:
@@ -687,20 +685,22 @@ def main():
     Y = out.cpu().numpy().astype(np.float64)
     psnr = psnr_db(Y, clean)
 
-    # per-kernel durations: the same steps with library-recorded events
+    # per-kernel durations: the same steps with library-recorded events (each
+    # kernel launched by itself; untimed, the matching launches hold the stacks)
     # the kernel variants this run launched, for the instruction counters
     def bm_variant(K):
         t = tuned.get(f"K{K}")
         if not t:
             return None
         s = t["split"]
-        return "bm_corr_kernel<6, 3, true, false>" if t["method"] == "corr" else f"bm_kernel<{K}, {4 // s}, {s}, false>"
+        return ("bm_corr_kernel<6, 3, true, false, -1>" if t["method"] == "corr"
+                else f"bm_kernel<{K}, {4 // s}, {s}, false>")
     # (the 512^2 stack launches are short ones: pixel loads all at once)
     variants = {"bm": [bm_variant(p.k_ht), bm_variant(p.k_wiener)],
-                "stack_bior": ["stack_kernel<0, false, true>"], "stack_dct": ["stack_kernel<1, false, true>"],
+                "stack_bior": ["stack_kernel<0, false, true>"], "stack_dct": ["stack_kernel<2, false, true>"],
                 "group_ht": [f"group_ht_kernel<{p.k_ht}, false, false, "
-                             f"{'false' if tuned.get('stage1_groups', {}).get('shape', '').startswith('one') else 'true'}>"],
-                "group_wiener": [f"group_wiener_kernel<{p.k_wiener}, false>"], "reduce": ["reduce_kernel<false>"] * 2}
+                             f"{1 if tuned.get('stage1_groups', {}).get('shape', '').startswith('one') else 0}>"],
+                "group_wiener": [f"group_wiener_kernel<{p.k_wiener}, false, 0>"], "reduce": ["reduce_kernel<false>"] * 2}
     # (the committed instruction counts are those of the 512^2 image)
     kernels = per_kernel(ctx, Zt, sigma, p, args.steps, variants if H == W == 512 else None)
     dom = max(kernels, key=lambda n: kernels[n]["ms_per_step"])
@@ -709,8 +709,6 @@ def main():
             "frac": k["frac"], "traffic": k["traffic_bytes"], "avg_us": k["avg_us"],
             "work_per_launch": k["work_per_launch"], "work_unit": k["work_unit"],
             "valu_issue_frac": k.get("valu_issue_frac")}
-    if "int8_view" in k:
-        roof["int8_view"] = k["int8_view"]
 
     rec = {
         "metric": "Mpixel/s two-stage denoise at sigma=25 (plain vs learned pilot) + PSNR gap, 1 GPU",

@@ -341,8 +341,8 @@ int gbm3d_timing_reset(gbm3d_ctx* ctx);
  *     warm-up run, and records the fastest;
  *   - when K == params.k_ht <= 16, also times whole stage-1 runs (that
  *     matching, sigma 25/255) with each of the two shapes of the stage-1
- *     group kernel (two tiles of 12 waves per compute unit, or one tile of
- *     16 waves that prefetches the next group) and records the faster.
+ *     group kernel (tiles sharing a compute unit, or one tile of 16 waves
+ *     that prefetches the next group) and records the faster.
  * Records are keyed by (K, search, shape class of (H, W): the number of 4x4
  * reference tiles rounded down to a power of two).  Later calls whose params
  * leave bm_method or bm_split at 0 use the record of their class (a batch:

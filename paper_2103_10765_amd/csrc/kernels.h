@@ -49,9 +49,9 @@ int group_items_for(int H, int W);
 
 // stage-1 groups: stack_a (bior) + idx -> partials (weights scaled by rec.eps);
 // recompute (one image only): the blocks' spectra from rec.noisy's pixels
-// instead of stack_a.  shape (K <= 16): 0 = two tiles of 12 waves per CU,
-// 1 = one tile of 16 waves with the next group's spectra prefetched; the
-// same result either way.
+// instead of stack_a.  shape (K <= 16): 0 = tiles sharing a CU (of a
+// size chosen by the image's), 1 = one tile of 16 waves with the next group's
+// spectra prefetched; the same result either way.
 hipError_t launch_group_ht(const ImgRec& one, const WorkList* wl, int R, int K, float ht_a, float ht_b,
                            int weight_mode, int keep_dc, int recompute, int shape, hipStream_t st);
 // zeroes the block-start weights and numerator sums of rec.partials (what the
