@@ -261,9 +261,11 @@ __device__ __forceinline__ void fused_store(uint4* __restrict__ out, int i, int 
 
 // A 3x3 layer over a region of RY x RX pixels (input row stride RX + 2), two
 // rows at a time: a block is 16 pixels of a row pair's raster, and its lanes'
-// four input rows serve both rows' taps, 12 LDS reads for 18.  (Bound by LDS
-// cycles: one row at a time they are twice the matrix cores', two at a time 1.5
-// times; 32 x 512^2 1.55 -> 1.38 ms.)  A wave takes the blocks g = wave, wave + kFWaves, ...: an operand
+// four input rows serve both rows' taps, 12 LDS reads and one address
+// computation for 18 and two.  (No single unit binds: the one wave per SIMD
+// issues its reads, addresses and epilogues between its products, and the LDS
+// cycles of the reads were twice the products', now 1.5 times; 32 x 512^2
+// 1.55 -> 1.38 ms.)  A wave takes the blocks g = wave, wave + kFWaves, ...: an operand
 // that the block has no more use for is replaced by the next block's, and the
 // results of a block are stored while the products of the next run.
 template <int RX, int RY, int HALVES, class Store>
