@@ -56,7 +56,7 @@ __device__ __forceinline__ const uint16_t* translated(const uint16_t* noisy, con
 template <int N>
 struct TileSmem {
   static constexpr int kRegion = kMaxSearch + N - 1;
-  // row pitch: the region plus the columns the last 8-wide displacement
+  // row pitch: the region plus the columns the last displacement
   // group reads past it, made odd so that lanes on consecutive rows fall on
   // different LDS banks
   static constexpr int kPitch = (kRegion + 2) | 1;
@@ -127,11 +127,14 @@ __global__ __launch_bounds__(kGlThreads, 4) void gl_match_kernel(const uint16_t*
   // exact squared distances as |a|^2 + |b|^2 - 2 <a, b>: every term an
   // integer below 2^41, so float64 holds each step exactly and the keys equal
   // those of summed squared differences.  A work item is one displacement
-  // row dy and eight consecutive dx: each reference pixel (one LDS word read
-  // by the whole wave) serves all eight; the candidates' norms are column
+  // row dy and seven consecutive dx (39 x 6 items for 256 threads; of eight,
+  // 39 x 5 left a quarter of them idle, 59 instead of 57 us for two 512^2
+  // translations): each reference pixel (one LDS word read by the whole wave)
+  // serves all seven; the candidates' norms are column
   // sums of squares over the same rows, then sums of N columns.
   const int S2 = S * S;
-  constexpr int kDx = 8;
+  constexpr int kDx = 7;
+  static_assert((kMaxSearch + kDx - 1) / kDx * kDx + N - 1 <= P, "the last displacements' columns lie in the region's rows");
   constexpr int kSeg = N + kDx - 1;
   const int groups = (S + kDx - 1) / kDx;
   for (int item = threadIdx.x; item < S * groups; item += blockDim.x) {
