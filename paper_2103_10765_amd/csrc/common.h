@@ -241,13 +241,13 @@ __device__ __forceinline__ long long to_fixed_scaled(float xs) {
 // Full-depth Haar along a group of K registers (K power of two).  The
 // orthonormal forward step turns pairs (2j, 2j+1) of the current sums into the
 // sum (x0+x1)/sqrt2 at j and the difference (x0-x1)/sqrt2 at half+j, the
-// group DC ending at index 0.  The kernels run it unnormalised:
+// group DC ending at index 0.  The kernels run it unnormalised: the same
+// butterflies without the 1/sqrt2.  Orthonormal coefficient k equals
+// haar_gain<K>(k) times unnormalised coefficient k, with haar_gain^2 = h/K for
+// the detail band [h, 2h) that holds k (1/K for the DC); the orthonormal
+// inverse of c is the unnormalised butterflies' transpose of haar_gain^2 * c',
+// c' the unnormalised coefficients.
 // ---------------------------------------------------------------------------
-// the same butterflies without the 1/sqrt2.  Orthonormal
-// coefficient k equals haar_gain<K>(k) times unnormalised coefficient k, with
-// haar_gain^2 = h/K for the detail band [h, 2h) that holds k (1/K for the
-// DC); the orthonormal inverse of c is haar_inv_raw of haar_gain^2 * c', since
-// the unnormalised inverse is the transpose of the unnormalised forward.
 template <int K>
 __host__ __device__ constexpr float haar_gain2(int k) {
   int h = 1;
@@ -272,21 +272,6 @@ __device__ __forceinline__ void haar_fwd_raw(float* v) {
     for (int j = 0; j < half; ++j) {
       t[j] = v[2 * j] + v[2 * j + 1];
       t[half + j] = v[2 * j] - v[2 * j + 1];
-    }
-#pragma unroll
-    for (int j = 0; j < 2 * half; ++j) v[j] = t[j];
-  }
-}
-
-template <int K>
-__device__ __forceinline__ void haar_inv_raw(float* v) {
-#pragma unroll
-  for (int half = 1; half <= K / 2; half *= 2) {
-    float t[K];
-#pragma unroll
-    for (int j = 0; j < half; ++j) {
-      t[2 * j] = v[j] + v[half + j];
-      t[2 * j + 1] = v[j] - v[half + j];
     }
 #pragma unroll
     for (int j = 0; j < 2 * half; ++j) v[j] = t[j];

@@ -430,7 +430,7 @@ constexpr bool gains_are_scaled() {
   return true;
 }
 
-// Unnormalised Haar inverse (haar_inv_raw) of v[k] haar_gain2<K>(k) K: the
+// Unnormalised Haar inverse of v[k] haar_gain2<K>(k) K: the
 // band [h, 2h) enters with its weight h (a power of two: an exact product).
 template <int K>
 __device__ __forceinline__ void haar_inv_banded(float* v) {
@@ -607,7 +607,7 @@ __device__ __forceinline__ void group_ht_body(acc_t* acc,
   flush_acc<T>(acc, g, fy0, fx0, numerator_sums(r));
 }
 
-// Unnormalised Haar inverse (haar_inv_raw) of v[k] wt[k], in place of v.
+// Unnormalised Haar inverse of v[k] wt[k], in place of v.
 template <int K>
 __device__ __forceinline__ void haar_inv_weighted(float* v, const float* wt) {
 #pragma clang fp contract(off)
