@@ -528,6 +528,28 @@ def test_single_image_tiles_equal_batch_tiles(torch, G, ctx, k, H, W):
     assert torch.equal(ctx.denoise_batch([x], [SIG], params=gp)[0], ctx.denoise(x, SIG, gp))
 
 
+@pytest.mark.parametrize("S", [15, 31, 39])
+def test_stacks_beside_matching_equal_separate_launches(torch, G, ctx, S):
+    """The matching launches write the stacks too, in workgroups of two stack
+    items spread among the tiles (odd counts of items, images narrower and
+    shorter than an item); while launches are timed each kernel runs by itself.
+    Same bits, for every shape of the matcher's candidate grid, single and
+    batched."""
+    gp = G.default_params(search=S)
+    xs = [up(torch, synth.make_case(H, W, SIG, 29 + H)[1]) for H, W in [(39, 40), (45, 131), (201, 77)]]
+    runs = []
+    try:
+        for timed in (False, True):
+            say("stacks beside matching", S, "timed" if timed else "together")
+            ctx.timing(timed)
+            runs.append([ctx.denoise(x, SIG, gp) for x in xs] + ctx.denoise_batch(xs, [SIG] * 3, params=gp))
+            torch.cuda.synchronize()
+    finally:
+        ctx.timing(False)
+    for a, b in zip(*runs):
+        assert torch.equal(a, b)
+
+
 def test_batch_many_small_images_equal_single_calls(torch, G, ctx):
     """Many images of 39..64 px (several images share each 64-item block of
     every phase's item -> image table) around two larger ones, some with a
