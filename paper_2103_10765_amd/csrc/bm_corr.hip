@@ -33,7 +33,7 @@
 // term far below one unit of distance, which survives while the norms are
 // small (constant regions); elsewhere they all pass and the exact keys decide,
 // at the cost of more of them (long lists are cut by the (K-1)-th smallest of
-// their first kPrune keys before the ranks are counted).
+// their first kSample keys before the ranks are counted).
 //
 // Bound by LDS cycles and vector issue about equally: per tile 6 200 LDS
 // cycles (the 144 blocks' operands 2 600 of them) and 9 000 vector
@@ -73,7 +73,8 @@ constexpr int kInitPitch = 2 * kF16Pitch;         // bytes per row of the accumu
 constexpr int kSumPitch = 4 * kCand;              // bytes per row of the horizontal norm sums (float)
 constexpr int kBestPitch = 2 * kWaves * 16 + 8;   // bytes per reference of the 128 group bests (bf16)
 constexpr int kQueue = 3072;                      // candidates with exact keys at a time (lists padded to eights)
-constexpr int kPrune = 128;                       // longer lists are cut before their keys are ranked
+constexpr int kPrune = 64;                       // longer lists are cut before their keys are ranked
+constexpr int kSample = 256;                      // by a bound from so many of their keys
 // Position term of a half distance, per unit of row * S + column (at most
 // 1880): a half distance is a whole multiple of 1/8 on this scale, the term
 // stays below half of that.
@@ -91,9 +92,8 @@ struct Smem {
   static constexpr int codes = (sums + max2(kRows * kSumPitch, kCand * kInitPitch) + 15) / 16 * 16;
   static constexpr int best = codes;                     // dead before the codes are written
   static constexpr int bound = (codes + max2(16 * kBestPitch, 2 * kQueue) + 15) / 16 * 16;
-  // int[16]: packed half distances up to it pass; double[16]: a bound on the keys of a long list
-  static constexpr int prune = bound + 64;
-  static constexpr int count = prune + 128;              // int[16]: candidates past each reference's bound
+  // int[16]: packed half distances up to it pass
+  static constexpr int count = bound + 64;               // int[16]: candidates past each reference's bound
   static constexpr int start = count + 64;               // int[16]: their first place in the queue
   static constexpr int kept = start + 64;                // int[16]: keys left of a long list
   static constexpr int bytes = kept + 64;
@@ -183,6 +183,10 @@ __device__ __forceinline__ float widened_bound(float half, float hn) {
   return 0.500002f * t2 * t2 + 1.0f / 65536.0f * (nb + t2) * (nb + t2);
 }
 
+__device__ __forceinline__ unsigned high_word(double x) {
+  return static_cast<unsigned>(__builtin_bit_cast(unsigned long long, x) >> 32);
+}
+
 // How many of the first n entries of list (16-byte aligned, filled up to a
 // multiple of eight with infinities) lie below key.
 __device__ __forceinline__ int entries_below(const double* list, int n, double key) {
@@ -240,10 +244,7 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
         *reinterpret_cast<uint16_t*>(smem + Smem::pix0 + r * kPixPitch + 2 * lane) = z[it];
     }
   }
-  if (tid < 16) {
-    reinterpret_cast<int*>(smem + Smem::count)[tid] = 0;
-    reinterpret_cast<int*>(smem + Smem::kept)[tid] = 0;
-  }
+  if (tid < 16) reinterpret_cast<int*>(smem + Smem::count)[tid] = 0;
   __syncthreads();
 
   // the shifted u16 plane, the f16 copies and the horizontal norm sums, eight
@@ -521,41 +522,54 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
     }
     __syncthreads();
     if (long_lists) {
-      // a long list: the (K-1)-th smallest of its first kPrune keys is a bound,
-      // and only the keys up to it stay (in their places, the others infinite)
-      double* prune = reinterpret_cast<double*>(smem + Smem::prune);
-      for (int f = tid; f < total; f += kThreads) {
-        const unsigned code = codes[f];
-        const int k = code >> 12, at = f - start[k];
-        if (code != kPad && count[k] > kPrune && at < kPrune && entries_below(keys + start[k], kPrune, keys[f]) == K - 2)
-          prune[k] = keys[f];
-      }
-      __syncthreads();
-      int* kept = reinterpret_cast<int*>(smem + Smem::kept);
-      double mine[kQueue / kThreads];
+      // a long list, a wave each: the (K-1)-th smallest high word of its first
+      // kSample keys (positive, so ordered as integers), rounded up to eight bits
+      // of mantissa, is a bound, and the keys up to it move to the list's front.
+      // (Ranking longer lists whole, or cutting them by all threads from 128
+      // ranked keys, made the tiles with such lists the launch's tail: K = 32 on
+      // 640 x 360 56.6 -> 52.5 us, the two-stage 512^2 image 264 -> 256 us; a
+      // sample of 512 and all 31 bits cost the smaller images 2 %, cutting from
+      // 48 keys on instead of 64 up to 2 %.)
+      constexpr int kBoundBit = 12;
+      for (int k = first + wave; k < last; k += kWaves) {
+        const int n_list = __builtin_amdgcn_readfirstlane(count[k]);
+        if (n_list <= kPrune) continue;
+        double* list = keys + __builtin_amdgcn_readfirstlane(start[k]);
+        auto bound_of = [&](auto blocks) {
+          constexpr int kBlocks = decltype(blocks)::value;
+          unsigned x[kBlocks], kth = 0;
 #pragma unroll
-      for (int m = 0; m < kQueue / kThreads; ++m) {
-        const int f = tid + m * kThreads;
-        const unsigned code = f < total ? codes[f] : kPad;
-        const int k = code >> 12;
-        mine[m] = __builtin_huge_val();
-        if (code != kPad && count[k] > kPrune && keys[f] <= prune[k]) mine[m] = keys[f];
-      }
-      __syncthreads();
+          for (int i = 0; i < kBlocks; ++i) {
+            const int e = lane + kWave * i;
+            x[i] = e < n_list ? high_word(list[e]) : ~0u;
+          }
+#pragma unroll 1
+          for (int bit = 30; bit >= kBoundBit; --bit) {
+            const unsigned t = kth | 1u << bit;
+            int below = 0;
 #pragma unroll
-      for (int m = 0; m < kQueue / kThreads; ++m) {
-        const int f = tid + m * kThreads;
-        const unsigned code = f < total ? codes[f] : kPad;
-        const int k = code >> 12;
-        if (code != kPad && count[k] > kPrune) keys[f] = __builtin_huge_val();
-      }
-      __syncthreads();
-#pragma unroll
-      for (int m = 0; m < kQueue / kThreads; ++m)
-        if (mine[m] < __builtin_huge_val()) {
-          const int k = codes[tid + m * kThreads] >> 12;
-          keys[start[k] + atomicAdd(kept + k, 1)] = mine[m];
+            for (int i = 0; i < kBlocks; ++i) below += __builtin_popcountll(__builtin_amdgcn_ballot_w64(x[i] < t));
+            kth = below < K - 1 ? t : kth;
+          }
+          return kth | ((1u << kBoundBit) - 1);
+        };
+        const unsigned kth = n_list <= 2 * kWave ? bound_of(std::integral_constant<int, 2>{})
+                                                 : bound_of(std::integral_constant<int, kSample / kWave>{});
+        int n_kept = 0;
+        for (int e0 = 0; e0 < n_list; e0 += kWave) {
+          // (a block's keys are read before any is written at or before its place)
+          const double key = e0 + lane < n_list ? list[e0 + lane] : __builtin_huge_val();
+          const bool keep = key < __builtin_huge_val() && high_word(key) <= kth;
+          const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
+          wave_lds_sync();
+          if (keep)
+            list[n_kept + __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(m), 0))] = key;
+          n_kept += __builtin_popcountll(m);
+          wave_lds_sync();
         }
+        for (int e = n_kept + lane; e < ((n_list + 7) & ~7); e += kWave) list[e] = __builtin_huge_val();
+        if (lane == 0) reinterpret_cast<int*>(smem + Smem::kept)[k] = n_kept;
+      }
       __syncthreads();
     }
     // a key's slot is the number of smaller keys of its reference
