@@ -42,8 +42,8 @@
 // distances and two workgroups per CU the 4096^2 image took 3.0 ms instead of
 // 2.6, and with f16 copies 22 instead of 8 banks apart 2.6 instead of 2.45.
 // Against the earlier kernel (exact float64 keys of all pairs from int8
-// products and a norm table), K = 16 / 32: 512^2 87 / 112 -> 47 / 75 us,
-// 4096^2 2.93 / 3.56 -> 2.46 / 3.03 ms, 128^2 26 / 31 -> 11 / 28 us.
+// products and a norm table), K = 16 / 32: 512^2 87 / 112 -> 46 / 61 us,
+// 4096^2 2.93 / 3.56 -> 2.46 / 3.0 ms, 128^2 26 / 31 -> 11 / 27 us.
 #include "common.h"
 #include "kernels.h"
 #include "stack_body.h"
