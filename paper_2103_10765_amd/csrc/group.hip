@@ -139,18 +139,18 @@ enum GroupShape {
 // an even four groups per wave); inverse transforms go 8 blocks at a time
 // through each wave's scratch, without a prefetch of the next group (the other
 // waves hide the loads).  kOneTile is a choice of the autotuner for the
-// hard-threshold kernel (K <= 16).  That kernel's filter holds all K inverse
-// blocks until its weight is known, so K = 32 runs eight waves and one tile per
-// CU.
+// hard-threshold kernel (K <= 16).  That kernel at K = 32 takes two tiles of
+// twelve waves, 80 registers; 16 blocks at a time through the scratch of eight
+// waves, two tiles a little too large for one CU's LDS ran one by one (kernel us
+// 512^2 107 -> 85, 1024^2 405 -> 287, 2048^2 1503 -> 1002).
 template <int K, bool HT, int SHAPE>
 struct GroupCfg {
-  static constexpr bool large = HT && K > 16;
   using T = std::conditional_t<SHAPE == kTiny, Tile<2, 4>, std::conditional_t<SHAPE == kSmall, Tile<4, 4>, Tile<8, 8>>>;
   static constexpr bool prefetch = SHAPE == kOneTile;
-  static constexpr int chunk = SHAPE == kOneTile || large ? (K > 16 ? 16 : K) : (K > 8 ? 8 : K);
+  static constexpr int chunk = SHAPE == kOneTile ? K : (K > 8 ? 8 : K);
   using SlotTable = Slots<K, T>;
-  static constexpr int waves = SHAPE == kOneTile ? 16 : large || SHAPE != kTwoTiles ? 8 : HT ? 16 : 12;
-  static constexpr int tiles = SHAPE == kOneTile || large ? 1 : SHAPE == kTwoTiles ? 2 : 3;
+  static constexpr int waves = SHAPE == kOneTile ? 16 : SHAPE != kTwoTiles ? 8 : HT && K <= 16 ? 16 : 12;
+  static constexpr int tiles = SHAPE == kOneTile ? 1 : SHAPE == kTwoTiles ? 2 : 3;
   static constexpr int threads = waves * kWave;
   static constexpr int min_waves_per_simd = waves * tiles / 4;
   static_assert(SHAPE != kOneTile || (HT && K <= 16), "only the hard-threshold kernel of small groups prefetches");
@@ -523,7 +523,7 @@ __device__ __forceinline__ void group_ht_body(acc_t* acc,
 #pragma unroll
     for (int k = 0; k < K; ++k) v[k] = keep(k, v[k]) ? v[k] : 0.0f;
     haar_inv_banded<K>(v);
-    // inverse 2-D transform.  The two coarse levels are a 4 x 4 corner: all K
+    // inverse 2-D transform.  The two coarse levels are a 4 x 4 corner: up to 16
     // blocks' corners go through the scratch together (fuller waves than a
     // chunk's), and come back in the registers ll, a column per lane.
     constexpr int CH = Cfg::chunk;
@@ -531,22 +531,25 @@ __device__ __forceinline__ void group_ht_body(acc_t* acc,
     constexpr Mat8 S4 = bior_synthesis(4);
     constexpr Mat8 S8 = bior_synthesis(8);
     constexpr int kCorner = 20, kCornerPitch = 5;  // conflict-free rows and columns
-    constexpr int kPasses = (K * 4 + kWave - 1) / kWave;
-    static_assert(K * kCorner <= CH * kBlockFloats, "the corners fit the scratch");
-    float ll[kPasses][4];
-    wave_lds_sync();  // earlier reads of the scratch are done
-    if (a < 4 && b < 4) {
-#pragma unroll
-      for (int k = 0; k < K; ++k) xw[k * kCorner + a * kCornerPitch + b] = v[k];
-    }
-    wave_lds_sync();
+    constexpr int KC = K > 16 ? 16 : K;
+    static_assert(KC * kCorner <= CH * kBlockFloats && KC * 4 <= kWave, "the corners fit the scratch and a wave");
+    float ll[K / KC][4];
     auto line4 = [&](const float* x, float* y) { apply_mat<4>(S4, x, y); };
-    transform_level<K, 2, kCorner, kCornerPitch>(xw, lane, [&](const float* x, float* y) { apply_mat<2>(S2, x, y); });
-    transform_rows<K, 4, kCorner, kCornerPitch>(xw, lane, line4);
-    transform_columns<K, 4, kCorner, kCornerPitch>(xw, lane, line4, [&](int pass, int, int, const float (&y)[8]) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) ll[pass][i] = y[i];
-    });
+    for (int part = 0; part < K / KC; ++part) {
+      wave_lds_sync();  // earlier reads of the scratch are done
+      if (a < 4 && b < 4) {
+#pragma unroll
+        for (int k = 0; k < KC; ++k) xw[k * kCorner + a * kCornerPitch + b] = v[part * KC + k];
+      }
+      wave_lds_sync();
+      transform_level<KC, 2, kCorner, kCornerPitch>(xw, lane, [&](const float* x, float* y) { apply_mat<2>(S2, x, y); });
+      transform_rows<KC, 4, kCorner, kCornerPitch>(xw, lane, line4);
+      transform_columns<KC, 4, kCorner, kCornerPitch>(xw, lane, line4, [&](int, int, int, const float (&y)[8]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ll[part][i] = y[i];
+      });
+    }
     // the fine level, kChunk blocks at a time; the spatial total-variation
     // terms are read while a chunk is parked there
     float u[K];
@@ -557,14 +560,11 @@ __device__ __forceinline__ void group_ht_body(acc_t* acc,
 #pragma unroll
       for (int k = 0; k < CH; ++k) own[k * kBlockFloats] = v[c0 + k];
       wave_lds_sync();
+      const int it = lane - 4 * (c0 % KC);  // corner column it % 4 of the chunk's block it / 4
+      if (it >= 0 && it < 4 * CH) {
+        float* col = xw + it / 4 * kBlockFloats + it % 4;
 #pragma unroll
-      for (int pass = 0; pass < kPasses; ++pass) {
-        const int it = pass * kWave + lane - 4 * c0;  // corner column it % 4 of the chunk's block it / 4
-        if (it >= 0 && it < 4 * CH) {
-          float* col = xw + it / 4 * kBlockFloats + it % 4;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) col[i * kScratchPitch] = ll[pass][i];
-        }
+        for (int i = 0; i < 4; ++i) col[i * kScratchPitch] = ll[c0 / KC][i];
       }
       wave_lds_sync();
       transform_level<CH, 8>(xw, lane, [&](const float* x, float* y) { apply_mat<8>(S8, x, y); });
