@@ -128,17 +128,20 @@ struct Slots {
 
 // Shapes of the group kernels.
 enum GroupShape {
-  kTwoTiles,  // 8 x 8 references by 12 waves (hard threshold: 16), two tiles per CU
+  kTwoTiles,  // 8 x 8 references by 16 waves (K = 32: 12), two tiles per CU
   kOneTile,   // 8 x 8 references by 16 waves, one tile per CU, the next group's spectra in flight
   kSmall,     // 4 x 4 references by 8 waves
   kTiny,      // 2 x 4 references by 8 waves
 };
 
-// Launch shape of a group kernel.  Tiles share a CU so that it has 24 waves
-// (six per SIMD; two of sixteen for the hard-threshold kernel at 54 registers,
-// an even four groups per wave); inverse transforms go 8 blocks at a time
-// through each wave's scratch, without a prefetch of the next group (the other
-// waves hide the loads).  kOneTile is a choice of the autotuner for the
+// Launch shape of a group kernel.  Tiles share a CU so that it has 32 waves (64
+// registers: K <= 16; an even four groups per wave) or 24 (80: K = 32);
+// inverse transforms go 8 blocks at a time through each wave's scratch, without
+// a prefetch of the next group (the other waves hide the loads).  The Wiener
+// kernel by 12 instead of 16 waves, us: K = 2, 4 (bound by latency) 1024^2 76 |
+// 92 against 66 | 81, 2048^2 247 | 296 against 221 | 273; K = 8, 16 2048^2 388 |
+// 599 against 379 | 594; at K = 32 sixteen waves leave room for one tile, 1097
+// against 1044.  kOneTile is a choice of the autotuner for the
 // hard-threshold kernel (K <= 16).  That kernel at K = 32 takes two tiles of
 // twelve waves, 80 registers; 16 blocks at a time through the scratch of eight
 // waves, two tiles a little too large for one CU's LDS ran one by one (kernel us
@@ -149,7 +152,7 @@ struct GroupCfg {
   static constexpr bool prefetch = SHAPE == kOneTile;
   static constexpr int chunk = SHAPE == kOneTile ? K : (K > 8 ? 8 : K);
   using SlotTable = Slots<K, T>;
-  static constexpr int waves = SHAPE == kOneTile ? 16 : SHAPE != kTwoTiles ? 8 : HT && K <= 16 ? 16 : 12;
+  static constexpr int waves = SHAPE == kOneTile ? 16 : SHAPE != kTwoTiles ? 8 : K <= 16 ? 16 : 12;
   static constexpr int tiles = SHAPE == kOneTile ? 1 : SHAPE == kTwoTiles ? 2 : 3;
   static constexpr int threads = waves * kWave;
   static constexpr int min_waves_per_simd = waves * tiles / 4;

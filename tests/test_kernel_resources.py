@@ -70,3 +70,12 @@ def test_first_stage_groups_of_32_share_a_cu(kernels, variant):
     24 waves per CU, nothing in scratch memory."""
     k = kernels[f"group_ht_kernel<32, {variant}, 0>"]
     assert waves_per_cu(k) >= 24 and k[".private_segment_fixed_size"] == 0
+
+
+@pytest.mark.parametrize("K", [2, 4, 8, 16])
+@pytest.mark.parametrize("batch", ["false", "true"])
+def test_second_stage_groups_of_up_to_16_fill_a_cu(kernels, K, batch):
+    """The Wiener kernel at K <= 16, single image and batch: 32 waves per CU
+    (small groups are bound by latency), nothing in scratch memory."""
+    k = kernels[f"group_wiener_kernel<{K}, {batch}, 0>"]
+    assert waves_per_cu(k) >= 32 and k[".private_segment_fixed_size"] == 0
