@@ -880,28 +880,31 @@ int group_items_for(int H, int W) { return tiles_of<Tile<8, 8>>(H, W); }
 
 int reduce_items_for(int H, int W) { return reduce_items(H, W); }
 
-// The shapes of a single image's launches, by its tiles of 8 x 8 references.
-// Two tiles per CU are 512 of them: below that CUs idle, or hold one tile while
-// others work on two, unless the tiles are smaller; small tiles pay for it with
-// more footprint cells to clear and add per reference.  Whole first stage, us,
-// 8 x 8 | 4 x 4 | 2 x 4 references: 36 tiles (128^2) 38 | 25 | 23; 64 (192^2)
-// 44 | 33 | 32; 121 (256^2) 52 | 45 | 46; 256 (384^2, one per CU) 66 | 68 | 70;
-// 294 (321 x 481) 81 | 73 | 75; 361 (448^2) 89 | 86 | 90; 484 (512^2)
-// 102 | 105 | 109; 1344 (1001 x 750) 262 | 255 | 274; 29241 (4096^2)
-// 4899 | 5342 | 5418.
-static GroupShape ht_shape_for(int H, int W) {
+// The shapes of a single image's launches, by its tiles of 8 x 8 references and
+// the 256 CUs.  A CU takes two tiles at a time.  Below 256 tiles CUs idle unless
+// the tiles are smaller, from 193 on hardly any; just above, a few CUs work on
+// two tiles while the rest have one.  Small tiles pay for it with more footprint
+// cells to clear and add per reference, the more the wider the window.
+// Kernel us, 8 x 8 | 4 x 4 | 2 x 4 references, windows of 39 and of 21:
+//   tiles  first stage K = 16              Wiener K = 16                  Wiener K = 32
+//     36   26 13 12    25 13 10            20 11 10    20 11 9            35 15 12    34 15 12
+//     64   26 15 16    26 14 13            20 13 13    20 12 12           35 18 17    35 17 16
+//    121   26 21 25    26 19 20            21 17 22    20 16 19           36 25 28    35 23 25
+//    196   28 28 36    27 22 26            22 24 30    21 22 26           38 37 41    36 33 34
+//    256   31 37 47    28 30 34            26 33 38    24 28 32           43 49 51    39 44 40
+//    289   44 42 53    41 34 40            36 37 43    33 32 36           59 56 61    55 48 48
+//    324   45 45 56    41 38 42            37 41 47    34 35 39           61 63 66    56 55 52
+//    361   46 48 59    42 39 44            38 42 50    35 36 41           65 65 71    57 55 56
+//    400   47 53 67    43 44 50            41 47 56    36 40 44           68 70 79    60 64 59
+//   1849  161 213 263  141 152 175        177 194 241  162 164 183       290 307 349  262 248 266
+// Smaller K go like K = 16, the first stage's K = 32 like the Wiener kernel's.
+// From 257 tiles on, 4 x 4 references where they win: the first stage and Wiener
+// groups of 32, up to 300 tiles, 380 for windows up to 31.
+static GroupShape shape_for(int H, int W, int R, bool above_256) {
   const int t = tiles_of<Tile<8, 8>>(H, W);
   if (t <= 64) return kTiny;
-  return t <= 192 || (t > 256 && t <= 420) ? kSmall : kTwoTiles;
+  return t <= 192 || (above_256 && t > 256 && t <= (R > 15 ? 300 : 380)) ? kSmall : kTwoTiles;
 }
-
-// The Wiener kernel (more arithmetic per footprint cell) takes the smallest
-// tile up to the same size.  Whole second stage, us, 8 x 8 | 4 x 4 | 2 x 4
-// references: 128^2 54 | 35 | 31; 192^2 59 | 41 | 38; 256^2 66 | 51 | 52; 384^2
-// 89 | 86 | 85; 321 x 481 106 | 93 | 92; 448^2 119 | 112 | 112; 512^2
-// 141 | 136 | 137 (other images 67 | 70 | 71 for the kernel alone); 1001 x 750
-// 372 | 365 | 368; 4096^2 8051 | 8200 | 8398.
-static GroupShape wiener_shape_for(int H, int W) { return tiles_of<Tile<8, 8>>(H, W) <= 420 ? kTiny : kTwoTiles; }
 
 template <int K, int SHAPE>
 static hipError_t launch_ht_shape(const ImgRec& one, const WorkList* wl, int R, const HtParams& hp, int recompute,
@@ -929,7 +932,7 @@ static hipError_t launch_ht_k(const ImgRec& one, const WorkList* wl, int R, cons
                               int shape, hipStream_t st) {
   if constexpr (K <= 16)
     if (shape == 1) return launch_ht_shape<K, kOneTile>(one, wl, R, hp, recompute, st);
-  switch (wl ? kTwoTiles : ht_shape_for(one.H, one.W)) {
+  switch (wl ? kTwoTiles : shape_for(one.H, one.W, R, true)) {
     case kTiny: return launch_ht_shape<K, kTiny>(one, wl, R, hp, recompute, st);
     case kSmall: return launch_ht_shape<K, kSmall>(one, wl, R, hp, recompute, st);
     default: return launch_ht_shape<K, kTwoTiles>(one, wl, R, hp, recompute, st);
@@ -972,8 +975,11 @@ static hipError_t launch_wiener_shape(const ImgRec& one, const WorkList* wl, int
 
 template <int K>
 static hipError_t launch_wiener_k(const ImgRec& one, const WorkList* wl, int R, hipStream_t st) {
-  if (!wl && wiener_shape_for(one.H, one.W) == kTiny) return launch_wiener_shape<K, kTiny>(one, wl, R, st);
-  return launch_wiener_shape<K, kTwoTiles>(one, wl, R, st);
+  switch (wl ? kTwoTiles : shape_for(one.H, one.W, R, K > 16)) {
+    case kTiny: return launch_wiener_shape<K, kTiny>(one, wl, R, st);
+    case kSmall: return launch_wiener_shape<K, kSmall>(one, wl, R, st);
+    default: return launch_wiener_shape<K, kTwoTiles>(one, wl, R, st);
+  }
 }
 
 hipError_t launch_group_wiener(const ImgRec& one, const WorkList* wl, int R, int K, hipStream_t st) {

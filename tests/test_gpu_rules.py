@@ -1,0 +1,68 @@
+"""The rules that choose a kernel's shape do not choose a slow one: times of
+the same work by two routes on one GPU, compared with each other (the smallest
+of several runs; the margins are wider than such runs differ)."""
+import numpy as np
+import pytest
+
+from paper_2103_10765_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+SIG = 25.0 / 255.0
+
+
+@pytest.fixture(scope="module")
+def G():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible to torch")
+    from paper_2103_10765_amd import gbm3d
+    return gbm3d
+
+
+@pytest.fixture(scope="module")
+def ctx(G):
+    c = G.Context(0)
+    yield c
+    c.close()
+
+
+def up(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def kernel_ms(ctx, kernel, run):
+    run()
+    best = float("inf")
+    ctx.timing(True)
+    try:
+        for _ in range(8):
+            ctx.timing_reset()
+            run()
+            run()
+            ms, n = ctx.timing_read(kernel)
+            best = min(best, ms / n)
+    finally:
+        ctx.timing(False)
+    return best
+
+
+@pytest.mark.parametrize("S", [21, 39])
+@pytest.mark.parametrize("n", [192, 320, 384, 416, 448, 480])
+def test_group_tiles_of_a_single_image(G, ctx, n, S):
+    """A batch's group launches take the largest reference tiles whatever the
+    number of tiles; a single image's tiles are chosen by that number and are
+    never much slower."""
+    x = up(synth.make_case(n, n, SIG, 3)[1])
+    pilot = up(synth.make_case(n, n, SIG / 12, 3)[1])
+    for K in (2, 8, 16, 32):
+        p = G.default_params(search=S, k_ht=K, k_wiener=K)
+        for kernel, one, batch in (
+                ("group_ht", lambda: ctx.basic(x, SIG, p),
+                 lambda: ctx.denoise_batch([x], [SIG], params=p, basic_only=True)),
+                ("group_wiener", lambda: ctx.wiener(x, pilot, SIG, p),
+                 lambda: ctx.denoise_batch([x], [SIG], pilots=[pilot], params=p))):
+            a, b = kernel_ms(ctx, kernel, one), kernel_ms(ctx, kernel, batch)
+            print(kernel, n, S, K, f"{1e3 * a:.1f} us, largest tiles {1e3 * b:.1f} us", flush=True)
+            assert a <= 1.2 * b, (kernel, n, S, K, a, b)
