@@ -58,7 +58,9 @@ extern "C" {
 
 /* block-matching kernels; both give the same indices (Sec. 2: eq. dfg
  * summed shift by shift, or the norm/cross-correlation split of Theorem 1) */
-#define GBM3D_BM_AUTO  0  /* the autotuned choice for the shape, else CORR  */
+#define GBM3D_BM_AUTO  0  /* the autotuned choice for the shape, else CORR;
+                             SHIFT for windows up to 5 (images from about
+                             400^2 on) and 11 (from about 660^2 on)          */
 #define GBM3D_BM_SHIFT 1  /* per displacement: squared differences, box sums
                              at the reference positions (float64 vector ALU) */
 #define GBM3D_BM_CORR  2  /* per 4x4 reference tile: f16 matrix-core distances
@@ -348,7 +350,7 @@ int gbm3d_timing_reset(gbm3d_ctx* ctx);
  * leave bm_method or bm_split at 0 use the record of their class (a batch:
  * the class of all its tiles together); without one, the method recorded for
  * the nearest class of the same K and search, with the split chosen by size;
- * else GBM3D_BM_CORR.  The stage-1 shape likewise (default: two tiles).
+ * else the rule at GBM3D_BM_AUTO.  The stage-1 shape likewise (default: two tiles).
  * Timing uses HIP events on `stream` (the call synchronises it).
  * best_method, best_split and best_ms (milliseconds per matching run) may be
  * NULL.  Errors: GBM3D_EINVAL for bad shapes, params, K or reps < 1. */

@@ -54,25 +54,6 @@ namespace {
 
 constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * kWave;
-constexpr int kMaxNb = (2 * kMaxR + 10 + 3) / 4;  // candidate blocks per axis: 12
-constexpr int kCand = 4 * kMaxNb;                 // candidate rows / columns: 48
-constexpr int kRows = kCand + 7;                  // pixel rows: 55
-constexpr int kGroups = kMaxNb + 1;               // 4-pixel column groups of the f16 planes: 13
-constexpr int kPixCols = 4 * (kMaxNb + 2);        // columns of the u16 planes: 56
-constexpr int kPixPitch = 2 * kPixCols;           // bytes per u16 plane row
-constexpr int kPixPlane = kRows * kPixPitch;
-// The f16 plane is kept in four copies shifted by 0..3 pixels, so that the
-// eight pixels of a candidate row start at an 8-byte boundary of the copy its
-// column asks for.  The LDS serves 16 lanes of an 8-byte read at a time from 32
-// banks: with rows 26 words apart and copies 8 words apart (modulo 32) the
-// four rows x four copies that 16 candidates read fall on all 32 banks once.
-constexpr int kF16Pitch = 8 * kGroups;            // 104 bytes
-constexpr int kF16Copy = (kRows * kF16Pitch - 32 + 127) / 128 * 128 + 32;
-static_assert(kF16Copy % 128 == 32 && kF16Copy >= kRows * kF16Pitch, "copies eight banks apart");
-constexpr int kInitPitch = 2 * kF16Pitch;         // bytes per row of the accumulator starts (float)
-constexpr int kSumPitch = 4 * kCand;              // bytes per row of the horizontal norm sums (float)
-constexpr int kBestPitch = 2 * kWaves * 16 + 8;   // bytes per reference of the 128 group bests (bf16)
-constexpr int kQueue = 3072;                      // candidates with exact keys at a time (lists padded to eights)
 constexpr int kPrune = 64;                       // longer lists are cut before their keys are ranked
 constexpr int kSample = 256;                      // by a bound from so many of their keys
 // Position term of a half distance, per unit of row * S + column (at most
@@ -81,28 +62,58 @@ constexpr int kSample = 256;                      // by a bound from so many of 
 constexpr float kTieStep = 1.0f / 32768.0f;
 
 constexpr int max2(int a, int b) { return a > b ? a : b; }
+constexpr int min2(int a, int b) { return a < b ? a : b; }
 
-struct Smem {
+// A tile's region and its LDS for a grid of 2 Q x 4 C candidate blocks, of which
+// a wave takes Q x C.  Windows up to 7, 15, 23 and 39 have grids of their own: a
+// fixed region of 12 x 12 blocks' size made every window up to 17 cost the same
+// (1024^2, K = 2 / 8, us: window 7 92 / 98 -> 59 / 64, window 15 95 / 101 -> 76 / 81).
+template <int Q, int C>
+struct Geo {
+  static constexpr int kSteps = Q * C;
+  static constexpr int kCandRows = 8 * Q, kCandCols = 16 * C;  // candidate positions
+  static constexpr int kRows = kCandRows + 7;                  // pixel rows
+  static constexpr int kGroups = kCandCols / 4 + 1;            // 4-pixel column groups of the f16 planes
+  static constexpr int kPixCols = kCandCols + 8;               // columns of the u16 planes
+  static constexpr int kPixPitch = 2 * kPixCols;               // bytes per u16 plane row
+  static constexpr int kPixPlane = kRows * kPixPitch;
+  // The f16 plane is kept in four copies shifted by 0..3 pixels, so that the
+  // eight pixels of a candidate row start at an 8-byte boundary of the copy its
+  // column asks for.  The LDS serves 16 lanes of an 8-byte read at a time from 32
+  // banks: with rows 26, 18 or 10 words apart and copies 8 words apart (modulo
+  // 32) the four rows x four copies that 16 candidates read fall on all 32 banks
+  // once.
+  static constexpr int kF16Pitch = 8 * kGroups;
+  static constexpr int kF16Copy = (kRows * kF16Pitch - 32 + 127) / 128 * 128 + 32;
+  static_assert(kF16Pitch / 4 % 8 == 2 && kF16Copy % 128 == 32 && kF16Copy >= kRows * kF16Pitch, "copies eight banks apart");
+  static constexpr int kInitPitch = 2 * kF16Pitch;   // bytes per row of the accumulator starts (float)
+  static constexpr int kSumPitch = 4 * kCandCols;    // bytes per row of the horizontal norm sums (float)
+  static constexpr int kBestPitch = 2 * kWaves * 16 + 8;  // bytes per reference of the 128 group bests (bf16)
+
   static constexpr int pix0 = 0;                         // u16 plane, and the same shifted by one pixel:
   static constexpr int pix1 = pix0 + kPixPlane;          // any candidate row starts at a word of one of them
   static constexpr int f16 = (pix1 + kPixPlane + 15) / 16 * 16;
   // the accumulator starts replace the horizontal norm sums they come from
   static constexpr int sums = (f16 + 4 * kF16Copy + 15) / 16 * 16;
   static constexpr int init = sums;
-  static constexpr int codes = (sums + max2(kRows * kSumPitch, kCand * kInitPitch) + 15) / 16 * 16;
+  static constexpr int codes = (sums + max2(kRows * kSumPitch, kCandRows * kInitPitch) + 15) / 16 * 16;
   static constexpr int best = codes;                     // dead before the codes are written
+  // candidates with exact keys at a time (lists padded to eights); the keys take
+  // the place of the products' operands, which are dead by then
+  static constexpr int kQueue = min2(3072, (codes - f16) / 64 * 8);
   static constexpr int bound = (codes + max2(16 * kBestPitch, 2 * kQueue) + 15) / 16 * 16;
   // int[16]: packed half distances up to it pass
   static constexpr int count = bound + 64;               // int[16]: candidates past each reference's bound
   static constexpr int start = count + 64;               // int[16]: their first place in the queue
   static constexpr int kept = start + 64;                // int[16]: keys left of a long list
   static constexpr int bytes = kept + 64;
-  static constexpr int keys = f16;                       // the products' operands are dead by then
+  static constexpr int keys = f16;
+  static constexpr int kMaxWindow = kCandRows < kCandCols ? kCandRows - 9 : kCandCols - 9;
+  static_assert(kQueue >= kMaxWindow * kMaxWindow + 7, "one reference always fits the queue");
+  static_assert(kGroups % 2 == 1 && kPixCols / 8 * 2 == kGroups + 1, "f16 planes end in half an eight-column item");
 };
-static_assert(Smem::bytes <= 160 * 1024 / 3 / 1280 * 1280, "three workgroups per CU");
-static_assert(8 * kQueue <= Smem::codes - Smem::f16, "keys fit the operands' area");
-static_assert(kGroups % 2 == 1 && kPixCols / 8 * 2 == kGroups + 1, "f16 planes end in half an eight-column item");
-static_assert(kQueue >= (2 * kMaxR + 1) * (2 * kMaxR + 1) + 7, "one reference always fits the queue");
+constexpr int kMaxNb = (2 * kMaxR + 10 + 3) / 4;  // candidate blocks per axis: 12
+static_assert(Geo<6, 3>::bytes <= 160 * 1024 / 3 / 1280 * 1280, "three workgroups per CU");
 
 __host__ __device__ constexpr int blocks_per_axis(int R) { return (2 * R + 10 + 3) / 4; }
 
@@ -140,14 +151,15 @@ __device__ __forceinline__ float square2(unsigned x) {
 // pixel planes, rank the candidate's displacement rank.  |a - b| is formed on
 // packed u16 and its square from byte digits, 65536 hh + 512 hl + ll, each
 // sum of 64 terms below 2^23.
+template <typename G>
 __device__ __forceinline__ double exact_key(const unsigned char* smem, int ry, int rx, int cy, int cx, int rank) {
-  const unsigned char* pa = smem + ((cx & 1) ? Smem::pix1 : Smem::pix0) + cy * kPixPitch + 2 * (cx & ~1);
-  const unsigned char* pb = smem + ((rx & 1) ? Smem::pix1 : Smem::pix0) + ry * kPixPitch + 2 * (rx & ~1);
+  const unsigned char* pa = smem + ((cx & 1) ? G::pix1 : G::pix0) + cy * G::kPixPitch + 2 * (cx & ~1);
+  const unsigned char* pb = smem + ((rx & 1) ? G::pix1 : G::pix0) + ry * G::kPixPitch + 2 * (rx & ~1);
   unsigned hh = 0, hl = 0, ll = 0;
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
-    const unsigned* a = reinterpret_cast<const unsigned*>(pa + r * kPixPitch);
-    const unsigned* b = reinterpret_cast<const unsigned*>(pb + r * kPixPitch);
+    const unsigned* a = reinterpret_cast<const unsigned*>(pa + r * G::kPixPitch);
+    const unsigned* b = reinterpret_cast<const unsigned*>(pb + r * G::kPixPitch);
     unsigned d[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -211,6 +223,7 @@ __device__ __forceinline__ int entries_below(const double* list, int n, double k
 template <int Q, int C, bool WIDE>
 __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* __restrict__ img_,
                                           int16_t* __restrict__ idx_, int H, int W, int R, int K, int item) {
+  using G = Geo<Q, C>;
   const auto img = to_global(img_);
   const auto idx = to_global(idx_);
   const int nRy = (H + kStep - 1) / kStep, nRx = (W + kStep - 1) / kStep;
@@ -225,11 +238,11 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
   // a column, all loads issued before the first store; rows and columns wrap
   // at most once when the image is larger than the region and its margin
   {
-    static_assert(kPixCols <= kWave, "a row per wave");
-    constexpr int kIter = (kRows + kWaves - 1) / kWaves;
+    static_assert(G::kPixCols <= kWave, "a row per wave");
+    constexpr int kIter = (G::kRows + kWaves - 1) / kWaves;
     const int xl = x0 + lane, x = W >= kWave + kMaxR ? xl + (xl < 0 ? W : (xl >= W ? -W : 0)) : pmod(xl, W);
     unsigned short z[kIter];
-    const bool near = H >= kRows + kMaxR;
+    const bool near = H >= G::kRows + kMaxR;
 #pragma unroll
     for (int it = 0; it < kIter; ++it) {
       const int r = wave + it * kWaves;
@@ -240,24 +253,24 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
 #pragma unroll
     for (int it = 0; it < kIter; ++it) {
       const int r = wave + it * kWaves;
-      if (r < rows && lane < kPixCols)
-        *reinterpret_cast<uint16_t*>(smem + Smem::pix0 + r * kPixPitch + 2 * lane) = z[it];
+      if (r < rows && lane < G::kPixCols)
+        *reinterpret_cast<uint16_t*>(smem + G::pix0 + r * G::kPixPitch + 2 * lane) = z[it];
     }
   }
-  if (tid < 16) reinterpret_cast<int*>(smem + Smem::count)[tid] = 0;
+  if (tid < 16) reinterpret_cast<int*>(smem + G::count)[tid] = 0;
   __syncthreads();
 
   // the shifted u16 plane, the f16 copies and the horizontal norm sums, eight
   // columns per item.  Sums of eight squares are formed in one association
   // for every column, so equal blocks get equal norms.
   {
-    const unsigned centre = *reinterpret_cast<const uint16_t*>(smem + Smem::pix0 + (R + 8) * kPixPitch + 2 * (R + 8));
+    const unsigned centre = *reinterpret_cast<const uint16_t*>(smem + G::pix0 + (R + 8) * G::kPixPitch + 2 * (R + 8));
     const float shift = -0.5f * static_cast<float>(centre);
-    constexpr int kCols = kPixCols / 8;  // 7
-    static_assert(kRows * kCols <= kThreads, "one item per thread");
+    constexpr int kCols = G::kPixCols / 8;  // 7
+    static_assert(G::kRows * kCols <= kThreads, "one item per thread");
     const int r = tid / kCols, q = tid - r * kCols;
     if (r < rows) {
-      const unsigned char* src = smem + Smem::pix0 + r * kPixPitch + 16 * q;
+      const unsigned char* src = smem + G::pix0 + r * G::kPixPitch + 16 * q;
       // (the last item has no pixels past its own and repeats them)
       const unsigned char* src2 = src + (q < kCols - 1 ? 16 : 0);
       unsigned w[8], P[8], O[7];
@@ -267,7 +280,7 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
         w[2 * k] = t.x;
         w[2 * k + 1] = t.y;
       }
-      u32x2* odd = reinterpret_cast<u32x2*>(smem + Smem::pix1 + r * kPixPitch + 16 * q);
+      u32x2* odd = reinterpret_cast<u32x2*>(smem + G::pix1 + r * G::kPixPitch + 16 * q);
       odd[0] = u32x2{join(w[0], w[1]), join(w[1], w[2])};
       odd[1] = u32x2{join(w[2], w[3]), join(w[3], w[4])};
 #pragma unroll
@@ -278,15 +291,15 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
                                               f16x2));
 #pragma unroll
       for (int k = 0; k < 7; ++k) O[k] = join(P[k], P[k + 1]);
-      unsigned char* dst = smem + Smem::f16 + r * kF16Pitch + 16 * q;
+      unsigned char* dst = smem + G::f16 + r * G::kF16Pitch + 16 * q;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         if (h == 1 && q == kCols - 1) break;  // the f16 planes end in half an item
         const int e = 2 * h;
         *reinterpret_cast<u32x2*>(dst + 8 * h) = u32x2{P[e], P[e + 1]};
-        *reinterpret_cast<u32x2*>(dst + 8 * h + kF16Copy) = u32x2{O[e], O[e + 1]};
-        *reinterpret_cast<u32x2*>(dst + 8 * h + 2 * kF16Copy) = u32x2{P[e + 1], P[e + 2]};
-        *reinterpret_cast<u32x2*>(dst + 8 * h + 3 * kF16Copy) = u32x2{O[e + 1], O[e + 2]};
+        *reinterpret_cast<u32x2*>(dst + 8 * h + G::kF16Copy) = u32x2{O[e], O[e + 1]};
+        *reinterpret_cast<u32x2*>(dst + 8 * h + 2 * G::kF16Copy) = u32x2{P[e + 1], P[e + 2]};
+        *reinterpret_cast<u32x2*>(dst + 8 * h + 3 * G::kF16Copy) = u32x2{O[e + 1], O[e + 2]};
       }
       if (q < kCols - 1) {
         float e[7], o[7];
@@ -300,7 +313,7 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
           e[k] += e[k + 1];
           o[k] += o[k + 1];
         }
-        f32x4* sums = reinterpret_cast<f32x4*>(smem + Smem::sums + r * kSumPitch + 32 * q);
+        f32x4* sums = reinterpret_cast<f32x4*>(smem + G::sums + r * G::kSumPitch + 32 * q);
         sums[0] = f32x4{e[0] + e[2], o[0] + o[2], e[1] + e[3], o[1] + o[3]};
         sums[1] = f32x4{e[2] + e[4], o[2] + o[4], e[3] + e[5], o[3] + o[5]};
       }
@@ -309,13 +322,13 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
   __syncthreads();
   // accumulator starts N / 2 + position term, eight rows of a column per item
   {
-    constexpr int kSegs = kCand / 8;
+    constexpr int kSegs = Q, kCand = G::kCandCols;
     static_assert(kSegs * kCand <= kThreads, "one item per thread");
     const int col = tid % kCand, seg = tid / kCand;
     const bool active = seg < kSegs && 8 * seg < 4 * nb && col < 4 * nb;
     float a[15];
     if (active) {
-      const float* h = reinterpret_cast<const float*>(smem + Smem::sums) + 8 * seg * kCand + col;
+      const float* h = reinterpret_cast<const float*>(smem + G::sums) + 8 * seg * kCand + col;
 #pragma unroll
       for (int k = 0; k < 15; ++k) a[k] = h[k * kCand];  // (rows past the region only reach unused outputs)
 #pragma unroll
@@ -325,11 +338,11 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
     }
     __syncthreads();
     if (active) {
-      float* c = reinterpret_cast<float*>(smem + Smem::init + 8 * seg * kInitPitch) + col;
+      float* c = reinterpret_cast<float*>(smem + G::init + 8 * seg * G::kInitPitch) + col;
       const float row = kTieStep * static_cast<float>(S);
       float at = kTieStep * static_cast<float>(8 * seg * S + col);  // (exact: whole multiples below 2^11)
 #pragma unroll
-      for (int k = 0; k < 8; ++k, at += row) c[k * (kInitPitch / 4)] = fmaf(a[k] + a[k + 4], 0.5f, at);
+      for (int k = 0; k < 8; ++k, at += row) c[k * (G::kInitPitch / 4)] = fmaf(a[k] + a[k + 4], 0.5f, at);
     }
   }
   __syncthreads();
@@ -338,10 +351,10 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
   // (block row m / 4, column m % 4) or, negated, of reference m, so product h
   // covers block rows 4 h .. 4 h + 3; result lane (g, n) holds candidates (row
   // g, columns 0..3) against reference n
-  constexpr int kSteps = Q * C;
+  constexpr int kSteps = G::kSteps;
   const int wy = wave >> 2, wx = wave & 3;
   auto half_norm = [&](int ref) {
-    return reinterpret_cast<const float*>(smem + Smem::init)[(R + 3 * (ref >> 2)) * (kInitPitch / 4) + R + 3 * (ref & 3)];
+    return reinterpret_cast<const float*>(smem + G::init)[(R + 3 * (ref >> 2)) * (G::kInitPitch / 4) + R + 3 * (ref & 3)];
   };
   unsigned half[kSteps][2];  // bf16 pairs, truncated: columns 0, 1 and 2, 3
   {
@@ -357,18 +370,18 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
         col_in[k][i] =
             __builtin_amdgcn_ballot_w64(static_cast<unsigned>(16 * k + 4 * wx + i - 3 * v) <= static_cast<unsigned>(2 * R));
     const int rc = R + 3 * v;
-    const lds_byte* rp = (const lds_byte*)(smem + Smem::f16 + (rc & 3) * kF16Copy + (R + 3 * u + g) * kF16Pitch + (rc >> 2) * 8);
-    const f16x8 b0 = -read_row(rp), b1 = -read_row(rp + 4 * kF16Pitch);
+    const lds_byte* rp = (const lds_byte*)(smem + G::f16 + (rc & 3) * G::kF16Copy + (R + 3 * u + g) * G::kF16Pitch + (rc >> 2) * 8);
+    const f16x8 b0 = -read_row(rp), b1 = -read_row(rp + 4 * G::kF16Pitch);
     const float hn = half_norm(n);
     // (one address register per row of blocks: the reads of a row reach their
     // columns by instruction offsets)
     const lds_byte* ap[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      ap[q] = (const lds_byte*)(smem + Smem::f16 + v * kF16Copy + (8 * q + 4 * wy + u + g) * kF16Pitch + 8 * wx);
+      ap[q] = (const lds_byte*)(smem + G::f16 + v * G::kF16Copy + (8 * q + 4 * wy + u + g) * G::kF16Pitch + 8 * wx);
       asm("" : "+v"(ap[q]));
     }
-    const lds_byte* cp = (const lds_byte*)(smem + Smem::init + (4 * wy + u) * kInitPitch + 16 * wx + 4 * v);
+    const lds_byte* cp = (const lds_byte*)(smem + G::init + (4 * wy + u) * G::kInitPitch + 16 * wx + 4 * v);
     constexpr float kInf = __builtin_huge_valf();
     float best[4] = {kInf, kInf, kInf, kInf};
     // the accumulator starts, N(a~) / 2 + N(b~) / 2, as a float product of
@@ -383,8 +396,8 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
     };
     auto load = [&](int s) {
       const int q = s / C, k = s % C;
-      return Operands{read_row(ap[q] + 32 * k), read_row(ap[q] + 32 * k + 4 * kF16Pitch),
-                      *(const lds_float*)(cp + 8 * q * kInitPitch + 64 * k)};
+      return Operands{read_row(ap[q] + 32 * k), read_row(ap[q] + 32 * k + 4 * G::kF16Pitch),
+                      *(const lds_float*)(cp + 8 * q * G::kInitPitch + 64 * k)};
     };
     // the next block's operands are read while this one's products run (and
     // no further ahead: the registers are the occupancy)
@@ -414,7 +427,7 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
     // the group bests (not below zero, so that their bit patterns are ordered)
 #pragma unroll
     for (int i = 0; i < 4; ++i) best[i] = fmaxf(best[i], 0.0f);
-    *reinterpret_cast<u32x2*>(smem + Smem::best + n * kBestPitch + (wave * 4 + g) * 8) =
+    *reinterpret_cast<u32x2*>(smem + G::best + n * G::kBestPitch + (wave * 4 + g) * 8) =
         u32x2{__builtin_amdgcn_perm(__float_as_uint(best[1]), __float_as_uint(best[0]), 0x07060302u),
               __builtin_amdgcn_perm(__float_as_uint(best[3]), __float_as_uint(best[2]), 0x07060302u)};
   }
@@ -424,8 +437,8 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
   // with fewer than K bests below it)
   constexpr unsigned kInfBits = 0x7F80u;
   {
-    const unsigned* bp = reinterpret_cast<const unsigned*>(smem + Smem::best + 2 * wave * kBestPitch) + lane;
-    const unsigned w0 = bp[0], w1 = bp[kBestPitch / 4];
+    const unsigned* bp = reinterpret_cast<const unsigned*>(smem + G::best + 2 * wave * G::kBestPitch) + lane;
+    const unsigned w0 = bp[0], w1 = bp[G::kBestPitch / 4];
     const unsigned x[2][2] = {{w0 & 0xFFFFu, w0 >> 16}, {w1 & 0xFFFFu, w1 >> 16}};
     unsigned kth[2] = {0, 0};
 #pragma unroll
@@ -442,22 +455,22 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
       const unsigned k = lane ? kth[1] : kth[0];
       unsigned b = kInfBits - 1;  // fewer than K groups have a candidate: all pass
       if (k < kInfBits) b = min(b, __float_as_uint(widened_bound(__uint_as_float(k << 16 | 0xFFFFu), half_norm(ref))) >> 16);
-      reinterpret_cast<unsigned*>(smem + Smem::bound)[ref] = b << 16 | b;
+      reinterpret_cast<unsigned*>(smem + G::bound)[ref] = b << 16 | b;
     }
   }
   __syncthreads();
   // candidates past the bound: one bit per half distance, and each lane's
   // place among its reference's candidates
-  int* count = reinterpret_cast<int*>(smem + Smem::count);
-  int* start = reinterpret_cast<int*>(smem + Smem::start);
-  constexpr int kPer = kSteps % 6 == 0 ? 6 : 4;  // blocks per mask word
+  int* count = reinterpret_cast<int*>(smem + G::count);
+  int* start = reinterpret_cast<int*>(smem + G::start);
+  constexpr int kPer = kSteps % 6 == 0 ? 6 : kSteps % 4 == 0 ? 4 : kSteps;  // blocks per mask word
   constexpr int kWords = kSteps / kPer, kLow = 16 - 2 * kPer;
   static_assert(kSteps % kPer == 0 && kWords <= 3, "whole mask words");
   unsigned pass[kWords];
   int n_pass = 0;
   {
     typedef short s16x2 __attribute__((ext_vector_type(2)));
-    const s16x2 bound = __builtin_bit_cast(s16x2, reinterpret_cast<const unsigned*>(smem + Smem::bound)[n]);
+    const s16x2 bound = __builtin_bit_cast(s16x2, reinterpret_cast<const unsigned*>(smem + G::bound)[n]);
 #pragma unroll
     for (int w = 0; w < kWords; ++w) {
       unsigned m = 0;
@@ -477,8 +490,8 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
   // exact keys and slots, as many references at a time as the queue holds
   // (nearly always all 16): their candidates' codes (reference << 12 |
   // row << 6 | column) end to end, each list padded to a multiple of eight
-  uint16_t* codes = reinterpret_cast<uint16_t*>(smem + Smem::codes);
-  double* keys = reinterpret_cast<double*>(smem + Smem::keys);
+  uint16_t* codes = reinterpret_cast<uint16_t*>(smem + G::codes);
+  double* keys = reinterpret_cast<double*>(smem + G::keys);
   constexpr unsigned kPad = 0xFFFFu;
   for (int first = 0; first < 16;) {
     // lane (g, n): the padded length of reference n's list, and the sum of the
@@ -490,7 +503,7 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
     upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xF, 0xF, true);  // row_shr:4
     upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xF, 0xF, true);  // row_shr:8
     const int my_start = upto - c8;
-    const unsigned full = static_cast<unsigned>(__builtin_amdgcn_ballot_w64(upto > kQueue)) & 0xFFFFu;
+    const unsigned full = static_cast<unsigned>(__builtin_amdgcn_ballot_w64(upto > G::kQueue)) & 0xFFFFu;
     const int last = full ? __builtin_ctz(full) : 16;  // > first: a list always fits an empty queue
     const int total = __builtin_amdgcn_readlane(upto, last - 1);
     const bool here = n >= first && n < last;
@@ -517,7 +530,7 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
       // (the reference itself takes no slot among the others)
       double key = __builtin_huge_val();
       if (code != kPad && (dy != R || dx != R))
-        key = exact_key(smem, R + 3 * (k >> 2), R + 3 * (k & 3), cy, cx, dy * S + dx);
+        key = exact_key<G>(smem, R + 3 * (k >> 2), R + 3 * (k & 3), cy, cx, dy * S + dx);
       keys[f] = key;
     }
     __syncthreads();
@@ -568,7 +581,7 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
           wave_lds_sync();
         }
         for (int e = n_kept + lane; e < ((n_list + 7) & ~7); e += kWave) list[e] = __builtin_huge_val();
-        if (lane == 0) reinterpret_cast<int*>(smem + Smem::kept)[k] = n_kept;
+        if (lane == 0) reinterpret_cast<int*>(smem + G::kept)[k] = n_kept;
       }
       __syncthreads();
     }
@@ -577,7 +590,7 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
       const double key = keys[f];
       const int k = codes[f] >> 12, p = p0 + (k >> 2), q = q0 + (k & 3);
       if (key == __builtin_huge_val()) continue;
-      const int n_keys = count[k] > kPrune ? reinterpret_cast<const int*>(smem + Smem::kept)[k] : count[k];
+      const int n_keys = count[k] > kPrune ? reinterpret_cast<const int*>(smem + G::kept)[k] : count[k];
       const int rank = entries_below(keys + start[k], n_keys, key);
       if (rank < K - 1 && p < nRy && q < nRx)
         idx[(static_cast<size_t>(p) * nRx + q) * K + 1 + rank] =
@@ -599,16 +612,20 @@ struct StackShare {
   unsigned share = 0;
 };
 
+// waves per SIMD: 80 registers for the largest grid and for the stacks' workgroups
+// (three workgroups per CU), 64 otherwise (four)
+constexpr int min_waves(int steps, int kind) { return kind < 0 && steps <= 8 ? 8 : 6; }
+
 template <int Q, int C, bool WIDE, bool BATCH, int KIND>
-__global__ __launch_bounds__(kThreads, 6) void bm_corr_kernel(ImgRec one, WorkList wl, WorkList stack_wl,
-                                                              StackShare ss, int R, int K, int use_pilot) {
-  __shared__ __align__(16) unsigned char smem[Smem::bytes];
+__global__ __launch_bounds__(kThreads, min_waves(Q * C, KIND)) void bm_corr_kernel(ImgRec one, WorkList wl,
+                                                                                   WorkList stack_wl, StackShare ss,
+                                                                                   int R, int K, int use_pilot) {
+  using Lds = StackLds<4>;
+  __shared__ __align__(16) unsigned char smem[KIND < 0 ? Geo<Q, C>::bytes : max2(Geo<Q, C>::bytes, 2 * sizeof(Lds))];
   unsigned b = blockIdx.z * gridDim.x + blockIdx.x;
   if constexpr (KIND >= 0) {
     const unsigned g = b >> 3, sg = __umulhi(g, ss.share);
     if (__umulhi(g + 1, ss.share) != sg) {
-      using Lds = StackLds<4>;
-      static_assert(2 * sizeof(Lds) <= Smem::bytes, "two stack items fit the matcher's LDS");
       const int s = static_cast<int>(sg * 8 + (b & 7));
       if (s >= ss.pairs) return;
       const int plane = s >= ss.per_plane ? 1 : 0;
@@ -696,6 +713,8 @@ hipError_t launch_bm_corr(const ImgRec& one, const WorkList* wl, const WorkList*
   if (K < 2 || K > 32 || R < 0 || R > kMaxR || stack_kind == 1 ||
       (wl && stack_kind >= 0 && !stack_wl)) return hipErrorInvalidValue;
   const int nb = blocks_per_axis(R);
+  if (nb <= 4) return launch_corr_grid<2, 1, false>(one, wl, stack_wl, R, K, use_pilot, stack_kind, st);
+  if (nb <= 6) return launch_corr_grid<3, 2, false>(one, wl, stack_wl, R, K, use_pilot, stack_kind, st);
   if (nb <= 8) return launch_corr_grid<4, 2, false>(one, wl, stack_wl, R, K, use_pilot, stack_kind, st);
   if (nb < kMaxNb) return launch_corr_grid<6, 3, false>(one, wl, stack_wl, R, K, use_pilot, stack_kind, st);
   return launch_corr_grid<6, 3, true>(one, wl, stack_wl, R, K, use_pilot, stack_kind, st);

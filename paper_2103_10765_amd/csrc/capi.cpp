@@ -320,6 +320,19 @@ struct BmChoice {
   int method, split;  // split 0: by size inside the launcher
 };
 
+// The matching kernel where neither the caller nor a tuning record chooses.  The
+// correlation kernel's work per tile hardly shrinks below its smallest grid of
+// candidate blocks, the shift-wise kernel's does with the window's area, but it
+// leaves the stacks to a launch of their own.  Matching | whole first stage at
+// K = 8, correlation against shift-wise, us: 1024^2 window 5 64 | 217 against 26 |
+// 174, window 7 64 | 217 against 52 | 199, window 11 81 | 234 against 82 | 225,
+// window 13 81 | 235 against 130 | 279; 512^2 window 5 21 | 66 against 12 | 61,
+// window 7 21 | 66 against 20 | 69; 256^2 window 5 10 | 31 against 10 | 33.
+int default_method(int search, long tiles) {
+  const bool shift = (search <= 5 && tiles > 1000) || (search <= 11 && tiles > 3000);
+  return shift ? GBM3D_BM_SHIFT : GBM3D_BM_CORR;
+}
+
 // Explicit params win.  Zeros take the tuned choice of the class (same K and
 // search); without one, the method of the nearest tuned class of the same K
 // and search (split then by size), else the default.
@@ -340,7 +353,7 @@ BmChoice choose_bm(const gbm3d_ctx* ctx, const gbm3d_params& p, long tiles, int 
       }
     }
   }
-  if (c.method == GBM3D_BM_AUTO) c.method = GBM3D_BM_CORR;  // the faster kernel on every measured shape
+  if (c.method == GBM3D_BM_AUTO) c.method = default_method(p.search, tiles);
   return c;
 }
 

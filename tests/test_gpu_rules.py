@@ -66,3 +66,15 @@ def test_group_tiles_of_a_single_image(G, ctx, n, S):
             a, b = kernel_ms(ctx, kernel, one), kernel_ms(ctx, kernel, batch)
             print(kernel, n, S, K, f"{1e3 * a:.1f} us, largest tiles {1e3 * b:.1f} us", flush=True)
             assert a <= 1.2 * b, (kernel, n, S, K, a, b)
+
+
+@pytest.mark.parametrize("K", [2, 8])
+def test_small_windows_cost_less(G, ctx, K):
+    """Matching 1024 x 1024: windows of 3, 7, 11 and 15 take at most a given
+    part of the default window's time (which has 169, 31, 12 and 7 times their
+    candidates)."""
+    x = up(synth.make_case(1024, 1024, SIG, 3)[1])
+    t = {S: kernel_ms(ctx, "bm", lambda: ctx.match(x, K, G.default_params(search=S))) for S in (3, 7, 11, 15, 39)}
+    print("matching 1024^2", K, {S: round(1e3 * v, 1) for S, v in t.items()}, flush=True)
+    for S, part in ((3, 0.25), (7, 0.5), (11, 0.65), (15, 0.65)):
+        assert t[S] <= part * t[39], (S, t)
