@@ -31,19 +31,34 @@
 //
 // Ties: candidates that are exactly as good are told apart by a position
 // term far below one unit of distance, which survives while the norms are
-// small (constant regions); elsewhere they all pass and the exact keys decide,
-// at the cost of more of them (long lists are cut by the (K-1)-th smallest of
-// their first kSample keys before the ranks are counted).
+// small (constant regions); elsewhere they all pass and the exact keys decide
+// (long lists are cut by the (K-1)-th smallest of their first kSample keys
+// before the ranks are counted).
+//
+// The widening grows with the reference's distance from the centre pixel and
+// with the noise it does not shrink: on a tile of two flat levels, on text,
+// graphics and periodic textures hundreds of candidates of a reference pass.
+// Such a tile (hard_tile, kLongList) goes through an exact pass: <a, b> from four
+// int8 products of the pixels' bytes, keys in float64 (integers below 2^49), the
+// group bests' exact K-th smallest, position and all, as the limit, and a second
+// pass over the products that marks the keys up to it: 18 / 40 candidates per
+// reference again, whatever the image.  It costs such a tile 16 000 vector
+// instructions.  Matching 512^2, K = 16 / 32, us, without the pass | with it |
+// by the earlier kernel of exact keys alone, which any image took: two levels
+// 4000 and 60000 with noise of 128 110 / 187 | 95 / 123 | 86 / 112, checkerboard
+// 432 / 445 | 114 / 118 | 82 / 107, texture of period 8 186 / 355 | 120 / 142 | 88 / 111,
+// strokes on white 150 / 273 | 114 / 150 | 90 / 115; noisy 47 / 59 | 47 / 59 | 91 / 115.
 //
 // Bound by LDS cycles and vector issue about equally: per tile 6 200 LDS
 // cycles (the 144 blocks' operands 2 600 of them) and 9 000 vector
 // instructions at K = 16, and by the latency of its eight phases, so three
-// workgroups share a CU (78 registers, 53 KB of LDS): with unpacked half
-// distances and two workgroups per CU the 4096^2 image took 3.0 ms instead of
-// 2.6, and with f16 copies 22 instead of 8 banks apart 2.6 instead of 2.45.
+// workgroups share a CU (80 registers, 53 KB of LDS; none in scratch memory but
+// for one to three of the stacks' workgroups): with unpacked half distances and
+// two workgroups per CU the 4096^2 image took 3.0 ms instead of 2.6, and with
+// f16 copies 22 instead of 8 banks apart 2.6 instead of 2.45.
 // Against the earlier kernel (exact float64 keys of all pairs from int8
-// products and a norm table), K = 16 / 32: 512^2 87 / 112 -> 46 / 61 us,
-// 4096^2 2.93 / 3.56 -> 2.46 / 3.0 ms, 128^2 26 / 31 -> 11 / 27 us.
+// products and a norm table), K = 16 / 32, noisy images: 512^2 87 / 112 -> 46 / 59
+// us, 4096^2 2.93 / 3.56 -> 2.46 / 3.0 ms, 128^2 26 / 31 -> 11 / 16 us.
 #include "common.h"
 #include "kernels.h"
 #include "stack_body.h"
@@ -60,6 +75,16 @@ constexpr int kSample = 256;                      // by a bound from so many of 
 // 1880): a half distance is a whole multiple of 1/8 on this scale, the term
 // stays below half of that.
 constexpr float kTieStep = 1.0f / 32768.0f;
+
+// A tile goes through the exact pass where its lists hold more candidates than
+// this in all, or one of them more than kLongList: a list of many hundreds is
+// slow to cut and rank, and a thousand candidates more cost as much as the pass.
+// (Noisy images have some 20 candidates per reference at K = 16, 45 at K = 32, at
+// most 2400 per tile.  Lines at 1340 / 1980 instead of 1700 / 2500: two-stage 128^2
+// 64 -> 69 us; a list line of 320: 64 -> 69, of 256: 512^2 262 -> 270; no list line:
+// two flat levels, 128^2, K = 32 35 -> 55.)
+__host__ __device__ constexpr int hard_tile(int K) { return 900 + 50 * K; }
+constexpr int kLongList = 448;
 
 constexpr int max2(int a, int b) { return a > b ? a : b; }
 constexpr int min2(int a, int b) { return a < b ? a : b; }
@@ -101,12 +126,22 @@ struct Geo {
   // candidates with exact keys at a time (lists padded to eights); the keys take
   // the place of the products' operands, which are dead by then
   static constexpr int kQueue = min2(3072, (codes - f16) / 64 * 8);
-  static constexpr int bound = (codes + max2(16 * kBestPitch, 2 * kQueue) + 15) / 16 * 16;
+  // The exact pass: norms with position (double, rows two entries longer than
+  // the candidates' so that four rows fall on different banks) and, before them,
+  // their horizontal sums, over the products' operands; 128 group bests
+  // (double), over the starts and codes.
+  static constexpr int kNormPitch = kCandCols + 2;
+  static constexpr int norms = f16;
+  static constexpr int kExactPitch = 8 * (kWaves * 16 + 2);
+  static constexpr int exact = sums;
+  static_assert(8 * kRows * kCandCols <= 4 * kF16Copy && 8 * kCandRows * kNormPitch <= 4 * kF16Copy, "norms fit the operands' area");
+  static constexpr int bound = (max2(codes + max2(16 * kBestPitch, 2 * kQueue), exact + 16 * kExactPitch) + 15) / 16 * 16;
   // int[16]: packed half distances up to it pass
   static constexpr int count = bound + 64;               // int[16]: candidates past each reference's bound
   static constexpr int start = count + 64;               // int[16]: their first place in the queue
   static constexpr int kept = start + 64;                // int[16]: keys left of a long list
-  static constexpr int bytes = kept + 64;
+  static constexpr int limit = kept + 64;                // double[16]: exact keys up to it pass
+  static constexpr int bytes = limit + 128;
   static constexpr int keys = f16;
   static constexpr int kMaxWindow = kCandRows < kCandCols ? kCandRows - 9 : kCandCols - 9;
   static_assert(kQueue >= kMaxWindow * kMaxWindow + 7, "one reference always fits the queue");
@@ -124,6 +159,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 __host__ __device__ constexpr int corr_items(int H, int W) {
   return ((H + kStep - 1) / kStep + 3) / 4 * (((W + kStep - 1) / kStep + 3) / 4);
@@ -180,6 +217,51 @@ __device__ __forceinline__ double exact_key(const unsigned char* smem, int ry, i
   return fma(dist, 2048.0, static_cast<double>(rank));
 }
 
+// The exact pass takes pixels as 256 h + l with signed bytes h and l, z - 32896:
+// z's bytes with their top bits flipped.
+constexpr int kMid = 32896;
+// a key outside the window, and the high word of one (above it)
+constexpr double kOutside = 1e300;
+constexpr unsigned kOutsideHigh = 0x7FE00000u;
+
+struct Digits {
+  i32x4 h, l;
+};
+
+// two rows of eight pixels (at a word of a flipped plane), and their digits
+struct Rows {
+  unsigned a[4], b[4];
+};
+template <typename G>
+__device__ __forceinline__ Rows read_rows(const lds_byte* p) {
+  typedef const __attribute__((address_space(3))) unsigned* lds_words;
+  const lds_words a = (lds_words)p, b = (lds_words)(p + G::kPixPitch);
+  return {{a[0], a[1], a[2], a[3]}, {b[0], b[1], b[2], b[3]}};
+}
+__device__ __forceinline__ Digits digits_of(const Rows& r) {
+  auto high = [](unsigned x, unsigned y) { return static_cast<int>(__builtin_amdgcn_perm(y, x, 0x07050301u)); };
+  auto low = [](unsigned x, unsigned y) { return static_cast<int>(__builtin_amdgcn_perm(y, x, 0x06040200u)); };
+  return {i32x4{high(r.a[0], r.a[1]), high(r.a[2], r.a[3]), high(r.b[0], r.b[1]), high(r.b[2], r.b[3])},
+          i32x4{low(r.a[0], r.a[1]), low(r.a[2], r.a[3]), low(r.b[0], r.b[1]), low(r.b[2], r.b[3])}};
+}
+
+// m = 2 m + the lane's bit
+__device__ __forceinline__ void shift_in(unsigned& m, unsigned long long bit) {
+  unsigned long long carry;
+  asm("v_addc_co_u32_e64 %0, %1, %2, %2, %3" : "=v"(m), "=s"(carry) : "0"(m), "s"(bit));
+}
+
+// The candidate row of a wave's block (q, k) in the exact pass.
+__device__ __forceinline__ int exact_row(int wave, int q, int k) { return 8 * q + ((wave - q - 3 * k) & 7); }
+
+// flips the top bits of the planes' bytes (and back)
+template <typename G>
+__device__ __forceinline__ void flip_digits(unsigned char* smem, int tid) {
+  static_assert(G::pix0 == 0 && G::pix1 == G::kPixPlane && G::kPixPlane % 8 == 0, "one run of words");
+  unsigned* w = reinterpret_cast<unsigned*>(smem);
+  for (int i = tid; i < 2 * G::kPixPlane / 4; i += kThreads) w[i] ^= 0x80808080u;
+}
+
 // The widened bound on the approximate half distances of a reference, from
 // the K-th best of its group bests, `half`, and hn = N(b~) / 2.  With
 // t = |a~ - b~| the distance that half stands for and e = 2^-11 the relative
@@ -202,7 +284,6 @@ __device__ __forceinline__ unsigned high_word(double x) {
 // How many of the first n entries of list (16-byte aligned, filled up to a
 // multiple of eight with infinities) lie below key.
 __device__ __forceinline__ int entries_below(const double* list, int n, double key) {
-  typedef double f64x2 __attribute__((ext_vector_type(2)));
   const f64x2* p = reinterpret_cast<const f64x2*>(list);
   int below = 0;
   for (int i = 0; i < n; i += 8, p += 4) {
@@ -467,10 +548,11 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
   constexpr int kWords = kSteps / kPer, kLow = 16 - 2 * kPer;
   static_assert(kSteps % kPer == 0 && kWords <= 3, "whole mask words");
   unsigned pass[kWords];
-  int n_pass = 0;
-  {
+  int n_pass, place;
+  auto mark = [&] {
     typedef short s16x2 __attribute__((ext_vector_type(2)));
     const s16x2 bound = __builtin_bit_cast(s16x2, reinterpret_cast<const unsigned*>(smem + G::bound)[n]);
+    n_pass = 0;
 #pragma unroll
     for (int w = 0; w < kWords; ++w) {
       unsigned m = 0;
@@ -483,9 +565,223 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
       pass[w] = ~m & (((1u << 2 * kPer) - 1) << kLow) * 0x10001u;
       n_pass += __builtin_popcount(pass[w]);
     }
-  }
-  const int place = n_pass ? atomicAdd(count + n, n_pass) : 0;
+    place = n_pass ? atomicAdd(count + n, n_pass) : 0;
+  };
+  // lane (g, n): the lengths of the references' lists up to n, each padded to a
+  // multiple of eight and those before `first` left out (along the 16 lanes of a row)
+  auto lengths_up_to = [&](int c8) {
+    int upto = c8;
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xF, 0xF, true);  // row_shr:1
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xF, 0xF, true);  // row_shr:2
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xF, 0xF, true);  // row_shr:4
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xF, 0xF, true);  // row_shr:8
+    return upto;
+  };
+  auto hard = [&] {
+    const int c = count[n];
+    return wave_any(c > kLongList) || __builtin_amdgcn_readlane(lengths_up_to((c + 7) & ~7), 15) > hard_tile(K);
+  };
+  mark();
   __syncthreads();
+  const bool exact = hard();
+  if (exact) {
+    // The exact pass.  Norms: sum over 8 x 8 pixels of (z - 32896)^2, times 2048,
+    // plus the position row * S + column; rows of eight sums per thread first.
+    double* norms = reinterpret_cast<double*>(smem + G::norms);
+    constexpr int kCand = G::kCandCols, kPitch = G::kNormPitch;
+    {
+      constexpr int kCols = kCand / 8;
+      static_assert(G::kRows * kCols <= kThreads, "one item per thread");
+      const int r = tid / kCols, q = tid - r * kCols;
+      if (r < G::kRows) {
+        const u32x2* src = reinterpret_cast<const u32x2*>(smem + G::pix0 + r * G::kPixPitch + 16 * q);
+        double e[16];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const u32x2 w = src[k];
+          const unsigned z[4] = {w.x & 0xFFFFu, w.x >> 16, w.y & 0xFFFFu, w.y >> 16};
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const double d = static_cast<double>(static_cast<int>(z[j]) - kMid);
+            e[4 * k + j] = d * d;
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < 15; ++k) e[k] += e[k + 1];
+#pragma unroll
+        for (int k = 0; k < 13; ++k) e[k] += e[k + 2];
+        double* h = norms + r * kCand + 8 * q;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) h[k] = e[k] + e[k + 4];
+      }
+    }
+    __syncthreads();
+    {
+      const int col = tid % kCand, seg = tid / kCand;
+      const bool active = seg < Q;
+      double a[15];
+      if (active) {
+        const double* h = norms + 8 * seg * kCand + col;
+#pragma unroll
+        for (int k = 0; k < 15; ++k) a[k] = h[k * kCand];
+#pragma unroll
+        for (int k = 0; k < 14; ++k) a[k] += a[k + 1];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) a[k] += a[k + 2];
+      }
+      flip_digits<G>(smem, tid);
+      __syncthreads();
+      if (active) {
+        double* c = norms + 8 * seg * kPitch + col;
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          c[k * kPitch] = fma(a[k] + a[k + 4], 2048.0, static_cast<double>((8 * seg + k) * S + col));
+      }
+    }
+    __syncthreads();
+    // key = norms - 4096 <a, b>, with signed byte digits <a, b> = 65536 hh +
+    // 256 (hl + lh) + ll.  Here a block is 16 columns of a row, 8 Q x C of them,
+    // of which wave w takes rows 8 q + (w - q - 3 k) mod 8: positions that a
+    // period of 2 to 16 pixels apart are alike fall into different groups too
+    // (of 4 x 4 blocks, a texture of period 8 has all its repeats in two groups).
+    // Operand lane (g, m) holds rows 2 g and 2 g + 1 of candidate (column) or
+    // reference m, result lane (g, n) candidates 4 g .. 4 g + 3 against
+    // reference n.
+    typedef const __attribute__((address_space(3))) f64x2* lds_pairs;
+    const lds_byte* px = (const lds_byte*)(smem + (n & 1 ? G::pix1 : G::pix0) + 2 * g * G::kPixPitch + 2 * (n & ~1));
+    const lds_byte* np = (const lds_byte*)(norms + 4 * g);
+    const int rc = R + 3 * v;
+    const Digits ref =
+        digits_of(read_rows<G>((const lds_byte*)smem + (rc & 1 ? G::pix1 : G::pix0) + (R + 3 * u + 2 * g) * G::kPixPitch + 2 * (rc & ~1)));
+    const double ref_norm = norms[(R + 3 * u) * kPitch + rc] - static_cast<double>((R + 6 * u) * S + R + 6 * v);
+    // use(key, in): keys less ref_norm and the lanes whose window holds them, from
+    // the last block to the first; end() after each mask word's blocks
+    auto exact_keys = [&](auto&& use, auto&& end) {
+      const int row = -3 * u, col = 4 * g - 3 * v;
+      unsigned long long col_in[C][4];
+#pragma unroll
+      for (int k = 0; k < C; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          col_in[k][i] = __builtin_amdgcn_ballot_w64(static_cast<unsigned>(col + 16 * k + i) <= static_cast<unsigned>(2 * R));
+      static_assert(kPer % C == 0, "whole rows of blocks per mask word");
+      constexpr int kQ = kPer / C;
+      auto rows = [&](int q, int k) { return read_rows<G>(px + exact_row(wave, q, k) * G::kPixPitch + 32 * k); };
+      // (the next block's rows are read while this one's products run, where the
+      // registers are not the occupancy)
+      constexpr bool kAhead = kSteps > 8;
+      Rows next = rows(Q - 1, C - 1);
+#pragma unroll 1
+      for (int w = kWords - 1; w >= 0; --w) {
+#pragma unroll
+        for (int t = kPer - 1; t >= 0; --t) {
+          const int q = w * kQ + t / C, k = t % C, r = exact_row(wave, q, k);
+          if (!kAhead) next = rows(q, k);
+          const Digits a = digits_of(next);
+          if (kAhead) next = t > 0 ? rows(w * kQ + (t - 1) / C, (t - 1) % C) : rows(max(w * kQ - 1, 0), C - 1);
+          const unsigned long long row_in = __builtin_amdgcn_ballot_w64(static_cast<unsigned>(row + r) <= static_cast<unsigned>(2 * R));
+          i32x4 x = __builtin_amdgcn_mfma_i32_16x16x64_i8(a.h, ref.h, i32x4{0, 0, 0, 0}, 0, 0, 0);
+          const i32x4 ll = __builtin_amdgcn_mfma_i32_16x16x64_i8(a.l, ref.l, i32x4{0, 0, 0, 0}, 0, 0, 0);
+          x <<= 8;
+          x = __builtin_amdgcn_mfma_i32_16x16x64_i8(a.h, ref.l, x, 0, 0, 0);
+          x = __builtin_amdgcn_mfma_i32_16x16x64_i8(a.l, ref.h, x, 0, 0, 0);
+          const lds_pairs nr = (lds_pairs)(np + 8 * (r * kPitch + 16 * k));
+          const f64x2 nk[2] = {nr[0], nr[1]};
+          double key[4];
+          unsigned long long in[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            key[i] = fma(static_cast<double>(ll[i]), -4096.0, nk[i / 2][i % 2]);
+            key[i] = fma(static_cast<double>(x[i]), -1048576.0, key[i]);
+            in[i] = row_in & col_in[k][i];
+          }
+          use(key, in);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        end();
+      }
+    };
+    double best[4] = {kOutside, kOutside, kOutside, kOutside};
+    exact_keys([&](const double (&key)[4], const unsigned long long (&in)[4]) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        // (the high word alone decides that a key is outside)
+        const unsigned long long bits = __builtin_bit_cast(unsigned long long, key[i]);
+        const unsigned hi = __builtin_amdgcn_inverse_ballot_w64(in[i]) ? static_cast<unsigned>(bits >> 32) : kOutsideHigh;
+        best[i] = fmin(best[i], __builtin_bit_cast(double, static_cast<unsigned long long>(hi) << 32 | static_cast<unsigned>(bits)));
+      }
+    }, [] {});
+    {
+      f64x2* to = reinterpret_cast<f64x2*>(smem + G::exact + n * G::kExactPitch + (wave * 4 + g) * 32);
+      to[0] = f64x2{best[0], best[1]} + ref_norm;
+      to[1] = f64x2{best[2], best[3]} + ref_norm;
+    }
+    __syncthreads();
+    // The K-th smallest of the 128 group bests: two references per wave, their
+    // bests (not below zero) two to a lane as integers, bit by bit from the top
+    // (fewer than K groups with a candidate: the limit comes out above kOutside)
+    if (tid < 16) count[tid] = 0;
+    {
+      const unsigned long long* bp = reinterpret_cast<const unsigned long long*>(smem + G::exact + 2 * wave * G::kExactPitch) + lane;
+      unsigned hi[2][2], lo[2][2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const unsigned long long x = bp[j * (G::kExactPitch / 8) + e * kWave];
+          hi[j][e] = static_cast<unsigned>(x >> 32);
+          lo[j][e] = static_cast<unsigned>(x);
+        }
+      unsigned kth[2] = {0, 0}, kth_lo[2] = {0, 0};
+      auto below = [](const unsigned (&x)[2], unsigned t) {
+        return __builtin_popcountll(__builtin_amdgcn_ballot_w64(x[0] < t)) + __builtin_popcountll(__builtin_amdgcn_ballot_w64(x[1] < t));
+      };
+#pragma unroll 1
+      for (unsigned bit = 1u << 30; bit != 0; bit >>= 1)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) kth[j] = below(hi[j], kth[j] | bit) < K ? kth[j] | bit : kth[j];
+      // the low word where several bests have this high word (near and exact ties);
+      // the last four bits of an integer below 2^49 are zero
+      int left[2];
+      bool ties = false;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        left[j] = K - below(hi[j], kth[j]);
+        ties |= below(hi[j], kth[j] + 1) - below(hi[j], kth[j]) > 1;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) lo[j][e] = hi[j][e] == kth[j] ? lo[j][e] : ~0u;
+      }
+      if (ties) {
+#pragma unroll 1
+        for (unsigned bit = 1u << 31; bit != 8u; bit >>= 1)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) kth_lo[j] = below(lo[j], kth_lo[j] | bit) < left[j] ? kth_lo[j] | bit : kth_lo[j];
+      } else {
+        kth_lo[0] = kth_lo[1] = ~0u;
+      }
+      if (lane < 2)
+        reinterpret_cast<unsigned long long*>(smem + G::limit)[2 * wave + lane] =
+            static_cast<unsigned long long>(lane ? kth[1] : kth[0]) << 32 | (lane ? kth_lo[1] : kth_lo[0]);
+    }
+    __syncthreads();
+    const double limit = reinterpret_cast<const double*>(smem + G::limit)[n] - ref_norm;
+    unsigned even = 0, odd = 0;  // columns 0, 2 and 1, 3 of a word's blocks: a bit each, the first block's last
+    n_pass = 0;
+    exact_keys([&](const double (&key)[4], const unsigned long long (&in)[4]) {
+#pragma unroll
+      for (int i = 3; i >= 0; --i)
+        shift_in(i & 1 ? odd : even, __builtin_amdgcn_ballot_w64(key[i] <= limit) & in[i]);
+    }, [&] {
+#pragma unroll
+      for (int w = kWords - 1; w > 0; --w) pass[w] = pass[w - 1];
+      pass[0] = (even | odd << 16) << kLow;
+      n_pass += __builtin_popcount(pass[0]);
+      even = odd = 0;
+    });
+    place = n_pass ? atomicAdd(count + n, n_pass) : 0;
+    __syncthreads();
+    flip_digits<G>(smem, tid);
+  }
 
   // exact keys and slots, as many references at a time as the queue holds
   // (nearly always all 16): their candidates' codes (reference << 12 |
@@ -494,14 +790,8 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
   double* keys = reinterpret_cast<double*>(smem + G::keys);
   constexpr unsigned kPad = 0xFFFFu;
   for (int first = 0; first < 16;) {
-    // lane (g, n): the padded length of reference n's list, and the sum of the
-    // lengths up to it (along the 16 lanes of a row)
     const int c = count[n], c8 = n >= first ? (c + 7) & ~7 : 0;
-    int upto = c8;
-    upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xF, 0xF, true);  // row_shr:1
-    upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xF, 0xF, true);  // row_shr:2
-    upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xF, 0xF, true);  // row_shr:4
-    upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xF, 0xF, true);  // row_shr:8
+    const int upto = lengths_up_to(c8);
     const int my_start = upto - c8;
     const unsigned full = static_cast<unsigned>(__builtin_amdgcn_ballot_w64(upto > G::kQueue)) & 0xFFFFu;
     const int last = full ? __builtin_ctz(full) : 16;  // > first: a list always fits an empty queue
@@ -515,13 +805,20 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
     }
     if (n_pass && here) {
       int at = my_start + place;
-      const int mine = n << 12 | (4 * wy + g) << 6 | 4 * wx;
+      auto list = [&](auto&& position) {  // position(q, k): row << 6 | column of the lane's first candidate
 #pragma unroll
-      for (int w = 0; w < kWords; ++w)
-        for (unsigned m = pass[w]; m != 0; m &= m - 1) {
-          const int bit = __builtin_ctz(m), t = (bit & 15) - kLow, s = w * kPer + (t >> 1), q = s / C, k = s - q * C;
-          codes[at++] = static_cast<uint16_t>(mine + 512 * q + 16 * k + 2 * (t & 1) + (bit >> 4));
-        }
+        for (int w = 0; w < kWords; ++w)
+          for (unsigned m = pass[w]; m != 0; m &= m - 1) {
+            const int bit = __builtin_ctz(m), t = (bit & 15) - kLow, s = w * kPer + (t >> 1), q = s / C, k = s - q * C;
+            codes[at++] = static_cast<uint16_t>((n << 12) + position(q, k) + 2 * (t & 1) + (bit >> 4));
+          }
+      };
+      if (exact) {
+        list([&](int q, int k) { return exact_row(wave, q, k) << 6 | (16 * k + 4 * g); });
+      } else {
+        const int mine = (4 * wy + g) << 6 | 4 * wx;
+        list([&](int q, int k) { return mine + 512 * q + 16 * k; });
+      }
     }
     __syncthreads();
     for (int f = tid; f < total; f += kThreads) {

@@ -687,3 +687,39 @@ def test_match_many_near_ties(torch, G, ctx, kind, S, K):
     exp = O.match(Z, K, O.DEFAULT.with_(search=S))
     bad = np.nonzero((got != exp).any(axis=1))[0]
     assert bad.size == 0, (bad[:5], got[bad[:2]], exp[bad[:2]])
+
+
+def _hard_image(kind, H, W):
+    rng = np.random.default_rng(83)
+    y, x = np.mgrid[:H, :W]
+    if kind == "strokes":          # black on white: many blocks at the same nonzero distance
+        z = np.full((H, W), 65535)
+        for _ in range(H * W // 90):
+            a, b = rng.integers(0, H), rng.integers(0, W)
+            h, w = (1, 5) if rng.random() < 0.5 else (6, 1)
+            z[a:a + h, b:b + w] = 0
+        return z.astype(np.uint16)
+    if kind == "dots":             # most blocks constant
+        return np.where(rng.random((H, W)) < 0.004, 65535, 12345).astype(np.uint16)
+    if kind == "steps":            # smooth ramps between far levels
+        return (np.clip(32768 + 60000 * np.sin(x / 9.0) * np.cos(y / 13.0), 0, 65535)).astype(np.uint16)
+    if kind == "levels":
+        return (np.where((x // 29 + y // 23) % 2, 60000, 4000) + rng.integers(-128, 129, (H, W))).astype(np.uint16)
+    if kind == "stripes":
+        return (x // 3 % 2 * 65535).astype(np.uint16)
+    return np.tile(rng.integers(0, 65536, (16, 4)), (H // 16 + 1, W // 4 + 1))[:H, :W].astype(np.uint16)
+
+
+@pytest.mark.parametrize("kind", ["strokes", "dots", "steps", "levels", "stripes", "period 16 x 4"])
+@pytest.mark.parametrize("S,K", [(39, 2), (39, 16), (39, 32), (33, 32), (21, 16), (23, 32), (15, 32), (9, 8), (7, 16)])
+def test_match_exact_pass(torch, G, ctx, kind, S, K):
+    """Images on whose tiles the correlation matcher's bound leaves hundreds of
+    candidates per reference, so that exact keys of all pairs give the limit:
+    every shape of its grid, an image larger than the region and its margin."""
+    H, W = 86, 101
+    say("match exact pass", kind, S, K)
+    Z = _hard_image(kind, H, W)
+    got = ctx.match(up(torch, Z), K, G.default_params(search=S, bm_method=2)).cpu().numpy().astype(np.int64)
+    exp = O.match(Z, K, O.DEFAULT.with_(search=S))
+    bad = np.nonzero((got != exp).any(axis=1))[0]
+    assert bad.size == 0, (bad[:5], got[bad[:2]], exp[bad[:2]])

@@ -78,3 +78,27 @@ def test_small_windows_cost_less(G, ctx, K):
     print("matching 1024^2", K, {S: round(1e3 * v, 1) for S, v in t.items()}, flush=True)
     for S, part in ((3, 0.25), (7, 0.5), (11, 0.65), (15, 0.65)):
         assert t[S] <= part * t[39], (S, t)
+
+
+def _image(kind, n):
+    rng = np.random.default_rng(5)
+    y, x = np.mgrid[:n, :n]
+    if kind == "levels":
+        return (np.where((x // 29 + y // 23) % 2, 60000, 4000) + rng.integers(-3, 4, (n, n))).astype(np.uint16)
+    if kind == "checkerboard":
+        return ((x + y) % 2 * 65535).astype(np.uint16)
+    if kind == "stripes":
+        return (x // 3 % 2 * 65535).astype(np.uint16)
+    return np.tile(rng.integers(0, 65536, (8, 8)), (n // 8, n // 8)).astype(np.uint16)
+
+
+@pytest.mark.parametrize("K", [16, 32])
+def test_matching_time_hardly_depends_on_the_image(G, ctx, K):
+    """Flat levels and periodic textures, where hundreds of candidates come near
+    the K-th best, take at most 3.2 times a noisy image's time."""
+    t = {}
+    for kind in ("noisy", "levels", "checkerboard", "stripes", "period 8"):
+        x = up(synth.make_case(512, 512, SIG, 3)[1] if kind == "noisy" else _image(kind, 512))
+        t[kind] = kernel_ms(ctx, "bm", lambda: ctx.match(x, K))
+    print("matching 512^2", K, {k: round(1e3 * v, 1) for k, v in t.items()}, flush=True)
+    assert max(t.values()) <= 3.2 * t["noisy"], t
