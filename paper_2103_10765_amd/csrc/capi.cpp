@@ -19,6 +19,7 @@
 #include "../../include/gbm3d.h"
 #include "kernels.h"
 #include "pilot.h"
+#include "tuning.h"
 
 namespace {
 
@@ -35,7 +36,11 @@ struct TraceRange {
 
 }  // namespace
 
+using gbm3d::BmChoice;
 using gbm3d::ImgRec;
+using gbm3d::ShapeEntry;
+using gbm3d::TuneEntry;
+using gbm3d::TuneKey;
 using gbm3d::WorkList;
 
 // Workspace of gbm3d_denoise_noalloc: one fixed array per device, reserved
@@ -96,26 +101,6 @@ struct BatchPlan {
   bool any_stage1 = false, any_stage2 = false;
 };
 
-// A block-matching launch choice recorded by the autotuner.
-struct TuneEntry {
-  int method = GBM3D_BM_SHIFT, split = 1;
-  float ms = 0.0f;
-};
-
-// A stage-1 group-kernel shape recorded by the autotuner.
-struct ShapeEntry {
-  int shape = 0;
-  float ms = 0.0f;
-};
-
-// Tuning key: group size, search window, shape class of the image(s).
-struct TuneKey {
-  int K, search, cls;
-  bool operator<(const TuneKey& o) const {
-    return K != o.K ? K < o.K : (search != o.search ? search < o.search : cls < o.cls);
-  }
-};
-
 struct GraphEntry {
   std::string key;
   hipGraph_t graph = nullptr;
@@ -131,9 +116,7 @@ struct gbm3d_ctx {
   Buffer stack_a, stack_b, idx, partials, basic, q;
   // global stage 1
   Buffer gl_a, gl_b, gl_num, gl_idx, gl_shift, gl_pad, gl_out;
-  // block-matching choices per (K, shape class)
-  std::map<TuneKey, TuneEntry> tuned;
-  std::map<TuneKey, ShapeEntry> tuned_shape;  // stage-1 group kernel, keyed by k_ht
+  gbm3d::Tuning tuning;
   // batches
   Buffer batch_ws, batch_table;
   void* host_stage = nullptr;  // pinned staging of the batch table
@@ -309,69 +292,12 @@ ImgRec blank_rec(int H, int W, float sigma) {
   return r;
 }
 
-// Shape class of a block-matching launch: floor(log2) of its 4x4 reference tiles.
-int tile_class(long tiles) {
-  int c = 0;
-  while (tiles >= (2L << c)) ++c;
-  return c;
-}
-
-struct BmChoice {
-  int method, split;  // split 0: by size inside the launcher
-};
-
-// The matching kernel where neither the caller nor a tuning record chooses.  The
-// correlation kernel's work per tile hardly shrinks below its smallest grid of
-// candidate blocks, the shift-wise kernel's does with the window's area, but it
-// leaves the stacks to a launch of their own.  Matching | whole first stage at
-// K = 8, correlation against shift-wise, us: 1024^2 window 5 64 | 217 against 26 |
-// 174, window 7 64 | 217 against 52 | 199, window 11 81 | 234 against 82 | 225,
-// window 13 81 | 235 against 130 | 279; 512^2 window 5 21 | 66 against 12 | 61,
-// window 7 21 | 66 against 20 | 69; 256^2 window 5 10 | 31 against 10 | 33.
-int default_method(int search, long tiles) {
-  const bool shift = (search <= 5 && tiles > 1000) || (search <= 11 && tiles > 3000);
-  return shift ? GBM3D_BM_SHIFT : GBM3D_BM_CORR;
-}
-
-// Explicit params win.  Zeros take the tuned choice of the class (same K and
-// search); without one, the method of the nearest tuned class of the same K
-// and search (split then by size), else the default.
 BmChoice choose_bm(const gbm3d_ctx* ctx, const gbm3d_params& p, long tiles, int K) {
-  BmChoice c{p.bm_method, p.bm_split};
-  const int cls = tile_class(tiles);
-  const auto it = ctx->tuned.find({K, p.search, cls});
-  if (it != ctx->tuned.end()) {
-    if (c.method == GBM3D_BM_AUTO) c.method = it->second.method;
-    if (c.split == 0 && c.method == it->second.method) c.split = it->second.split;
-  } else if (c.method == GBM3D_BM_AUTO) {
-    int best = 1 << 30;
-    for (const auto& kv : ctx->tuned) {
-      const int d = std::abs(kv.first.cls - cls);
-      if (kv.first.K == K && kv.first.search == p.search && d < best) {
-        best = d;
-        c.method = kv.second.method;
-      }
-    }
-  }
-  if (c.method == GBM3D_BM_AUTO) c.method = default_method(p.search, tiles);
-  return c;
+  return gbm3d::choose_bm(ctx->tuning, p.bm_method, p.bm_split, p.search, tiles, K);
 }
 
-// The stage-1 group-kernel shape: the tuned one of the class, else that of
-// the nearest tuned class of the same k_ht and search, else two tiles per CU.
-int choose_shape(const gbm3d_ctx* ctx, const gbm3d_params& p, long tiles) {
-  const int cls = tile_class(tiles);
-  const auto it = ctx->tuned_shape.find({p.k_ht, p.search, cls});
-  if (it != ctx->tuned_shape.end()) return it->second.shape;
-  int best = 1 << 30, shape = 0;
-  for (const auto& kv : ctx->tuned_shape) {
-    const int d = std::abs(kv.first.cls - cls);
-    if (kv.first.K == p.k_ht && kv.first.search == p.search && d < best) {
-      best = d;
-      shape = kv.second.shape;
-    }
-  }
-  return shape;
+int choose_shape(const gbm3d_ctx* ctx, const gbm3d_params& p, long tiles, bool batch) {
+  return gbm3d::choose_shape(ctx->tuning, p.k_ht, p.search, tiles, batch);
 }
 
 // Block matching of one image (r.noisy, or r.pilot with use_pilot) into r.idx.
@@ -457,7 +383,7 @@ int run_basic(gbm3d_ctx* ctx, const uint16_t* noisy, int H, int W, float sigma, 
   }
   HIP_TRY(ctx, timed(ctx, "group_ht", st, [&] {
             return gbm3d::launch_group_ht(r, nullptr, R, p.k_ht, p.ht_a, p.ht_b, p.ht_weight, p.keep_dc, recompute,
-                                          choose_shape(ctx, p, gbm3d::corr_tiles(H, W)), st);
+                                          choose_shape(ctx, p, gbm3d::corr_tiles(H, W), false), st);
           }),
           "hard-threshold group launch");
   HIP_TRY(ctx, timed(ctx, "reduce", st, [&] { return gbm3d::launch_reduce(r, nullptr, 0, st); }),
@@ -540,7 +466,7 @@ int plan_batch(gbm3d_ctx* ctx, const gbm3d_image* imgs, int n, const gbm3d_param
   };
   plan.bm_split1 = split_of(c1, waves1);
   plan.bm_split2 = split_of(c2, waves2);
-  plan.ht_shape = choose_shape(ctx, p, tiles1);
+  plan.ht_shape = choose_shape(ctx, p, tiles1, true);
   // workspace slices
   size_t total = 0;
   std::vector<size_t> off(n);
@@ -915,8 +841,8 @@ int gbm3d_autotune(gbm3d_ctx* ctx, const uint16_t* img, int H, int W, int K, con
       if (ms < best.ms) best = TuneEntry{method, split, ms};
     }
   }
-  const int cls = tile_class(gbm3d::corr_tiles(H, W));
-  ctx->tuned[{K, p.search, cls}] = best;
+  const int cls = gbm3d::tile_class(gbm3d::corr_tiles(H, W));
+  ctx->tuning.matching[{K, p.search, cls}] = best;
   if (tune_shape) {
     // the stage-1 group kernel's shape: whole stage-1 runs (matching as just
     // tuned) at a nominal noise level, one per shape
@@ -927,7 +853,7 @@ int gbm3d_autotune(gbm3d_ctx* ctx, const uint16_t* img, int H, int W, int K, con
     ShapeEntry sbest;
     sbest.ms = INFINITY;
     for (int shape : {0, 1}) {
-      ctx->tuned_shape[{K, p.search, cls}] = ShapeEntry{shape, 0.0f};
+      ctx->tuning.shapes[{K, p.search, cls}] = ShapeEntry{shape, 0.0f};
       float ms = 0.0f;
       CHECK(time_runs(
           [&] {
@@ -936,7 +862,7 @@ int gbm3d_autotune(gbm3d_ctx* ctx, const uint16_t* img, int H, int W, int K, con
           ms));
       if (ms < sbest.ms) sbest = ShapeEntry{shape, ms};
     }
-    ctx->tuned_shape[{K, p.search, cls}] = sbest;
+    ctx->tuning.shapes[{K, p.search, cls}] = sbest;
   }
   if (best_method) *best_method = best.method;
   if (best_split) *best_split = best.split;
@@ -950,10 +876,10 @@ int gbm3d_tune_save(const gbm3d_ctx* ctx, const char* path) {
   if (!path) return fail(c, GBM3D_EINVAL, "NULL path");
   FILE* f = std::fopen(path, "w");
   if (!f) return fail(c, GBM3D_EINVAL, "cannot write %s", path);
-  for (const auto& kv : ctx->tuned)
+  for (const auto& kv : ctx->tuning.matching)
     std::fprintf(f, "bm %d %d %d %d %d %.6f\n", kv.first.K, kv.first.search, kv.first.cls, kv.second.method,
                  kv.second.split, static_cast<double>(kv.second.ms));
-  for (const auto& kv : ctx->tuned_shape)
+  for (const auto& kv : ctx->tuning.shapes)
     std::fprintf(f, "ht %d %d %d %d %.6f\n", kv.first.K, kv.first.search, kv.first.cls, kv.second.shape,
                  static_cast<double>(kv.second.ms));
   const bool ok = std::fclose(f) == 0;
@@ -993,8 +919,8 @@ int gbm3d_tune_load(gbm3d_ctx* ctx, const char* path) {
   }
   std::fclose(f);
   if (bad) return fail(ctx, GBM3D_EINVAL, "%s: cannot parse entry %d", path, n);
-  for (const auto& r : rows) ctx->tuned[r.first] = r.second;
-  for (const auto& r : shapes) ctx->tuned_shape[r.first] = r.second;
+  for (const auto& r : rows) ctx->tuning.matching[r.first] = r.second;
+  for (const auto& r : shapes) ctx->tuning.shapes[r.first] = r.second;
   return GBM3D_OK;
 }
 
