@@ -340,7 +340,9 @@ int gbm3d_timing_reset(gbm3d_ctx* ctx);
  * options), on the device image img [H][W]:
  *   - times every block-matching variant (GBM3D_BM_SHIFT with bm_split 1, 2
  *     and 4, and GBM3D_BM_CORR) with group size K, `reps` runs each after one
- *     warm-up run, and records the fastest;
+ *     warm-up run, and records the fastest (with the patch stacks of the
+ *     stage whose group size K is: k_ht or k_wiener; of matching alone for
+ *     another K, or if the stacks cannot be allocated);
  *   - when K == params.k_ht <= 16, also times whole stage-1 runs (that
  *     matching, sigma 25/255) with each of the two shapes of the stage-1
  *     group kernel (tiles sharing a compute unit, or one tile of 16 waves
@@ -350,7 +352,9 @@ int gbm3d_timing_reset(gbm3d_ctx* ctx);
  * leave bm_method or bm_split at 0 use the record of their class (a batch:
  * the class of all its tiles together); without one, the method recorded for
  * the nearest class of the same K and search, with the split chosen by size;
- * else the rule at GBM3D_BM_AUTO.  The stage-1 shape likewise (default: two tiles).
+ * else the rule at GBM3D_BM_AUTO.  The stage-1 shape likewise (default: tiles
+ * sharing a compute unit); a record of a class below 2048 tiles answers for
+ * single images of its class only.
  * Timing uses HIP events on `stream` (the call synchronises it).
  * best_method, best_split and best_ms (milliseconds per matching run) may be
  * NULL.  Errors: GBM3D_EINVAL for bad shapes, params, K or reps < 1. */

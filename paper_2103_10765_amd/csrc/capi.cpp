@@ -832,15 +832,31 @@ int gbm3d_autotune(gbm3d_ctx* ctx, const uint16_t* img, int H, int W, int K, con
   TuneEntry best;
   best.ms = INFINITY;
   const int R = p.search / 2;
+  // The kernels are compared as a stage of this group size runs them, with its
+  // stacks (kind 0, 2), which the correlation kernel's launch writes beside the
+  // matching: by matching alone the shift-wise kernel was chosen where it made
+  // the stage up to 8 % slower (512^2, window 11, K = 16: 29 against 30 us, the first
+  // stage 97 against 90).  Matching alone (-1) for other group sizes, or where the
+  // stacks do not fit.
+  int kind = K == p.k_ht && p.ht_source == GBM3D_HT_STACK ? 0 : K == p.k_wiener ? 2 : -1;
+  if (kind >= 0 && (ensure(ctx, ctx->stack_a, stack_bytes(H, W), "stack_a") != GBM3D_OK ||
+                    (kind == 2 && ensure(ctx, ctx->stack_b, stack_bytes(H, W), "stack_b") != GBM3D_OK)))
+    kind = -1;
+  r.pilot = img;
+  r.stack_a = static_cast<float*>(ctx->stack_a.p);
+  r.stack_b = static_cast<float*>(ctx->stack_b.p);
   for (int method : {GBM3D_BM_SHIFT, GBM3D_BM_CORR}) {
     for (int split : {1, 2, 4}) {
       if (method == GBM3D_BM_CORR && split > 1) continue;  // one launch shape
       const BmChoice c{method, split};
       float ms = 0.0f;
-      CHECK(time_runs([&] { return run_match(ctx, r, R, K, c, 0, st); }, ms));
+      CHECK(time_runs(
+          [&] { return kind < 0 ? run_match(ctx, r, R, K, c, 0, st) : run_match_stacks(ctx, r, R, K, c, kind, st); }, ms));
       if (ms < best.ms) best = TuneEntry{method, split, ms};
     }
   }
+  if (kind >= 0)
+    CHECK(time_runs([&] { return run_match(ctx, r, R, K, BmChoice{best.method, best.split}, 0, st); }, best.ms));
   const int cls = gbm3d::tile_class(gbm3d::corr_tiles(H, W));
   ctx->tuning.matching[{K, p.search, cls}] = best;
   if (tune_shape) {

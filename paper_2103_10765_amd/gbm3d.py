@@ -414,9 +414,10 @@ class Context:
         return ms.value, n.value
 
     def autotune(self, img: torch.Tensor, K: int, reps: int = 3, params: Params | None = None, stream=None):
-        """Times every block-matching variant on img (and, for K == k_ht <= 16,
-        both stage-1 group-kernel shapes) and records the fastest for its
-        (K, search, shape class); returns (method, split, ms per matching run)."""
+        """Times every block-matching variant on img, with the stacks of K's stage
+        (and, for K == k_ht <= 16, both stage-1 group-kernel shapes), and records
+        the fastest for its (K, search, shape class); returns (method, split, ms
+        per matching run)."""
         H, W = _hw(img)
         m, sp, ms = _I(), _I(), _F()
         self._check(lib().gbm3d_autotune(self._h, _dev(img, torch.uint16, "img"), H, W, K,

@@ -102,3 +102,18 @@ def test_matching_time_hardly_depends_on_the_image(G, ctx, K):
         t[kind] = kernel_ms(ctx, "bm", lambda: ctx.match(x, K))
     print("matching 512^2", K, {k: round(1e3 * v, 1) for k, v in t.items()}, flush=True)
     assert max(t.values()) <= 3.2 * t["noisy"], t
+
+
+def test_autotuner_compares_whole_stages(G):
+    """512 x 512, window 11, K = 16: matching alone is a little faster shift-wise
+    (1), matching with the stage's stacks by the correlation kernel (2), whose
+    launch writes them too."""
+    c = G.Context(0)
+    try:
+        x = up(synth.make_case(512, 512, SIG, 3)[1])
+        p = G.default_params(search=11)
+        assert c.autotune(x, 16, reps=50, params=p)[0] == 2
+        # a group size of no stage: matching alone
+        assert c.autotune(x, 8, reps=2, params=p)[0] in (1, 2)
+    finally:
+        c.close()
