@@ -74,7 +74,7 @@ def bm_int8_view(H, W, search, avg_us):
 TRAFFIC_FILES = {512: os.path.join(ROOT, "profiles", "hbm_traffic_denoise_512.txt"),
                  4096: os.path.join(ROOT, "profiles", "hbm_traffic_denoise_4096.txt")}
 KERNEL_SOURCES = {
-    "bm": ["bm.hip", "bm_corr.hip", "stack_body.h", "common.h", "topk.h"],
+    "bm": ["bm.hip", "bm_corr.hip", "match_bound.h", "stack_body.h", "common.h", "topk.h"],
     "stack_bior": ["stack.hip", "stack_body.h", "common.h"], "stack_dct": ["stack.hip", "stack_body.h", "common.h"],
     "group_ht": ["group.hip", "common.h"], "group_wiener": ["group.hip", "common.h"], "reduce": ["group.hip", "common.h"],
 }

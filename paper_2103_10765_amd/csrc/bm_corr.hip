@@ -23,7 +23,7 @@
 //     group lie far apart, so neighbours, which are good together, fall into
 //     different groups: on noisy images 18 candidates of 1521 pass the bound
 //     for K = 16, on first estimates 37 for K = 32.  The bound is widened by
-//     what the roundings can do (widened_bound below), so that no candidate of
+//     what the roundings can do (widened_bound), so that no candidate of
 //     the exact answer is lost.
 //  3. Candidates past the bound go to a queue in LDS, one thread forms each
 //     one's exact integer distance from the u16 pixels, and a key's rank among
@@ -61,6 +61,7 @@
 // us, 4096^2 2.93 / 3.56 -> 2.46 / 3.0 ms, 128^2 26 / 31 -> 11 / 16 us.
 #include "common.h"
 #include "kernels.h"
+#include "match_bound.h"
 #include "stack_body.h"
 
 namespace gbm3d {
@@ -71,11 +72,6 @@ constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * kWave;
 constexpr int kPrune = 64;                       // longer lists are cut before their keys are ranked
 constexpr int kSample = 256;                      // by a bound from so many of their keys
-// Position term of a half distance, per unit of row * S + column (at most
-// 1880): a half distance is a whole multiple of 1/8 on this scale, the term
-// stays below half of that.
-constexpr float kTieStep = 1.0f / 32768.0f;
-
 // A tile goes through the exact pass where its lists hold more candidates than
 // this in all, or one of them more than kLongList: a list of many hundreds is
 // slow to cut and rank, and a thousand candidates more cost as much as the pass.
@@ -260,21 +256,6 @@ __device__ __forceinline__ void flip_digits(unsigned char* smem, int tid) {
   static_assert(G::pix0 == 0 && G::pix1 == G::kPixPlane && G::kPixPlane % 8 == 0, "one run of words");
   unsigned* w = reinterpret_cast<unsigned*>(smem);
   for (int i = tid; i < 2 * G::kPixPlane / 4; i += kThreads) w[i] ^= 0x80808080u;
-}
-
-// The widened bound on the approximate half distances of a reference, from
-// the K-th best of its group bests, `half`, and hn = N(b~) / 2.  With
-// t = |a~ - b~| the distance that half stands for and e = 2^-11 the relative
-// rounding of f16, a candidate at approximate distance <= t has true distance
-// at most t + e (|a| + |b|), and a candidate truly that close has approximate
-// distance at most t + e (4 |b~| + 2 t) to first order in e (|a| <= |b| + t
-// for both).  The accumulation of a half distance, 64 products and the start
-// value, is off by less than 2^-17 (|b~| + t)^2 (65 roundings of 2^-23 of sums
-// below (|b~| + t)^2); this counts twice.
-__device__ __forceinline__ float widened_bound(float half, float hn) {
-  const float nb = __builtin_amdgcn_sqrtf(2.0f * hn) * 1.000002f, t = __builtin_amdgcn_sqrtf(2.0f * half) * 1.000002f;
-  const float t2 = t + (1.01f / 2048.0f) * (4.0f * nb + 2.0f * t);
-  return 0.500002f * t2 * t2 + 1.0f / 65536.0f * (nb + t2) * (nb + t2);
 }
 
 __device__ __forceinline__ unsigned high_word(double x) {
@@ -534,8 +515,9 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
     if (lane < 2) {
       const int ref = 2 * wave + lane;
       const unsigned k = lane ? kth[1] : kth[0];
+      auto root = [](float x) { return __builtin_amdgcn_sqrtf(x); };
       unsigned b = kInfBits - 1;  // fewer than K groups have a candidate: all pass
-      if (k < kInfBits) b = min(b, __float_as_uint(widened_bound(__uint_as_float(k << 16 | 0xFFFFu), half_norm(ref))) >> 16);
+      if (k < kInfBits) b = min(b, __float_as_uint(widened_bound(__uint_as_float(k << 16 | 0xFFFFu), half_norm(ref), root)) >> 16);
       reinterpret_cast<unsigned*>(smem + G::bound)[ref] = b << 16 | b;
     }
   }

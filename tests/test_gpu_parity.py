@@ -707,10 +707,16 @@ def _hard_image(kind, H, W):
         return (np.where((x // 29 + y // 23) % 2, 60000, 4000) + rng.integers(-128, 129, (H, W))).astype(np.uint16)
     if kind == "stripes":
         return (x // 3 % 2 * 65535).astype(np.uint16)
+    if kind == "rounding":         # f16 roundings that put the nearer candidates last, around lone references
+        z = np.kron(rng.choice([33809, 31819], (H // 10 + 1, W // 10 + 1)), np.ones((10, 10), np.int64))[:H, :W]
+        for p0, q0 in ((12, 36), (48, 60)):
+            z[p0 - 7:p0 + 15, q0 + 2:q0 + 24] = 0
+            z[p0:p0 + 8, q0 + 9:q0 + 17] = 32815
+        return z.astype(np.uint16)
     return np.tile(rng.integers(0, 65536, (16, 4)), (H // 16 + 1, W // 4 + 1))[:H, :W].astype(np.uint16)
 
 
-@pytest.mark.parametrize("kind", ["strokes", "dots", "steps", "levels", "stripes", "period 16 x 4"])
+@pytest.mark.parametrize("kind", ["strokes", "dots", "steps", "levels", "stripes", "rounding", "period 16 x 4"])
 @pytest.mark.parametrize("S,K", [(39, 2), (39, 16), (39, 32), (33, 32), (21, 16), (23, 32), (15, 32), (9, 8), (7, 16)])
 def test_match_exact_pass(torch, G, ctx, kind, S, K):
     """Images on whose tiles the correlation matcher's bound leaves hundreds of
