@@ -5,7 +5,9 @@ A step is one full denoise (block matching, stacks, hard-threshold stage,
 pilot quantisation, block matching on the pilot, Wiener stage, aggregation)
 of a device-resident uint16 image into a device float image.  Prints one JSON
 line.  Per-kernel durations come from HIP events the library records on the
-launch stream (a second pass of the same K steps), the roofline entry is for
+launch stream (a second pass of the same K steps, in which the library launches
+each stage's matching and stacks by themselves; in the timed steps they are one
+launch, so the kernels' times add up to more than a step), the roofline entry is for
 the kernel with the largest share of the step.
 """
 import argparse
@@ -31,9 +33,13 @@ def algorithmic_work(H, W, search, k1, k2, norm_in_stacks=False):
     ones; for block matching (either kernel) 5 FLOP of exact arithmetic per
     (pixel, displacement) pair -- one difference, one fused square-accumulate
     (2 FLOP) and the two running-sum additions of the box filter -- on the
-    fp64 vector ALU.  norm_in_stacks: the correlation matcher's norm table is
-    formed in each stage's stack launch (an earlier form of that matcher; the
-    present one needs no table)."""
+    fp64 vector ALU.  That is the work the shift-wise kernel does; the
+    correlation kernel replaces it by f16 matrix products and integer distances
+    for the few candidates that they leave, so against this peak its figure
+    compares the two methods and is no bound of its own (it is bound by vector
+    issue and LDS cycles: `valu_issue_frac`).  "bm_norm" and norm_in_stacks price
+    the norm table that an earlier form of the correlation kernel read, in a
+    launch of its own or in each stage's stack launch; no kernel writes one now."""
     from paper_2103_10765_amd import gbm3d
     nref = gbm3d.n_refs(H, W, 3)
     weight_bytes = H * W * 8  # 64-bit block-start weights
@@ -61,9 +67,11 @@ BM_FLOP_PER_PAIR = 5
 
 
 def bm_int8_view(H, W, search, avg_us):
-    """The correlation matcher read against the int8 matrix cores instead:
-    the 64 multiply-accumulates of one block inner product (2 operations
-    each) per (reference, displacement) pair."""
+    """Matching read against the int8 matrix cores: the 64 multiply-accumulates
+    of one block inner product (2 operations each) per (reference,
+    displacement) pair, as one of the correlation matcher's exact passes forms
+    four times over on the tiles that go through it.  (Not part of the
+    benchmark line.)"""
     from paper_2103_10765_amd import gbm3d
     ops = 2.0 * 64 * gbm3d.n_refs(H, W, 3) * (search * search - 1)
     tops = ops / (avg_us * 1e-6) / 1e12

@@ -234,15 +234,17 @@ int gbm3d_global_match(gbm3d_ctx* ctx, const uint16_t* img, int H, int W,
 /* gbm3d_denoise for callers that cannot allocate device memory: code under
  * hipGraph stream capture, tight serving loops, hosts that forbid hipMalloc.
  * Same arguments, validation and result (bit for bit) as gbm3d_denoise, but
- * every intermediate buffer (two patch stacks, match indices, aggregation sums, and the basic estimate and pilot when basic_out / q_out
- * are NULL) is a slice of one static device array of
+ * every intermediate buffer (two patch stacks, match indices, aggregation
+ * sums, and the basic estimate and pilot when basic_out / q_out are NULL) is a
+ * slice of one static device array of
  * GBM3D_NOALLOC_SCRATCH_BYTES per device, which the library holds on every
  * device it runs on until the process ends.  The call makes no hipMalloc,
  * hipFree or other allocating call and records no timing events.  It
- * returns GBM3D_EINVAL, launching nothing, when the image needs more scratch
- * than that (with the default parameters square images up to 551 x 551
- * fit, when basic_out and q_out are NULL; the error text gives the bytes
- * needed).  Every call on a device shares that device's
+ * returns GBM3D_EINVAL, launching nothing, when these buffers and 8 bytes per
+ * pixel of the image with a border of 32 (a fixed part of the limit; nothing is
+ * kept there) come to more than that: with the default parameters square
+ * images up to 551 x 551 are accepted when basic_out and q_out are NULL (the
+ * error text gives the bytes counted).  Every call on a device shares that device's
  * array and leaves its contents behind (the kernels clear what must start
  * at zero), so calls that overlap on one device — on two streams, from two
  * contexts or two threads — race and give undefined results; serialise them.
@@ -324,7 +326,11 @@ int gbm3d_pilot_adam(gbm3d_ctx* ctx, float* master, float* m, float* v, const fl
                      float lr, float beta1, float beta2, float eps, void* stream);
 
 /* Per-kernel timing for benchmarking.  While enabled, the context brackets
- * every kernel it launches with two HIP events recorded on the launch stream.
+ * every kernel it launches with two HIP events recorded on the launch stream,
+ * and launches every kernel by itself: a stage's correlation matching and
+ * patch stacks, which are one launch otherwise, are two, and batches are not
+ * replayed from a graph.  The results are the same; the call is slower than an
+ * untimed one, so its kernels' times add up to more than that one takes.
  * gbm3d_timing_read synchronises the pending events and returns, for one
  * kernel name ("bm", "stack_bior", "stack_dct", "group_ht",
  * "group_wiener", "reduce"), the summed elapsed milliseconds and the number of

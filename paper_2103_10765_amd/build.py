@@ -28,9 +28,11 @@ FLAGS = [
 ]
 
 
-# The matching kernels hold only finite keys, scores or infinities in their
+# The matching kernels compare only finite keys, scores or infinities in their
 # min/max operations: with NaNs ruled out these need no NaN-quieting operand
-# canonicalisation.
+# canonicalisation.  (For windows below its grid of candidate blocks the
+# correlation matcher also forms scores from LDS that no one wrote, which may be
+# NaNs; each is replaced by infinity, a selection, before it is compared.)
 # The correlation matcher and the learned pilot's fused inference keep their
 # products' accumulators in ordinary VGPRs (vector instructions read them
 # without copies out of AGPRs); the pilot's values are finite throughout.

@@ -316,7 +316,8 @@ int run_match(gbm3d_ctx* ctx, ImgRec& r, int R, int K, const gbm3d_params& p, in
 
 // True if a stage's matching launch also writes its stacks: the matcher is
 // bound by vector issue and LDS, the stacks by memory writes.  While launches
-// are timed, each kernel is launched, and recorded, by itself.
+// are timed, each kernel is launched, and recorded, by itself (the header says
+// so: a timed call is a slower one).
 bool match_with_stacks(const gbm3d_ctx* ctx, int method) { return method == GBM3D_BM_CORR && !ctx->timing; }
 
 // A stage's matching and stacks (kind 0: the bior1.5 stack of the noisy image
@@ -1164,16 +1165,18 @@ int gbm3d_denoise_noalloc(gbm3d_ctx* ctx, const uint16_t* noisy, int H, int W, f
     off += align256(bytes);
     return o;
   };
-  // (the first slice is not used; it holds the documented size limit where it is)
-  take(static_cast<size_t>(H + 64) * (W + 64) * sizeof(double));
   const size_t o_sa = take(stack_bytes(H, W));
   const size_t o_sb = take(stack_bytes(H, W));
   const size_t o_idx = take(n_refs(H, W) * std::max(p.k_ht, p.k_wiener) * sizeof(int16_t));
   const size_t o_part = take(gbm3d::partials_bytes(H, W));
   const size_t o_basic = basic_out ? 0 : take(hw * sizeof(float));
   const size_t o_q = q_out ? 0 : take(hw * sizeof(uint16_t));
-  if (off > static_cast<size_t>(GBM3D_NOALLOC_SCRATCH_BYTES))
-    return fail(ctx, GBM3D_EINVAL, "image %dx%d needs %zu bytes of scratch; the static scratch holds %zu", H, W, off,
+  // (the documented limit counts 8 bytes per pixel of the image with a border of
+  // 32 beside the buffers, although none needs them: which images are accepted
+  // is part of the interface)
+  const size_t counted = off + align256(static_cast<size_t>(H + 64) * (W + 64) * 8);
+  if (counted > static_cast<size_t>(GBM3D_NOALLOC_SCRATCH_BYTES))
+    return fail(ctx, GBM3D_EINVAL, "image %dx%d counts %zu bytes of scratch; the static scratch holds %zu", H, W, counted,
                 static_cast<size_t>(GBM3D_NOALLOC_SCRATCH_BYTES));
   DeviceGuard g(ctx->device);
   if (!g.ok) return fail(ctx, GBM3D_EHIP, "hipSetDevice(%d) failed", ctx->device);

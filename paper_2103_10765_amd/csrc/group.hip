@@ -18,8 +18,8 @@
 // of that array (periodic).
 // All sums are 64-bit fixed point (2^-40), so their value does not depend on
 // the order in which waves add: results are bit-reproducible.  The footprint
-// is written once per tile to a partial-sum buffer; a second kernel adds the
-// overlapping footprints of every pixel (periodic), forms the box sum,
+// is added once per tile into the image's numerator sums (global integer
+// atomics at the periodic positions); a second kernel forms the box sum,
 // divides and optionally quantises.
 //
 // Stage 1 (Sec. 3.1, Sec. 5): bior1.5 stack, hard threshold |C| >= tau_l with

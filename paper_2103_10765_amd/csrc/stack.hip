@@ -17,6 +17,11 @@ namespace gbm3d {
 
 namespace {
 
+// These launches are the patch stacks by themselves: gbm3d_stack, matching by the
+// shift-wise kernel (the default for small windows on large images) and timed
+// calls.  The correlation matcher's launches write the stacks beside their own
+// work with the same body.
+
 // Workgroups up to which a stack launch counts as short: 32 per CU of the 256.
 constexpr int kShortLaunchItems = 32 * 256;
 
