@@ -45,9 +45,9 @@
 // reference again, whatever the image.  It costs such a tile 16 000 vector
 // instructions.  Matching 512^2, K = 16 / 32, us, without the pass | with it |
 // by the earlier kernel of exact keys alone, which any image took: two levels
-// 4000 and 60000 with noise of 128 110 / 187 | 95 / 123 | 86 / 112, checkerboard
-// 432 / 445 | 114 / 118 | 82 / 107, texture of period 8 186 / 355 | 120 / 142 | 88 / 111,
-// strokes on white 150 / 273 | 114 / 150 | 90 / 115; noisy 47 / 59 | 47 / 59 | 91 / 115.
+// 4000 and 60000 with noise of 128 110 / 187 | 88 / 123 | 86 / 112, checkerboard
+// 432 / 445 | 115 / 120 | 82 / 107, texture of period 8 186 / 355 | 123 / 146 | 88 / 111,
+// strokes on white 150 / 273 | 121 / 169 | 90 / 115; noisy 47 / 59 | 47 / 59 | 91 / 115.
 //
 // Bound by LDS cycles and vector issue about equally: per tile 6 200 LDS
 // cycles (the 144 blocks' operands 2 600 of them) and 9 000 vector
@@ -73,13 +73,18 @@ constexpr int kThreads = kWaves * kWave;
 constexpr int kPrune = 64;                       // longer lists are cut before their keys are ranked
 constexpr int kSample = 256;                      // by a bound from so many of their keys
 // A tile goes through the exact pass where its lists hold more candidates than
-// this in all, or one of them more than kLongList: a list of many hundreds is
+// this in all, or three of them more than kLongList: lists of many hundreds are
 // slow to cut and rank, and a thousand candidates more cost as much as the pass.
-// (Noisy images have some 20 candidates per reference at K = 16, 45 at K = 32, at
-// most 2400 per tile.  Lines at 1340 / 1980 instead of 1700 / 2500: two-stage 128^2
-// 64 -> 69 us; a list line of 320: 64 -> 69, of 256: 512^2 262 -> 270; no list line:
-// two flat levels, 128^2, K = 32 35 -> 55.)
-__host__ __device__ constexpr int hard_tile(int K) { return 900 + 50 * K; }
+// (Noisy images have some 20 candidates per reference at K = 16, 45 at K = 32.  A
+// first estimate has a few references with lists of 450 to 1000 in tiles of 1000 to
+// 2000 in all, which are the tail of a small image's launch: sent through the pass
+// for one long list they made two-stage calls of 128^2 up to 12 %, of 200 x 256 up
+// to 7 % slower.  Two-stage calls of 16 noisy images of 512^2, of a 128^2 image of
+// two flat levels, of one of strokes, us: one list, 1700 / 2500 in all at K = 16 / 32
+// 260, 86, 109; three lists, 1824 / 2848 257, 103, 119; three, 2240 / 2880 258, 104,
+// 127; four, 1824 / 2848 257, 105, 119, levels at 512^2 405 instead of 377; without
+// the pass 262, 198, 180.)
+__host__ __device__ constexpr int hard_tile(int K) { return 800 + 64 * K; }
 constexpr int kLongList = 448;
 
 constexpr int max2(int a, int b) { return a > b ? a : b; }
@@ -561,7 +566,9 @@ __device__ __forceinline__ void corr_body(unsigned char* smem, const uint16_t* _
   };
   auto hard = [&] {
     const int c = count[n];
-    return wave_any(c > kLongList) || __builtin_amdgcn_readlane(lengths_up_to((c + 7) & ~7), 15) > hard_tile(K);
+    // (four lanes hold each length)
+    return __builtin_popcountll(__builtin_amdgcn_ballot_w64(c > kLongList)) > 4 * 2 ||
+           __builtin_amdgcn_readlane(lengths_up_to((c + 7) & ~7), 15) > hard_tile(K);
   };
   mark();
   __syncthreads();

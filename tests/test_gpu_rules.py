@@ -104,6 +104,20 @@ def test_matching_time_hardly_depends_on_the_image(G, ctx, K):
     assert max(t.values()) <= 3.2 * t["noisy"], t
 
 
+def test_one_long_list_does_not_slow_a_first_estimate(G, ctx):
+    """First estimates of 128 x 128 images: in some a tile or two have one
+    reference with 450 to 480 near candidates in some 1000.  They cost about
+    what the others do."""
+    def ms(sigma, seed):
+        x = up(synth.make_case(128, 128, sigma / 255, seed)[1])
+        q = ctx.quantize(ctx.basic(x, sigma / 255))
+        return kernel_ms(ctx, "bm", lambda: ctx.match(q, 32))
+    plain = max(ms(25, seed) for seed in (18, 22))
+    t = {c: ms(*c) for c in ((25, 20), (25, 24), (50, 16), (50, 20))}
+    print("matching first estimates", round(1e3 * plain, 1), {c: round(1e3 * v, 1) for c, v in t.items()}, flush=True)
+    assert max(t.values()) <= 1.25 * plain, (plain, t)
+
+
 def test_autotuner_compares_whole_stages(G):
     """512 x 512, window 11, K = 16: matching alone is a little faster shift-wise
     (1), matching with the stage's stacks by the correlation kernel (2), whose
